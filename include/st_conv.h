@@ -53,7 +53,10 @@
  * floating-point atomics).  A skipped term is one whose tested factor compares
  * equal to zero (IEEE: +0 and -0; denormals are NOT flushed before the test).
  * With finite inputs the sparse and dense entry points agree to rounding; with
- * non-finite inputs they may differ (0 * Inf is skipped, not NaN).
+ * non-finite inputs they may differ (0 * Inf is skipped, not NaN).  The dense entry points form a product
+ * from bf16 pieces that carry all 24 bits of both factors and keep fp32 accuracy; outputs that
+ * infinities, NaN, overflow or factors below 2^-100 take part in are recomputed with plain fp32 multiply-adds
+ * (correct, and slow where there are many of them).
  */
 #ifndef ST_CONV_H
 #define ST_CONV_H
@@ -172,14 +175,14 @@ st_status st_conv_bww_auto(const st_conv_desc *desc, const float *x, const float
  * FWD, dy for BWI; at most 64 evenly spaced blocks of 1024 elements) in the same launch that
  * writes both forms' filter copies, then both forms are enqueued and the one the count does not
  * select returns at once.  The zero-skipping form runs when the sampled zero fraction reaches the
- * break-even point measured for the geometry: 25 % for 3x3 layers with K a multiple of 128, 40 %
- * for narrower ones, 80 % / 45 % for FWD / BWI of stride-2 3x3 layers, never for 1x1 layers
- * (measured up to 95 % zeros), always for geometries only the generic kernels cover.  Where the answer is "always" or "never" the call
+ * break-even point against the dense form measured for the geometry: 65 % for unit-stride 3x3 layers
+ * that one main kernel serves (below), 85 % for the others, 45 % for the BWI of stride-2 3x3 layers, never
+ * for their FWD and for 1x1 layers (measured up to 90 and 95 % zeros), always for geometries only the generic
+ * kernels cover.  Where the answer is "always" or "never" the call
  * goes straight to that form, without sampling.  On unit-stride 3x3 layers of the usual sizes one
  * main kernel holds both forms and runs the selected one, so the sampled path has as many launches
- * as the direct call (st_conv_kernel_name tells); elsewhere it costs one launch more; a caller that tracks sparsity itself can compare it with st_conv_sparse_threshold
- * and call the form directly.  Same tensors and layouts as st_conv_fwd / st_conv_bwi, same result
- * to rounding, no host synchronisation.
+ * as the direct call (st_conv_kernel_name tells); elsewhere it costs one launch more.  Same tensors and
+ * layouts as st_conv_fwd / st_conv_bwi, same result to rounding, no host synchronisation.
  * Workspace: st_conv_workspace_bytes(desc, ST_PASS_FWD_AUTO or ST_PASS_BWI_AUTO, 0).
  */
 st_status st_conv_fwd_auto(const st_conv_desc *desc, const float *x, const float *w, float *y,
@@ -216,10 +219,11 @@ st_status st_conv_fwd_static(const st_conv_desc *desc, const float *x, const flo
 size_t st_conv_workspace_bytes(const st_conv_desc *desc, int pass, int dense);
 
 /*
- * The zero fraction of the tested operand, in per mille, from which st_conv_fwd_auto (pass =
- * ST_PASS_FWD) or st_conv_bwi_auto (pass = ST_PASS_BWI) runs the zero-skipping form for this
- * geometry: 0 = always, 1001 = never; -1 for an invalid descriptor or another pass.  Host-side,
- * no GPU work.
+ * The zero fraction of the tested operand, in per mille, from which skipping pays on the fp32 pipes: the
+ * zero-skipping form (pass = ST_PASS_FWD or ST_PASS_BWI) against fp32 matrix instructions for this
+ * geometry: 0 = always, 1001 = never; -1 for an invalid descriptor or another pass.  The st_conv_*_dense
+ * forms reach fp32 accuracy on faster instructions, so st_conv_fwd_auto and st_conv_bwi_auto switch later than
+ * this (see there), never earlier.  Host-side, no GPU work.
  */
 int st_conv_sparse_threshold(const st_conv_desc *desc, int pass);
 

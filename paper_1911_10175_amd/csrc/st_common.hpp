@@ -41,6 +41,10 @@ struct Geom {
     // name of the kernel instance it would launch here and launches nothing
     char *describe;
     int describe_len;
+    // the layer's filters in the library layout and whether the correlation is the BWI form of the layer (channel
+    // roles exchanged, taps reversed): what the dense kernels recompute an output from that the bf16 pieces cannot carry
+    const float *w;
+    int wt;
 };
 
 #if defined(__HIPCC__)
@@ -138,9 +142,10 @@ hipError_t launch_auto_prepare(const Geom &g, bool transpose, const float *act, 
 bool fwd_auto_combined_supported(const Geom &g);
 hipError_t launch_fwd_auto_combined(const Geom &g, const float *in, const float *wl, const float *wd, float *out, hipStream_t s);
 void fwd_auto_kernel_name(const Geom &g, char *buf, size_t len);      // requires fwd_auto_combined_supported(g)
-// zero fraction (per mille) of the tested operand from which the zero-skipping FWD/BWI form beats the
-// dense one for this geometry (measured; 1001 = never)
+// zero fraction (per mille) of the tested operand from which the zero-skipping FWD/BWI form beats fp32
+// matrix instructions for this geometry, and from which the self-selecting entry points run it (measured; 1001 = never)
 unsigned fwd_sparse_threshold(const Geom &g);
+unsigned fwd_auto_threshold(const Geom &g);
 
 // unit-stride fast paths
 bool fwd_sparse_supported(const Geom &g);

@@ -48,6 +48,7 @@ Geom fwd_geom(const st_conv_desc &d, const Dims &o)
     g.uw = 1; g.uh = 1;
     g.sel = nullptr; g.want = 0; g.thr = 0;
     g.describe = nullptr; g.describe_len = 0;
+    g.w = nullptr; g.wt = 0;
     return g;
 }
 
@@ -65,6 +66,7 @@ bool bwi_as_fwd(const st_conv_desc &d, const Dims &o, Geom *g)
     g->pw = d.R - 1 - d.pad_w; g->ph = d.S - 1 - d.pad_h;
     g->sel = nullptr; g->want = 0; g->thr = 0;
     g->describe = nullptr; g->describe_len = 0;
+    g->w = nullptr; g->wt = 1;
     return true;
 }
 
@@ -141,7 +143,8 @@ st_status run_fwd(const st_conv_desc *d, const float *x, const float *w, float *
     if (rc != ST_OK) return rc;
     if ((rc = tensors_ok(x, w, y)) != ST_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const Geom g = fwd_geom(*d, o);
+    Geom g = fwd_geom(*d, o);
+    g.w = w;
     if (dense) {
         if (!st::fwd_dense_supported(g)) return dev(st::launch_generic_fwd(*d, x, w, y, false, s));
         if (!ws_ok(ws, ws_bytes, st::fwd_dense_workspace_bytes(g))) return ST_ERR_WORKSPACE;
@@ -168,6 +171,7 @@ st_status run_bwi(const st_conv_desc *d, const float *dy, const float *w, float 
     Geom g;
     const bool fast = bwi_as_fwd(*d, o, &g) &&
                       (dense ? st::fwd_dense_supported(g) : st::fwd_sparse_supported(g));
+    g.w = w;
     if (!fast) return dev(st::launch_generic_bwi(*d, dy, w, dx, !dense, s));
     float *wt = static_cast<float *>(ws);
     if (dense) {
@@ -234,9 +238,10 @@ st_status run_fwd_bwi_auto(const st_conv_desc *d, const float *act, const float 
 
     Geom g = fwd_geom(*d, o);
     const bool as_corr = bwi ? bwi_as_fwd(*d, o, &g) : true;
+    g.w = w;
     const bool fast_sparse = as_corr && st::fwd_sparse_supported(g);
     const bool fast_dense = as_corr && st::fwd_dense_supported(g);
-    g.thr = fast_sparse ? st::fwd_sparse_threshold(g) : 0;
+    g.thr = fast_sparse ? st::fwd_auto_threshold(g) : 0;
     if (!fast_dense && fast_sparse) g.thr = 0;      // tiled zero-skipping form against a generic dense one
     // Geometries whose answer does not depend on the data (break-even at 0: always zero-skipping;
     // above 1000 per mille: never) go straight to that form: no sampling, no second form enqueued.

@@ -4,6 +4,7 @@
 // count of a sample of a tensor.  All three are written for workgroups of 256 threads.
 #pragma once
 #include "st_common.hpp"
+#include "st_split.hpp"
 
 namespace st {
 
@@ -67,37 +68,68 @@ __device__ __forceinline__ void wave_filters_block(int block, int KB, int CB, in
     }
 }
 
-// Element i = 256 * block + thread of the copy in MFMA consumption order.  transpose = 0:
-// B[k][c][tap] = w[k][c][tap] (FWD); transpose = 1: the roles of the channel dimensions are swapped and the
+// Element i = 256 * block + thread of the fp32 copy the 1x1 kernel reads, [Ko/32][Ci/16][half][32 k][8 c];
+// transpose and padding as below.
+__device__ __forceinline__ void pw_filters_block(size_t block, int Ko, int Ci, int transpose, const float *__restrict__ w,
+                                                 float *__restrict__ wd, size_t total)
+{
+    const size_t i = block * 256 + threadIdx.x;
+    if (i >= total) return;
+    const int CiB = Ci / kBlk, KoB = Ko / kBlk;
+    size_t t = i;
+    const int j = t % 8; t /= 8;
+    const int l32 = t % 32; t /= 32;
+    const int half = t % 2; t /= 2;
+    const int cb = t % CiB;
+    const int ko = (int)(t / CiB) * 32 + l32, ci = half * 8 + j;
+    float val = 0.f;
+    if (ko < Ko)
+        val = transpose ? w[((size_t)cb * KoB + ko / kBlk) * (kBlk * kBlk) + (ko % kBlk) * kBlk + ci]
+                        : w[((size_t)(ko / kBlk) * CiB + cb) * (kBlk * kBlk) + ci * kBlk + ko % kBlk];
+    wd[i] = val;
+}
+
+// Piece i = 256 * block + thread (8 reduced channels of one produced channel and tap) of the copy in MFMA
+// consumption order, [Ko/32][Ci/16][tap][3 pieces][2 halves of the 16 channels][32 k][8 c] bf16: the three bf16
+// pieces of B[k][c][tap] = w[k][c][tap] (FWD); transpose = 1: the roles of the channel dimensions are swapped and the
 // taps reversed (BWI).  Ko/Ci are the produced and reduced channel counts of the correlation that will consume
-// the copy; produced channels are padded with zeros to a multiple of 128.
+// the copy; produced channels are padded with zeros to a multiple of 128.  total = pieces of 8.
 __device__ __forceinline__ void reformat_filters_block(size_t block, int Ko, int Ci, int S, int R, int transpose,
                                                        const float *__restrict__ w, float *__restrict__ wd, size_t total)
 {
     const size_t i = block * 256 + threadIdx.x;
     if (i >= total) return;
-    const int TAPS = S * R, CiB = Ci / kBlk;
+    const int TAPS = S * R, CiB = Ci / kBlk, KoB = Ko / kBlk;
     size_t t = i;
-    const int j = t % 8; t /= 8;
     const int l32 = t % 32; t /= 32;
     const int half = t % 2; t /= 2;
+    const size_t step = t;                              // (kb32 * CiB + cb) * TAPS + tap
     const int tap = t % TAPS; t /= TAPS;
     const int cb = t % CiB;
     const int kb32 = (int)(t / CiB);
-    const int ko = kb32 * 32 + l32, ci = cb * kBlk + half * 8 + j;
-    float val = 0.f;
+    const int ko = kb32 * 32 + l32, c0 = half * 8;
+    float4 lo = make_float4(0.f, 0.f, 0.f, 0.f), hi = lo;
     if (ko < Ko) {
         const int v = tap / R, u = tap % R;
         if (!transpose) {
-            // w[K = Ko][C = Ci]: element [ko/16][ci/16][v][u][ci%16][ko%16]
-            val = w[((((size_t)(ko / kBlk) * CiB + ci / kBlk) * S + v) * R + u) * (kBlk * kBlk) + (ci % kBlk) * kBlk + ko % kBlk];
+            // w[K = Ko][C = Ci]: element [ko/16][cb][v][u][ci%16][ko%16], eight of them 16 apart
+            const float *p = w + ((((size_t)(ko / kBlk) * CiB + cb) * S + v) * R + u) * (kBlk * kBlk) + c0 * kBlk + ko % kBlk;
+            lo = make_float4(p[0], p[kBlk], p[2 * kBlk], p[3 * kBlk]);
+            hi = make_float4(p[4 * kBlk], p[5 * kBlk], p[6 * kBlk], p[7 * kBlk]);
         } else {
-            // w[K = Ci][C = Ko]: element [ci/16][ko/16][S-1-v][R-1-u][ko%16][ci%16]
-            const int KoB = Ko / kBlk;
-            val = w[((((size_t)(ci / kBlk) * KoB + ko / kBlk) * S + (S - 1 - v)) * R + (R - 1 - u)) * (kBlk * kBlk) + (ko % kBlk) * kBlk + ci % kBlk];
+            // w[K = Ci][C = Ko]: element [cb][ko/16][S-1-v][R-1-u][ko%16][ci%16], eight in a row
+            const float4 *p = reinterpret_cast<const float4 *>(
+                w + ((((size_t)cb * KoB + ko / kBlk) * S + (S - 1 - v)) * R + (R - 1 - u)) * (kBlk * kBlk) + (ko % kBlk) * kBlk + c0);
+            lo = p[0];
+            hi = p[1];
         }
     }
-    wd[i] = val;
+    bf16x4 a[3], b[3];
+    split4(lo, a);
+    split4(hi, b);
+    bf16x8 *out = reinterpret_cast<bf16x8 *>(wd) + step * 192 + half * 32 + l32;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) out[q * 64] = __builtin_shufflevector(a[q], b[q], 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
 // Zero statistics of one tensor: the elements equal to zero in a sample of the tensor, one block of 1024

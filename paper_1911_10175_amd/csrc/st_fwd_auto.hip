@@ -37,7 +37,7 @@ __global__ __launch_bounds__(256, 4) void fwd_auto_kernel(Geom g, const float *_
                                                sq.kt_major, lds);
     } else {
         if ((long long)blockIdx.x >= dq.blocks) return;
-        fwd_dense_body<3, 3, KQ, TWD>(g, in, wd, out, dq.tiles_w, dq.tiles_h, dq.kgroups, dq.total_tiles, 1, 0, (int)blockIdx.x, 0, lds);
+        fwd_dense_body<3, 3, KQ, TWD>(g, in, wd, out, nullptr, dq.tiles_w, dq.tiles_h, dq.kgroups, dq.total_tiles, 1, 0, (int)blockIdx.x, 0, lds);
     }
 }
 

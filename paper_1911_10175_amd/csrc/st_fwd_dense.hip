@@ -1,20 +1,23 @@
-// Dense unit-stride correlation on the matrix cores: the control the zero-skipping kernels are
+// Dense correlation on the matrix cores, 3x3 at stride 1 and 2: the form without tests the zero-skipping kernels are
 // measured against (the role the library's dense "direct" convolution plays in SparseTrain
 // Sec. 4).  Used for FWD and, with transposed filters, for BWI.
 //
-// Implicit GEMM with v_mfma_f32_32x32x2_f32: rows = 32 output pixels, columns = 32 output
-// channels, reduction = 2 input channels of one filter tap per instruction.  A wavefront owns an
-// 8x8 pixel tile times 32 output channels (two accumulator blocks).  The 4 wavefronts of a
-// workgroup cover KQ column blocks of 4/KQ pixel tiles; the wavefronts that share a pixel tile
-// stage its input halo for one 16-channel block cooperatively in LDS (zero padding is applied
-// there once), double-buffered: the global loads for block cb+1 are issued at the first tap of
-// block cb and written to the other buffer after the last tap, one barrier per block.  For every
-// tap the A operand is read from LDS at the shifted pixel.  The B operand (filters) is read from
-// a copy that a small prologue kernel writes into the workspace in the order the MFMA lanes
-// consume it, [K/32][C/16][tap][c half][32 k][8 c]: a lane fetches its 8 values of a step with
-// two 16-byte loads and a wavefront reads 2 KB contiguously (fetching them element-wise from the
-// library layout takes 8 load instructions per 16 MFMAs and holds the matrix pipe at about half
-// rate); the loads for step s+1 are in flight during the MFMAs of step s.  No tests, no skipping.
+// Implicit GEMM with v_mfma_f32_32x32x16_bf16 on the bf16 pieces of both operands (st_split.hpp): rows = 32 output
+// channels, columns = 32 output pixels, reduction = the 16 input channels of a block for one filter tap, six
+// instructions per tap and block.  A wavefront owns an 8x8 (4x14, 2x28) pixel tile times 32 output channels (two
+// accumulator blocks).  The 4 wavefronts of a workgroup cover KQ column blocks of 4/KQ pixel tiles; the wavefronts
+// that share a pixel tile stage its input halo for one 16-channel block cooperatively in LDS, split into pieces on
+// the way (zero padding is applied there once), double-buffered: the global loads for block cb+1 are issued at
+// the first tap of block cb and written to the other buffer after the last tap, one barrier per block.  For every
+// tap the input operand is read from LDS at the shifted pixel.  The filters come from
+// a copy that a small prologue kernel writes into the workspace, already split, in the order the MFMA lanes
+// consume it, [K/32][C/16][tap][piece][c half][32 k][8 c].  No tests, no skipping.
+//
+// Measured (N = 32; the same structure on v_mfma_f32_32x32x2_f32 -> now): 256->256 @56 1022 -> 555 us (213 TFLOP/s;
+// the bare instruction stream reaches 1800 / 6 = 300), 512->512 @28 1090 -> 613, 512->512 @14 292 -> 182,
+// 128->128 @28 78 -> 49, 512->512 @7 92 -> 67, 128->128 @56 stride 2 86 -> 52.  Counters on 256->256 @56: matrix pipe
+// busy 65 % of the time (3136 workgroups are 3.06 rounds of the 1024 resident ones), LDS 50 %, two thirds of it bank
+// conflicts where a tile row ends.
 #include <cstdlib>
 
 #include "st_common.hpp"
@@ -34,15 +37,25 @@ __global__ __launch_bounds__(256) void reformat_filters_kernel(int Ko, int Ci, i
     reformat_filters_block(blockIdx.x, Ko, Ci, S, R, transpose, w, wd, total);
 }
 
-// out = part[0] + part[1] + ... (fixed order), float4 at a time, on a capped grid
+__global__ __launch_bounds__(256) void pw_filters_kernel(int Ko, int Ci, int transpose, const float *__restrict__ w,
+                                                         float *__restrict__ wd, size_t total, const unsigned *sel, unsigned thr)
+{
+    if (form_deselected(sel, 1, thr)) return;
+    pw_filters_block(blockIdx.x, Ko, Ci, transpose, w, wd, total);
+}
+
+// 1x1 layers served by the pixel-wise kernel (st_pw_dense.hip); its minibatch-wide pixel numbers are kept in int
+bool pointwise(const Geom &g) { return g.R == 1 && g.S == 1 && (long long)g.N * g.Ho * g.Wo <= 0x7fffff00LL; }
+
+// out += part[0] + part[1] + ... (splits - 1 of them, in that order), float4 at a time, on a capped grid
 __global__ __launch_bounds__(256) void sum_partials_kernel(const float4 *__restrict__ part, float4 *__restrict__ out,
                                                            size_t n4, int splits, const unsigned *sel, unsigned thr)
 {
     if (form_deselected(sel, 1, thr)) return;
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 256) {
-        float4 a = part[i];
+        float4 a = out[i];
         for (int p = 1; p < splits; ++p) {
-            const float4 v = part[(size_t)p * n4 + i];
+            const float4 v = part[(size_t)(p - 1) * n4 + i];
             a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
         }
         out[i] = a;
@@ -64,10 +77,10 @@ hipError_t launch_cfg(const Geom &g, const float *in, const float *wd, float *ou
     if (total_tiles > 0x7fffffffLL || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const int cs = MODE == 0 ? dense_channel_split(g) : 1;
     const size_t n_out = (size_t)g.N * g.Ko * g.Ho * g.Wo;
-    // partial outputs sit behind the filter copy in the workspace
-    float *part = cs > 1 ? const_cast<float *>(wd) + (fwd_dense_filter_bytes(g) + 255) / 256 * 256 / sizeof(float) : out;
+    // partial outputs of the shares after the first sit behind the filter copy in the workspace
+    float *part = cs > 1 ? const_cast<float *>(wd) + (fwd_dense_filter_bytes(g) + 255) / 256 * 256 / sizeof(float) : nullptr;
     hipLaunchKernelGGL((fwd_dense_kernel<R, S, KQ, TWD, MODE, PI, PJ>), dim3((unsigned)blocks, cs), dim3(256), 0, s, g, in, wd,
-                       part, tiles_w, tiles_h, kgroups, (int)total_tiles, cs, n_out);
+                       out, part, tiles_w, tiles_h, kgroups, (int)total_tiles, cs, n_out);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || cs == 1) return e;
     const size_t n4 = n_out / 4;
@@ -142,21 +155,32 @@ bool fwd_dense_supported(const Geom &g)
 size_t fwd_dense_filter_bytes(const Geom &g)
 {
     // output channels padded to a multiple of 128 so that every column block a workgroup touches exists
-    return (size_t)ceil_div(g.Ko, 128) * 128 * g.Ci * g.S * g.R * sizeof(float);
+    // (three bf16 pieces per element; the pixel-wise 1x1 kernel takes fp32)
+    return (size_t)ceil_div(g.Ko, 128) * 128 * g.Ci * g.S * g.R * (pointwise(g) ? 4 : 6);
 }
 
 size_t fwd_dense_workspace_bytes(const Geom &g)
 {
     // filter copy, then the partial outputs of a channel-split launch
-    const size_t n = fwd_dense_filter_bytes(g);
+    // (the first share writes the output itself)
+    const size_t n = fwd_dense_filter_bytes(g), out = (size_t)g.N * g.Ko * g.Ho * g.Wo * sizeof(float);
     const int cs = dense_channel_split(g);
     if (cs == 1) return n;
-    return (n + 255) / 256 * 256 + (size_t)cs * g.N * g.Ko * g.Ho * g.Wo * sizeof(float);
+    const size_t need = (n + 255) / 256 * 256 + (size_t)(cs - 1) * out;
+    // never less than the fp32 copy and the partial outputs this query has always counted for such a launch
+    const size_t before = (n / 6 * 4 + 255) / 256 * 256 + (size_t)dense_channel_split_pow2(g) * out;
+    return need > before ? need : before;
 }
 
 hipError_t launch_reformat_filters(const Geom &g, bool transpose, const float *w, float *wd, hipStream_t s)
 {
-    const size_t total = fwd_dense_filter_bytes(g) / sizeof(float);
+    if (pointwise(g)) {
+        const size_t n = fwd_dense_filter_bytes(g) / 4;
+        hipLaunchKernelGGL(pw_filters_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, g.Ko, g.Ci, transpose ? 1 : 0, w, wd, n,
+                           g.sel, g.thr);
+        return hipGetLastError();
+    }
+    const size_t total = fwd_dense_filter_bytes(g) / 48;                 // 8 elements per thread
     hipLaunchKernelGGL(reformat_filters_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, g.Ko, g.Ci,
                        g.S, g.R, transpose ? 1 : 0, w, wd, total, g.sel, g.thr);
     return hipGetLastError();
@@ -167,11 +191,7 @@ hipError_t launch_fwd_dense(const Geom &g, const float *in, const float *wd, flo
     if (g.sw == 2) return launch_s2_fwd(g, in, wd, out, s);
     if (g.uw == 2) return launch_s2_bwi(g, in, wd, out, s);
     if (g.R == 3 && g.S == 3) return launch_rs<3, 3>(g, in, wd, out, s);
-    if (g.R == 1 && g.S == 1) {
-        // minibatch-wide pixel numbering of the pointwise kernel is kept in int
-        if ((long long)g.N * g.Ho * g.Wo <= 0x7fffff00LL) return launch_pw_dense(g, in, wd, out, s);
-        return launch_rs<1, 1>(g, in, wd, out, s);
-    }
+    if (g.R == 1 && g.S == 1) return pointwise(g) ? launch_pw_dense(g, in, wd, out, s) : launch_rs<1, 1>(g, in, wd, out, s);
     return hipErrorInvalidValue;
 }
 

@@ -2,6 +2,7 @@
 // fwd_dense_kernel) and the tiling choices of its launches, for the files that instantiate it.
 #pragma once
 #include "st_common.hpp"
+#include "st_split.hpp"
 
 namespace st {
 namespace {
@@ -38,8 +39,9 @@ struct FwdDenseCfg {
         const int fit = 163840 / (2 * (4 / kq) * BUF * 4);
         return fit >= 4 ? 4 : (fit >= 1 ? fit : 1);
     }
-    static constexpr int XST = 20;                  // floats per staged pixel (16 channels + 4 pad)
-    static constexpr int BUF = ((HP * XST + 63) / 64) * 64;   // floats per halo buffer
+    // halo buffer: [3 pieces][2 halves of the 16 channels][halo pixel][8 channels] bf16, i.e. 16 bytes per pixel and
+    // half, so that neighbouring lanes (pixels) of an operand read are 16 bytes apart
+    static constexpr int BUF = ((HP * 24 + 63) / 64) * 64;    // floats per halo buffer
 };
 
 // KQ = column blocks (of 32 output channels) per workgroup: 1, 2 or 4; TQ = 4/KQ pixel tiles.
@@ -51,12 +53,12 @@ constexpr int fwd_dense_lds_floats() { return 2 * (4 / KQ) * FwdDenseCfg<R, S, T
 
 template <int R, int S, int KQ, int TWD, int MODE = 0, int PI = 0, int PJ = 0>
 __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__restrict__ in, const float *__restrict__ wd,
-                                               float *__restrict__ out, int tiles_w, int tiles_h, int kgroups,
+                                               float *__restrict__ out, float *__restrict__ parts, int tiles_w, int tiles_h, int kgroups,
                                                int total_tiles, int csplit, size_t part_stride, int wg, int cshare,
                                                float *lds_base)
 {
     using Cfg = FwdDenseCfg<R, S, TWD, MODE, PI, PJ>;
-    constexpr int TH = Cfg::TH, TW = Cfg::TW, HW = Cfg::HW, HP = Cfg::HP, XST = Cfg::XST, BUF = Cfg::BUF;
+    constexpr int TH = Cfg::TH, TW = Cfg::TW, HW = Cfg::HW, HP = Cfg::HP, BUF = Cfg::BUF;
     constexpr int TAPS = S * R, TQ = 4 / KQ, NPIX = Cfg::NPIX, NT = Cfg::NT, PSTEP = Cfg::PSTEP;
     constexpr int NLD = (HP * 4 + KQ * 64 - 1) / (KQ * 64);      // float4 loads per lane and block
 
@@ -73,32 +75,28 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
     const int oh0 = th * TH, ow0 = tw * TW;         // MODE 2: in units of the parity class's own grid
     const int ih0 = MODE == 2 ? oh0 : oh0 * PSTEP - g.ph, iw0 = MODE == 2 ? ow0 : ow0 * PSTEP - g.pw;
     const int CiB = g.Ci / kBlk, KoB = g.Ko / kBlk;
-    // channel split (launches with few tiles): share cshare reduces its part of the channel blocks
-    // into its own partial output, which sum_partials_kernel adds up afterwards
-    const int cb0 = cshare * (CiB / csplit), cb1 = cb0 + CiB / csplit;            // CiB % csplit == 0
-    out += cshare * part_stride;
+    // channel split (launches with few tiles): share 0 reduces its part of the channel blocks into the output,
+    // the others into partial outputs of their own, which sum_partials_kernel adds to it afterwards
+    const int cb0 = CiB * cshare / csplit, cb1 = CiB * (cshare + 1) / csplit;
+    if (cshare > 0) out = parts + (cshare - 1) * part_stride;
     const int kb32 = kg * KQ + kqi;                 // this wavefront's column block
     const bool k_ok = kb32 * 32 < g.Ko;
     const bool active = tile_ok && k_ok;
 
     const int l32 = lane % 32, half = lane / 32;
 
-    floatx16 acc[2];
+    // running sums of the two pixel blocks, and the matrix cores' own accumulators of the current channel block
+    floatx16 acc[2], part[2];
 #pragma unroll
     for (int pb = 0; pb < 2; ++pb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[pb][r] = 0.f;
 
-    // B operand: lane supplies filter element (k = kb32*32 + l32, c = j + 8*half), j = 0..7, from
-    // the reformatted copy: element offset (kb32*CiB*TAPS + step)*512 + half*256 + l32*8 + j
-    const float *bbase = wd + (size_t)(k_ok ? kb32 : 0) * CiB * TAPS * 512 + half * 256 + l32 * 8;
-    auto load_b = [&](int s, float (&b)[8]) __attribute__((always_inline)) {
-        const float4 *p = reinterpret_cast<const float4 *>(bbase + (size_t)s * 512);
-        const float4 lo = p[0], hi = p[1];
-        b[0] = lo.x; b[1] = lo.y; b[2] = lo.z; b[3] = lo.w;
-        b[4] = hi.x; b[5] = hi.y; b[6] = hi.z; b[7] = hi.w;
-    };
-    // A operand: lane supplies input (pixel = pb*32 + l32 of the tile, channels half*8 .. half*8+7)
+    // filter operand: lane supplies the pieces of element (k = kb32*32 + l32, c = half*8 .. half*8+7) from the
+    // reformatted copy: 16-byte unit (kb32*CiB*TAPS + step)*192 + piece*64 + lane
+    const bf16x8 *bbase = reinterpret_cast<const bf16x8 *>(wd) + (size_t)(k_ok ? kb32 : 0) * CiB * TAPS * 192;
+    auto filters = [&](int step, int q) __attribute__((always_inline)) { return bbase[(size_t)step * 192 + q * 64 + lane]; };
+    // input operand: lane supplies pixel pb*32 + l32 of the tile, channels half*8 .. half*8+7
     int apix[2];
 #pragma unroll
     for (int pb = 0; pb < 2; ++pb) {
@@ -107,8 +105,12 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
     }
 
     // halo staging: the KQ wavefronts of a tile split its HP*4 float4 among their KQ*64 lanes
-    const int sl = kqi * kWave + lane;
+    // (lane index the compiler cannot see through: the addresses are worked out per block instead of being kept in
+    // registers across its MFMAs)
     auto load_halo = [&](int cb, float4 (&h)[NLD]) __attribute__((always_inline)) {
+        int sl = lane;
+        asm volatile("" : "+v"(sl));
+        sl += kqi * kWave;
 #pragma unroll
         for (int jj = 0; jj < NLD; ++jj) {
             const int idx = jj * (KQ * kWave) + sl;
@@ -121,90 +123,127 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
         }
     };
     auto store_halo = [&](float *buf, const float4 (&h)[NLD]) __attribute__((always_inline)) {
+        int sl = lane;
+        asm volatile("" : "+v"(sl));
+        sl += kqi * kWave;
 #pragma unroll
         for (int jj = 0; jj < NLD; ++jj) {
             const int idx = jj * (KQ * kWave) + sl;
             const int pix = idx >> 2, q = idx & 3;
-            if (pix < HP) *reinterpret_cast<float4 *>(buf + pix * XST + q * 4) = h[jj];
+            if (pix < HP) {
+                bf16x4 p[3];
+                split4(h[jj], p);
+                bf16x4 *dst = reinterpret_cast<bf16x4 *>(buf) + ((q >> 1) * HP + pix) * 2 + (q & 1);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) dst[i * (4 * HP)] = p[i];
+            }
         }
     };
 
-    constexpr int kWaitOlder = vmcnt_imm(2);          // all but the 2 newest loads
-    float bcur[8], bnxt[8];
     float4 hreg[NLD];
     load_halo(cb0, hreg);
     store_halo(lds_base + tqi * BUF, hreg);
-    load_b(cb0 * TAPS + Cfg::ftap(0), bcur);
+    bf16x8 f0 = filters(cb0 * TAPS + Cfg::ftap(0), 0), f1 = filters(cb0 * TAPS + Cfg::ftap(0), 1), f2 = filters(cb0 * TAPS + Cfg::ftap(0), 2);
     __syncthreads();
 
     for (int cb = cb0; cb < cb1; ++cb) {
-        const float *lds = lds_base + (((cb - cb0) & 1) * TQ + tqi) * BUF;
+        const bf16x8 *lds = reinterpret_cast<const bf16x8 *>(lds_base + (((cb - cb0) & 1) * TQ + tqi) * BUF) + half * HP;
+        auto input = [&](int tp, int pb, int q) __attribute__((always_inline)) {
+            return lds[apix[pb] + Cfg::dv(tp) * HW + Cfg::du(tp) + q * 2 * HP];
+        };
+        bf16x8 x0[2], x1[2], x2[2];
 #pragma unroll
-        for (int tp = 0; tp < NT; ++tp) {
-            {
-                const int v = Cfg::dv(tp), u = Cfg::du(tp);
-                // next step's filters fly during this step's MFMAs (the last step re-reads its own)
-                const int nstep = tp + 1 < NT ? cb * TAPS + Cfg::ftap(tp + 1 < NT ? tp + 1 : 0)
-                                              : min(cb + 1, cb1 - 1) * TAPS + Cfg::ftap(0);
-                load_b(nstep, bnxt);
-                __builtin_amdgcn_sched_barrier(0);              // keep these loads ahead of the MFMAs below
-                float a[2][8];
+        for (int pb = 0; pb < 2; ++pb) {
+            x0[pb] = input(0, pb, 0);
+            x1[pb] = input(0, pb, 1);
+            x2[pb] = input(0, pb, 2);
+        }
+        if (cb + 1 < cb1) load_halo(cb + 1, hreg);          // lands during this block's MFMAs
+        // One tap = six products of two pixel blocks.  Every operand register is refilled for the next tap as soon as
+        // its last product of this one has been issued (only filter piece 0, used first and last, has a second
+        // set), which is what fits the accumulators and both operands into the 128 registers of four wavefronts per
+        // SIMD.  The last tap requests the filters of the next block's first one.
+        static_for<0, NT>([&](auto T) __attribute__((always_inline)) {
+            constexpr int tp = decltype(T)::value;
+            constexpr bool last = tp + 1 == NT;
+            constexpr int nt = last ? 0 : tp + 1;
+            const int nstep = (last ? min(cb + 1, cb1 - 1) : cb) * TAPS + Cfg::ftap(nt);
+            auto mul = [&](const bf16x8 &f, const bf16x8 (&x)[2], bool first) __attribute__((always_inline)) {
+                if (active) {                               // rows = output channels, columns = pixels
 #pragma unroll
-                for (int pb = 0; pb < 2; ++pb) {
-                    const float *p = lds + (apix[pb] + v * HW + u) * XST + half * 8;
-                    const float4 lo = *reinterpret_cast<const float4 *>(p);
-                    const float4 hi = *reinterpret_cast<const float4 *>(p + 4);
-                    a[pb][0] = lo.x; a[pb][1] = lo.y; a[pb][2] = lo.z; a[pb][3] = lo.w;
-                    a[pb][4] = hi.x; a[pb][5] = hi.y; a[pb][6] = hi.z; a[pb][7] = hi.w;
+                    for (int pb = 0; pb < 2; ++pb)
+                        part[pb] = first ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, x[pb], floatx16{}, 0, 0, 0)
+                                         : __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, x[pb], part[pb], 0, 0, 0);
                 }
-                __builtin_amdgcn_s_waitcnt(kWaitOlder);         // bcur (and anything older) has arrived
                 __builtin_amdgcn_sched_barrier(0);
-                // The next block's halo is requested here, after the wait, so that the first wait
-                // that covers these loads is the one of the next tap: they land during the MFMAs.
-                if (tp == 0 && cb + 1 < cb1) {
-                    load_halo(cb + 1, hreg);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                if (active) {
+            };
+            const bf16x8 f0n = filters(nstep, 0);
+            mul(f0, x0, tp == 0);
+            mul(f2, x0, false);
+            f2 = filters(nstep, 2);
+            mul(f1, x0, false);
+            if constexpr (!last) { x0[0] = input(nt, 0, 0); x0[1] = input(nt, 1, 0); }
+            mul(f1, x1, false);
+            f1 = filters(nstep, 1);
+            mul(f0, x1, false);
+            if constexpr (!last) { x1[0] = input(nt, 0, 1); x1[1] = input(nt, 1, 1); }
+            mul(f0, x2, false);
+            if constexpr (!last) { x2[0] = input(nt, 0, 2); x2[1] = input(nt, 1, 2); }
+            f0 = f0n;
+        });
+        if (active) {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j)
+            for (int pb = 0; pb < 2; ++pb)
 #pragma unroll
-                        for (int pb = 0; pb < 2; ++pb)
-                            acc[pb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[pb][j], bcur[j], acc[pb], 0, 0, 0);
-                }
-#pragma unroll
-                for (int j = 0; j < 8; ++j) bcur[j] = bnxt[j];
-            }
+                for (int r = 0; r < 16; ++r) acc[pb][r] += part[pb][r];
         }
         if (cb + 1 < cb1) store_halo(lds_base + (((cb + 1 - cb0) & 1) * TQ + tqi) * BUF, hreg);
         __syncthreads();
     }
 
-    // D layout of the 32x32 block: column = lane % 32, row = 8*(r/4) + 4*(lane/32) + r%4
-    const int k = kb32 * 32 + l32;
-    if (active && k < g.Ko) {
-        const int kb = k / kBlk, ki = k % kBlk;
+    // D layout of the 32x32 block: column (pixel) = lane % 32, row (channel) = 8*(r/4) + 4*(lane/32) + r%4:
+    // four consecutive channels per group of 4 accumulators, one 16-byte store each
+    if (!active) return;
+    auto where = [&](int pb, int &oh, int &ow) __attribute__((always_inline)) {
+        const int p = pb * 32 + l32;
+        oh = MODE == 2 ? 2 * (oh0 + p / TW) + PI : oh0 + p / TW;
+        ow = MODE == 2 ? 2 * (ow0 + p % TW) + PJ : ow0 + p % TW;
+        return p < NPIX && oh < g.Ho && ow < g.Wo;
+    };
+    bool finite = true;
 #pragma unroll
-        for (int pb = 0; pb < 2; ++pb)
+    for (int pb = 0; pb < 2; ++pb) {
+        int oh, ow;
+        if (!where(pb, oh, ow)) continue;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int p = pb * 32 + 8 * (r / 4) + 4 * half + (r % 4);
-                const int oh = MODE == 2 ? 2 * (oh0 + p / TW) + PI : oh0 + p / TW;
-                const int ow = MODE == 2 ? 2 * (ow0 + p % TW) + PJ : ow0 + p % TW;
-                if (p < NPIX && oh < g.Ho && ow < g.Wo)
-                    out[act_off(n, kb, oh, ow, KoB, g.Ho, g.Wo) + ki] = acc[pb][r];
-            }
+        for (int gq = 0; gq < 4; ++gq) {
+            const int k = kb32 * 32 + 8 * gq + 4 * half;
+            if (k >= g.Ko) continue;
+            const float4 r = make_float4(acc[pb][4 * gq], acc[pb][4 * gq + 1], acc[pb][4 * gq + 2], acc[pb][4 * gq + 3]);
+            finite = finite && split_finite(r.x) && split_finite(r.y) && split_finite(r.z) && split_finite(r.w);
+            *reinterpret_cast<float4 *>(out + act_off(n, k / kBlk, oh, ow, KoB, g.Ho, g.Wo) + k % kBlk) = r;
+        }
+    }
+    if (__builtin_expect(!finite, 0)) {             // values outside the range of the bf16 pieces took part
+#pragma unroll 1
+        for (int i = 0; i < 32; ++i) {
+            int oh, ow;
+            const int k = kb32 * 32 + 8 * (i % 16 / 4) + 4 * half + i % 4;
+            if (!where(i / 16, oh, ow) || k >= g.Ko) continue;
+            float *o = out + act_off(n, k / kBlk, oh, ow, KoB, g.Ho, g.Wo) + k % kBlk;
+            if (!split_finite(*o)) *o = split_exact_corr(g, in, n, k, oh, ow, cb0, cb1);
+        }
     }
 }
 
 template <int R, int S, int KQ, int TWD, int MODE = 0, int PI = 0, int PJ = 0>
 __global__ __launch_bounds__(256, (FwdDenseCfg<R, S, TWD, MODE, PI, PJ>::minw(KQ))) void fwd_dense_kernel(
-    Geom g, const float *__restrict__ in, const float *__restrict__ wd, float *__restrict__ out, int tiles_w, int tiles_h,
-    int kgroups, int total_tiles, int csplit, size_t part_stride)
+    Geom g, const float *__restrict__ in, const float *__restrict__ wd, float *__restrict__ out, float *__restrict__ parts,
+    int tiles_w, int tiles_h, int kgroups, int total_tiles, int csplit, size_t part_stride)
 {
     if (form_deselected(g.sel, g.want, g.thr)) return;
     __shared__ __attribute__((aligned(16))) float lds_all[fwd_dense_lds_floats<R, S, KQ, TWD, MODE, PI, PJ>()];
-    fwd_dense_body<R, S, KQ, TWD, MODE, PI, PJ>(g, in, wd, out, tiles_w, tiles_h, kgroups, total_tiles, csplit, part_stride,
+    fwd_dense_body<R, S, KQ, TWD, MODE, PI, PJ>(g, in, wd, out, parts, tiles_w, tiles_h, kgroups, total_tiles, csplit, part_stride,
                                                  (int)blockIdx.x, (int)blockIdx.y, lds_all);
 }
 
@@ -223,15 +262,26 @@ inline void dense_tiling(const Geom &g, int *twd, int *kq, long long *blocks)
 
 // Channel split of the unit-stride 3x3 launches that would leave most of the chip idle (7x7 and 14x14
 // layers: a workgroup per pixel tile and 128 output channels gives 128 workgroups for 512 -> 512 @7,
-// N = 32, each walking all 512 input channels): 2, 4 or 8 shares, enough for about two workgroups per
-// compute unit.  Depends on the geometry only, so that the workspace query and the launch agree.
+// N = 32, each walking all 512 input channels): up to 8 shares of at least two channel blocks, enough for
+// 384 workgroups.  Depends on the geometry only, so that the workspace query and the launch agree.
 inline int dense_channel_split(const Geom &g)
 {
     if (g.R != 3 || g.S != 3 || g.sw != 1 || g.uw != 1) return 1;
     int twd, kq;
     long long blocks;
     dense_tiling(g, &twd, &kq, &blocks);
-    if (blocks >= 384) return 1;
+    const int CiB = g.Ci / kBlk;
+    int cs = 1;
+    while (cs < 8 && blocks * cs < 384 && CiB / (cs + 1) >= 2) ++cs;
+    return cs;
+}
+
+// The partial outputs counted by the workspace query for such a launch (a power of two of them)
+inline int dense_channel_split_pow2(const Geom &g)
+{
+    int twd, kq;
+    long long blocks;
+    dense_tiling(g, &twd, &kq, &blocks);
     const int CiB = g.Ci / kBlk;
     int cs = 1;
     while (cs < 8 && blocks * cs < 512 && CiB % (cs * 2) == 0 && CiB / (cs * 2) >= 2) cs *= 2;

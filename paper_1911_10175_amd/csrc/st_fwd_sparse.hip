@@ -31,7 +31,8 @@ bool fwd_sparse_supported(const Geom &g)
     return false;
 }
 
-// Break-even points measured on the layer shapes of the paper's Table 1: the zero-skipping form needs 20-25 % zeros
+// Break-even points of the zero-skipping kernel against fp32 matrix instructions (what st_conv_sparse_threshold
+// reports), measured on the layer shapes of the paper's Table 1: it needs 20-25 % zeros
 // with 128 output channels per wavefront and 36-41 % with 64; the stride-2 FWD tests 2.25 taps
 // per element and its BWI is held by the filter stream of small tiles; a 1x1 layer saves K/64
 // multiply-adds per zero.
@@ -43,6 +44,23 @@ unsigned fwd_sparse_threshold(const Geom &g)
     if (g.uw == 2) return 450;
     const bool wide = g.Ko % 128 == 0;
     return wide ? 250 : 400;
+}
+
+// Where the self-selecting entry points switch.  Against the dense kernels of today (fp32 accuracy from bf16 pieces)
+// zero-skipping pays much later; N = 32, us, zero-skipping at 70 / 90 % zeros against dense:
+//   256->256 @56 603 / 495 : 553   512->512 @28 613 / 505 : 613   128->128 @28 56 / 49 : 49   256->256 @14 59 / 53 : 58
+//   64->64 @56 71 / 57 : 54        512->512 @7 64 / 60 : 67       N = 1 512->512 @14 67 / 60 : 34
+// i.e. at about 70-75 % on the large layers with whole groups of 128 produced channels (650: what takes part in the
+// one-kernel launch of st_fwd_auto.hip) and at or above 85-90 % on the others.  The stride-2 FWD stays behind at 90 %
+// (128->128 @56 76 : 52, 256->256 @28 129 : 77); its BWI, four short launches per layer in the dense form, does not
+// (256->256 @28 106 / 85 : 114).
+unsigned fwd_auto_threshold(const Geom &g)
+{
+    const unsigned t = fwd_sparse_threshold(g);
+    if (t == 0 || t > 1000 || !fwd_dense_supported(g)) return t;
+    if (g.sw == 2) return 1001;
+    if (g.uw == 2) return t;
+    return fwd_auto_combined_supported(g) ? 650 : 850;
 }
 
 namespace {

@@ -194,7 +194,7 @@ struct PrepareArgs {
     int transpose;              // BWI
     int paired;                 // layout of the first copy (fwd_sparse_filters_paired)
     unsigned n_wave;            // workgroups of the first copy
-    size_t total_dense;         // elements of the second copy
+    size_t total_dense;         // pieces of 8 elements of the second copy
 };
 
 __global__ __launch_bounds__(256) void auto_prepare_kernel(PrepareArgs a)
@@ -286,7 +286,7 @@ hipError_t launch_auto_prepare(const Geom &g, bool transpose, const float *act, 
     a.S = g.S; a.R = g.R; a.Ko = g.Ko; a.Ci = g.Ci; a.transpose = transpose ? 1 : 0;
     a.paired = fwd_sparse_filters_paired(g) ? 1 : 0;
     const long long n_wave = (long long)a.KB * a.CB * g.S * g.R;
-    a.total_dense = fwd_dense_filter_bytes(g) / sizeof(float);
+    a.total_dense = fwd_dense_filter_bytes(g) / 48;
     const long long n_dense = (long long)((a.total_dense + 255) / 256);
     if (n_wave + n_dense + kSampleParts > 0x7fffffffLL) return hipErrorInvalidValue;
     a.n_wave = (unsigned)n_wave;

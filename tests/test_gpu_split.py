@@ -1,0 +1,92 @@
+"""The dense kernels form fp32 products from bf16 pieces on the matrix cores: fp32 accuracy on ordinary values, and
+plain fp32 results where a value lies outside the range of the pieces.  Every test here needs an MI355X."""
+import numpy as np
+import pytest
+import torch
+
+import stgen
+from oracle import st_ref
+from oracle.st_ref import Geom
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from tests.gpu_harness import DeviceLayer
+
+# one geometry per kernel shape: column blocks per workgroup (16 / 48 / 80 and more produced channels), tile widths
+# 8, 14 and 28, rows and columns left over, the channel split, stride 2 (and its four parity classes in BWI), 1x1
+GEOMS = {
+    "3x3 16->48": Geom(2, 16, 48, 9, 11, 3, 3, 1, 1, 1, 1),
+    "3x3 80->144": Geom(2, 80, 144, 7, 28, 3, 3, 1, 1, 1, 1),
+    "3x3 48->32 pad2": Geom(1, 48, 32, 5, 12, 3, 3, 1, 1, 2, 2),
+    "3x3 split": Geom(1, 256, 256, 7, 7, 3, 3, 1, 1, 1, 1),
+    "3x3 stride 2": Geom(2, 48, 80, 13, 10, 3, 3, 2, 2, 1, 1),
+    "1x1 64->64": Geom(3, 64, 64, 53, 53, 1, 1),
+    "1x1 80->48": Geom(2, 80, 48, 5, 7, 1, 1),
+}
+
+
+def inputs(g, seed):
+    x = stgen.relu_sparse(g.x_shape, 0.5, 4 * seed)
+    w = stgen.he_normal(g.w_shape, 4 * seed + 1)
+    dy = stgen.bernoulli_masked(g.y_shape, 0.5, 4 * seed + 2, 4 * seed + 3)
+    return x, w, dy
+
+
+def refs(g, x, w, dy):
+    return {"fwd": st_ref.conv_fwd(g, x, w), "bwi": st_ref.conv_bwi(g, dy, w)}
+
+
+def terms(g):
+    """Products per output.  An fp32 sum of n products in any order is within (n + 1) 2^-24 of the sum of their
+    magnitudes, the pieces left out of a product are within 2^-23 of it, and n results below the smallest normal number
+    may each be off by half the smallest subnormal."""
+    return {"fwd": g.C * g.R * g.S, "bwi": g.K * g.R * g.S}
+
+
+def check(g, x, w, dy, label):
+    L = DeviceLayer(g, x, w, dy)
+    for p, (ref, ref_abs) in refs(g, x, w, dy).items():
+        got = getattr(L, p)(True).astype(np.float64)
+        n = terms(g)[p]
+        fine = np.isfinite(ref)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)), f"{label} {p}: NaN elsewhere"
+        inf = np.isinf(ref)
+        assert np.array_equal(got[inf], ref[inf]), f"{label} {p}: infinities"
+        off = np.abs(got[fine] - ref[fine])
+        bound = (n + 3) * 2.0 ** -24 * ref_abs[fine] + n * 2.0 ** -150
+        assert np.all(off <= bound), f"{label} {p}: {np.max(off / np.maximum(bound, 1e-300))} of the bound"
+
+
+@pytest.mark.parametrize("name", GEOMS)
+def test_dense_forms_keep_fp32_accuracy(name):
+    """Values of very different size side by side: every bit of each of them counts somewhere."""
+    g = GEOMS[name]
+    x, w, dy = inputs(g, 11)
+    rng = np.random.default_rng(5)
+    for t in (x, w, dy):
+        t *= np.float32(2.0) ** rng.integers(-20, 21, t.shape).astype(np.float32)
+    check(g, x, w, dy, name)
+
+
+@pytest.mark.parametrize("name", GEOMS)
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.4e38, 1e-30, 1e-35, 1e-42])
+def test_dense_forms_outside_the_range_of_the_pieces(name, value):
+    """Infinities, NaN, the largest and the smallest values: in x, in dy and in w, a few elements each."""
+    g = GEOMS[name]
+    for where in range(3):
+        x, w, dy = inputs(g, 13)
+        # no zeros in the other tensors (0 * inf: the padding's share is not defined) and no overflow of finite sums
+        for t in (x, w, dy):
+            t[t == 0] = 0.25
+            t *= 2.0 ** -6
+        t = (x, w, dy)[where].reshape(-1)
+        t[[0, t.size // 3, t.size - 1]] = value
+        check(g, x, w, dy, f"{name} {value} in {'x w dy'.split()[where]}")
+
+
+def test_dense_forms_on_subnormal_tensors():
+    """A whole tensor below the smallest normal number against huge filters."""
+    g = GEOMS["3x3 16->48"]
+    x, w, dy = inputs(g, 17)
+    check(g, x * np.float32(1e-39), w * np.float32(1e34), dy * np.float32(1e-39), "subnormal")
