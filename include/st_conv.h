@@ -157,8 +157,8 @@ st_status st_conv_bww_dy(const st_conv_desc *desc, const float *x, const float *
  * the x-testing form is the faster one).  Same tensors, same result, no host
  * synchronisation; the cost is the sampling pass (at most 256 KB of x and of dy are read once more)
  * and the empty launches.  Where tiled kernels exist, the dense form (st_conv_bww_dense) is the
- * third candidate: it runs when even the sparser operand has fewer zeros than the measured
- * break-even, 25 % for 3x3 layers (Sec. 5.3 combines the kernels with dense ones layer by layer).
+ * third candidate: it runs when even the sparser operand has fewer than 75 % zeros on 3x3 layers
+ * (measured break-even 85-90 %; Sec. 5.3 combines the kernels with dense ones layer by layer).
  * Two kinds of layer are decided without sampling: 1x1 layers, where a zero saves too few
  * multiply-adds to beat the matrix cores at any zero fraction measured (up to 95 %), go straight to the dense form;
  * stride-2 3x3 layers always test dy (x has four times the elements and each feeds fewer taps,

@@ -29,6 +29,7 @@
 #include <type_traits>
 
 #include "st_common.hpp"
+#include "st_split.hpp"
 
 namespace st {
 namespace {
@@ -469,21 +470,60 @@ __global__ __launch_bounds__(512, 4) void bww_sparse_either_kernel(BwwArgs A, Bw
 }
 
 // ------------------------------------------------------------------------------------------
-// dense kernel: tiles run over the OUTPUT image; LDS holds the dy tile and the x halo.
-// v_mfma_f32_32x32x2_f32 with rows = 32 input channels, columns = 32 output channels, reduction
-// = 2 pixels per instruction; one accumulator block per filter tap.
+// dense kernel: tiles run over the OUTPUT image; LDS holds the dy tile and the x halo as bf16 pieces (st_split.hpp).
+// v_mfma_f32_32x32x16_bf16 with rows = 32 output channels, columns = 32 input channels, reduction = 16 pixels per
+// instruction, six instructions per filter tap.  The reduction runs over thousands of pixels: the six products of 16
+// pixels are added up in a fresh accumulator and joined to the tap's fp32 sum on the vector ALUs, so a sum takes one
+// rounding per 16 pixels (3136 terms: error 2e-7 of the norm; 7e-7 with v_mfma_f32_32x32x2_f32, 8e-7 with the matrix
+// cores' own long sums).
+//
+// Tiles have at most 32 pixels: 144 sums, two short accumulators, the operands of a tap and the next tile's loads then
+// fit the 256 registers of two wavefronts per SIMD, and two workgroups share a compute unit, so that one's staging
+// (two barriers per 108 matrix instructions of a wavefront) meets the other's arithmetic.  Measured (N = 32, the same
+// structure on v_mfma_f32_32x32x2_f32 and 98-pixel tiles -> now): 256->256 @56 987 -> 580 us (204 TFLOP/s), 512->512
+// @28 991 -> 650, 512->512 @14 268 -> 185, 128->128 @28 88 -> 64 (of which 20 are the sum of the partial gradients),
+// stride 2 128->128 @56 98 -> 82.
 // ------------------------------------------------------------------------------------------
-template <int R, int S, int TH, int TW, int PSTEP = 1>
-__global__ __launch_bounds__(256) void bww_dense_kernel(BwwArgs A, const float *__restrict__ x,
-                                                        const float *__restrict__ dy,
-                                                        float *__restrict__ part)
+template <int R, int S, int TH, int TW, int PSTEP>
+struct BwwDenseCfg {
+    using Halo = BwwCfg<R, S, TH, TW, PSTEP>;
+    static constexpr int TP = TH * TW, P = (TP + 15) / 16 * 16;         // tile pixels, padded to whole steps
+    // [piece][half of the 64 channels][pixel][32 channels], 64 bytes a pixel
+    static constexpr int XB = Halo::HP * 64, DB = P * 64;
+    static constexpr int LDS = 6 * (XB + DB);
+};
+
+// One element of a partial gradient with plain fp32 multiply-adds: the tiles u0 .. u1-1 of k, c, tap (v, u)
+template <int TH, int TW, int PSTEP>
+__device__ __forceinline__ float bww_exact(const BwwArgs &A, const float *x, const float *dy, int k, int c, int v, int u, int u0, int u1)
 {
-    using Cfg = BwwCfg<R, S, TH, TW, PSTEP>;
+    float s = 0.f;
+#pragma unroll 1
+    for (int unit = u0; unit < u1 && s == s; ++unit) {
+        int t = unit;
+        const int tw = t % A.tiles_w; t /= A.tiles_w;
+        const int th = t % A.tiles_h, n = t / A.tiles_h;
+#pragma unroll 1
+        for (int p = 0; p < TH * TW; ++p) {
+            const int oh = th * TH + p / TW, ow = tw * TW + p % TW;
+            const int ih = oh * PSTEP - A.ph + v, iw = ow * PSTEP - A.pw + u;
+            if (oh < A.OH && ow < A.OW && ih >= 0 && ih < A.H && iw >= 0 && iw < A.W)
+                s = fmaf(x[act_off(n, c / kBlk, ih, iw, A.C / kBlk, A.H, A.W) + c % kBlk],
+                         dy[act_off(n, k / kBlk, oh, ow, A.K / kBlk, A.OH, A.OW) + k % kBlk], s);
+        }
+    }
+    return s;
+}
+
+template <int R, int S, int TH, int TW, int PSTEP = 1>
+__global__ __launch_bounds__(256, 2) void bww_dense_kernel(BwwArgs A, const float *__restrict__ x,
+                                                           const float *__restrict__ dy, float *__restrict__ part)
+{
+    using Cfg = BwwDenseCfg<R, S, TH, TW, PSTEP>;
     if (deselected(A.sel, A.want)) return;              // uniform over the grid, before any barrier
-    constexpr int HW = Cfg::HW, HP = Cfg::HP, TP = TH * TW;
-    static_assert(TW % 2 == 0, "pixel pairs must not straddle rows");
-    __shared__ __attribute__((aligned(16))) float dyT[TP * 64];
-    __shared__ __attribute__((aligned(16))) float xT[HP * 64];
+    constexpr int HW = Cfg::Halo::HW, HP = Cfg::Halo::HP, TP = Cfg::TP, P = Cfg::P, XB = Cfg::XB, DB = Cfg::DB;
+    __shared__ __attribute__((aligned(16))) char lds[Cfg::LDS];
+    char *const dyT = lds, *const xT = lds + 6 * DB;
 
     // the wavefront index is the same in every lane: kept in a scalar register, and with it every tile coordinate
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
@@ -492,6 +532,7 @@ __global__ __launch_bounds__(256) void bww_dense_kernel(BwwArgs A, const float *
     const int split = blockIdx.x;
     const int kt = blockIdx.y / A.cgroups, cg = blockIdx.y % A.cgroups;
     const int CB = A.C / kBlk, KB = A.K / kBlk;
+    const bool active = kt * 64 + kh * 32 < A.K && cg * 64 + ch * 32 < A.C;
 
     floatx16 acc[S * R];
 #pragma unroll
@@ -503,10 +544,9 @@ __global__ __launch_bounds__(256) void bww_dense_kernel(BwwArgs A, const float *
     const int u1 = (int)((long long)A.units * (split + 1) / A.splits);
 
     // A thread's 16-byte pieces of a tile (dy tile, then x halo: 16 float4 per pixel, zeros outside the image
-    // and beyond the channel count) are asked for while the previous tile is being multiplied and written to LDS
-    // after it: the memory round trip is hidden behind the matrix work.  (A plain staging loop compiles to
-    // load, wait, write per piece: 16 round trips per tile, about as long as the tile's MFMAs.)
-    constexpr int ND = (TP * 16 + 255) / 256, NXH = (HP * 16 + 255) / 256;
+    // and beyond the channel count) are asked for while the previous tile is being multiplied, split and written to
+    // LDS after it: the memory round trip is hidden behind the matrix work.
+    constexpr int ND = (P * 16 + 255) / 256, NXH = (HP * 16 + 255) / 256;
     float4 sd[ND], sx[NXH];
     auto fetch = [&](int unit) __attribute__((always_inline)) {
         int t = unit;
@@ -526,7 +566,7 @@ __global__ __launch_bounds__(256) void bww_dense_kernel(BwwArgs A, const float *
             const int oh = oh0 + pix / TW, ow = ow0 + pix % TW;
             const int kb = kt * 4 + (q >> 2);
             sd[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (idx < TP * 16 && oh < A.OH && ow < A.OW && kb < KB)
+            if (pix < TP && oh < A.OH && ow < A.OW && kb < KB)
                 sd[i] = *reinterpret_cast<const float4 *>(dy + act_off(n, kb, oh, ow, KB, A.OH, A.OW) + (q & 3) * 4);
         }
 #pragma unroll
@@ -536,57 +576,117 @@ __global__ __launch_bounds__(256) void bww_dense_kernel(BwwArgs A, const float *
             const int ih = ih0 + pix / HW, iw = iw0 + pix % HW;
             const int cb = cg * 4 + (q >> 2);
             sx[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (idx < HP * 16 && ih >= 0 && ih < A.H && iw >= 0 && iw < A.W && cb < CB)
+            if (pix < HP && ih >= 0 && ih < A.H && iw >= 0 && iw < A.W && cb < CB)
                 sx[i] = *reinterpret_cast<const float4 *>(x + act_off(n, cb, ih, iw, CB, A.H, A.W) + (q & 3) * 4);
         }
     };
-    if (u0 < u1) fetch(u0);
-
-    for (int unit = u0; unit < u1; ++unit) {
-        __syncthreads();                                     // every wavefront is done with the previous tile
-        {
-            int tid = threadIdx.x;
-            asm volatile("" : "+v"(tid));
+    // Every other step of 16 pixels is added up with the opposite sign (its dy negated here, its sum subtracted): the
+    // matrix cores cut off towards minus infinity, and over 10^5 pixels that bias would outgrow the rounding errors
+    // (256->256 @56, N = 32: error 7.8e-7 of the norm with one sign, 2.7e-7 with both).
+    constexpr int NS = P / 16;
+    auto flipped = [&](int unit, int s) __attribute__((always_inline)) { return NS % 2 == 0 ? s % 2 != 0 : (unit + s) % 2 != 0; };
+    auto stash = [&](int unit) __attribute__((always_inline)) {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
 #pragma unroll
-            for (int i = 0; i < ND; ++i) {
-                const int idx = tid + i * 256;
-                if (idx < TP * 16) *reinterpret_cast<float4 *>(dyT + idx * 4) = sd[i];        // = [pix][q*4]
-            }
+        for (int i = 0; i < ND + NXH; ++i) {
+            const bool isx = i >= ND;
+            const int idx = tid + (isx ? i - ND : i) * 256, pix = idx >> 4, q = idx & 15, bytes = isx ? XB : DB;
+            if (pix >= (isx ? HP : P)) continue;
+            bf16x4 p[3];
+            float4 v = isx ? sx[isx ? i - ND : 0] : sd[isx ? 0 : i];
+            if (!isx && flipped(unit, i)) v = make_float4(-v.x, -v.y, -v.z, -v.w);      // (256 pieces = one step)
+            split4(v, p);
+            char *dst = (isx ? xT : dyT) + (q >> 3) * bytes + pix * 64 + (q & 7) * 8;
 #pragma unroll
-            for (int i = 0; i < NXH; ++i) {
-                const int idx = tid + i * 256;
-                if (idx < HP * 16) *reinterpret_cast<float4 *>(xT + idx * 4) = sx[i];
-            }
+            for (int j = 0; j < 3; ++j) *reinterpret_cast<bf16x4 *>(dst + j * 2 * bytes) = p[j];
         }
-        __syncthreads();
-        if (unit + 1 < u1) fetch(unit + 1);                  // in flight during this tile's MFMAs
+    };
 
-        for (int pp = 0; pp < TP / 2; ++pp) {
-            const int p = 2 * pp + half;
-            const int a = p / TW, b = p % TW;
-            const float bv = dyT[p * 64 + kh * 32 + l32];                  // B[kk = half][j = k]
+    // this lane's addresses: pixel s*16 + half*8 + i*4 + (lane % 16) / 4 of the tile for read i of step s
+    LdsTr dp, xp[NS][2];
+    {
+        const int px = half * 8 + lane % 16 / 4;
+        dp = (LdsTr)(dyT + kh * DB + px * 64 + split_tr_lane(lane));
 #pragma unroll
-            for (int v = 0; v < S; ++v)
+        for (int s = 0; s < NS; ++s)
 #pragma unroll
-                for (int u = 0; u < R; ++u) {
-                    const float av = xT[((a * PSTEP + v) * HW + (b * PSTEP + u)) * 64 + ch * 32 + l32];   // A[i = c][kk]
-                    acc[v * R + u] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[v * R + u], 0, 0, 0);
-                }
-        }
+            for (int i = 0; i < 2; ++i) {
+                const int p = min(s * 16 + i * 4 + px, TP - 1);         // (the padding's dy is zero)
+                xp[s][i] = (LdsTr)(xT + ch * XB + (p / TW * HW + p % TW) * (PSTEP * 64) + split_tr_lane(lane));
+            }
     }
 
-    // D[i = c][j = k]: column = lane % 32, row = 8*(r/4) + 4*(lane/32) + r%4
-    const int k = kt * 64 + kh * 32 + l32;
-    if (k < A.K) {
-        const int kb = k / kBlk, ki = k % kBlk;
-        float *pbase = part + (size_t)split * A.K * A.C * (S * R);
+    if (u0 < u1) fetch(u0);
+    for (int unit = u0; unit < u1; ++unit) {
+        __syncthreads();                                     // every wavefront is done with the previous tile
+        stash(unit);
+        __syncthreads();
+        if (unit + 1 < u1) fetch(unit + 1);                  // in flight during this tile's MFMAs
+        if (!active) continue;
+
+        static_for<0, NS>([&](auto SI) __attribute__((always_inline)) {
+            constexpr int s = decltype(SI)::value;
+            bf16x8 d[3];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int c = cg * 64 + ch * 32 + 8 * (r / 4) + 4 * half + (r % 4);
-            if (c >= A.C) continue;
-            float *p = pbase + ((size_t)kb * CB + c / kBlk) * (S * R * kBlk * kBlk) + (c % kBlk) * kBlk + ki;
+            for (int q = 0; q < 3; ++q) d[q] = split_tr_read(dp + (q * 2 * DB + s * 1024) / 8, dp + (q * 2 * DB + s * 1024 + 256) / 8);
+            auto input = [&](int tap, bf16x8 (&f)[3]) __attribute__((always_inline)) {
 #pragma unroll
-            for (int tp = 0; tp < S * R; ++tp) p[tp * (kBlk * kBlk)] = acc[tp][r];
+                for (int q = 0; q < 3; ++q) {
+                    const int off = (q * 2 * XB + (tap / R * HW + tap % R) * 64) / 8;
+                    f[q] = split_tr_read(xp[s][0] + off, xp[s][1] + off);
+                }
+            };
+            bf16x8 f[3];
+            input(0, f);
+            static_for<0, S * R>([&](auto T) __attribute__((always_inline)) {
+                constexpr int tap = decltype(T)::value;
+                bf16x8 fn[3];
+                if constexpr (tap + 1 < S * R) input(tap + 1, fn);
+                __builtin_amdgcn_sched_barrier(0);              // the next tap's reads go ahead of this tap's products
+                floatx16 t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[2], f[0], floatx16{}, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[0], f[2], t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[1], f[1], t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[1], f[0], t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[0], f[1], t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[0], f[0], t, 0, 0, 0);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[tap][r] = flipped(unit, s) ? acc[tap][r] - t[r] : acc[tap][r] + t[r];
+                if constexpr (tap + 1 < S * R) {
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) f[q] = fn[q];
+                }
+            });
+        });
+    }
+    if (!active) return;
+
+    // D layout of the 32x32 block: column (c) = lane % 32, row (k) = 8*(r/4) + 4*(lane/32) + r%4: four consecutive output
+    // channels per group of 4 accumulators, one 16-byte store each
+    const int c = cg * 64 + ch * 32 + l32;
+    if (c >= A.C) return;
+    float *pbase = part + (size_t)split * A.K * A.C * (S * R);
+    auto element = [&](int k, int tap) __attribute__((always_inline)) {
+        return pbase + (((size_t)(k / kBlk) * CB + c / kBlk) * (S * R) + tap) * (kBlk * kBlk) + (c % kBlk) * kBlk + k % kBlk;
+    };
+    bool finite = true;
+#pragma unroll
+    for (int tap = 0; tap < S * R; ++tap)
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq) {
+            const int k = kt * 64 + kh * 32 + 8 * gq + 4 * half;
+            if (k >= A.K) continue;
+            const float4 v = make_float4(acc[tap][4 * gq], acc[tap][4 * gq + 1], acc[tap][4 * gq + 2], acc[tap][4 * gq + 3]);
+            finite = finite && split_finite(v.x) && split_finite(v.y) && split_finite(v.z) && split_finite(v.w);
+            *reinterpret_cast<float4 *>(element(k, tap)) = v;
+        }
+    if (__builtin_expect(!finite, 0)) {             // values outside the range of the bf16 pieces took part
+#pragma unroll 1
+        for (int i = 0; i < S * R * 16; ++i) {
+            const int k = kt * 64 + kh * 32 + 8 * (i % 16 / 4) + 4 * half + i % 4, tap = i / 16;
+            if (k >= A.K) continue;
+            float *o = element(k, tap);
+            if (!split_finite(*o)) *o = bww_exact<TH, TW, PSTEP>(A, x, dy, k, c, tap / R, tap % R, u0, u1);
         }
     }
 }
@@ -949,12 +1049,13 @@ hipError_t allow_dynamic_lds(K kern, size_t bytes)
 BwwArgs make_args(const st_conv_desc &d, int TH, int TW, bool tiles_over_input);
 BwwArgs sparse_args(const st_conv_desc &d);
 BwwArgs dense_args(const st_conv_desc &d);
-bool dense_narrow(const st_conv_desc &d);
+bool dense_wide(const st_conv_desc &d);
 bool bww_s2(const st_conv_desc &d);
-constexpr int kDenseTH = 7, kDenseTW = 14;   // 224, 112, 56, 28 and 14 are multiples of both: no ragged tiles
-constexpr int kDenseNarrowTW = 8;            // output rows of at most 8 pixels (7 x 7 layers): half of a 14-wide tile would be padding
-// stride-2 layers: 4x8 tiles keep the strided halo of the other operand (9x17 pixels x 64 channels) in LDS
-constexpr int kS2TH = 4, kS2TW = 8;
+// dense unit-stride 3x3 kernel: 4 x 8 pixels, or 2 x 14 (two steps of 16 as well, 4 pixels of padding)
+constexpr int kDenseTH = 4, kDenseTW = 8, kDenseWideTH = 2, kDenseWideTW = 14;
+// stride-2 layers: 4x8 tiles keep the strided halo of the other operand (9x17 pixels x 64 channels) in LDS; the
+// dense kernel takes 2x8 (5x17), whose next tile fits in registers beside its sums
+constexpr int kS2TH = 4, kS2TW = 8, kDenseS2TH = 2, kDenseS2TW = 8;
 
 constexpr int kBwwTargetWorkgroups = 512;
 
@@ -969,7 +1070,8 @@ BwwArgs make_args(const st_conv_desc &d, int TH, int TW, bool tiles_over_input)
     const int eh = tiles_over_input ? d.H : A.OH, ew = tiles_over_input ? d.W : A.OW;
     A.tiles_h = ceil_div(eh, TH);
     A.tiles_w = ceil_div(ew, TW);
-    A.units = d.N * A.tiles_h * A.tiles_w;
+    const long long units = (long long)d.N * A.tiles_h * A.tiles_w;      // bounded by bww_fast_supported up to the tile size
+    A.units = units < 0x7fffffffLL ? (int)units : 0x7fffffff;
     A.cgroups = ceil_div(d.C, 64);
     const int groups = ceil_div(d.K, 64) * A.cgroups;
     // number of partial sums: enough workgroups to fill the chip (256 compute units, 2 resident
@@ -981,11 +1083,16 @@ BwwArgs make_args(const st_conv_desc &d, int TH, int TW, bool tiles_over_input)
     return A;
 }
 
-// tiles of the dense unit-stride 3x3 kernel
-bool dense_narrow(const st_conv_desc &d) { return d.W + 2 * d.pad_w - d.R + 1 <= kDenseNarrowTW; }
+// tiles of the dense unit-stride 3x3 kernel: the shape that covers an image with fewer of them
+bool dense_wide(const st_conv_desc &d)
+{
+    const int oh = d.H + 2 * d.pad_h - d.S + 1, ow = d.W + 2 * d.pad_w - d.R + 1;
+    return (long long)ceil_div(oh, kDenseWideTH) * ceil_div(ow, kDenseWideTW) < (long long)ceil_div(oh, kDenseTH) * ceil_div(ow, kDenseTW);
+}
 BwwArgs dense_args(const st_conv_desc &d)
 {
-    return make_args(d, kDenseTH, dense_narrow(d) ? kDenseNarrowTW : kDenseTW, false);
+    if (bww_s2(d)) return make_args(d, kDenseS2TH, kDenseS2TW, false);
+    return dense_wide(d) ? make_args(d, kDenseWideTH, kDenseWideTW, false) : make_args(d, kDenseTH, kDenseTW, false);
 }
 
 // tiles of the zero-skipping 3x3 kernel that tests the input of layer d
@@ -1089,7 +1196,6 @@ size_t bww_sparse_workspace(const st_conv_desc &d)
 size_t bww_dense_workspace(const st_conv_desc &d)
 {
     if (d.R == 1 && d.S == 1) return partial_bytes(d, make_args_pw_dense(d));
-    if (bww_s2(d)) return partial_bytes(d, make_args(d, kS2TH, kS2TW, false));
     return partial_bytes(d, dense_args(d));
 }
 
@@ -1227,7 +1333,7 @@ hipError_t launch_bww_auto_merged(const st_conv_desc &d, const float *x, const f
     hipLaunchKernelGGL((bww_sparse_either_kernel<3, 3, kSparseTH, kSparseTW>), grid, dim3(512), kSparseLds, s, A0, A1, x, dy, ws);
     err = hipGetLastError();
     if (err != hipSuccess) return err;
-    if (dense_narrow(d)) hipLaunchKernelGGL((bww_dense_kernel<3, 3, kDenseTH, kDenseNarrowTW>), dim3(A2.splits, ygroups), dim3(256), 0, s, A2, x, dy, ws);
+    if (dense_wide(d)) hipLaunchKernelGGL((bww_dense_kernel<3, 3, kDenseWideTH, kDenseWideTW>), dim3(A2.splits, ygroups), dim3(256), 0, s, A2, x, dy, ws);
     else hipLaunchKernelGGL((bww_dense_kernel<3, 3, kDenseTH, kDenseTW>), dim3(A2.splits, ygroups), dim3(256), 0, s, A2, x, dy, ws);
     if ((err = hipGetLastError()) != hipSuccess) return err;
     const size_t n4 = (size_t)d.K * d.C * d.S * d.R / 4;
@@ -1242,10 +1348,10 @@ hipError_t launch_bww_dense(const st_conv_desc &d, const float *x, const float *
                             float *ws, hipStream_t s, const unsigned *sel)
 {
     if (bww_s2(d)) {
-        BwwArgs A2 = make_args(d, kS2TH, kS2TW, false);
+        BwwArgs A2 = dense_args(d);
         A2.sel = sel; A2.want = 2;
         dim3 grid2(A2.splits, ceil_div(d.K, 64) * A2.cgroups);
-        hipLaunchKernelGGL((bww_dense_kernel<3, 3, kS2TH, kS2TW, 2>), grid2, dim3(256), 0, s, A2, x, dy,
+        hipLaunchKernelGGL((bww_dense_kernel<3, 3, kDenseS2TH, kDenseS2TW, 2>), grid2, dim3(256), 0, s, A2, x, dy,
                            A2.splits == 1 ? dw : ws);
         hipError_t err = hipGetLastError();
         return err != hipSuccess ? err : reduce(d, A2, ws, dw, s);
@@ -1267,21 +1373,23 @@ hipError_t launch_bww_dense(const st_conv_desc &d, const float *x, const float *
     A.sel = sel; A.want = 2;
     float *part = A.splits == 1 ? dw : ws;
     dim3 grid(A.splits, ceil_div(d.K, 64) * A.cgroups);
-    if (dense_narrow(d)) hipLaunchKernelGGL((bww_dense_kernel<3, 3, kDenseTH, kDenseNarrowTW>), grid, dim3(256), 0, s, A, x, dy, part);
+    if (dense_wide(d)) hipLaunchKernelGGL((bww_dense_kernel<3, 3, kDenseWideTH, kDenseWideTW>), grid, dim3(256), 0, s, A, x, dy, part);
     else hipLaunchKernelGGL((bww_dense_kernel<3, 3, kDenseTH, kDenseTW>), grid, dim3(256), 0, s, A, x, dy, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return reduce(d, A, part, dw, s);
 }
 
-// Measured on the layer shapes of the paper's Table 1: the 3x3 zero-skipping forms pass the dense one at
-// 20-25 % zeros; a 1x1 layer saves at most K/64 (or C/64) multiply-adds per zero and stays behind the
+// Measured on the layer shapes of the paper's Table 1 (N = 32, us, zero-skipping at 70 / 90 % zeros against dense:
+// 256->256 @56 716 / 578 : 579, 512->512 @14 215 / 179 : 184, 64->64 @56 73 / 63 : 63, 128->128 @28 71 / 62 : 64): the
+// 3x3 zero-skipping forms pass the dense one at 85-90 % zeros.  The line is drawn at 75 %: from 80 % on the entry point
+// tests the sparser operand.  A 1x1 layer saves at most K/64 (or C/64) multiply-adds per zero and stays behind the
 // matrix cores at every zero fraction measured (up to 95 %): never (1001).  (Stride-2 layers never get
-// here: their dy-testing form beats the dense one even without zeros.)
+// here: they test dy, unsampled.)
 unsigned bww_sparse_threshold(const st_conv_desc &d)
 {
     if (!bww_fast_supported(d)) return 0;           // generic kernels: the test only ever removes work
-    return d.R == 1 ? 1001 : 250;
+    return d.R == 1 ? 1001 : 750;
 }
 
 }  // namespace st

@@ -124,6 +124,10 @@ __device__ __forceinline__ void reformat_filters_block(size_t block, int Ko, int
             hi = p[1];
         }
     }
+    if (cb % 2) {                                       // odd channel blocks with the opposite sign
+        lo = make_float4(-lo.x, -lo.y, -lo.z, -lo.w);
+        hi = make_float4(-hi.x, -hi.y, -hi.z, -hi.w);
+    }
     bf16x4 a[3], b[3];
     split4(lo, a);
     split4(hi, b);

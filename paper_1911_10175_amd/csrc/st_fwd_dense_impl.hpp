@@ -195,7 +195,7 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
 #pragma unroll
             for (int pb = 0; pb < 2; ++pb)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[pb][r] += part[pb][r];
+                for (int r = 0; r < 16; ++r) acc[pb][r] = fmaf(cb % 2 ? -1.f : 1.f, part[pb][r], acc[pb][r]);
         }
         if (cb + 1 < cb1) store_halo(lds_base + (((cb + 1 - cb0) & 1) * TQ + tqi) * BUF, hreg);
         __syncthreads();

@@ -8,10 +8,12 @@
 // v_mfma_f32_32x32x2_f32 does one, so six of them cost 6/16 of the fp32 instruction's time per product.
 //
 // The matrix core adds the 16 products of an instruction to the accumulator at the accumulator's own precision,
-// small terms cut off rather than rounded (measured: 1 + 16 * 2^-27 returns 1).  Over a long reduction that is
-// 10-20 % more error than the fp32 instruction has; the kernels therefore start a fresh accumulator per block of
-// 16 channels (at most 9 taps x 6 instructions) and add it to the running fp32 sum on the vector ALUs, which leaves
-// a third of the fp32 instruction's error (2304 terms: 6.1e-7 -> 2e-7 of the result's norm).
+// small terms cut off towards minus infinity rather than rounded (measured: 1 + 16 * 2^-27 returns 1).  Over a long
+// reduction that is 10-20 % more error than the fp32 instruction has, and a bias that grows with the number of terms.
+// Two measures take both away: the kernels start a fresh accumulator per block of the reduction (16 channels x 9
+// taps, or 16 pixels) and add it to the running fp32 sum on the vector ALUs, and every other block is computed with one
+// operand negated and subtracted, so that the biases cancel.  What is left is a third of the fp32 instruction's error
+// in FWD / BWI (2304 terms: 6.1e-7 -> 2e-7 of the result's norm) and about half in BWW (10^5 terms: 5e-7 -> 2.7e-7).
 //
 // The decomposition is exact for 2^-100 <= |a| < 2^127.99: smaller values lose their last pieces below the
 // smallest bf16, larger ones round to infinity.  Every element outside that range is handed to the matrix
@@ -29,6 +31,22 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));      // MFMA operand:
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
+
+// Operand of a reduction over pixels from a [pixel][32 channels] bf16 tile in LDS: lane l takes channel l % 32 and 8
+// of the 16 pixels of the step, four per transposing read (a group of 16 lanes reads 4 pixels x 16 channels, 8 bytes
+// a lane, and gets them back with a lane per channel).  p0, p1 = this lane's addresses for pixels 0-3 and 4-7 of its
+// half of the step: split_tr_lane(lane) bytes into the row of the first of them.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 *LdsTr;
+__device__ __forceinline__ bf16x8 split_tr_read(LdsTr p0, LdsTr p1)
+{
+    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16(p0), b = __builtin_amdgcn_ds_read_tr16_b64_v4i16(p1);
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    const s16x8 v = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(bf16x8, v);
+}
+// channel part of a lane's address; its pixel of the four is (lane % 16) / 4
+__device__ __forceinline__ int split_tr_lane(int lane) { return lane / 16 % 2 * 32 + lane % 4 * 8; }
 
 constexpr unsigned kSplitTiny = 0x0D800000u;        // bits of 2^-100
 
@@ -80,7 +98,7 @@ __device__ __forceinline__ float split_exact_corr(const Geom &g, const float *in
     const int CiB = g.Ci / kBlk, KoB = g.Ko / kBlk;
     float s = 0.f;
 #pragma unroll 1
-    for (int v = 0; v < g.S; ++v) {
+    for (int v = 0; v < g.S && s == s; ++v) {               // (NaN stays NaN)
         const int ph = oh * g.sh - g.ph + v;
         if (ph < 0 || ph % g.uh != 0 || ph / g.uh >= g.Hi) continue;
 #pragma unroll 1
@@ -88,7 +106,7 @@ __device__ __forceinline__ float split_exact_corr(const Geom &g, const float *in
             const int pw = ow * g.sw - g.pw + u;
             if (pw < 0 || pw % g.uw != 0 || pw / g.uw >= g.Wi) continue;
 #pragma unroll 1
-            for (int ci = cb0 * kBlk; ci < cb1 * kBlk; ++ci) {
+            for (int ci = cb0 * kBlk; ci < cb1 * kBlk && s == s; ++ci) {
                 const float a = in[act_off(n, ci / kBlk, ph / g.uh, pw / g.uw, CiB, g.Hi, g.Wi) + ci % kBlk];
                 const size_t blk = g.wt ? (((size_t)(ci / kBlk) * KoB + ko / kBlk) * g.S + (g.S - 1 - v)) * g.R + (g.R - 1 - u)
                                         : (((size_t)(ko / kBlk) * CiB + ci / kBlk) * g.S + v) * g.R + u;

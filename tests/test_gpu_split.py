@@ -34,14 +34,14 @@ def inputs(g, seed):
 
 
 def refs(g, x, w, dy):
-    return {"fwd": st_ref.conv_fwd(g, x, w), "bwi": st_ref.conv_bwi(g, dy, w)}
+    return {"fwd": st_ref.conv_fwd(g, x, w), "bwi": st_ref.conv_bwi(g, dy, w), "bww": st_ref.conv_bww(g, x, dy)}
 
 
 def terms(g):
     """Products per output.  An fp32 sum of n products in any order is within (n + 1) 2^-24 of the sum of their
     magnitudes, the pieces left out of a product are within 2^-23 of it, and n results below the smallest normal number
     may each be off by half the smallest subnormal."""
-    return {"fwd": g.C * g.R * g.S, "bwi": g.K * g.R * g.S}
+    return {"fwd": g.C * g.R * g.S, "bwi": g.K * g.R * g.S, "bww": g.N * g.OH * g.OW}
 
 
 def check(g, x, w, dy, label):
