@@ -176,9 +176,8 @@ st_status st_conv_bww_auto(const st_conv_desc *desc, const float *x, const float
  * writes both forms' filter copies, then both forms are enqueued and the one the count does not
  * select returns at once.  The zero-skipping form runs when the sampled zero fraction reaches the
  * break-even point against the dense form measured for the geometry: 65 % for unit-stride 3x3 layers
- * that one main kernel serves (below), 85 % for the others, 45 % for the BWI of stride-2 3x3 layers, never
- * for their FWD and for 1x1 layers (measured up to 90 and 95 % zeros), always for geometries only the generic
- * kernels cover.  Where the answer is "always" or "never" the call
+ * that one main kernel serves (below), 85 % for the others, never for stride-2 3x3 and for 1x1 layers
+ * (measured up to 90 and 95 % zeros), always for geometries only the generic kernels cover.  Where the answer is "always" or "never" the call
  * goes straight to that form, without sampling.  On unit-stride 3x3 layers of the usual sizes one
  * main kernel holds both forms and runs the selected one, so the sampled path has as many launches
  * as the direct call (st_conv_kernel_name tells); elsewhere it costs one launch more.  Same tensors and

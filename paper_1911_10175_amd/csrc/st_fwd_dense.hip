@@ -110,15 +110,57 @@ hipError_t launch_s2_fwd(const Geom &g, const float *in, const float *wd, float 
     return launch_kq<3, 3, 8, 1>(g, in, wd, out, s);
 }
 
-// BWI of a stride-2 layer: the four parity classes of the dx positions, one launch each
+// BWI of a stride-2 layer: the four parity classes of the dx positions in one launch, the longest (4 taps) first.  As
+// four launches of a quarter of the workgroups each they left most of the chip idle (N = 32, us: 128->128 @56 77 -> 58,
+// 256->256 @28 114 -> 63, 512->512 @14 194 -> 91).
+struct ParityGrid {
+    int tiles_w[4], tiles_h[4], total_tiles[4];     // of class 3 - 2*PI - PJ
+    unsigned first[5];                              // first workgroup of each class
+};
+
+template <int KQ, int TWD>
+__global__ __launch_bounds__(256, (FwdDenseCfg<3, 3, TWD, 2, 1, 1>::minw(KQ))) void fwd_dense_s2_bwi_kernel(
+    Geom g, const float *__restrict__ in, const float *__restrict__ wd, float *__restrict__ out, ParityGrid q, int kgroups)
+{
+    if (form_deselected(g.sel, g.want, g.thr)) return;
+    __shared__ __attribute__((aligned(16))) float lds_all[fwd_dense_lds_floats<3, 3, KQ, TWD, 2, 1, 1>()];     // the largest of the four
+    static_for<0, 4>([&](auto I) __attribute__((always_inline)) {
+        constexpr int i = decltype(I)::value, PI = (3 - i) / 2, PJ = (3 - i) % 2;
+        if (blockIdx.x >= q.first[i] && blockIdx.x < q.first[i + 1])            // uniform over the workgroup
+            fwd_dense_body<3, 3, KQ, TWD, 2, PI, PJ>(g, in, wd, out, nullptr, q.tiles_w[i], q.tiles_h[i], kgroups, q.total_tiles[i], 1, 0,
+                                                     (int)(blockIdx.x - q.first[i]), 0, lds_all);
+    });
+}
+
+template <int KQ, int TWD>
+hipError_t launch_s2_bwi_kq(const Geom &g, const float *in, const float *wd, float *out, hipStream_t s)
+{
+    constexpr int TQ = 4 / KQ, TH = 64 / TWD;
+    ParityGrid q;
+    const int kgroups = ceil_div(g.Ko, 32 * KQ);
+    long long blocks = 0;
+    for (int i = 0; i < 4; ++i) {
+        const int PI = (3 - i) / 2, PJ = (3 - i) % 2;
+        q.tiles_w[i] = ceil_div((g.Wo - PJ + 1) / 2, TWD);
+        q.tiles_h[i] = ceil_div((g.Ho - PI + 1) / 2, TH);
+        const long long tiles = (long long)q.tiles_w[i] * q.tiles_h[i] * g.N;
+        if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
+        q.total_tiles[i] = (int)tiles;
+        q.first[i] = (unsigned)blocks;
+        blocks += (tiles + TQ - 1) / TQ * kgroups;
+        if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    }
+    q.first[4] = (unsigned)blocks;
+    hipLaunchKernelGGL((fwd_dense_s2_bwi_kernel<KQ, TWD>), dim3((unsigned)blocks), dim3(256), 0, s, g, in, wd, out, q, kgroups);
+    return hipGetLastError();
+}
+
 template <int TWD>
 hipError_t launch_s2_bwi_tw(const Geom &g, const float *in, const float *wd, float *out, hipStream_t s)
 {
-    hipError_t e = launch_kq<3, 3, TWD, 2, 1, 1>(g, in, wd, out, s);        // 4 taps: the longest first
-    if (e == hipSuccess) e = launch_kq<3, 3, TWD, 2, 1, 0>(g, in, wd, out, s);
-    if (e == hipSuccess) e = launch_kq<3, 3, TWD, 2, 0, 1>(g, in, wd, out, s);
-    if (e == hipSuccess) e = launch_kq<3, 3, TWD, 2, 0, 0>(g, in, wd, out, s);
-    return e;
+    if (g.Ko > 64) return launch_s2_bwi_kq<4, TWD>(g, in, wd, out, s);
+    if (g.Ko > 32) return launch_s2_bwi_kq<2, TWD>(g, in, wd, out, s);
+    return launch_s2_bwi_kq<1, TWD>(g, in, wd, out, s);
 }
 
 hipError_t launch_s2_bwi(const Geom &g, const float *in, const float *wd, float *out, hipStream_t s)

@@ -13,7 +13,7 @@ namespace {
 // MODE selects how tile pixels, taps and input samples relate:
 //   0  unit stride: tile pixel (ty,tx), tap (v,u) reads halo pixel (ty+v, tx+u).
 //   1  stride 2 (FWD of the stride-2 3x3 layers): halo pixel (2*ty+v, 2*tx+u).
-//   2  BWI of a stride-2 3x3 layer with padding 1, one launch per parity class (PI,PJ) of the dx
+//   2  BWI of a stride-2 3x3 layer with padding 1, one body per parity class (PI,PJ) of the dx
 //      positions: the tile is an 8x8 (or 4x14, 2x28) block of the positions (2*i+PI, 2*j+PJ); only
 //      the taps whose grid position holds a dy sample contribute (SparseTrain Sec. 3.3): for PI = 0
 //      the middle tap reading dy row i, for PI = 1 the outer taps reading dy rows i and i+1; the

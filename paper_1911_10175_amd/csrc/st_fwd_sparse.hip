@@ -51,15 +51,13 @@ unsigned fwd_sparse_threshold(const Geom &g)
 //   256->256 @56 603 / 495 : 553   512->512 @28 613 / 505 : 613   128->128 @28 56 / 49 : 49   256->256 @14 59 / 53 : 58
 //   64->64 @56 71 / 57 : 54        512->512 @7 64 / 60 : 67       N = 1 512->512 @14 67 / 60 : 34
 // i.e. at about 70-75 % on the large layers with whole groups of 128 produced channels (650: what takes part in the
-// one-kernel launch of st_fwd_auto.hip) and at or above 85-90 % on the others.  The stride-2 FWD stays behind at 90 %
-// (128->128 @56 76 : 52, 256->256 @28 129 : 77); its BWI, four short launches per layer in the dense form, does not
-// (256->256 @28 106 / 85 : 114).
+// one-kernel launch of st_fwd_auto.hip) and at or above 85-90 % on the others.  The stride-2 layers stay behind at 90 %:
+// FWD 128->128 @56 76 : 52, 256->256 @28 129 : 77, BWI 75 : 58, 85 : 63 (512->512 @14 89 : 91).
 unsigned fwd_auto_threshold(const Geom &g)
 {
     const unsigned t = fwd_sparse_threshold(g);
     if (t == 0 || t > 1000 || !fwd_dense_supported(g)) return t;
-    if (g.sw == 2) return 1001;
-    if (g.uw == 2) return t;
+    if (g.sw == 2 || g.uw == 2) return 1001;
     return fwd_auto_combined_supported(g) ? 650 : 850;
 }
 
