@@ -165,6 +165,7 @@ size_t fwd_dense_filter_bytes(const Geom &g);
 // reduction is split over workgroups (few pixel tiles)
 size_t fwd_dense_workspace_bytes(const Geom &g);
 hipError_t launch_reformat_filters(const Geom &g, bool transpose, const float *w, float *wd, hipStream_t s);
+int dense_images_per_launch(const Geom &g);
 hipError_t launch_fwd_dense(const Geom &g, const float *in, const float *wd, float *out, hipStream_t s);
 // 1x1 layers with small filter matrices: whole filter in LDS, read from the library layout (no copy
 // in the workspace needed); transpose selects the BWI form

@@ -14,22 +14,24 @@ namespace st {
 namespace {
 
 struct DenseGrid {
-    int tiles_w, tiles_h, kgroups, total_tiles;
+    FlatGrid q;
+    int kgroups;
     long long blocks;
 };
 
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
 
 // TH x TW pixels and KPL channels per lane, CS wavefronts per task: the zero-skipping form; KQ column blocks
-// per workgroup and TWD-wide tiles: the dense form
+// per workgroup and strips of TWD pixels: the dense form
 template <int TH, int TW, int KPL, int CS, int KQ, int TWD>
 __global__ __launch_bounds__(256, 4) void fwd_auto_kernel(Geom g, const float *__restrict__ in, const float *__restrict__ wl,
                                                           const float *__restrict__ wd, float *__restrict__ out,
                                                           SparseGrid sq, DenseGrid dq)
 {
     static_assert(CS <= 4, "both forms run in workgroups of four wavefronts");
-    __shared__ __attribute__((aligned(16))) float lds[cmax(fwd_sparse_lds_floats<3, 3, TH, TW, KPL, CS>(),
-                                                           fwd_dense_lds_floats<3, 3, KQ, TWD>())];
+    constexpr int HPC = TWD > 16 ? kHaloWide : kHalo;
+    __shared__ __attribute__((aligned(16))) float lds[cmax(fwd_sparse_lds_floats<3, 3, TH, TW, KPL, CS>(), FlatLds<KQ, HPC>::FLOATS)];
+    __shared__ __attribute__((aligned(16))) float raw[FlatLds<KQ, HPC>::RAWFLOATS];
     // uniform over the grid, before any barrier
     if (!form_deselected(g.sel, 0, g.thr)) {
         if ((long long)blockIdx.x >= sq.blocks) return;
@@ -37,7 +39,7 @@ __global__ __launch_bounds__(256, 4) void fwd_auto_kernel(Geom g, const float *_
                                                sq.kt_major, lds);
     } else {
         if ((long long)blockIdx.x >= dq.blocks) return;
-        fwd_dense_body<3, 3, KQ, TWD>(g, in, wd, out, nullptr, dq.tiles_w, dq.tiles_h, dq.kgroups, dq.total_tiles, 1, 0, (int)blockIdx.x, 0, lds);
+        fwd_dense_body<KQ, HPC>(g, in, wd, out, nullptr, dq.q, dq.kgroups, 1, 0, (int)blockIdx.x, 0, lds, raw);
     }
 }
 
@@ -45,17 +47,13 @@ template <int TH, int TW, int KPL, int CS, int KQ, int TWD>
 hipError_t launch_pair(const Geom &g, const float *in, const float *wl, const float *wd, float *out, hipStream_t s)
 {
     using SCfg = FwdSparseCfg<3, 3, TH, TW, KPL>;
-    using DCfg = FwdDenseCfg<3, 3, TWD>;
     const SparseGrid sq = sparse_grid<TH, TW, SCfg::KT, CS>(g);
     DenseGrid dq;
-    dq.tiles_w = ceil_div(g.Wo, DCfg::TW);
-    dq.tiles_h = ceil_div(g.Ho, DCfg::TH);
-    const long long total_tiles = (long long)dq.tiles_w * dq.tiles_h * g.N;
+    dq.q = flat_grid(g.N, g.Ho, g.Wo, 1, 3, 3, TWD > 16 ? kHaloWide : kHalo, TWD);
     dq.kgroups = ceil_div(g.Ko, 32 * KQ);
     constexpr int TQ = 4 / KQ;
-    dq.blocks = (total_tiles + TQ - 1) / TQ * dq.kgroups;
-    if (!sq.ok || total_tiles > 0x7fffffffLL || dq.blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    dq.total_tiles = (int)total_tiles;
+    dq.blocks = ((long long)dq.q.tiles + TQ - 1) / TQ * dq.kgroups;
+    if (!sq.ok || dq.blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const long long blocks = sq.blocks > dq.blocks ? sq.blocks : dq.blocks;
     hipLaunchKernelGGL((fwd_auto_kernel<TH, TW, KPL, CS, KQ, TWD>), dim3((unsigned)blocks), dim3(256), 0, s, g, in, wl, wd, out, sq, dq);
     return hipGetLastError();
@@ -80,9 +78,9 @@ bool pick_pair(const Geom &g, Pair *p)
     const int th = p->kpl == 2 ? 4 : 8;
     p->cs = sparse_channel_split(g, th, p->tw, 64 * p->kpl, true);
     if (p->cs != 2 && p->cs != 4) return false;
-    long long blocks;
-    dense_tiling(g, &p->twd, &p->kq, &blocks);
-    if (p->kq != 4) return false;
+    if (dense_images_per_launch(g) != g.N) return false;
+    dense_rect_blocks(g, &p->twd);
+    p->kq = 4;                                     // g.Ko > 64
     return p->twd == 8 || (p->tw == 7 && (p->twd == 28 || p->twd == 14));
 }
 

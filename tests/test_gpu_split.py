@@ -13,14 +13,18 @@ pytestmark = pytest.mark.gpu
 if torch.cuda.is_available():
     from tests.gpu_harness import DeviceLayer
 
-# one geometry per kernel shape: column blocks per workgroup (16 / 48 / 80 and more produced channels), tile widths
-# 8, 14 and 28, rows and columns left over, the channel split, stride 2 (and its four parity classes in BWI), 1x1
+# one geometry per kernel shape: column blocks per workgroup (16 / 48 / 80 and more produced channels), strips of unequal
+# widths, tiles that span many images or are cut short by their halo, the channel split, stride 2 (and its four parity
+# classes in BWI), 1x1
 GEOMS = {
     "3x3 16->48": Geom(2, 16, 48, 9, 11, 3, 3, 1, 1, 1, 1),
     "3x3 80->144": Geom(2, 80, 144, 7, 28, 3, 3, 1, 1, 1, 1),
     "3x3 48->32 pad2": Geom(1, 48, 32, 5, 12, 3, 3, 1, 1, 2, 2),
     "3x3 split": Geom(1, 256, 256, 7, 7, 3, 3, 1, 1, 1, 1),
     "3x3 stride 2": Geom(2, 48, 80, 13, 10, 3, 3, 2, 2, 1, 1),
+    "3x3 tiny images": Geom(70, 16, 144, 2, 3, 3, 3, 1, 1, 1, 1),
+    "3x3 one row": Geom(5, 16, 32, 1, 230, 3, 3, 1, 1, 1, 1),
+    "3x3 stride 2 tiny images": Geom(40, 32, 16, 3, 4, 3, 3, 2, 2, 1, 1),
     "1x1 64->64": Geom(3, 64, 64, 53, 53, 1, 1),
     "1x1 80->48": Geom(2, 80, 48, 5, 7, 1, 1),
 }
