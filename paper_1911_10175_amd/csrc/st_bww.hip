@@ -698,38 +698,59 @@ __global__ __launch_bounds__(256, 2) void bww_dense_kernel(BwwArgs A, const floa
 // ------------------------------------------------------------------------------------------
 constexpr int kPwP = 32;            // pixels per staged chunk
 
-// Dense: workgroup = CW input channels x KW output channels (128 or 64 each), its four wavefronts a 2 x 2
-// grid of (CW/2) x (KW/2) sub-tiles of 32x32 MFMA blocks; the next chunk of P pixels is fetched into registers
-// while the current one is multiplied.  128 x 128 uses a staged pixel for four MFMAs per pair of LDS reads;
-// layers with only 64 channels on a side get the narrower tile (no padded blocks) and chunks of 64 pixels,
-// so that there are as many MFMAs between two barriers.
+// One element of a 1x1 partial gradient with plain fp32 multiply-adds: pixels p0 .. p1-1 of the minibatch
+__device__ __forceinline__ float pw_bww_exact(const BwwArgs &A, const float *x, const float *dy, int k, int c, long long p0, long long p1)
+{
+    const int HW = A.H * A.W;
+    float s = 0.f;
+#pragma unroll 1
+    for (long long q = p0; q < p1 && s == s; ++q) {
+        const size_t n = (size_t)(q / HW), p = (size_t)(q % HW);
+        s = fmaf(x[((n * (A.C / kBlk) + c / kBlk) * HW + p) * kBlk + c % kBlk], dy[((n * (A.K / kBlk) + k / kBlk) * HW + p) * kBlk + k % kBlk], s);
+    }
+    return s;
+}
+
+// Dense, on bf16 pieces (st_split.hpp): workgroup = CW input channels x KW output channels (128 or 64 each).  Its eight
+// wavefronts are two teams of four that take alternate chunks of P pixels and add up their sums through LDS at the end: half
+// the partial gradients of as many separate workgroups (on 512->2048 @7 they are 33 MB written and read again, as
+// long as the arithmetic).  The four wavefronts of a team are a 2 x 2 grid of (KW/2) x (CW/2) sub-tiles of 32x32 MFMA blocks
+// (rows = output channels, columns = input channels, reduction = 16 pixels); the team's next chunk is fetched into
+// registers while the current one is multiplied.  128 x 128 uses a staged pixel for four blocks; layers with only 64
+// channels on a side get the narrower tile (no padded blocks) and chunks of 64 pixels, so that there are as many
+// matrix instructions between two barriers.  Between two barriers one team multiplies while the other splits and stashes
+// its next chunk, so the matrix cores and the vector ALUs work at the same time.  The matrix cores' accumulators are
+// joined to the fp32 sums every 128 pixels of a team, with alternating sign.
 template <int CW, int KW, int P>
-__global__ __launch_bounds__(256) void pw_bww_dense_kernel(BwwArgs A, const float *__restrict__ x,
-                                                           const float *__restrict__ dy,
-                                                           float *__restrict__ part)
+__global__ __launch_bounds__(512, 2) void pw_bww_dense_kernel(BwwArgs A, const float *__restrict__ x,
+                                                              const float *__restrict__ dy, float *__restrict__ part)
 {
     if (deselected(A.sel, A.want)) return;              // uniform over the grid, before any barrier
-    constexpr int CI = CW / 64, KJ = KW / 64;           // 32x32 blocks per wavefront along c and along k
-    constexpr int NX = P * CW / 4 / 256, ND = P * KW / 4 / 256;      // float4 staging slots per thread
-    __shared__ __attribute__((aligned(16))) float xs[P * CW];
-    __shared__ __attribute__((aligned(16))) float ds[P * KW];
+    constexpr int CI = CW / 64, KJ = KW / 64;           // 32-channel blocks of a wavefront
+    constexpr int NX = P * (CW / 4) / 256, ND = P * (KW / 4) / 256;
+    constexpr int XB = CW * P * 2, DB = KW * P * 2;     // bytes of one piece of a chunk: [32-channel block][pixel][32 channels]
+    constexpr int TEAM = 3 * (XB + DB), SUMS = 256 * CI * KJ * 64;
+    constexpr int kPwFlush = 128 / P;
+    static_assert(SUMS <= 2 * TEAM, "the second team's sums go through the same LDS");
+    extern __shared__ __attribute__((aligned(16))) char pw_lds[];       // 2 * TEAM bytes
 
-    // the wavefront index is the same in every lane: kept in a scalar register, and with it every tile coordinate
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
     const int l32 = lane % 32, half = lane / 32;
-    const int wk = wave % 2, wc = wave / 2;
+    const int team = wave / 4, wk = wave % 2, wc = wave / 2 % 2;
     const int split = blockIdx.x;
-    const int kt = blockIdx.y / A.cgroups, cg = blockIdx.y % A.cgroups;     // groups of KW / CW channels here
+    const int kt = blockIdx.y / A.cgroups, cg = blockIdx.y % A.cgroups;
     const int CB = A.C / kBlk, KB = A.K / kBlk;
     const int HW = A.H * A.W;
+    char *const xs = pw_lds + team * TEAM, *const ds = xs + 3 * XB;
+    const bool active = kt * KW + wk * (KW / 2) < A.K && cg * CW + wc * (CW / 2) < A.C;
 
-    floatx16 acc[CI][KJ];                               // [c block of 32][k block of 32]
+    floatx16 acc[KJ][CI], sum[KJ][CI];
 #pragma unroll
-    for (int i = 0; i < CI; ++i)
+    for (int j = 0; j < KJ; ++j)
 #pragma unroll
-        for (int j = 0; j < KJ; ++j)
+        for (int i = 0; i < CI; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+            for (int r = 0; r < 16; ++r) acc[j][i][r] = sum[j][i][r] = 0.f;
 
     const int u0 = (int)((long long)A.units * split / A.splits);
     const int u1 = (int)((long long)A.units * (split + 1) / A.splits);
@@ -738,80 +759,150 @@ __global__ __launch_bounds__(256) void pw_bww_dense_kernel(BwwArgs A, const floa
     // carried from chunk to chunk (one 64-bit division per workgroup instead of one per slot and chunk); a
     // slot's pixel is that plus its offset, wrapped into the following images.
     float4 rx[NX], rd[ND];
-    int n0 = (int)((long long)u0 * P / HW), p0 = (int)((long long)u0 * P % HW);
-    auto locate = [&](int pix, int &n, int &p) __attribute__((always_inline)) {
-        n = n0;
-        p = p0 + pix;
-        while (p >= HW) { p -= HW; ++n; }
-        return n < A.N;
-    };
-    auto fetch = [&]() __attribute__((always_inline)) {      // the chunk that starts at (n0, p0)
+    const int t256 = threadIdx.x % 256;
+    int n0 = (int)((long long)(u0 + team) * P / HW), p0 = (int)((long long)(u0 + team) * P % HW);
+    auto fetch = [&]() __attribute__((always_inline)) {      // the chunk that starts at (n0, p0); zeros past the last image
 #pragma unroll
-        for (int jj = 0; jj < NX; ++jj) {
-            const int idx = jj * 256 + (int)threadIdx.x;
-            const int pix = idx / (CW / 4), q = idx % (CW / 4);
-            const int cb = cg * (CW / kBlk) + (q >> 2);
-            int n, p;
-            rx[jj] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (locate(pix, n, p) && cb < CB)
-                rx[jj] = *reinterpret_cast<const float4 *>(x + (((size_t)n * CB + cb) * HW + p) * kBlk + (q & 3) * 4);
+        for (int jj = 0; jj < NX + ND; ++jj) {
+            const bool isx = jj < NX;
+            const int idx = (isx ? jj : jj - NX) * 256 + t256, quads = (isx ? CW : KW) / 4;
+            const int pix = idx / quads, q = idx % quads;
+            const int blk = isx ? cg * (CW / kBlk) + (q >> 2) : kt * (KW / kBlk) + (q >> 2);
+            int n = n0, p = p0 + pix;
+            while (p >= HW) { p -= HW; ++n; }
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (n < A.N && blk < (isx ? CB : KB))
+                v = *reinterpret_cast<const float4 *>((isx ? x : dy) + (((size_t)n * (isx ? CB : KB) + blk) * HW + p) * kBlk + (q & 3) * 4);
+            if (isx) rx[isx ? jj : 0] = v;
+            else rd[isx ? 0 : jj - NX] = v;
         }
-#pragma unroll
-        for (int jj = 0; jj < ND; ++jj) {
-            const int idx = jj * 256 + (int)threadIdx.x;
-            const int pix = idx / (KW / 4), q = idx % (KW / 4);
-            const int kb = kt * (KW / kBlk) + (q >> 2);
-            int n, p;
-            rd[jj] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (locate(pix, n, p) && kb < KB)
-                rd[jj] = *reinterpret_cast<const float4 *>(dy + (((size_t)n * KB + kb) * HW + p) * kBlk + (q & 3) * 4);
-        }
-        p0 += P;
+        p0 += 2 * P;
         while (p0 >= HW) { p0 -= HW; ++n0; }
     };
-    auto stash = [&]() __attribute__((always_inline)) {
+    auto stash = [&](bool flip) __attribute__((always_inline)) {
 #pragma unroll
-        for (int jj = 0; jj < NX; ++jj) *reinterpret_cast<float4 *>(xs + (jj * 256 + (int)threadIdx.x) * 4) = rx[jj];     // [pixel][CW c]
+        for (int jj = 0; jj < NX + ND; ++jj) {
+            const bool isx = jj < NX;
+            const int idx = (isx ? jj : jj - NX) * 256 + t256, quads = (isx ? CW : KW) / 4;
+            const int pix = idx / quads, q = idx % quads;
+            float4 v = isx ? rx[isx ? jj : 0] : rd[isx ? 0 : jj - NX];
+            if (!isx && flip) v = make_float4(-v.x, -v.y, -v.z, -v.w);
+            bf16x4 w[3];
+            split4(v, w);
+            char *dst = (isx ? xs : ds) + (q >> 3) * (P * 64) + pix * 64 + (q & 7) * 8;
 #pragma unroll
-        for (int jj = 0; jj < ND; ++jj) *reinterpret_cast<float4 *>(ds + (jj * 256 + (int)threadIdx.x) * 4) = rd[jj];     // [pixel][KW k]
+            for (int i = 0; i < 3; ++i) *reinterpret_cast<bf16x4 *>(dst + i * (isx ? XB : DB)) = w[i];
+        }
     };
 
-    if (u0 < u1) fetch();
-    for (int unit = u0; unit < u1; ++unit) {
-        __syncthreads();                                // the previous chunk is no longer read
-        stash();
+    // this lane's address for the first four pixels of its half of step 0
+    const int lane_off = (half * 8 + lane % 16 / 4) * 64 + split_tr_lane(lane);
+    const LdsTr xp = (LdsTr)(xs + wc * CI * (P * 64) + lane_off), dp = (LdsTr)(ds + wk * KJ * (P * 64) + lane_off);
+
+    // Phases of team 0: multiply chunk 0, stash 1, multiply 1, ...; of team 1, one behind: stash 0, multiply 0, ...
+    const int rounds = (u1 - u0 + 1) / 2;               // the same for both teams (barriers); the last may be one team's only
+    auto flip = [&](int it) __attribute__((always_inline)) { return (it / kPwFlush + split + team) % 2 != 0; };
+    if (u0 + team < u1) fetch();
+    if (team == 0) stash(flip(0));                      // (a workgroup has at least one chunk)
+    __syncthreads();
+    for (int ph = 0; ph < 2 * rounds; ++ph) {
+        const int it = (ph + (team == 0 ? ph % 2 : 0)) / 2, unit = u0 + 2 * it + team;
+        if (ph % 2 != team) {
+            if (unit < u1) stash(flip(it));
+        } else if (unit < u1) {
+            if (unit + 2 < u1) fetch();                 // in flight during the MFMAs below
+            if (active) {
+#pragma unroll
+                for (int s = 0; s < P / 16; ++s) {
+                    bf16x8 d[KJ][3], f[CI][3];
+#pragma unroll
+                    for (int j = 0; j < KJ; ++j)
+#pragma unroll
+                        for (int q = 0; q < 3; ++q) {
+                            const int off = (j * (P * 64) + q * DB + s * 1024) / 8;
+                            d[j][q] = split_tr_read(dp + off, dp + off + 32);
+                        }
+#pragma unroll
+                    for (int i = 0; i < CI; ++i)
+#pragma unroll
+                        for (int q = 0; q < 3; ++q) {
+                            const int off = (i * (P * 64) + q * XB + s * 1024) / 8;
+                            f[i][q] = split_tr_read(xp + off, xp + off + 32);
+                        }
+                    constexpr int ta[6] = {2, 0, 1, 1, 0, 0}, tb[6] = {0, 2, 1, 0, 1, 0};      // smallest products first
+#pragma unroll
+                    for (int t = 0; t < 6; ++t)
+#pragma unroll
+                        for (int j = 0; j < KJ; ++j)
+#pragma unroll
+                            for (int i = 0; i < CI; ++i)
+                                acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[j][ta[t]], f[i][tb[t]], acc[j][i], 0, 0, 0);
+                }
+                if (it % kPwFlush == kPwFlush - 1 || unit + 2 >= u1) {
+                    const float sg = flip(it) ? -1.f : 1.f;
+#pragma unroll
+                    for (int j = 0; j < KJ; ++j)
+#pragma unroll
+                        for (int i = 0; i < CI; ++i)
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) {
+                                sum[j][i][r] = fmaf(sg, acc[j][i][r], sum[j][i][r]);
+                                acc[j][i][r] = 0.f;
+                            }
+                }
+            }
+        }
         __syncthreads();
-        if (unit + 1 < u1) fetch();                     // in flight during the MFMAs below
-#pragma unroll 4
-        for (int pp = 0; pp < P / 2; ++pp) {
-            const int p = 2 * pp + half;                // A[i = c][kk = half], B[kk = half][j = k]
-            float av[CI], bv[KJ];
+    }
+
+    // the second team's sums join the first's: [register][thread of the team]
+    float *red = reinterpret_cast<float *>(pw_lds) + t256;
+    if (team == 1) {
 #pragma unroll
-            for (int i = 0; i < CI; ++i) av[i] = xs[p * CW + wc * (CW / 2) + i * 32 + l32];
-#pragma unroll
-            for (int j = 0; j < KJ; ++j) bv[j] = ds[p * KW + wk * (KW / 2) + j * 32 + l32];
+        for (int j = 0; j < KJ; ++j)
 #pragma unroll
             for (int i = 0; i < CI; ++i)
 #pragma unroll
-                for (int j = 0; j < KJ; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bv[j], acc[i][j], 0, 0, 0);
-        }
+                for (int r = 0; r < 16; ++r) red[((j * CI + i) * 16 + r) * 256] = sum[j][i][r];
     }
+    __syncthreads();
+    if (team == 1 || !active) return;
 
-    // D[i = c][j = k]: column = lane % 32, row = 8*(r/4) + 4*(lane/32) + r%4
+    // D[row = k][column = c]: column = lane % 32, row = 8*(r/4) + 4*(lane/32) + r%4
     float *pbase = part + (size_t)split * A.K * A.C;
+    auto element = [&](int k, int c) __attribute__((always_inline)) {
+        return pbase + ((size_t)(k / kBlk) * CB + c / kBlk) * (kBlk * kBlk) + (c % kBlk) * kBlk + k % kBlk;
+    };
+    bool finite = true;
 #pragma unroll
-    for (int j = 0; j < KJ; ++j) {
-        const int k = kt * KW + wk * (KW / 2) + j * 32 + l32;
-        if (k >= A.K) continue;
+    for (int j = 0; j < KJ; ++j)
 #pragma unroll
-        for (int i = 0; i < CI; ++i)
+        for (int i = 0; i < CI; ++i) {
+            const int c = cg * CW + wc * (CW / 2) + i * 32 + l32;
+            if (c >= A.C) continue;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int c = cg * CW + wc * (CW / 2) + i * 32 + 8 * (r / 4) + 4 * half + (r % 4);
-                if (c < A.C)
-                    pbase[((size_t)(k / kBlk) * CB + c / kBlk) * (kBlk * kBlk) + (c % kBlk) * kBlk + k % kBlk] = acc[i][j][r];
+            for (int gq = 0; gq < 4; ++gq) {
+                const int k = kt * KW + wk * (KW / 2) + j * 32 + 8 * gq + 4 * half;
+                if (k >= A.K) continue;
+                float v[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    v[r] = sum[j][i][4 * gq + r] + red[((j * CI + i) * 16 + 4 * gq + r) * 256];
+                    finite = finite && split_finite(v[r]);
+                }
+                *reinterpret_cast<float4 *>(element(k, c)) = make_float4(v[0], v[1], v[2], v[3]);
             }
+        }
+    if (__builtin_expect(!finite, 0)) {             // values outside the range of the bf16 pieces took part
+        const long long end = (long long)A.N * HW, last = (long long)u1 * P;
+#pragma unroll 1
+        for (int e = 0; e < KJ * CI * 16; ++e) {
+            const int c = cg * CW + wc * (CW / 2) + e / 16 % CI * 32 + l32;
+            const int k = kt * KW + wk * (KW / 2) + e / 16 / CI * 32 + 8 * (e % 16 / 4) + 4 * half + e % 4;
+            if (c >= A.C || k >= A.K) continue;
+            float *o = element(k, c);
+            if (!split_finite(*o)) *o = pw_bww_exact(A, x, dy, k, c, (long long)u0 * P, last < end ? last : end);
+        }
     }
 }
 
@@ -1030,8 +1121,8 @@ constexpr size_t kSparseLds = bww_async_lds_bytes<3, 3, kSparseTH, kSparseTW>();
 
 // The zero-skipping unit-stride kernels use more dynamic LDS than a kernel may without being allowed to: once per
 // device, outside any launch sequence a caller may be capturing into a graph later.
-template <class K>
-hipError_t allow_dynamic_lds(K kern, size_t bytes)
+template <auto Kern>
+hipError_t allow_dynamic_lds(size_t bytes)
 {
     constexpr int kMaxDev = 64;
     static bool allowed[kMaxDev] = {};
@@ -1040,7 +1131,7 @@ hipError_t allow_dynamic_lds(K kern, size_t bytes)
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= kMaxDev) return hipErrorInvalidDevice;
     if (!allowed[dev]) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(Kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
         if (e != hipSuccess) return e;
         allowed[dev] = true;
     }
@@ -1122,7 +1213,10 @@ BwwArgs make_args_pw(const st_conv_desc &d, int kw, int cw, int chunk = kPwP, in
 // dense 1x1 BWW: channels of one operand per workgroup (128, or 64 for layers with no more than that), and the
 // pixels per staged chunk that go with the tile
 int pw_dense_tile(int channels) { return channels > 64 ? 128 : 64; }
-constexpr int kPwDenseWorkgroups = 512;         // two per compute unit: measured best of 256 / 512 / 1024
+constexpr int kPwDenseWorkgroups = 256;         // one of eight wavefronts per compute unit
+template <int CW_, int KW_, int P_>
+struct PwTile { static constexpr int CW = CW_, KW = KW_, P = P_; };
+constexpr size_t pw_dense_lds(int cw, int kw, int p) { return (size_t)2 * 3 * (cw + kw) * p * 2; }
 BwwArgs make_args_pw_dense(const st_conv_desc &d)
 {
     const int cw = pw_dense_tile(d.C), kw = pw_dense_tile(d.K);
@@ -1240,7 +1334,7 @@ hipError_t launch_bww_sparse(const st_conv_desc &d, const float *x, const float 
         hipError_t err = hipGetLastError();
         return err != hipSuccess ? err : reduce(d, A, part, dw, s);
     }
-    hipError_t e = allow_dynamic_lds(bww_sparse_kernel<3, 3, kSparseTH, kSparseTW, 0>, kSparseLds);
+    hipError_t e = allow_dynamic_lds<bww_sparse_kernel<3, 3, kSparseTH, kSparseTW, 0>>(kSparseLds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((bww_sparse_kernel<3, 3, kSparseTH, kSparseTW, 0>), grid, dim3(512), kSparseLds, s, A, x, dy, part);
     e = hipGetLastError();
@@ -1302,7 +1396,7 @@ hipError_t launch_bww_sparse_dy(const st_conv_desc &d, const float *x, const flo
     A.sel = sel; A.want = 1; A.swapped = 1;
     float *part = A.splits == 1 ? dw : ws;
     dim3 grid(A.splits, ceil_div(e.K, 64) * A.cgroups);
-    hipError_t err = allow_dynamic_lds(bww_sparse_kernel<3, 3, kSparseTH, kSparseTW, 0>, kSparseLds);
+    hipError_t err = allow_dynamic_lds<bww_sparse_kernel<3, 3, kSparseTH, kSparseTW, 0>>(kSparseLds);
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL((bww_sparse_kernel<3, 3, kSparseTH, kSparseTW, 0>), grid, dim3(512), kSparseLds, s, A, dy, x, part);
     err = hipGetLastError();
@@ -1328,7 +1422,7 @@ hipError_t launch_bww_auto_merged(const st_conv_desc &d, const float *x, const f
     A0.want = kEitherOperand; A1.want = kEitherOperand; A1.swapped = 1; A2.want = 2;
     const int ygroups = ceil_div(d.K, 64) * ceil_div(d.C, 64);      // the same for both operand roles
     dim3 grid(A0.splits > A1.splits ? A0.splits : A1.splits, ygroups);
-    hipError_t err = allow_dynamic_lds(bww_sparse_either_kernel<3, 3, kSparseTH, kSparseTW>, kSparseLds);
+    hipError_t err = allow_dynamic_lds<bww_sparse_either_kernel<3, 3, kSparseTH, kSparseTW>>(kSparseLds);
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL((bww_sparse_either_kernel<3, 3, kSparseTH, kSparseTW>), grid, dim3(512), kSparseLds, s, A0, A1, x, dy, ws);
     err = hipGetLastError();
@@ -1362,11 +1456,18 @@ hipError_t launch_bww_dense(const st_conv_desc &d, const float *x, const float *
         const int cw = pw_dense_tile(d.C), kw = pw_dense_tile(d.K);
         dim3 grid1(A1.splits, ceil_div(d.K, kw) * A1.cgroups);
         float *part1 = A1.splits == 1 ? dw : ws;
-        if (cw == 128 && kw == 128) hipLaunchKernelGGL((pw_bww_dense_kernel<128, 128, 32>), grid1, dim3(256), 0, s, A1, x, dy, part1);
-        else if (cw == 128) hipLaunchKernelGGL((pw_bww_dense_kernel<128, 64, 64>), grid1, dim3(256), 0, s, A1, x, dy, part1);
-        else if (kw == 128) hipLaunchKernelGGL((pw_bww_dense_kernel<64, 128, 64>), grid1, dim3(256), 0, s, A1, x, dy, part1);
-        else hipLaunchKernelGGL((pw_bww_dense_kernel<64, 64, 64>), grid1, dim3(256), 0, s, A1, x, dy, part1);
-        hipError_t err = hipGetLastError();
+        auto launch = [&](auto cfg) {
+            using C = decltype(cfg);
+            constexpr auto kern = pw_bww_dense_kernel<C::CW, C::KW, C::P>;
+            constexpr size_t lds = pw_dense_lds(C::CW, C::KW, C::P);
+            const hipError_t e = allow_dynamic_lds<kern>(lds);
+            if (e == hipSuccess) hipLaunchKernelGGL(kern, grid1, dim3(512), lds, s, A1, x, dy, part1);
+            return e;
+        };
+        hipError_t err = cw == 128 ? (kw == 128 ? launch(PwTile<128, 128, 32>{}) : launch(PwTile<128, 64, 64>{}))
+                                   : (kw == 128 ? launch(PwTile<64, 128, 64>{}) : launch(PwTile<64, 64, 64>{}));
+        if (err != hipSuccess) return err;
+        err = hipGetLastError();
         return err != hipSuccess ? err : reduce(d, A1, ws, dw, s);
     }
     BwwArgs A = dense_args(d);
