@@ -172,8 +172,14 @@ hipError_t launch_fwd_dense(const Geom &g, const float *in, const float *wd, flo
 bool pw_dense_direct_supported(const Geom &g);
 hipError_t launch_pw_dense_direct(const Geom &g, bool transpose, const float *in, const float *w, float *out,
                                   hipStream_t s);
-// 1x1 layers: matrix product per pixel, no LDS (called by launch_fwd_dense)
-hipError_t launch_pw_dense(const Geom &g, const float *in, const float *wd, float *out, hipStream_t s);
+// 1x1 layers: matrix product per pixel (called by launch_fwd_dense); shares of its channel split; channel blocks per
+// sign of its filter copy
+hipError_t launch_pw_dense(const Geom &g, int cs, const float *in, const float *wd, float *out, float *parts, hipStream_t s);
+int pw_channel_split(const Geom &g);
+// 1x1 launches of few workgroups stay on fp32 instructions, with an fp32 filter copy
+bool pw_small(const Geom &g);
+hipError_t launch_pw_small(const Geom &g, const float *in, const float *wd, float *out, hipStream_t s);
+int pw_sign_group(const Geom &g);
 
 bool bww_fast_supported(const st_conv_desc &d);
 size_t bww_sparse_workspace(const st_conv_desc &d);

@@ -68,7 +68,7 @@ __device__ __forceinline__ void wave_filters_block(int block, int KB, int CB, in
     }
 }
 
-// Element i = 256 * block + thread of the fp32 copy the 1x1 kernel reads, [Ko/32][Ci/16][half][32 k][8 c];
+// Element i = 256 * block + thread of the fp32 copy the 1x1 kernel of small launches reads, [Ko/32][Ci/16][half][32 k][8 c];
 // transpose and padding as below.
 __device__ __forceinline__ void pw_filters_block(size_t block, int Ko, int Ci, int transpose, const float *__restrict__ w,
                                                  float *__restrict__ wd, size_t total)
@@ -93,8 +93,9 @@ __device__ __forceinline__ void pw_filters_block(size_t block, int Ko, int Ci, i
 // consumption order, [Ko/32][Ci/16][tap][3 pieces][2 halves of the 16 channels][32 k][8 c] bf16: the three bf16
 // pieces of B[k][c][tap] = w[k][c][tap] (FWD); transpose = 1: the roles of the channel dimensions are swapped and the
 // taps reversed (BWI).  Ko/Ci are the produced and reduced channel counts of the correlation that will consume
-// the copy; produced channels are padded with zeros to a multiple of 128.  total = pieces of 8.
-__device__ __forceinline__ void reformat_filters_block(size_t block, int Ko, int Ci, int S, int R, int transpose,
+// the copy; produced channels are padded with zeros to a multiple of 128.  Every second group of `group` reduced channel
+// blocks is negated (st_split.hpp).  total = pieces of 8.
+__device__ __forceinline__ void reformat_filters_block(size_t block, int Ko, int Ci, int S, int R, int transpose, int group,
                                                        const float *__restrict__ w, float *__restrict__ wd, size_t total)
 {
     const size_t i = block * 256 + threadIdx.x;
@@ -124,7 +125,7 @@ __device__ __forceinline__ void reformat_filters_block(size_t block, int Ko, int
             hi = p[1];
         }
     }
-    if (cb % 2) {                                       // odd channel blocks with the opposite sign
+    if (cb / group % 2) {
         lo = make_float4(-lo.x, -lo.y, -lo.z, -lo.w);
         hi = make_float4(-hi.x, -hi.y, -hi.z, -hi.w);
     }

@@ -31,13 +31,13 @@ namespace st {
 namespace {
 
 // Prologue: filters in MFMA consumption order (st_filter_copies.hpp).
-__global__ __launch_bounds__(256) void reformat_filters_kernel(int Ko, int Ci, int S, int R, int transpose,
+__global__ __launch_bounds__(256) void reformat_filters_kernel(int Ko, int Ci, int S, int R, int transpose, int group,
                                                                const float *__restrict__ w,
                                                                float *__restrict__ wd, size_t total,
                                                                const unsigned *sel, unsigned thr)
 {
     if (form_deselected(sel, 1, thr)) return;       // the copy of a form that will not run is not written
-    reformat_filters_block(blockIdx.x, Ko, Ci, S, R, transpose, w, wd, total);
+    reformat_filters_block(blockIdx.x, Ko, Ci, S, R, transpose, group, w, wd, total);
 }
 
 __global__ __launch_bounds__(256) void pw_filters_kernel(int Ko, int Ci, int transpose, const float *__restrict__ w,
@@ -64,36 +64,30 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const float4 *__restr
     }
 }
 
-template <int KQ, int HPC, int MODE>
-hipError_t launch_cfg(const Geom &g, const FlatGrid &fq, int cs, const float *in, const float *wd, float *out, hipStream_t s)
+template <int KQ, int HPC, bool DEEP, int MODE>
+hipError_t launch_cfg(const Geom &g, const FlatGrid &fq, int cs, const float *in, const float *wd, float *out, float *parts, hipStream_t s)
 {
     constexpr int TQ = 4 / KQ;
     const int kgroups = ceil_div(g.Ko, 32 * KQ);
     const long long blocks = ((long long)fq.tiles + TQ - 1) / TQ * kgroups;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const size_t n_out = (size_t)g.N * g.Ko * g.Ho * g.Wo;
-    // partial outputs of the shares after the first sit behind the filter copy in the workspace
-    float *part = cs > 1 ? const_cast<float *>(wd) + (fwd_dense_filter_bytes(g) + 255) / 256 * 256 / sizeof(float) : nullptr;
-    hipLaunchKernelGGL((fwd_dense_kernel<KQ, HPC, MODE>), dim3((unsigned)blocks, cs), dim3(256), 0, s, g, in, wd, out, part, fq, kgroups,
-                       cs, n_out);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || cs == 1) return e;
-    const size_t n4 = n_out / 4;
-    hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)(n4 / 256 + 1 < 1024 ? n4 / 256 + 1 : 1024)), dim3(256), 0, s,
-                       reinterpret_cast<const float4 *>(part), reinterpret_cast<float4 *>(out), n4, cs, g.sel, g.thr);
+    hipLaunchKernelGGL((fwd_dense_kernel<KQ, HPC, DEEP, MODE>), dim3((unsigned)blocks, cs), dim3(256), 0, s, g, in, wd, out, parts, fq, kgroups,
+                       cs, (size_t)g.N * g.Ko * g.Ho * g.Wo);
     return hipGetLastError();
 }
 
-// FWD at either stride and unit-stride BWI
-hipError_t launch_flat(const Geom &g, int cs, const float *in, const float *wd, float *out, hipStream_t s)
+// FWD at either stride and unit-stride BWI.  With whole column blocks the filters are requested three taps ahead at three
+// wavefronts per SIMD instead of one tap at four (N = 32, us: 256->256 @56 541 -> 532, 512->512 @14 167 -> 158, one image
+// 512->512 @14 35 -> 30); with 64 produced channels, where that costs a third wavefront, it is 4 % slower.
+hipError_t launch_flat(const Geom &g, int cs, const float *in, const float *wd, float *out, float *parts, hipStream_t s)
 {
     int kq;
     long long blocks;
     const FlatGrid q = dense_tiling(g, &kq, &blocks);
-    if (g.sw == 2) return launch_cfg<4, kHaloS2, 1>(g, q, cs, in, wd, out, s);
-    if (kq == 4) return launch_cfg<4, kHalo, 0>(g, q, cs, in, wd, out, s);
-    if (kq == 2) return launch_cfg<2, kHalo, 0>(g, q, cs, in, wd, out, s);
-    return launch_cfg<1, kHalo, 0>(g, q, cs, in, wd, out, s);
+    if (g.sw == 2) return launch_cfg<4, kHaloS2, true, 1>(g, q, cs, in, wd, out, parts, s);
+    if (kq == 4) return launch_cfg<4, kHalo, true, 0>(g, q, cs, in, wd, out, parts, s);
+    if (kq == 2) return launch_cfg<2, kHalo, false, 0>(g, q, cs, in, wd, out, parts, s);
+    return launch_cfg<1, kHalo, false, 0>(g, q, cs, in, wd, out, parts, s);
 }
 
 // BWI of a stride-2 layer: the four parity classes of the dx positions in one launch, the longest (4 taps) first.  As
@@ -114,7 +108,7 @@ __global__ __launch_bounds__(256, (FlatLds<KQ, kHalo>::MINW)) void fwd_dense_s2_
     static_for<0, 4>([&](auto I) __attribute__((always_inline)) {
         constexpr int i = decltype(I)::value, PI = (3 - i) / 2, PJ = (3 - i) % 2;
         if (blockIdx.x >= q.first[i] && blockIdx.x < q.first[i + 1])            // uniform over the workgroup
-            fwd_dense_body<KQ, kHalo, 2, PI, PJ>(g, in, wd, out, nullptr, q.q[i], kgroups, 1, 0, (int)(blockIdx.x - q.first[i]), 0, lds, raw);
+            fwd_dense_body<KQ, kHalo, false, 2, PI, PJ>(g, in, wd, out, nullptr, q.q[i], kgroups, 1, 0, (int)(blockIdx.x - q.first[i]), 0, lds, raw);
     });
 }
 
@@ -137,14 +131,15 @@ hipError_t launch_s2_bwi(const Geom &g, const float *in, const float *wd, float 
     return hipGetLastError();
 }
 
-hipError_t launch_dense_images(const Geom &g, int cs, const float *in, const float *wd, float *out, hipStream_t s)
+hipError_t launch_dense_images(const Geom &g, int cs, const float *in, const float *wd, float *out, float *parts, hipStream_t s)
 {
+    if (pointwise(g)) return launch_pw_dense(g, cs, in, wd, out, parts, s);
     if (g.uw == 2) {
         if (g.Ko > 64) return launch_s2_bwi<4>(g, in, wd, out, s);
         if (g.Ko > 32) return launch_s2_bwi<2>(g, in, wd, out, s);
         return launch_s2_bwi<1>(g, in, wd, out, s);
     }
-    return launch_flat(g, cs, in, wd, out, s);
+    return launch_flat(g, cs, in, wd, out, parts, s);
 }
 
 }  // namespace
@@ -163,8 +158,7 @@ bool fwd_dense_supported(const Geom &g)
 size_t fwd_dense_filter_bytes(const Geom &g)
 {
     // output channels padded to a multiple of 128 so that every column block a workgroup touches exists
-    // (three bf16 pieces per element; the pixel-wise 1x1 kernel takes fp32)
-    return (size_t)ceil_div(g.Ko, 128) * 128 * g.Ci * g.S * g.R * (pointwise(g) ? 4 : 6);
+    return (size_t)ceil_div(g.Ko, 128) * 128 * g.Ci * g.S * g.R * (pw_small(g) ? 4 : 6);       // (three bf16 pieces per element)
 }
 
 size_t fwd_dense_workspace_bytes(const Geom &g)
@@ -176,21 +170,21 @@ size_t fwd_dense_workspace_bytes(const Geom &g)
     if (cs == 1) return n;
     const size_t need = (n + 255) / 256 * 256 + (size_t)(cs - 1) * out;
     // never less than the fp32 copy and the partial outputs this query has always counted for such a launch
-    const size_t before = (n / 6 * 4 + 255) / 256 * 256 + (size_t)dense_channel_split_pow2(g) * out;
+    const size_t before = pointwise(g) || g.sw != 1 ? 0 : (n / 6 * 4 + 255) / 256 * 256 + (size_t)dense_channel_split_pow2(g) * out;
     return need > before ? need : before;
 }
 
 hipError_t launch_reformat_filters(const Geom &g, bool transpose, const float *w, float *wd, hipStream_t s)
 {
-    if (pointwise(g)) {
-        const size_t n = fwd_dense_filter_bytes(g) / 4;
+    if (pw_small(g)) {
+        const size_t n = (size_t)ceil_div(g.Ko, 128) * 128 * g.Ci;
         hipLaunchKernelGGL(pw_filters_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, g.Ko, g.Ci, transpose ? 1 : 0, w, wd, n,
                            g.sel, g.thr);
         return hipGetLastError();
     }
     const size_t total = fwd_dense_filter_bytes(g) / 48;                 // 8 elements per thread
     hipLaunchKernelGGL(reformat_filters_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, g.Ko, g.Ci,
-                       g.S, g.R, transpose ? 1 : 0, w, wd, total, g.sel, g.thr);
+                       g.S, g.R, transpose ? 1 : 0, pointwise(g) ? pw_sign_group(g) : 1, w, wd, total, g.sel, g.thr);
     return hipGetLastError();
 }
 
@@ -207,16 +201,21 @@ int dense_images_per_launch(const Geom &g)
 hipError_t launch_fwd_dense(const Geom &g, const float *in, const float *wd, float *out, hipStream_t s)
 {
     if (!fwd_dense_supported(g)) return hipErrorInvalidValue;
+    if (pw_small(g)) return launch_pw_small(g, in, wd, out, s);
     const int step = dense_images_per_launch(g), cs = step < g.N ? 1 : dense_channel_split(g);
+    // partial outputs of the shares after the first sit behind the filter copy in the workspace
+    float *parts = cs > 1 ? const_cast<float *>(wd) + (fwd_dense_filter_bytes(g) + 255) / 256 * 256 / sizeof(float) : nullptr;
     for (int n = 0; n < g.N; n += step) {           // (one launch but for tensors of tens of GB)
         Geom h = g;
         h.N = g.N - n < step ? g.N - n : step;
-        const float *hin = in + (size_t)n * g.Ci * g.Hi * g.Wi;
-        float *hout = out + (size_t)n * g.Ko * g.Ho * g.Wo;
-        const hipError_t e = pointwise(h) ? launch_pw_dense(h, hin, wd, hout, s) : launch_dense_images(h, cs, hin, wd, hout, s);
+        const hipError_t e = launch_dense_images(h, cs, in + (size_t)n * g.Ci * g.Hi * g.Wi, wd, out + (size_t)n * g.Ko * g.Ho * g.Wo, parts, s);
         if (e != hipSuccess) return e;
     }
-    return hipSuccess;
+    if (cs == 1) return hipSuccess;
+    const size_t n4 = (size_t)g.N * g.Ko * g.Ho * g.Wo / 4;
+    hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)(n4 / 256 + 1 < 1024 ? n4 / 256 + 1 : 1024)), dim3(256), 0, s,
+                       reinterpret_cast<const float4 *>(parts), reinterpret_cast<float4 *>(out), n4, cs, g.sel, g.thr);
+    return hipGetLastError();
 }
 
 }  // namespace st

@@ -85,7 +85,8 @@ inline FlatGrid flat_grid(int N, int rows, int cols, int pstep, int nv, int nu, 
 // KQ = column blocks (of 32 output channels) per workgroup: 1, 2 or 4; TQ = 4/KQ pixel tiles; HPC = samples of a halo
 // buffer.  With KQ = 4 the next channel block travels through a buffer of raw samples that the loads write
 // directly (no registers: the accumulators and operands of four wavefronts per SIMD leave none), else through registers.
-template <int KQ, int HPC>
+// DEEP: filters are requested three taps ahead instead of one (three wavefronts per SIMD instead of four)
+template <int KQ, int HPC, bool DEEP = false>
 struct FlatLds {
     static constexpr bool RAW = KQ == 4;
     static constexpr int TQ = 4 / KQ;
@@ -94,7 +95,7 @@ struct FlatLds {
     static constexpr int BUF = HPC * 24;                        // floats per tile
     static constexpr int FLOATS = TQ * BUF, RAWFLOATS = RAW ? HPC * 16 : 4;
     // wavefronts per SIMD the register allocator should aim for
-    static constexpr int MINW = KQ == 4 ? (HPC <= kHaloWide ? 4 : 2) : (KQ == 2 ? (HPC <= kHalo ? 3 : 2) : (HPC <= kHalo ? 2 : 1));
+    static constexpr int MINW = KQ == 4 ? (HPC <= kHaloWide ? (DEEP ? 3 : 4) : 2) : (KQ == 2 && !DEEP ? 3 : 2);
 };
 
 typedef const __attribute__((address_space(1))) void *SplitGlobalPtr;
@@ -104,7 +105,7 @@ static __device__ __attribute__((aligned(16))) float kSplitZeros[4] = {0.f, 0.f,
 // wg = index of the workgroup among those of the launch, cshare = its share of the channel split;
 // lds, raw: FlatLds::FLOATS and RAWFLOATS floats, 16-byte aligned.  Every thread of
 // the workgroup makes the call (the body contains barriers).
-template <int KQ, int HPC, int MODE = 0, int PI = 0, int PJ = 0>
+template <int KQ, int HPC, bool DEEP = false, int MODE = 0, int PI = 0, int PJ = 0>
 __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__restrict__ in, const float *__restrict__ wd,
                                                float *__restrict__ out, float *__restrict__ parts, const FlatGrid &fq, int kgroups,
                                                int csplit, size_t part_stride, int wg, int cshare, float *lds_base, float *raw)
@@ -113,6 +114,7 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
     using Lds = FlatLds<KQ, HPC>;
     constexpr int TAPS = 9, TQ = Lds::TQ, NT = Cfg::NT, PSTEP = Cfg::PSTEP, NV = Cfg::NV, NU = Cfg::NU;
     constexpr bool RAW = Lds::RAW;
+    constexpr int D = !DEEP ? 1 : (NT == 9 ? 3 : NT);            // taps the filters are requested ahead; divides NT
     constexpr int NLD = (HPC * 4 + KQ * 64 - 1) / (KQ * 64);     // 16-byte pieces per lane and block
 
     // the wavefront index is the same in every lane: kept in a scalar register, and with it every tile coordinate
@@ -215,8 +217,12 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
 
     float *buf = lds_base + tqi * Lds::BUF;
     fetch(cb0);
-    bf16x8 f0 = filters(cb0 * TAPS + Cfg::ftap(0), 0), f1 = filters(cb0 * TAPS + Cfg::ftap(0), 1), f2 = filters(cb0 * TAPS + Cfg::ftap(0), 2);
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(3));       // all but the filters
+    bf16x8 f[D][3];
+#pragma unroll
+    for (int t = 0; t < D; ++t)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) f[t][q] = filters(cb0 * TAPS + Cfg::ftap(t), q);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * D));   // all but the filters
     stash(buf);
     if (cb0 + 1 < cb1) fetch(cb0 + 1);
     __syncthreads();
@@ -234,35 +240,41 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
                 x1[pb] = input(0, pb, 1);
                 x2[pb] = input(0, pb, 2);
             }
-            // One tap = six products of two pixel blocks.  Every operand register is refilled for the next tap as soon
-            // as its last product of this one has been issued (only filter piece 0, used first and last, has a second
-            // set), which is what fits the accumulators and both operands into the 128 registers of four wavefronts
-            // per SIMD.  The last tap requests the filters of the next block's first one.
+            // One tap = six products of two pixel blocks.  Every operand register is refilled, the input for the next tap
+            // and the filters for D taps on, as soon as its last product of this one has been issued, which is what
+            // fits the accumulators and both operands into the 128 registers of four wavefronts per SIMD with D = 1
+            // (filter piece 0, used first and last, has a second set then).  The last taps request the filters of the
+            // next block's first ones.
             static_for<0, NT>([&](auto T) __attribute__((always_inline)) {
                 constexpr int tp = decltype(T)::value;
                 constexpr bool last = tp + 1 == NT;
                 constexpr int nt = last ? 0 : tp + 1;
-                const int nstep = (last ? min(cb + 1, cb1 - 1) : cb) * TAPS + Cfg::ftap(nt);
-                auto mul = [&](const bf16x8 &f, const bf16x8 (&x)[2], bool first) __attribute__((always_inline)) {
+                constexpr bool wrap = tp + D >= NT;
+                constexpr int ft = wrap ? tp + D - NT : tp + D;
+                const int nstep = (wrap ? min(cb + 1, cb1 - 1) : cb) * TAPS + Cfg::ftap(ft);
+                bf16x8 (&fc)[3] = f[tp % D];
+                auto mul = [&](const bf16x8 &w8, const bf16x8 (&x)[2], bool first) __attribute__((always_inline)) {
 #pragma unroll
                     for (int pb = 0; pb < 2; ++pb)              // rows = output channels, columns = pixels
-                        part[pb] = first ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, x[pb], floatx16{}, 0, 0, 0)
-                                         : __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, x[pb], part[pb], 0, 0, 0);
+                        part[pb] = first ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(w8, x[pb], floatx16{}, 0, 0, 0)
+                                         : __builtin_amdgcn_mfma_f32_32x32x16_bf16(w8, x[pb], part[pb], 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
                 };
-                const bf16x8 f0n = filters(nstep, 0);
-                mul(f0, x0, tp == 0);
-                mul(f2, x0, false);
-                f2 = filters(nstep, 2);
-                mul(f1, x0, false);
+                bf16x8 f0n;
+                if constexpr (D == 1) f0n = filters(nstep, 0);
+                mul(fc[0], x0, tp == 0);
+                mul(fc[2], x0, false);
+                fc[2] = filters(nstep, 2);
+                mul(fc[1], x0, false);
                 if constexpr (!last) { x0[0] = input(nt, 0, 0); x0[1] = input(nt, 1, 0); }
-                mul(f1, x1, false);
-                f1 = filters(nstep, 1);
-                mul(f0, x1, false);
+                mul(fc[1], x1, false);
+                fc[1] = filters(nstep, 1);
+                mul(fc[0], x1, false);
                 if constexpr (!last) { x1[0] = input(nt, 0, 1); x1[1] = input(nt, 1, 1); }
-                mul(f0, x2, false);
+                mul(fc[0], x2, false);
                 if constexpr (!last) { x2[0] = input(nt, 0, 2); x2[1] = input(nt, 1, 2); }
-                f0 = f0n;
+                if constexpr (D == 1) fc[0] = f0n;
+                else fc[0] = filters(nstep, 0);
             });
             // (odd channel blocks have their filters negated: st_split.hpp)
 #pragma unroll
@@ -272,7 +284,7 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
         }
         if (cb + 1 == cb1) break;
         __syncthreads();                            // every wavefront is done with this block
-        if (active) __builtin_amdgcn_s_waitcnt(vmcnt_imm(3));      // the next one has landed (the three newest are filters)
+        if (active) __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * D));  // the next one has landed (the newest 3 D are filters)
         else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
         stash(buf);
         if (cb + 2 < cb1) fetch(cb + 2);            // in flight during the next block's products
@@ -316,15 +328,15 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
     }
 }
 
-template <int KQ, int HPC, int MODE>
-__global__ __launch_bounds__(256, (FlatLds<KQ, HPC>::MINW)) void fwd_dense_kernel(
+template <int KQ, int HPC, bool DEEP, int MODE>
+__global__ __launch_bounds__(256, (FlatLds<KQ, HPC, DEEP>::MINW)) void fwd_dense_kernel(
     Geom g, const float *__restrict__ in, const float *__restrict__ wd, float *__restrict__ out, float *__restrict__ parts,
     FlatGrid fq, int kgroups, int csplit, size_t part_stride)
 {
     if (form_deselected(g.sel, g.want, g.thr)) return;
     __shared__ __attribute__((aligned(16))) float lds[FlatLds<KQ, HPC>::FLOATS];
     __shared__ __attribute__((aligned(16))) float raw[FlatLds<KQ, HPC>::RAWFLOATS];
-    fwd_dense_body<KQ, HPC, MODE>(g, in, wd, out, parts, fq, kgroups, csplit, part_stride, (int)blockIdx.x, (int)blockIdx.y, lds, raw);
+    fwd_dense_body<KQ, HPC, DEEP, MODE>(g, in, wd, out, parts, fq, kgroups, csplit, part_stride, (int)blockIdx.x, (int)blockIdx.y, lds, raw);
 }
 
 // Column blocks per workgroup, tiles and number of workgroups of a 3x3 launch (MODE 0 or 1 of g)
@@ -358,7 +370,8 @@ inline long long dense_rect_blocks(const Geom &g, int *twd)
 // workgroup per compute unit and some.  Depends on the geometry only, so that the workspace query and the launch agree.
 inline int dense_channel_split(const Geom &g)
 {
-    if (g.R != 3 || g.S != 3 || g.uw != 1) return 1;
+    if (g.R == 1) return pw_channel_split(g);
+    if (g.uw != 1) return 1;
     int kq, twd;
     if (g.sw == 1 && dense_rect_blocks(g, &twd) >= 384) return 1;
     if ((long long)g.N * g.Ho * g.Wo > 1 << 20) return 1;

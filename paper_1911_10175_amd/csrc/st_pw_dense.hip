@@ -1,32 +1,243 @@
-// Dense 1x1 (pointwise) unit-stride correlation on the matrix cores: the dense control of the
+// Dense 1x1 (pointwise) unit-stride correlation on the matrix cores: the dense form of the
 // 1x1 layers (SparseTrain Table 1, the resnet*_1*, *_3 rows), used for FWD and, with transposed
 // filters, for BWI.
 //
 // A 1x1 layer is a plain matrix product per pixel (Sec. 5.2 of the paper makes the same remark):
-// out[k][pixel] = sum_c f[k][c] * in[c][pixel] over all N*H*W pixels.  There is no halo and no
-// reuse of an input element between pixels, so nothing is staged in LDS and there are no
-// barriers: with v_mfma_f32_32x32x2_f32 (rows = 32 output channels, columns = 32 pixels,
-// reduction = 2 input channels) a lane supplies, for its pixel, 8 of the 16 channels of a block,
-// which are 32 contiguous bytes of the blocked activation layout, i.e. the operand is loaded
-// from global memory in the order the instruction consumes it.  The filter operand comes from
-// the reformatted copy the 3x3 dense kernel uses, [K/32][C/16][c half][32 k][8 c].
+// out[k][pixel] = sum_c f[k][c] * in[c][pixel] over all N*H*W pixels, numbered across the whole minibatch, so image
+// sizes that are no multiple of the tile leave no ragged tiles except the very last one.
 //
-// These layers sit at or below the ridge of the roofline (25 flop/B for 256 -> 64 channels), so
-// the kernel is built to keep many bytes in flight: each wavefront owns PB*32 pixels and KB*32
-// output channels and keeps the input of the next DEPTH-1 channel blocks and the filters of the
-// next block in registers while the MFMAs of the current block run.  Pixels are numbered across
-// the whole minibatch (n*H*W + p), so image sizes that are no multiple of the tile (28x28,
-// 14x14, 7x7) leave no ragged tiles except the very last one.
+// pw_dense_kernel: fp32 products from bf16 pieces (st_split.hpp), built like the 3x3 kernel (st_fwd_dense.hip) with the
+// channel blocks of a stage in the place of the taps: a wavefront owns 64 pixels times 32 output channels, the four
+// wavefronts of a workgroup cover KQ column blocks of 4/KQ pixel tiles.  A stage of NCB channel blocks of the tile's
+// input is split on its way into LDS, once per workgroup, while the next stage's is in flight (into a raw LDS buffer
+// or registers); the filters come, already split, from the copy the 3x3 kernel uses, one channel block ahead.  A stage
+// is one chain of the matrix cores' accumulators; the filters of odd stages are negated in the copy (st_split.hpp).
+// Against operands taken straight from memory into v_mfma_f32_32x32x2_f32 (pw_small_kernel below), N = 32, us: 256->128
+// @56 74 -> 49, its BWI 84 -> 53, 512->128 @28 38 -> 30, 512->256 @28 69 -> 49, 1024->512 @14 70 -> 51, 512->2048 @7 43 -> 32.
+// Bound by a stage's fixed costs where a compute unit holds one or two workgroups (7x7, 14x14), by the matrix cores and
+// the splitting (130 vector instructions a stage and wavefront against 48 matrix instructions) elsewhere.  Filters
+// requested a whole stage ahead (three wavefronts per SIMD) were measured and are 6-12 % slower.
 #include <cstdlib>
 #include <type_traits>
 
 #include "st_common.hpp"
+#include "st_split.hpp"
 
 namespace st {
 namespace {
 
+constexpr int kPwPx = 64;                               // pixels of a tile: two 32-column MFMA blocks
+constexpr int pw_stage_blocks(int kq) { return kq == 1 ? 2 : 4; }
+
+template <int KQ>
+struct PwCfg {
+    static constexpr bool RAW = KQ == 4;
+    static constexpr int TQ = 4 / KQ, NCB = pw_stage_blocks(KQ);
+    // pieces: [channel block][piece][half of the 16 channels][pixel][8 channels] bf16
+    static constexpr int BUF = NCB * kPwPx * 24, FLOATS = TQ * BUF, RAWFLOATS = RAW ? NCB * kPwPx * 16 : 4;
+    static constexpr int MINW = KQ == 4 ? 4 : (KQ == 2 ? 3 : 2);
+};
+
+typedef const __attribute__((address_space(1))) void *PwGlobalPtr;
+typedef __attribute__((address_space(3))) void *PwLdsPtr;
+static __device__ __attribute__((aligned(16))) float kPwZeros[4] = {0.f, 0.f, 0.f, 0.f};
+
+template <int KQ>
+__global__ __launch_bounds__(256, (PwCfg<KQ>::MINW)) void pw_dense_kernel(Geom g, const float *__restrict__ in,
+                                                                          const float *__restrict__ wd, float *__restrict__ out,
+                                                                          float *__restrict__ parts, int kgroups, int csplit,
+                                                                          size_t part_stride)
+{
+    if (form_deselected(g.sel, 1, g.thr)) return;
+    using Cfg = PwCfg<KQ>;
+    constexpr int TQ = Cfg::TQ, NCB = Cfg::NCB;
+    constexpr bool RAW = Cfg::RAW;
+    constexpr int PPL = 4 / KQ, NLD = NCB * PPL;        // pixels and 16-byte pieces of a stage per lane
+    __shared__ __attribute__((aligned(16))) float lds[Cfg::FLOATS];
+    __shared__ __attribute__((aligned(16))) float raw[Cfg::RAWFLOATS];
+
+    // the wavefront index is the same in every lane: kept in a scalar register, and with it every tile coordinate
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+    const int l32 = lane % 32, half = lane / 32;
+    const int kqi = wave % KQ, tqi = wave / KQ;
+    const int kg = blockIdx.x % kgroups, tg = blockIdx.x / kgroups;
+    const int CiB = g.Ci / kBlk, KoB = g.Ko / kBlk, HW = g.Ho * g.Wo, npx = g.N * HW;
+    const int q0 = (tg * TQ + tqi) * kPwPx;             // (the host keeps npx + 4 tiles in int range)
+    const bool tile_ok = q0 < npx;
+    // shares of the channel split are whole stages; share 0 writes the output, the others partial outputs
+    const int NST = (CiB + NCB - 1) / NCB, cshare = blockIdx.y;
+    const int st0 = NST * cshare / csplit, st1 = NST * (cshare + 1) / csplit, cb1 = min(st1 * NCB, CiB);
+    if (cshare > 0) out = parts + (cshare - 1) * part_stride;
+    const int kb32 = kg * KQ + kqi;                     // this wavefront's column block
+    const bool k_ok = kb32 * 32 < g.Ko, active = tile_ok && k_ok;
+
+    floatx16 acc[2], part[2];
+#pragma unroll
+    for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[pb][r] = 0.f;
+
+    const bf16x8 *bbase = reinterpret_cast<const bf16x8 *>(wd) + (size_t)(k_ok ? kb32 : 0) * CiB * 192;
+    auto filters = [&](int cb, int q) __attribute__((always_inline)) { return (bbase + (size_t)cb * 192 + q * 64)[lane]; };
+
+    // staging: a lane's pieces are one quarter of its PPL pixels' channel block, for every block of the stage; pixels past
+    // the end are staged as zeros
+    const int sl = kqi * kWave + lane, n0 = tile_ok ? q0 / HW : 0;
+    long long poff[PPL];                                // pixel offset relative to image n0
+#pragma unroll
+    for (int i = 0; i < PPL; ++i) {
+        const int q = q0 + i * (KQ * 16) + (sl >> 2);
+        poff[i] = q < npx ? (long long)(q / HW - n0) * CiB * HW + q % HW : -1;
+    }
+    const float *in0 = in + (size_t)n0 * CiB * HW * kBlk + sl % 4 * 4;
+    float4 hreg[RAW ? 1 : NLD];
+    auto fetch = [&](int st) __attribute__((always_inline)) {
+#pragma unroll
+        for (int jj = 0; jj < NLD; ++jj) {
+            const int cb = st * NCB + jj / PPL, i = jj % PPL;
+            const float *src = in0 + ((size_t)cb * HW + poff[i]) * kBlk;
+            if constexpr (RAW) {
+                if (cb < CiB)                           // uniform
+                    __builtin_amdgcn_global_load_lds((PwGlobalPtr)(poff[i] < 0 ? kPwZeros : src),
+                                                     (PwLdsPtr)(raw + (jj * 256 + wave * kWave) * 4), 16, 0, 0);
+            } else {
+                hreg[jj] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (cb < CiB && poff[i] >= 0) hreg[jj] = *reinterpret_cast<const float4 *>(src);
+            }
+        }
+    };
+    float *buf = lds + tqi * Cfg::BUF;
+    auto stash = [&](int st) __attribute__((always_inline)) {
+#pragma unroll
+        for (int jj = 0; jj < NLD; ++jj) {
+            const int sub = jj / PPL, px = jj % PPL * (KQ * 16) + (sl >> 2);
+            if (st * NCB + sub >= CiB) break;           // uniform
+            bf16x4 p[3];
+            if constexpr (RAW) split4(reinterpret_cast<const float4 *>(raw)[jj * 256 + sl], p);
+            else split4(hreg[jj], p);
+            bf16x4 *dst = reinterpret_cast<bf16x4 *>(buf) + (sub * 384 + (sl >> 1 & 1) * 64 + px) * 2 + (sl & 1);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) dst[i * 256] = p[i];
+        }
+    };
+
+    fetch(st0);
+    bf16x8 f0 = filters(st0 * NCB, 0), f1 = filters(st0 * NCB, 1), f2 = filters(st0 * NCB, 2);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(3));           // all but the filters
+    stash(st0);
+    if (st0 + 1 < st1) fetch(st0 + 1);
+    __syncthreads();
+
+    const bf16x8 *xin = reinterpret_cast<const bf16x8 *>(buf) + half * 64 + l32;
+    for (int st = st0; st < st1; ++st) {
+        if (active) {
+            auto input = [&](int sub, int pb, int q) __attribute__((always_inline)) { return xin[sub * 384 + q * 128 + pb * 32]; };
+            bf16x8 x0[2], x1[2], x2[2];
+#pragma unroll
+            for (int pb = 0; pb < 2; ++pb) {
+                x0[pb] = input(0, pb, 0);
+                x1[pb] = input(0, pb, 1);
+                x2[pb] = input(0, pb, 2);
+            }
+            // six products per channel block, operands refilled after their last use (as in the 3x3 kernel)
+            static_for<0, NCB>([&](auto T) __attribute__((always_inline)) {
+                constexpr int sub = decltype(T)::value;
+                constexpr bool last = sub + 1 == NCB;
+                constexpr int ns = last ? 0 : sub + 1;
+                const int cb = st * NCB + sub, ncb = min(cb + 1, cb1 - 1);
+                if (cb >= cb1) return;                  // uniform: the last stage may be short
+                auto mul = [&](const bf16x8 &f, const bf16x8 (&x)[2], bool first) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int pb = 0; pb < 2; ++pb)          // rows = output channels, columns = pixels
+                        part[pb] = first ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, x[pb], floatx16{}, 0, 0, 0)
+                                         : __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, x[pb], part[pb], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                const bf16x8 f0n = filters(ncb, 0);
+                mul(f0, x0, sub == 0);
+                mul(f2, x0, false);
+                f2 = filters(ncb, 2);
+                mul(f1, x0, false);
+                if constexpr (!last) { x0[0] = input(ns, 0, 0); x0[1] = input(ns, 1, 0); }
+                mul(f1, x1, false);
+                f1 = filters(ncb, 1);
+                mul(f0, x1, false);
+                if constexpr (!last) { x1[0] = input(ns, 0, 1); x1[1] = input(ns, 1, 1); }
+                mul(f0, x2, false);
+                if constexpr (!last) { x2[0] = input(ns, 0, 2); x2[1] = input(ns, 1, 2); }
+                f0 = f0n;
+            });
+#pragma unroll
+            for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[pb][r] = fmaf(st % 2 ? -1.f : 1.f, part[pb][r], acc[pb][r]);
+        }
+        if (st + 1 == st1) break;
+        __syncthreads();                                // every wavefront is done with this stage
+        if (active) __builtin_amdgcn_s_waitcnt(vmcnt_imm(3));      // the next one has landed (the three newest are filters)
+        else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        stash(st + 1);
+        if (st + 2 < st1) fetch(st + 2);                // in flight during the next stage's products
+        __syncthreads();
+    }
+
+    // D layout of a 32x32 block: column (pixel) = lane % 32, row (channel) = 8*(r/4) + 4*(lane/32) + r%4:
+    // four consecutive channels per group of 4 accumulators, one 16-byte store each
+    if (!active) return;
+    bool finite = true;
+#pragma unroll
+    for (int pb = 0; pb < 2; ++pb) {
+        const int q = q0 + pb * 32 + l32;
+        if (q >= npx) continue;
+        float *o = out + ((size_t)(q / HW) * KoB * HW + q % HW) * kBlk;
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq) {
+            const int k = kb32 * 32 + 8 * gq + 4 * half;
+            if (k >= g.Ko) continue;
+            const float4 r = make_float4(acc[pb][4 * gq], acc[pb][4 * gq + 1], acc[pb][4 * gq + 2], acc[pb][4 * gq + 3]);
+            finite = finite && split_finite(r.x) && split_finite(r.y) && split_finite(r.z) && split_finite(r.w);
+            *reinterpret_cast<float4 *>(o + (size_t)(k / kBlk) * HW * kBlk + k % kBlk) = r;
+        }
+    }
+    if (__builtin_expect(!finite, 0)) {                 // values outside the range of the bf16 pieces took part
+#pragma unroll 1
+        for (int i = 0; i < 32; ++i) {
+            const int q = q0 + i / 16 * 32 + l32, k = kb32 * 32 + 8 * (i % 16 / 4) + 4 * half + i % 4;
+            if (q >= npx || k >= g.Ko) continue;
+            const int n = q / HW, p = q % HW;
+            float *o = out + (((size_t)n * KoB + k / kBlk) * HW + p) * kBlk + k % kBlk;
+            if (!split_finite(*o)) *o = split_exact_corr(g, in, n, k, p / g.Wo, p % g.Wo, st0 * NCB, cb1);
+        }
+    }
+}
+
+inline int pw_column_blocks(const Geom &g) { return g.Ko > 64 ? 4 : (g.Ko > 32 ? 2 : 1); }
+
+template <int KQ>
+hipError_t launch_pw(const Geom &g, int cs, const float *in, const float *wd, float *out, float *parts, hipStream_t s)
+{
+    constexpr int TQ = PwCfg<KQ>::TQ;
+    const long long tiles = ((long long)g.N * g.Ho * g.Wo + kPwPx - 1) / kPwPx;
+    const int kgroups = ceil_div(g.Ko, 32 * KQ);
+    const long long blocks = (tiles + TQ - 1) / TQ * kgroups;
+    if (blocks > 0x7fffffffLL || tiles * kPwPx > 0x7fff0000LL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((pw_dense_kernel<KQ>), dim3((unsigned)blocks, cs), dim3(256), 0, s, g, in, wd, out, parts, kgroups, cs,
+                       (size_t)g.N * g.Ko * g.Ho * g.Wo);
+    return hipGetLastError();
+}
+
+// Launches of few pixels and channels (fewer than kPwSmall workgroups of the kernel above): with a workgroup or less per
+// compute unit nothing hides a stage's two barriers there, about 2 us a stage.  Here every wavefront works by
+// itself on v_mfma_f32_32x32x2_f32: a lane supplies, for its pixel, 8 of the 16 channels of a block, which are 32
+// contiguous bytes of the blocked activation layout, loaded from global memory in the order the instruction consumes
+// them; the filters come from an fp32 copy, [K/32][C/16][c half][32 k][8 c].  Each wavefront owns PB*32 pixels and KB*32
+// output channels and keeps the input of the next DEPTH-1 channel blocks and the filters of the next block in
+// registers.  Both ways, us: 80->336 @19x23 N = 5 8.4 against 9.4, its BWI 9.6 against 17.5, one image 256->1024 @14 10.1
+// against 14.9, 2048->512 @7 N = 32 (100 workgroups) 40.2 against 41.9; 1024->256 @14 (196) 37.9 against 35.
+constexpr long long kPwSmall = 128;
+
 template <int PB, int KB, int DEPTH>
-__global__ __launch_bounds__(256) void pw_dense_kernel(int total_px, int HW, int CiB, int KoB,
+__global__ __launch_bounds__(256) void pw_small_kernel(int total_px, int HW, int CiB, int KoB,
                                                        const float *__restrict__ in,
                                                        const float *__restrict__ wd,
                                                        float *__restrict__ out, int kgroups,
@@ -145,7 +356,7 @@ __global__ __launch_bounds__(256) void pw_dense_kernel(int total_px, int HW, int
 }
 
 template <int PB, int KB, int DEPTH>
-hipError_t launch_pw(const Geom &g, const float *in, const float *wd, float *out, hipStream_t s)
+hipError_t launch_small(const Geom &g, const float *in, const float *wd, float *out, hipStream_t s)
 {
     const int HW = g.Ho * g.Wo;
     const long long total_px = (long long)g.N * HW;
@@ -153,7 +364,7 @@ hipError_t launch_pw(const Geom &g, const float *in, const float *wd, float *out
     const long long pgroups = (total_px + 4 * 32 * PB - 1) / (4 * 32 * PB);
     const long long blocks = (pgroups + 7) / 8 * 8 * kgroups;
     if (blocks > 0x7fffffffLL || total_px > 0x7fffff00LL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((pw_dense_kernel<PB, KB, DEPTH>), dim3((unsigned)blocks), dim3(256), 0, s, (int)total_px, HW,
+    hipLaunchKernelGGL((pw_small_kernel<PB, KB, DEPTH>), dim3((unsigned)blocks), dim3(256), 0, s, (int)total_px, HW,
                        g.Ci / kBlk, g.Ko / kBlk, in, wd, out, kgroups, g.sel, g.thr);
     return hipGetLastError();
 }
@@ -396,14 +607,38 @@ hipError_t launch_pw_dense_direct(const Geom &g, bool transpose, const float *in
     return launch_pw_lds<8, 4, 4>(g, transpose, in, w, out, s);
 }
 
-// Requires fwd_dense_supported(g) with R = S = 1 (unit stride, no padding: Ho = Hi, Wo = Wi) and the
-// filter copy of launch_reformat_filters, whose output channels are padded to a multiple of 128.
-hipError_t launch_pw_dense(const Geom &g, const float *in, const float *wd, float *out, hipStream_t s)
+// Channel blocks of a stage: the filter copy negates those of odd stages
+int pw_sign_group(const Geom &g) { return pw_stage_blocks(pw_column_blocks(g)); }
+
+namespace {
+long long pw_blocks(const Geom &g)
+{
+    const int kq = pw_column_blocks(g), tq = 4 / kq;
+    const long long tiles = ((long long)g.N * g.Ho * g.Wo + kPwPx - 1) / kPwPx;
+    return (tiles + tq - 1) / tq * ceil_div(g.Ko, 32 * kq);
+}
+}  // namespace
+
+bool pw_small(const Geom &g) { return g.R == 1 && g.S == 1 && pw_blocks(g) < kPwSmall; }
+
+// Shares of the channel reduction of launches with few pixels: enough workgroups for every compute unit and some, at
+// least four whole stages each (fewer cost less than the launch that adds the shares up)
+int pw_channel_split(const Geom &g)
+{
+    if (pw_small(g)) return 1;
+    const int nst = ceil_div(g.Ci / kBlk, pw_stage_blocks(pw_column_blocks(g)));
+    const long long blocks = pw_blocks(g);
+    int cs = 1;
+    while (cs < 8 && blocks * cs < 288 && nst / (cs + 1) >= 4) ++cs;
+    return cs;
+}
+
+// Requires pw_small(g) and the fp32 filter copy of launch_reformat_filters
+hipError_t launch_pw_small(const Geom &g, const float *in, const float *wd, float *out, hipStream_t s)
 {
     const long long total_px = (long long)g.N * g.Ho * g.Wo;
-    // Tile choice (measured on the 1x1 shapes of Table 1 at N = 32): the largest tile that still
-    // yields about one wavefront per SIMD (1024 on the chip); layers with at most 64 output channels
-    // are bandwidth-bound and do best with the most wavefronts in flight.
+    // the largest tile that still yields about one wavefront per SIMD (1024 on the chip); layers with at most 64 output
+    // channels do best with the most wavefronts in flight
     const int cand[6][2] = {{2, 4}, {1, 4}, {2, 2}, {1, 2}, {2, 1}, {1, 1}};
     int pb = 1, kb = 1;
     if (g.Ko > 64)
@@ -412,9 +647,21 @@ hipError_t launch_pw_dense(const Geom &g, const float *in, const float *wd, floa
             const long long waves = (total_px + 32 * c[0] - 1) / (32 * c[0]) * ceil_div(g.Ko, 32 * c[1]);
             if (waves >= 768) { pb = c[0]; kb = c[1]; break; }
         }
-    if (kb == 1) return pb == 1 ? launch_pw<1, 1, 4>(g, in, wd, out, s) : launch_pw<2, 1, 4>(g, in, wd, out, s);
-    if (kb == 2) return pb == 1 ? launch_pw<1, 2, 4>(g, in, wd, out, s) : launch_pw<2, 2, 4>(g, in, wd, out, s);
-    return pb == 1 ? launch_pw<1, 4, 3>(g, in, wd, out, s) : launch_pw<2, 4, 3>(g, in, wd, out, s);
+    if (kb == 1) return pb == 1 ? launch_small<1, 1, 4>(g, in, wd, out, s) : launch_small<2, 1, 4>(g, in, wd, out, s);
+    if (kb == 2) return pb == 1 ? launch_small<1, 2, 4>(g, in, wd, out, s) : launch_small<2, 2, 4>(g, in, wd, out, s);
+    return pb == 1 ? launch_small<1, 4, 3>(g, in, wd, out, s) : launch_small<2, 4, 3>(g, in, wd, out, s);
+}
+
+
+// Requires fwd_dense_supported(g) with R = S = 1 (unit stride, no padding: Ho = Hi, Wo = Wi) and the
+// filter copy of launch_reformat_filters; parts = the partial outputs of the cs - 1 shares after the first
+hipError_t launch_pw_dense(const Geom &g, int cs, const float *in, const float *wd, float *out, float *parts, hipStream_t s)
+{
+    switch (pw_column_blocks(g)) {
+    case 4: return launch_pw<4>(g, cs, in, wd, out, parts, s);
+    case 2: return launch_pw<2>(g, cs, in, wd, out, parts, s);
+    default: return launch_pw<1>(g, cs, in, wd, out, parts, s);
+    }
 }
 
 }  // namespace st
