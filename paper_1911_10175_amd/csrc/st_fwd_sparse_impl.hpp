@@ -326,8 +326,11 @@ __device__ __forceinline__ void fwd_sparse_body(const Geom &g, const float *__re
 
     constexpr int NST = (HP * 4 + 63) / 64;         // halo staging slots (pixel, channel quarter) per lane
 
-    const int cb_begin = cpart * (CiB / CS), cb_end = cb_begin + CiB / CS;      // CiB % CS == 0
-    const int c_last = cb_end * kBlk - 1;
+    // this wavefront's share of the input channels, c_begin .. c_last.  A share need not be whole blocks of 16 where single
+    // channels can be left out of a block (WALK)
+    const int unit = WALK ? 1 : kBlk;
+    const int c_begin = g.Ci / unit * cpart / CS * unit, c_last = g.Ci / unit * (cpart + 1) / CS * unit - 1;
+    const int cb_begin = c_begin / kBlk, cb_end = c_last / kBlk + 1;
     WSet wA;
     std::conditional_t<ROLL, float[1][1], WSet> wB;     // second set: only without the row-by-row refill
     if constexpr (!ROLL) load_w(cb_begin * kBlk, wA, All{});
@@ -355,7 +358,8 @@ __device__ __forceinline__ void fwd_sparse_body(const Geom &g, const float *__re
             // channels per lane have four wavefronts per SIMD either way and gain 1-2 % at 50 % zeros, 2-4 % at
             // 90 %, the 1x1 shapes 2-5 %; the other 3x3 shapes would fall from five wavefronts to four and
             // lose 5-11 %.
-            constexpr int NB = ((PAIRED && TW == 8) || R * S == 1) ? NST : 1;
+            // (With 8 or 16 wavefronts per task a launch never fills four wavefronts per SIMD.)
+            constexpr int NB = ((PAIRED && TW == 8) || R * S == 1 || (CS >= 8 && SD == 1)) ? NST : 1;
 #pragma unroll
             for (int j0 = 0; j0 < NST; j0 += NB) {
                 float4 sv[NB];
@@ -400,6 +404,9 @@ __device__ __forceinline__ void fwd_sparse_body(const Geom &g, const float *__re
                 for (int q = 0; q < 4; ++q)
                     if (m & (0x1111111111111111ull << q)) alive |= 1u << (q * 4 + comp);
             }
+            // channels of the block that belong to other shares are left to them
+            if (cb == cb_begin) alive &= 0xffffu << (c_begin % kBlk);
+            if (cb == cb_end - 1) alive &= 0xffffu >> (kBlk - 1 - c_last % kBlk);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -581,7 +588,11 @@ hipError_t launch_cs(const Geom &g, const float *in, const float *f, float *out,
 // (1024 SIMDs x 4 resident wavefronts) is filled and the tail is short: a wavefront walks its share
 // of the input channels one after the other, about 1.7 us per channel, so a launch that leaves
 // half the wavefront slots empty is as slow as one that fills them.  deep = 8- and 16-way splits allowed
-// (unit-stride 3x3 only).
+// (unit-stride 3x3; the others go up to 8).  Launches with less than a wavefront per SIMD go on splitting, down to two
+// channels a share (3x3: a share of single channels stages whole blocks and skips the rest) or one block (1x1), also
+// where the channel blocks do not divide evenly.  Measured at 50 % zeros, us: 16->16 @8 N = 1 34 -> 14,
+// 80->48 @37x53 N = 3 180 -> 30, 32->64 @20 N = 2 74 -> 21, 96->96 @28 N = 1 94 -> 29, 64->64 @28 N = 4 38 -> 24,
+// stride 2 128->128 @14 N = 1 90 -> 50, 1x1 336->80 @19x23 N = 5 335 -> 59.
 inline int sparse_channel_split(const Geom &g, int TH, int TW, int KT, bool deep)
 {
     const long long tasks = (long long)ceil_div(g.Wo, TW) * ceil_div(g.Ho, TH) * ceil_div(g.Ko, KT) * g.N;
@@ -591,6 +602,7 @@ inline int sparse_channel_split(const Geom &g, int TH, int TW, int KT, bool deep
     if ((CiB >= 16 || tasks < 3072) && CiB % 4 == 0) cs = 4;
     if (deep && tasks <= 512 && CiB % 8 == 0) cs = 8;
     if (deep && tasks <= 256 && CiB % 16 == 0) cs = 16;
+    while (cs < (deep ? 16 : 8) && tasks * cs < 1024 && g.Ci / (cs * 2) >= (g.R == 1 ? kBlk : 2)) cs *= 2;
     return cs;
 }
 
@@ -602,8 +614,8 @@ hipError_t launch_cfg(const Geom &g, const float *in, const float *f, float *out
     const int cs = sparse_channel_split(g, TH, TW, Cfg::KT, deep);
     if constexpr (deep) {
         if (cs == 16) return launch_cs<R, S, TH, TW, KPL, MINW, 16, SD, SU, OFF>(g, in, f, out, s);
-        if (cs == 8) return launch_cs<R, S, TH, TW, KPL, MINW, 8, SD, SU, OFF>(g, in, f, out, s);
     }
+    if (cs == 8) return launch_cs<R, S, TH, TW, KPL, MINW, 8, SD, SU, OFF>(g, in, f, out, s);
     if (cs == 4) return launch_cs<R, S, TH, TW, KPL, MINW, 4, SD, SU, OFF>(g, in, f, out, s);
     if (cs == 2) return launch_cs<R, S, TH, TW, KPL, MINW, 2, SD, SU, OFF>(g, in, f, out, s);
     return launch_cs<R, S, TH, TW, KPL, MINW, 1, SD, SU, OFF>(g, in, f, out, s);
