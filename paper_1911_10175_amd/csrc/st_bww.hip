@@ -1080,6 +1080,26 @@ __global__ __launch_bounds__(512, 4) void pw_bww_sparse_kernel(BwwArgs A, const 
 // belongs to the form `want` and does nothing when another one was selected.
 struct Splits3 { int f[3]; };
 constexpr int kAnyForm = -2;
+// 0 + part[first] + part[first + step] + ... below `splits` (n4 float4 apart), eight loads in flight at a time
+__device__ __forceinline__ float4 add_partials(const float4 *part, size_t n4, int first, int splits, int step)
+{
+    constexpr int BATCH = 8;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    int p = first;
+    for (; p + (BATCH - 1) * step < splits; p += BATCH * step) {
+        float4 v[BATCH];
+#pragma unroll
+        for (int b = 0; b < BATCH; ++b) v[b] = part[(size_t)(p + b * step) * n4];
+#pragma unroll
+        for (int b = 0; b < BATCH; ++b) { s.x += v[b].x; s.y += v[b].y; s.z += v[b].z; s.w += v[b].w; }
+    }
+    for (; p < splits; p += step) {
+        const float4 v = part[(size_t)p * n4];
+        s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+    }
+    return s;
+}
+
 __global__ __launch_bounds__(1024) void bww_reduce_kernel(const float4 *part, float4 *dw, size_t n4, Splits3 sp,
                                                           const unsigned *sel, int want)
 {
@@ -1089,6 +1109,12 @@ __global__ __launch_bounds__(1024) void bww_reduce_kernel(const float4 *part, fl
         if (want != kAnyForm && form != want) return;
     }
     const int splits = form == 0 ? sp.f[0] : form == 1 ? sp.f[1] : sp.f[2];
+    // few splits: a thread per output (the order of the sum is the same)
+    if (splits <= 16) {
+        for (size_t i = (size_t)blockIdx.x * 1024 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 1024)
+            dw[i] = add_partials(part + i, n4, 0, splits, 1);
+        return;
+    }
     __shared__ float4 red[16][64];
     const int o = threadIdx.x % 64, sl = threadIdx.x / 64;
     const size_t nblk = (n4 + 63) / 64;
@@ -1096,10 +1122,7 @@ __global__ __launch_bounds__(1024) void bww_reduce_kernel(const float4 *part, fl
         const size_t i = blk * 64 + o;
         float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
         if (i < n4)
-            for (int p = sl; p < splits; p += 16) {
-                const float4 v = part[(size_t)p * n4 + i];
-                s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-            }
+            s = add_partials(part + i, n4, sl, splits, 16);
         red[sl][o] = s;
         __syncthreads();
         if (sl == 0 && i < n4) {
