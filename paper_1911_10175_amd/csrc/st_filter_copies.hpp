@@ -9,62 +9,67 @@
 namespace st {
 
 #if defined(__HIPCC__)
-// One 16x16 filter block (kb, cb, v, u) = `block` of the LAYER's filters w (library layout) into the
+// The 16x16 filter blocks of all taps of (kb, cb) = `block` of the LAYER's filters w (library layout) into the
 // wavefront-ordered copy wl[Ko/64][Ci][S][R][64 k] (Ko rounded up to whole groups of 64; the padding is never
 // written and never used), or, with paired set, wl[Ko/128][Ci][S][R][64][2]: produced channels k and k + 64 of a
 // group of 128 side by side (Ko is then a multiple of 128).  TRANSPOSE selects the BWI form (channel roles
-// exchanged, taps reversed; SparseTrain Sec. 3.3).  tile: 32 x 17 floats of LDS; with TRANSPOSE every thread of
-// the workgroup must make the call.
+// exchanged, taps reversed; SparseTrain Sec. 3.3).  Nine taps are loaded at a time (a workgroup per tap had one load in
+// flight per thread: 512->512, both copies and the sample 18 -> 12).  tile: kWaveTile floats of LDS; with TRANSPOSE
+// every thread of the workgroup must make the call.
 __device__ __forceinline__ size_t wave_filters_index(int ko, int ci, int tap, int Ci, int SR, int paired)
 {
     if (paired) return ((size_t)(ko / 128) * Ci + ci) * (SR * 128) + tap * 128 + (ko % kWave) * 2 + (ko / kWave) % 2;
     return ((size_t)(ko / kWave) * Ci + ci) * (SR * kWave) + tap * kWave + ko % kWave;
 }
 
+
+constexpr int kTapBatch = 9, kWaveTile = 2 * kTapBatch * kBlk * (kBlk + 1);
 template <bool TRANSPOSE>
 __device__ __forceinline__ void wave_filters_block(int block, int KB, int CB, int S, int R, const float *__restrict__ w,
-                                                   float *__restrict__ wl, float (*tile)[kBlk + 1], int paired)
+                                                   float *__restrict__ wl, float *tile, int paired)
 {
-    int t = block;
-    const int u = t % R; t /= R;
-    const int v = t % S; t /= S;
-    const int cb = t % CB;
-    const int kb = t / CB;
+    const int cb = block % CB, kb = block / CB, SR = S * R;
     const int a = threadIdx.x / kBlk, b = threadIdx.x % kBlk;
-    const size_t blk = (size_t)S * R * (kBlk * kBlk);
-    const size_t src = (((size_t)kb * CB + cb) * S + v) * R * (kBlk * kBlk) + (size_t)u * (kBlk * kBlk);     // [ci = a][ki = b]
-    const int SR = S * R;
-    if (paired) {
-        // The block of the lower 64 channels of a group of 128 writes both partners, 8 contiguous bytes per
-        // thread; the block of the upper 64 has nothing left to do (uniform: the whole workgroup leaves).
-        // tile: 32 x 17 floats here.
-        const int pb = TRANSPOSE ? cb : kb;             // block of the produced channel
-        if (pb % 8 >= 4) return;
-        const size_t src1 = src + (TRANSPOSE ? 4 * blk : 4 * (size_t)CB * blk);      // partner: cb + 4 or kb + 4
-        float2 val;
-        if constexpr (!TRANSPOSE) {
-            const int k = kb * kBlk + b, c = cb * kBlk + a;
-            val = make_float2(w[src + a * kBlk + b], w[src1 + a * kBlk + b]);
-            *reinterpret_cast<float2 *>(wl + wave_filters_index(k, c, v * R + u, CB * kBlk, SR, 1)) = val;
-        } else {
-            tile[a][b] = w[src + a * kBlk + b];
-            tile[kBlk + a][b] = w[src1 + a * kBlk + b];
-            __syncthreads();
-            const int c = cb * kBlk + b, k = kb * kBlk + a;
-            val = make_float2(tile[b][a], tile[kBlk + b][a]);
-            *reinterpret_cast<float2 *>(wl + wave_filters_index(c, k, (S - 1 - v) * R + (R - 1 - u), KB * kBlk, SR, 1)) = val;
+    // paired: the block of the lower 64 channels of a group of 128 writes both partners, 8 contiguous bytes per
+    // thread; the block of the upper 64 has nothing left to do (uniform: the whole workgroup leaves)
+    if (paired && (TRANSPOSE ? cb : kb) % 8 >= 4) return;
+    const float *src = w + ((size_t)kb * CB + cb) * SR * (kBlk * kBlk) + a * kBlk + b;                    // [tap][ci = a][ki = b]
+    const float *src1 = src + (TRANSPOSE ? 4 : 4 * (size_t)CB) * SR * (kBlk * kBlk);                      // partner: cb + 4 or kb + 4
+    // element of the copy: produced channel, reduced channel
+    const int ko = TRANSPOSE ? cb * kBlk + b : kb * kBlk + b, ci = TRANSPOSE ? kb * kBlk + a : cb * kBlk + a;
+    const int Ci = (TRANSPOSE ? KB : CB) * kBlk;
+    auto slot = [&](int i, int partner, int row, int col) __attribute__((always_inline)) {
+        return ((partner * kTapBatch + i) * kBlk + row) * (kBlk + 1) + col;
+    };
+    for (int t0 = 0; t0 < SR; t0 += kTapBatch) {
+        float v0[kTapBatch], v1[kTapBatch];
+#pragma unroll
+        for (int i = 0; i < kTapBatch; ++i) {
+            v0[i] = t0 + i < SR ? src[(t0 + i) * (kBlk * kBlk)] : 0.f;
+            v1[i] = paired && t0 + i < SR ? src1[(t0 + i) * (kBlk * kBlk)] : 0.f;
         }
-        return;
-    }
-    if constexpr (!TRANSPOSE) {
-        const int k = kb * kBlk + b, c = cb * kBlk + a;
-        wl[wave_filters_index(k, c, v * R + u, CB * kBlk, SR, 0)] = w[src + a * kBlk + b];
-    } else {
-        tile[a][b] = w[src + a * kBlk + b];
-        __syncthreads();
-        // produced channel = c (fast index b), reduced channel = k (a)
-        const int c = cb * kBlk + b, k = kb * kBlk + a;
-        wl[wave_filters_index(c, k, (S - 1 - v) * R + (R - 1 - u), KB * kBlk, SR, 0)] = tile[b][a];
+        if constexpr (TRANSPOSE) {
+            if (t0 > 0) __syncthreads();
+#pragma unroll
+            for (int i = 0; i < kTapBatch; ++i) {
+                tile[slot(i, 0, a, b)] = v0[i];
+                if (paired) tile[slot(i, 1, a, b)] = v1[i];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < kTapBatch; ++i) {
+                v0[i] = tile[slot(i, 0, b, a)];
+                if (paired) v1[i] = tile[slot(i, 1, b, a)];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kTapBatch; ++i) {
+            if (t0 + i >= SR) break;
+            const int tap = TRANSPOSE ? SR - 1 - (t0 + i) : t0 + i;
+            float *dst = wl + wave_filters_index(ko, ci, tap, Ci, SR, paired);
+            if (paired) *reinterpret_cast<float2 *>(dst) = make_float2(v0[i], v1[i]);
+            else *dst = v0[i];
+        }
     }
 }
 

@@ -22,14 +22,15 @@ struct DenseGrid {
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
 
 // TH x TW pixels and KPL channels per lane, CS wavefronts per task: the zero-skipping form; KQ column blocks
-// per workgroup and strips of TWD pixels: the dense form
+// per workgroup and strips of TWD pixels: the dense form (28: two strips of 14 a row; whole rows of 28 need a halo half as
+// large again and take 583 instead of 567 us on 512->512 @28, N = 32)
 template <int TH, int TW, int KPL, int CS, int KQ, int TWD>
 __global__ __launch_bounds__(256, 4) void fwd_auto_kernel(Geom g, const float *__restrict__ in, const float *__restrict__ wl,
                                                           const float *__restrict__ wd, float *__restrict__ out,
                                                           SparseGrid sq, DenseGrid dq)
 {
     static_assert(CS <= 4, "both forms run in workgroups of four wavefronts");
-    constexpr int HPC = TWD > 16 ? kHaloWide : kHalo;
+    constexpr int HPC = kHalo;
     __shared__ __attribute__((aligned(16))) float lds[cmax(fwd_sparse_lds_floats<3, 3, TH, TW, KPL, CS>(), FlatLds<KQ, HPC>::FLOATS)];
     __shared__ __attribute__((aligned(16))) float raw[FlatLds<KQ, HPC>::RAWFLOATS];
     // uniform over the grid, before any barrier
@@ -49,7 +50,7 @@ hipError_t launch_pair(const Geom &g, const float *in, const float *wl, const fl
     using SCfg = FwdSparseCfg<3, 3, TH, TW, KPL>;
     const SparseGrid sq = sparse_grid<TH, TW, SCfg::KT, CS>(g);
     DenseGrid dq;
-    dq.q = flat_grid(g.N, g.Ho, g.Wo, 1, 3, 3, TWD > 16 ? kHaloWide : kHalo, TWD);
+    dq.q = flat_grid(g.N, g.Ho, g.Wo, 1, 3, 3, kHalo, TWD > 16 ? TWD / 2 : TWD);
     dq.kgroups = ceil_div(g.Ko, 32 * KQ);
     constexpr int TQ = 4 / KQ;
     dq.blocks = ((long long)dq.q.tiles + TQ - 1) / TQ * dq.kgroups;

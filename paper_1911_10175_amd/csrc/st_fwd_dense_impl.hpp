@@ -34,8 +34,8 @@ struct FlatCfg {
 };
 
 constexpr int kTilePx = 64;                 // two 32-column MFMA blocks
-// Samples a halo buffer holds, by the instance: strips of 8 to 16 pixels at unit stride, of up to 28, and stride 2
-constexpr int kHalo = 160, kHaloWide = 240, kHaloS2 = 320;
+// Samples a halo buffer holds, at unit stride and at stride 2
+constexpr int kHalo = 160, kHaloS2 = 320;
 
 struct FlatGrid {
     int rows, cols;                         // output grid (of the parity class)
@@ -95,7 +95,7 @@ struct FlatLds {
     static constexpr int BUF = HPC * 24;                        // floats per tile
     static constexpr int FLOATS = TQ * BUF, RAWFLOATS = RAW ? HPC * 16 : 4;
     // wavefronts per SIMD the register allocator should aim for
-    static constexpr int MINW = KQ == 4 ? (HPC <= kHaloWide ? (DEEP ? 3 : 4) : 2) : (KQ == 2 && !DEEP ? 3 : 2);
+    static constexpr int MINW = KQ == 4 ? (HPC <= kHalo ? (DEEP ? 3 : 4) : 2) : (KQ == 2 && !DEEP ? 3 : 2);
 };
 
 typedef const __attribute__((address_space(1))) void *SplitGlobalPtr;

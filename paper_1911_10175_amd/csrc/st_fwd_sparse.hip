@@ -72,7 +72,7 @@ __global__ __launch_bounds__(256) void wave_filters_kernel(int KB, int CB, int S
                                                            const unsigned *sel, unsigned thr, int paired)
 {
     if (form_deselected(sel, 0, thr)) return;       // the copy of a form that will not run is not written
-    __shared__ float tile[2 * kBlk][kBlk + 1];
+    __shared__ float tile[kWaveTile];
     wave_filters_block<TRANSPOSE>((int)blockIdx.x, KB, CB, S, R, w, wl, tile, paired);
 }
 
@@ -86,7 +86,7 @@ size_t fwd_sparse_filter_bytes(const Geom &g)
 hipError_t launch_wave_filters(const Geom &g, bool transpose, const float *w, float *wl, hipStream_t s)
 {
     const int KB = (transpose ? g.Ci : g.Ko) / kBlk, CB = (transpose ? g.Ko : g.Ci) / kBlk;     // of the layer
-    const long long blocks = (long long)KB * CB * g.S * g.R;
+    const long long blocks = (long long)KB * CB;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const int paired = fwd_sparse_filters_paired(g) ? 1 : 0;
     if (transpose)

@@ -199,7 +199,7 @@ struct PrepareArgs {
 
 __global__ __launch_bounds__(256) void auto_prepare_kernel(PrepareArgs a)
 {
-    __shared__ float tile[2 * kBlk][kBlk + 1];
+    __shared__ float tile[kWaveTile];
     __shared__ unsigned red[8];
     const unsigned b = blockIdx.x;
     if (b < kSampleParts) {
@@ -285,7 +285,7 @@ hipError_t launch_auto_prepare(const Geom &g, bool transpose, const float *act, 
     a.KB = (transpose ? g.Ci : g.Ko) / kBlk; a.CB = (transpose ? g.Ko : g.Ci) / kBlk;       // of the layer
     a.S = g.S; a.R = g.R; a.Ko = g.Ko; a.Ci = g.Ci; a.transpose = transpose ? 1 : 0;
     a.paired = fwd_sparse_filters_paired(g) ? 1 : 0;
-    const long long n_wave = (long long)a.KB * a.CB * g.S * g.R;
+    const long long n_wave = (long long)a.KB * a.CB;
     a.total_dense = fwd_dense_filter_bytes(g) / 48;
     const long long n_dense = (long long)((a.total_dense + 255) / 256);
     if (n_wave + n_dense + kSampleParts > 0x7fffffffLL) return hipErrorInvalidValue;

@@ -369,8 +369,8 @@ hipError_t launch_small(const Geom &g, const float *in, const float *wd, float *
     return hipGetLastError();
 }
 
-// Variant for layers whose filters fit in LDS (at most 16 K elements: 256 -> 64, 64 -> 256, 64 -> 64,
-// 128 -> 128: the bandwidth-bound 1x1 layers of the 56x56 ResNet stage, 25 flop/B against a ridge of 20).
+// Variant for layers whose filters fit in LDS (at most 16 K elements: 256 -> 64, 64 -> 64, 64 -> 128: the
+// bandwidth-bound 1x1 layers of the 56x56 ResNet stage, 25 flop/B against a ridge of 20), on v_mfma_f32_32x32x2_f32.
 // Time is lost there in four ways, and the structure answers each:
 //  * one persistent workgroup of 8 wavefronts per compute unit copies the whole filter matrix into LDS
 //    once, straight from the library layout with 16-byte coalesced reads, while the input of its first
@@ -581,14 +581,15 @@ hipError_t launch_pw_lds(const Geom &g, bool transpose, const float *in, const f
 
 }  // namespace
 
-// 1x1 layers whose filters fit in 64 KB of LDS, with 64, 128 or 256 output channels, and that have enough
-// pixels to occupy the chip: computed straight from the library filter layout.
+// 1x1 layers whose filters fit in 64 KB of LDS, with 64 or (64 input channels) 128 output channels, and that have enough
+// pixels to occupy the chip: computed straight from the library filter layout.  With more products per pixel the
+// kernel on bf16 pieces is ahead in spite of its filter copy (56x56, N = 32, us, this form : that one: 64->64 13 : 18, 256->64
+// 34 : 40, 128->64 20 : 26, 64->128 23 : 24, 128->128 35 : 33, 64->256 41 : 36).
 bool pw_dense_direct_supported(const Geom &g)
 {
     if (g.R != 1 || g.S != 1 || g.sw != 1 || g.sh != 1 || g.uw != 1 || g.uh != 1 || g.pw != 0 || g.ph != 0) return false;
     const long long total_px = (long long)g.N * g.Ho * g.Wo;
-    const bool shape = (g.Ko == 64 && (g.Ci == 64 || g.Ci == 128 || g.Ci == 256)) ||
-                       (g.Ko == 128 && (g.Ci == 64 || g.Ci == 128)) || (g.Ko == 256 && g.Ci == 64);
+    const bool shape = (g.Ko == 64 && (g.Ci == 64 || g.Ci == 128 || g.Ci == 256)) || (g.Ko == 128 && g.Ci == 64);
     return shape && total_px >= 8192 && total_px <= 0x7fffff00LL;
 }
 
@@ -600,11 +601,7 @@ hipError_t launch_pw_dense_direct(const Geom &g, bool transpose, const float *in
         if (g.Ci == 128) return launch_pw_lds<2, 2, 8>(g, transpose, in, w, out, s);
         return launch_pw_lds<2, 2, 16>(g, transpose, in, w, out, s);
     }
-    if (g.Ko == 128) {
-        if (g.Ci == 64) return launch_pw_lds<4, 4, 4>(g, transpose, in, w, out, s);
-        return launch_pw_lds<4, 4, 8>(g, transpose, in, w, out, s);
-    }
-    return launch_pw_lds<8, 4, 4>(g, transpose, in, w, out, s);
+    return launch_pw_lds<4, 4, 4>(g, transpose, in, w, out, s);
 }
 
 // Channel blocks of a stage: the filter copy negates those of odd stages
