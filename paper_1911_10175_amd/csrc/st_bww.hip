@@ -720,7 +720,7 @@ __device__ __forceinline__ float pw_bww_exact(const BwwArgs &A, const float *x, 
 // channels on a side get the narrower tile (no padded blocks) and chunks of 64 pixels, so that there are as many
 // matrix instructions between two barriers.  Between two barriers one team multiplies while the other splits and stashes
 // its next chunk, so the matrix cores and the vector ALUs work at the same time.  The matrix cores' accumulators are
-// joined to the fp32 sums every 128 pixels of a team, with alternating sign.
+// joined to the fp32 sums every 32 pixels, with a sign that alternates by chunk.
 template <int CW, int KW, int P>
 __global__ __launch_bounds__(512, 2) void pw_bww_dense_kernel(BwwArgs A, const float *__restrict__ x,
                                                               const float *__restrict__ dy, float *__restrict__ part)
@@ -730,7 +730,6 @@ __global__ __launch_bounds__(512, 2) void pw_bww_dense_kernel(BwwArgs A, const f
     constexpr int NX = P * (CW / 4) / 256, ND = P * (KW / 4) / 256;
     constexpr int XB = CW * P * 2, DB = KW * P * 2;     // bytes of one piece of a chunk: [32-channel block][pixel][32 channels]
     constexpr int TEAM = 3 * (XB + DB), SUMS = 256 * CI * KJ * 64;
-    constexpr int kPwFlush = 128 / P;
     static_assert(SUMS <= 2 * TEAM, "the second team's sums go through the same LDS");
     extern __shared__ __attribute__((aligned(16))) char pw_lds[];       // 2 * TEAM bytes
 
@@ -744,13 +743,13 @@ __global__ __launch_bounds__(512, 2) void pw_bww_dense_kernel(BwwArgs A, const f
     char *const xs = pw_lds + team * TEAM, *const ds = xs + 3 * XB;
     const bool active = kt * KW + wk * (KW / 2) < A.K && cg * CW + wc * (CW / 2) < A.C;
 
-    floatx16 acc[KJ][CI], sum[KJ][CI];
+    floatx16 sum[KJ][CI];
 #pragma unroll
     for (int j = 0; j < KJ; ++j)
 #pragma unroll
         for (int i = 0; i < CI; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[j][i][r] = sum[j][i][r] = 0.f;
+            for (int r = 0; r < 16; ++r) sum[j][i][r] = 0.f;
 
     const int u0 = (int)((long long)A.units * split / A.splits);
     const int u1 = (int)((long long)A.units * (split + 1) / A.splits);
@@ -801,7 +800,7 @@ __global__ __launch_bounds__(512, 2) void pw_bww_dense_kernel(BwwArgs A, const f
 
     // Phases of team 0: multiply chunk 0, stash 1, multiply 1, ...; of team 1, one behind: stash 0, multiply 0, ...
     const int rounds = (u1 - u0 + 1) / 2;               // the same for both teams (barriers); the last may be one team's only
-    auto flip = [&](int it) __attribute__((always_inline)) { return (it / kPwFlush + split + team) % 2 != 0; };
+    auto flip = [&](int it) __attribute__((always_inline)) { return (it + split + team) % 2 != 0; };
     if (u0 + team < u1) fetch();
     if (team == 0) stash(flip(0));                      // (a workgroup has at least one chunk)
     __syncthreads();
@@ -812,6 +811,8 @@ __global__ __launch_bounds__(512, 2) void pw_bww_dense_kernel(BwwArgs A, const f
         } else if (unit < u1) {
             if (unit + 2 < u1) fetch();                 // in flight during the MFMAs below
             if (active) {
+                const float sg = flip(it) ? -1.f : 1.f;
+                floatx16 acc[KJ][CI];
 #pragma unroll
                 for (int s = 0; s < P / 16; ++s) {
                     bf16x8 d[KJ][3], f[CI][3];
@@ -836,19 +837,16 @@ __global__ __launch_bounds__(512, 2) void pw_bww_dense_kernel(BwwArgs A, const f
                         for (int j = 0; j < KJ; ++j)
 #pragma unroll
                             for (int i = 0; i < CI; ++i)
-                                acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[j][ta[t]], f[i][tb[t]], acc[j][i], 0, 0, 0);
-                }
-                if (it % kPwFlush == kPwFlush - 1 || unit + 2 >= u1) {
-                    const float sg = flip(it) ? -1.f : 1.f;
+                                acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[j][ta[t]], f[i][tb[t]],
+                                                                                    s % 2 == 0 && t == 0 ? floatx16{} : acc[j][i], 0, 0, 0);
+                    if (s % 2 == 1) {
 #pragma unroll
-                    for (int j = 0; j < KJ; ++j)
+                        for (int j = 0; j < KJ; ++j)
 #pragma unroll
-                        for (int i = 0; i < CI; ++i)
+                            for (int i = 0; i < CI; ++i)
 #pragma unroll
-                            for (int r = 0; r < 16; ++r) {
-                                sum[j][i][r] = fmaf(sg, acc[j][i][r], sum[j][i][r]);
-                                acc[j][i][r] = 0.f;
-                            }
+                                for (int r = 0; r < 16; ++r) sum[j][i][r] = fmaf(sg, acc[j][i][r], sum[j][i][r]);
+                    }
                 }
             }
         }

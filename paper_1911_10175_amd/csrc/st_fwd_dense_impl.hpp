@@ -105,7 +105,11 @@ static __device__ __attribute__((aligned(16))) float kSplitZeros[4] = {0.f, 0.f,
 // wg = index of the workgroup among those of the launch, cshare = its share of the channel split;
 // lds, raw: FlatLds::FLOATS and RAWFLOATS floats, 16-byte aligned.  Every thread of
 // the workgroup makes the call (the body contains barriers).
-template <int KQ, int HPC, bool DEEP = false, int MODE = 0, int PI = 0, int PJ = 0>
+// CHAIN: taps added up in the matrix cores' accumulators before they join the fp32 sum: all of a channel block (0), or a
+// filter row where the whole reduction is one channel block and its rounding is all there is (16 channels: error 1.7e-7 of the norm
+// with 9 taps, 1.2e-7 with 3, 1.4e-7 with v_mfma_f32_32x32x2_f32; with more channels 9 taps are below the fp32 instruction
+// too, and 3 cost 4 % and the combined kernel of st_fwd_auto.hip 15 % in spilled registers).
+template <int KQ, int HPC, bool DEEP = false, int CHAIN = 0, int MODE = 0, int PI = 0, int PJ = 0>
 __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__restrict__ in, const float *__restrict__ wd,
                                                float *__restrict__ out, float *__restrict__ parts, const FlatGrid &fq, int kgroups,
                                                int csplit, size_t part_stride, int wg, int cshare, float *lds_base, float *raw)
@@ -114,6 +118,7 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
     using Lds = FlatLds<KQ, HPC>;
     constexpr int TAPS = 9, TQ = Lds::TQ, NT = Cfg::NT, PSTEP = Cfg::PSTEP, NV = Cfg::NV, NU = Cfg::NU;
     constexpr bool RAW = Lds::RAW;
+    constexpr int CH = CHAIN && CHAIN < NT ? CHAIN : NT;
     constexpr int D = !DEEP ? 1 : (NT == 9 ? 3 : NT);            // taps the filters are requested ahead; divides NT
     constexpr int NLD = (HPC * 4 + KQ * 64 - 1) / (KQ * 64);     // 16-byte pieces per lane and block
 
@@ -149,7 +154,7 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
     const bool k_ok = kb32 * 32 < g.Ko;
     const bool active = tile_ok && k_ok;
 
-    // running sums of the two pixel blocks, and the matrix cores' own accumulators of the current channel block
+    // running sums of the two pixel blocks, and the matrix cores' own accumulators of the current chain
     floatx16 acc[2], part[2];
 #pragma unroll
     for (int pb = 0; pb < 2; ++pb)
@@ -262,7 +267,7 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
                 };
                 bf16x8 f0n;
                 if constexpr (D == 1) f0n = filters(nstep, 0);
-                mul(fc[0], x0, tp == 0);
+                mul(fc[0], x0, tp % CH == 0);
                 mul(fc[2], x0, false);
                 fc[2] = filters(nstep, 2);
                 mul(fc[1], x0, false);
@@ -275,12 +280,14 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
                 if constexpr (!last) { x2[0] = input(nt, 0, 2); x2[1] = input(nt, 1, 2); }
                 if constexpr (D == 1) fc[0] = f0n;
                 else fc[0] = filters(nstep, 0);
+                // (odd channel blocks have their filters negated: st_split.hpp)
+                if constexpr (tp % CH == CH - 1) {
+#pragma unroll
+                    for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[pb][r] = fmaf(cb % 2 ? -1.f : 1.f, part[pb][r], acc[pb][r]);
+                }
             });
-            // (odd channel blocks have their filters negated: st_split.hpp)
-#pragma unroll
-            for (int pb = 0; pb < 2; ++pb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[pb][r] = fmaf(cb % 2 ? -1.f : 1.f, part[pb][r], acc[pb][r]);
         }
         if (cb + 1 == cb1) break;
         __syncthreads();                            // every wavefront is done with this block
@@ -328,7 +335,7 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
     }
 }
 
-template <int KQ, int HPC, bool DEEP, int MODE>
+template <int KQ, int HPC, bool DEEP, int CHAIN, int MODE>
 __global__ __launch_bounds__(256, (FlatLds<KQ, HPC, DEEP>::MINW)) void fwd_dense_kernel(
     Geom g, const float *__restrict__ in, const float *__restrict__ wd, float *__restrict__ out, float *__restrict__ parts,
     FlatGrid fq, int kgroups, int csplit, size_t part_stride)
@@ -336,7 +343,7 @@ __global__ __launch_bounds__(256, (FlatLds<KQ, HPC, DEEP>::MINW)) void fwd_dense
     if (form_deselected(g.sel, g.want, g.thr)) return;
     __shared__ __attribute__((aligned(16))) float lds[FlatLds<KQ, HPC>::FLOATS];
     __shared__ __attribute__((aligned(16))) float raw[FlatLds<KQ, HPC>::RAWFLOATS];
-    fwd_dense_body<KQ, HPC, DEEP, MODE>(g, in, wd, out, parts, fq, kgroups, csplit, part_stride, (int)blockIdx.x, (int)blockIdx.y, lds, raw);
+    fwd_dense_body<KQ, HPC, DEEP, CHAIN, MODE>(g, in, wd, out, parts, fq, kgroups, csplit, part_stride, (int)blockIdx.x, (int)blockIdx.y, lds, raw);
 }
 
 // Column blocks per workgroup, tiles and number of workgroups of a 3x3 launch (MODE 0 or 1 of g)

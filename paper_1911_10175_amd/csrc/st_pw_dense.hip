@@ -10,8 +10,8 @@
 // channel blocks of a stage in the place of the taps: a wavefront owns 64 pixels times 32 output channels, the four
 // wavefronts of a workgroup cover KQ column blocks of 4/KQ pixel tiles.  A stage of NCB channel blocks of the tile's
 // input is split on its way into LDS, once per workgroup, while the next stage's is in flight (into a raw LDS buffer
-// or registers); the filters come, already split, from the copy the 3x3 kernel uses, one channel block ahead.  A stage
-// is one chain of the matrix cores' accumulators; the filters of odd stages are negated in the copy (st_split.hpp).
+// or registers); the filters come, already split, from the copy the 3x3 kernel uses, one channel block ahead; the
+// filters of odd stages are negated in it (st_split.hpp).
 // Against operands taken straight from memory into v_mfma_f32_32x32x2_f32 (pw_small_kernel below), N = 32, us: 256->128
 // @56 74 -> 49, its BWI 84 -> 53, 512->128 @28 38 -> 30, 512->256 @28 69 -> 49, 1024->512 @14 70 -> 51, 512->2048 @7 43 -> 32.
 // Bound by a stage's fixed costs where a compute unit holds one or two workgroups (7x7, 14x14), by the matrix cores and
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(256, (PwCfg<KQ>::MINW)) void pw_dense_kernel(Geom g
                     __builtin_amdgcn_sched_barrier(0);
                 };
                 const bf16x8 f0n = filters(ncb, 0);
-                mul(f0, x0, sub == 0);
+                mul(f0, x0, true);
                 mul(f2, x0, false);
                 f2 = filters(ncb, 2);
                 mul(f1, x0, false);
@@ -166,11 +166,13 @@ __global__ __launch_bounds__(256, (PwCfg<KQ>::MINW)) void pw_dense_kernel(Geom g
                 mul(f0, x2, false);
                 if constexpr (!last) { x2[0] = input(ns, 0, 2); x2[1] = input(ns, 1, 2); }
                 f0 = f0n;
+                // (a channel block is one chain of the matrix cores' accumulators: with a whole stage in a chain the
+                // short reductions, 64 channels, have 1.3e-7 of the norm as error, with one block 1.0e-7)
+#pragma unroll
+                for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[pb][r] = fmaf(st % 2 ? -1.f : 1.f, part[pb][r], acc[pb][r]);
             });
-#pragma unroll
-            for (int pb = 0; pb < 2; ++pb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[pb][r] = fmaf(st % 2 ? -1.f : 1.f, part[pb][r], acc[pb][r]);
         }
         if (st + 1 == st1) break;
         __syncthreads();                                // every wavefront is done with this stage

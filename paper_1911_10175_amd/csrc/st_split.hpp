@@ -11,7 +11,7 @@
 // small terms cut off towards minus infinity rather than rounded (measured: 1 + 16 * 2^-27 returns 1).  Over a long
 // reduction that is 10-20 % more error than the fp32 instruction has, and a bias that grows with the number of terms.
 // Two measures take both away: the kernels start a fresh accumulator per block of the reduction (16 channels x 9
-// taps, or 16 pixels) and add it to the running fp32 sum on the vector ALUs, and every other block is computed with one
+// taps, 3 where the layer has no more than 16 channels; 16 channels of a 1x1; 16 or 32 pixels) and add it to the running fp32 sum on the vector ALUs, and every other block is computed with one
 // operand negated and subtracted, so that the biases cancel.  What is left is a third of the fp32 instruction's error
 // in FWD / BWI (2304 terms: 6.1e-7 -> 2e-7 of the result's norm) and about half in BWW (10^5 terms: 5e-7 -> 2.7e-7).
 //

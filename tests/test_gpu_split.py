@@ -25,6 +25,7 @@ GEOMS = {
     "3x3 tiny images": Geom(70, 16, 144, 2, 3, 3, 3, 1, 1, 1, 1),
     "3x3 one row": Geom(5, 16, 32, 1, 230, 3, 3, 1, 1, 1, 1),
     "3x3 stride 2 tiny images": Geom(40, 32, 16, 3, 4, 3, 3, 2, 2, 1, 1),
+    "3x3 stride 2 16->80": Geom(2, 16, 80, 9, 12, 3, 3, 2, 2, 1, 1),
     "1x1 64->64": Geom(3, 64, 64, 53, 53, 1, 1),
     "1x1 80->48": Geom(2, 80, 48, 5, 7, 1, 1),
 }
