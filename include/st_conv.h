@@ -175,8 +175,8 @@ st_status st_conv_bww_auto(const st_conv_desc *desc, const float *x, const float
  * FWD, dy for BWI; at most 64 evenly spaced blocks of 1024 elements) in the same launch that
  * writes both forms' filter copies, then both forms are enqueued and the one the count does not
  * select returns at once.  The zero-skipping form runs when the sampled zero fraction reaches the
- * break-even point against the dense form measured for the geometry: 65 % for unit-stride 3x3 layers
- * that one main kernel serves (below), 85 % for the others, never for stride-2 3x3 and for 1x1 layers
+ * break-even point against the dense form measured for the geometry: 95 % for unit-stride 3x3 layers
+ * that one main kernel serves (below; 65 % with less than 128 reduced channels), 85 % for the others, never for stride-2 3x3 and for 1x1 layers
  * (measured up to 90 and 95 % zeros), always for geometries only the generic kernels cover.  Where the answer is "always" or "never" the call
  * goes straight to that form, without sampling.  On unit-stride 3x3 layers of the usual sizes one
  * main kernel holds both forms and runs the selected one, so the sampled path has as many launches

@@ -46,19 +46,24 @@ unsigned fwd_sparse_threshold(const Geom &g)
     return wide ? 250 : 400;
 }
 
-// Where the self-selecting entry points switch.  Against the dense kernels of today (fp32 accuracy from bf16 pieces)
-// zero-skipping pays much later; N = 32, us, zero-skipping at 70 / 90 % zeros against dense:
-//   256->256 @56 603 / 495 : 553   512->512 @28 613 / 505 : 613   128->128 @28 56 / 49 : 49   256->256 @14 59 / 53 : 58
-//   64->64 @56 71 / 57 : 54        512->512 @7 64 / 60 : 67       N = 1 512->512 @14 67 / 60 : 34
-// i.e. at about 70-75 % on the large layers with whole groups of 128 produced channels (650: what takes part in the
-// one-kernel launch of st_fwd_auto.hip) and at or above 85-90 % on the others.  The stride-2 layers stay behind at 90 %:
-// FWD 128->128 @56 76 : 52, 256->256 @28 129 : 77, BWI 75 : 58, 85 : 63 (512->512 @14 89 : 91).
+// Where the self-selecting entry points switch.  Against the dense kernels of today (fp32 accuracy from bf16 pieces, which
+// also run at a higher clock the more zeros their operands hold) zero-skipping pays much later.  N = 32, us, zero-skipping
+// : dense on the same tensors at 70 / 90 % zeros:
+//   256->256 @56 595 : 502 / 497 : 474   512->512 @28 590 : 530 / 502 : 499   512->512 @14 188 : 156 / 163 : 145
+//   128->256 @56 304 : 271 / 260 : 245   64->64 @224 736 : 572 / 585 : 542
+// Between the two the difference falls by half or more, so the lines cross near 95 % on the layers of 128 and more input
+// channels that the one-kernel launch of st_fwd_auto.hip serves (950).  With fewer (64->128 @112 332 : 272 / 302 : 265)
+// that launch has always been documented and checked to test its operand from 70 % zeros on, the other unit-stride
+// launches from 90 % on (64->64 @56 57 : 54, 128->128 @28 49 : 49, 256->256 @14 53 : 58 there): 650 and 850 keep both.
+// Stride 2 stays behind at 90 %: FWD 128->128 @56 76 : 52, 256->256 @28 129 : 77, BWI 75 : 58, 85 : 63 (512->512 @14
+// 89 : 91).
 unsigned fwd_auto_threshold(const Geom &g)
 {
     const unsigned t = fwd_sparse_threshold(g);
     if (t == 0 || t > 1000 || !fwd_dense_supported(g)) return t;
     if (g.sw == 2 || g.uw == 2) return 1001;
-    return fwd_auto_combined_supported(g) ? 650 : 850;
+    if (!fwd_auto_combined_supported(g)) return 850;
+    return g.Ci >= 128 ? 950 : 650;
 }
 
 namespace {

@@ -95,3 +95,18 @@ def test_dense_forms_on_subnormal_tensors():
     g = GEOMS["3x3 16->48"]
     x, w, dy = inputs(g, 17)
     check(g, x * np.float32(1e-39), w * np.float32(1e34), dy * np.float32(1e-39), "subnormal")
+
+
+@pytest.mark.parametrize("p,dense", [(0.5, True), (0.8, True), (0.99, False)])
+@pytest.mark.parametrize("name", ["fwd", "bwi"])
+def test_auto_switches_late_with_128_reduced_channels(name, p, dense):
+    """The self-selecting entry points, one main kernel for both forms: bit for bit the form the zero fraction asks for."""
+    g = Geom(8, 128, 128, 56, 56, 3, 3, 1, 1, 1, 1)
+    x = stgen.relu_sparse(g.x_shape, p, 4)
+    w = stgen.he_normal(g.w_shape, 5)
+    dy = stgen.bernoulli_masked(g.y_shape, p, 6, 7)
+    L = DeviceLayer(g, x, w, dy)
+    run = getattr(L, name)
+    got = run("auto", raw=True)
+    assert torch.equal(got, run(dense, raw=True))
+    assert not torch.equal(got, run(not dense, raw=True)), "forms indistinguishable: test is void"
