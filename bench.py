@@ -247,7 +247,7 @@ def write_table1(path, st, stgen, torch, dev, stream, sustain_ms=30.0, iters=7):
                 "auto = st_conv_*_auto, BWW(dy) = st_conv_bww_dy; dense HBM = bytes of every tensor of the pass once / dense time /\n"
                 "8 TB/s; auto / fastest = the self-selecting entry point against the fastest direct call of the row.\n\n")
         f.write("| layer | pass | zeros of tested operand | sparse us | dense us | auto us | BWW(dy) us | effective TFLOP/s | "
-                "executed / 157.3 | dense / 157.3 (MFMA peak) | dense HBM | speed-up | auto / fastest |\n"
+                "executed / 157.3 | dense / 157.3 (fp32 peak) | dense HBM | speed-up | auto / fastest |\n"
                 "|---|---|---|---|---|---|---|---|---|---|---|---|---|\n")
         f.write("\n".join(rows) + "\n")
         f.write(f"\nSums over all rows (us): zero-skipping {tot[0]:.0f}, dense {tot[1]:.0f}, auto {tot[2]:.0f}, "
