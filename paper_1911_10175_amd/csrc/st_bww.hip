@@ -493,26 +493,46 @@ struct BwwDenseCfg {
     static constexpr int LDS = 6 * (XB + DB);
 };
 
-// One element of a partial gradient with plain fp32 multiply-adds: the tiles u0 .. u1-1 of k, c, tap (v, u)
-template <int TH, int TW, int PSTEP>
-__device__ __forceinline__ float bww_exact(const BwwArgs &A, const float *x, const float *dy, int k, int c, int v, int u, int u0, int u1)
+// The 32 x 32 block (output channels k32 .., input channels c32 ..) of a partial gradient once more with fp32 multiply-adds
+// on the matrix cores, operands straight from memory: tiles u0 .. u1-1, all taps.  A sample outside the image takes its
+// dy factor out with it (0 * inf would be NaN).  The 64 lanes of a wavefront make the call together.
+// 256->256 @56, N = 8, us: 170 for ordinary values, one infinity 563, everywhere 607 (element by element, each by one lane, one
+// infinity or subnormal took 27000).
+template <int R, int S, int TH, int TW, int PSTEP>
+__device__ __forceinline__ void bww_redo(const BwwArgs &A, const float *x, const float *dy, int k32, int c32, int u0, int u1, floatx16 (&acc)[S * R])
 {
-    float s = 0.f;
+    static_assert(TH * TW % 2 == 0, "an instruction takes two pixels");
+    const int lane = threadIdx.x % kWave, l32 = lane % 32, half = lane / 32;
+    const int k = min(k32 + l32, A.K - 1), c = min(c32 + l32, A.C - 1);        // (rows and columns past the end are not stored)
+#pragma unroll
+    for (int t = 0; t < S * R; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
 #pragma unroll 1
-    for (int unit = u0; unit < u1 && s == s; ++unit) {
+    for (int unit = u0; unit < u1; ++unit) {
         int t = unit;
         const int tw = t % A.tiles_w; t /= A.tiles_w;
         const int th = t % A.tiles_h, n = t / A.tiles_h;
-#pragma unroll 1
-        for (int p = 0; p < TH * TW; ++p) {
-            const int oh = th * TH + p / TW, ow = tw * TW + p % TW;
-            const int ih = oh * PSTEP - A.ph + v, iw = ow * PSTEP - A.pw + u;
-            if (oh < A.OH && ow < A.OW && ih >= 0 && ih < A.H && iw >= 0 && iw < A.W)
-                s = fmaf(x[act_off(n, c / kBlk, ih, iw, A.C / kBlk, A.H, A.W) + c % kBlk],
-                         dy[act_off(n, k / kBlk, oh, ow, A.K / kBlk, A.OH, A.OW) + k % kBlk], s);
+        const float *xc = x + act_off(n, c / kBlk, 0, 0, A.C / kBlk, A.H, A.W) + c % kBlk;
+        const float *dk = dy + act_off(n, k / kBlk, 0, 0, A.K / kBlk, A.OH, A.OW) + k % kBlk;
+#pragma unroll 2
+        for (int pp = 0; pp < TH * TW / 2; ++pp) {
+            const int p = 2 * pp + half, oh = th * TH + p / TW, ow = tw * TW + p % TW;
+            const bool in = oh < A.OH && ow < A.OW;
+            const float d = dk[in ? (oh * A.OW + ow) * kBlk : 0];
+            float xv[S * R];
+            bool meets[S * R];
+#pragma unroll
+            for (int tap = 0; tap < S * R; ++tap) {
+                const int ih = oh * PSTEP - A.ph + tap / R, iw = ow * PSTEP - A.pw + tap % R;
+                meets[tap] = in && ih >= 0 && ih < A.H && iw >= 0 && iw < A.W;
+                xv[tap] = xc[meets[tap] ? (ih * A.W + iw) * kBlk : 0];
+            }
+#pragma unroll
+            for (int tap = 0; tap < S * R; ++tap)
+                acc[tap] = __builtin_amdgcn_mfma_f32_32x32x2f32(meets[tap] ? d : 0.f, meets[tap] ? xv[tap] : 0.f, acc[tap], 0, 0, 0);
         }
     }
-    return s;
 }
 
 template <int R, int S, int TH, int TW, int PSTEP = 1>
@@ -594,9 +614,8 @@ __global__ __launch_bounds__(256, 2) void bww_dense_kernel(BwwArgs A, const floa
             const int idx = tid + (isx ? i - ND : i) * 256, pix = idx >> 4, q = idx & 15, bytes = isx ? XB : DB;
             if (pix >= (isx ? HP : P)) continue;
             bf16x4 p[3];
-            float4 v = isx ? sx[isx ? i - ND : 0] : sd[isx ? 0 : i];
-            if (!isx && flipped(unit, i)) v = make_float4(-v.x, -v.y, -v.z, -v.w);      // (256 pieces = one step)
-            split4(v, p);
+            const bool flip = !isx && flipped(unit, i);                                 // (256 pieces = one step)
+            split4(isx ? sx[isx ? i - ND : 0] : sd[isx ? 0 : i], flip ? -kSplitScale : kSplitScale, p);
             char *dst = (isx ? xT : dyT) + (q >> 3) * bytes + pix * 64 + (q & 7) * 8;
 #pragma unroll
             for (int j = 0; j < 3; ++j) *reinterpret_cast<bf16x4 *>(dst + j * 2 * bytes) = p[j];
@@ -663,31 +682,36 @@ __global__ __launch_bounds__(256, 2) void bww_dense_kernel(BwwArgs A, const floa
 
     // D layout of the 32x32 block: column (c) = lane % 32, row (k) = 8*(r/4) + 4*(lane/32) + r%4: four consecutive output
     // channels per group of 4 accumulators, one 16-byte store each
-    const int c = cg * 64 + ch * 32 + l32;
-    if (c >= A.C) return;
+    const int k32 = kt * 64 + kh * 32, c32 = cg * 64 + ch * 32, c = c32 + l32;
     float *pbase = part + (size_t)split * A.K * A.C * (S * R);
     auto element = [&](int k, int tap) __attribute__((always_inline)) {
         return pbase + (((size_t)(k / kBlk) * CB + c / kBlk) * (S * R) + tap) * (kBlk * kBlk) + (c % kBlk) * kBlk + k % kBlk;
     };
     bool finite = true;
+    if (c < A.C) {
 #pragma unroll
-    for (int tap = 0; tap < S * R; ++tap)
+        for (int tap = 0; tap < S * R; ++tap)
 #pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-            const int k = kt * 64 + kh * 32 + 8 * gq + 4 * half;
-            if (k >= A.K) continue;
-            const float4 v = make_float4(acc[tap][4 * gq], acc[tap][4 * gq + 1], acc[tap][4 * gq + 2], acc[tap][4 * gq + 3]);
-            finite = finite && split_finite(v.x) && split_finite(v.y) && split_finite(v.z) && split_finite(v.w);
-            *reinterpret_cast<float4 *>(element(k, tap)) = v;
-        }
-    if (__builtin_expect(!finite, 0)) {             // values outside the range of the bf16 pieces took part
-#pragma unroll 1
-        for (int i = 0; i < S * R * 16; ++i) {
-            const int k = kt * 64 + kh * 32 + 8 * (i % 16 / 4) + 4 * half + i % 4, tap = i / 16;
-            if (k >= A.K) continue;
-            float *o = element(k, tap);
-            if (!split_finite(*o)) *o = bww_exact<TH, TW, PSTEP>(A, x, dy, k, c, tap / R, tap % R, u0, u1);
-        }
+            for (int gq = 0; gq < 4; ++gq) {
+                const int k = k32 + 8 * gq + 4 * half;
+                if (k >= A.K) continue;
+                const float4 v = make_float4(acc[tap][4 * gq] * kSplitUnscale, acc[tap][4 * gq + 1] * kSplitUnscale,
+                                             acc[tap][4 * gq + 2] * kSplitUnscale, acc[tap][4 * gq + 3] * kSplitUnscale);
+                finite = finite && split_finite(v);
+                *reinterpret_cast<float4 *>(element(k, tap)) = v;
+            }
+    }
+    // sums that values outside the range of the scaled pieces took part in
+    if (__builtin_expect(__ballot(!finite) != 0, 0)) {
+        bww_redo<R, S, TH, TW, PSTEP>(A, x, dy, k32, c32, u0, u1, acc);
+        if (c >= A.C) return;
+#pragma unroll
+        for (int tap = 0; tap < S * R; ++tap)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int k = k32 + 8 * (r / 4) + 4 * half + r % 4;
+                if (k < A.K && !split_finite(*element(k, tap))) *element(k, tap) = acc[tap][r];
+            }
     }
 }
 
@@ -698,17 +722,43 @@ __global__ __launch_bounds__(256, 2) void bww_dense_kernel(BwwArgs A, const floa
 // ------------------------------------------------------------------------------------------
 constexpr int kPwP = 32;            // pixels per staged chunk
 
-// One element of a 1x1 partial gradient with plain fp32 multiply-adds: pixels p0 .. p1-1 of the minibatch
-__device__ __forceinline__ float pw_bww_exact(const BwwArgs &A, const float *x, const float *dy, int k, int c, long long p0, long long p1)
+// KJ x CI blocks of 32 x 32 elements of a 1x1 partial gradient once more with fp32 multiply-adds on the matrix cores (as
+// bww_redo): `count` pixels of the minibatch from pixel (n, p) on
+template <int KJ, int CI>
+__device__ __forceinline__ void pw_bww_redo(const BwwArgs &A, const float *x, const float *dy, int k0, int c0, int n, int p, long long count,
+                                            floatx16 (&acc)[KJ][CI])
 {
+    const int lane = threadIdx.x % kWave, l32 = lane % 32, half = lane / 32;
     const int HW = A.H * A.W;
-    float s = 0.f;
-#pragma unroll 1
-    for (long long q = p0; q < p1 && s == s; ++q) {
-        const size_t n = (size_t)(q / HW), p = (size_t)(q % HW);
-        s = fmaf(x[((n * (A.C / kBlk) + c / kBlk) * HW + p) * kBlk + c % kBlk], dy[((n * (A.K / kBlk) + k / kBlk) * HW + p) * kBlk + k % kBlk], s);
+#pragma unroll
+    for (int j = 0; j < KJ; ++j)
+#pragma unroll
+        for (int i = 0; i < CI; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.f;
+    p += half;
+#pragma unroll 4
+    for (long long q = 0; q < count; q += 2) {
+        while (p >= HW) { p -= HW; ++n; }
+        const bool in = q + half < count && n < A.N;
+        float d[KJ], xv[CI];
+#pragma unroll
+        for (int j = 0; j < KJ; ++j) {
+            const int k = min(k0 + j * 32 + l32, A.K - 1);                      // (past the end: not stored)
+            d[j] = dy[in ? (((size_t)n * (A.K / kBlk) + k / kBlk) * HW + p) * kBlk + k % kBlk : 0];
+        }
+#pragma unroll
+        for (int i = 0; i < CI; ++i) {
+            const int c = min(c0 + i * 32 + l32, A.C - 1);
+            xv[i] = x[in ? (((size_t)n * (A.C / kBlk) + c / kBlk) * HW + p) * kBlk + c % kBlk : 0];
+        }
+#pragma unroll
+        for (int j = 0; j < KJ; ++j)
+#pragma unroll
+            for (int i = 0; i < CI; ++i)
+                acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? d[j] : 0.f, in ? xv[i] : 0.f, acc[j][i], 0, 0, 0);
+        p += 2;
     }
-    return s;
 }
 
 // Dense, on bf16 pieces (st_split.hpp): workgroup = CW input channels x KW output channels (128 or 64 each).  Its eight
@@ -784,10 +834,8 @@ __global__ __launch_bounds__(512, 2) void pw_bww_dense_kernel(BwwArgs A, const f
             const bool isx = jj < NX;
             const int idx = (isx ? jj : jj - NX) * 256 + t256, quads = (isx ? CW : KW) / 4;
             const int pix = idx / quads, q = idx % quads;
-            float4 v = isx ? rx[isx ? jj : 0] : rd[isx ? 0 : jj - NX];
-            if (!isx && flip) v = make_float4(-v.x, -v.y, -v.z, -v.w);
             bf16x4 w[3];
-            split4(v, w);
+            split4(isx ? rx[isx ? jj : 0] : rd[isx ? 0 : jj - NX], !isx && flip ? -kSplitScale : kSplitScale, w);
             char *dst = (isx ? xs : ds) + (q >> 3) * (P * 64) + pix * 64 + (q & 7) * 8;
 #pragma unroll
             for (int i = 0; i < 3; ++i) *reinterpret_cast<bf16x4 *>(dst + i * (isx ? XB : DB)) = w[i];
@@ -885,22 +933,26 @@ __global__ __launch_bounds__(512, 2) void pw_bww_dense_kernel(BwwArgs A, const f
                 float v[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    v[r] = sum[j][i][4 * gq + r] + red[((j * CI + i) * 16 + 4 * gq + r) * 256];
+                    v[r] = (sum[j][i][4 * gq + r] + red[((j * CI + i) * 16 + 4 * gq + r) * 256]) * kSplitUnscale;
                     finite = finite && split_finite(v[r]);
                 }
                 *reinterpret_cast<float4 *>(element(k, c)) = make_float4(v[0], v[1], v[2], v[3]);
             }
         }
-    if (__builtin_expect(!finite, 0)) {             // values outside the range of the bf16 pieces took part
-        const long long end = (long long)A.N * HW, last = (long long)u1 * P;
-#pragma unroll 1
-        for (int e = 0; e < KJ * CI * 16; ++e) {
-            const int c = cg * CW + wc * (CW / 2) + e / 16 % CI * 32 + l32;
-            const int k = kt * KW + wk * (KW / 2) + e / 16 / CI * 32 + 8 * (e % 16 / 4) + 4 * half + e % 4;
-            if (c >= A.C || k >= A.K) continue;
-            float *o = element(k, c);
-            if (!split_finite(*o)) *o = pw_bww_exact(A, x, dy, k, c, (long long)u0 * P, last < end ? last : end);
-        }
+    // sums that values outside the range of the scaled pieces took part in
+    if (__builtin_expect(__ballot(!finite) != 0, 0)) {
+        const int k0 = kt * KW + wk * (KW / 2), c0 = cg * CW + wc * (CW / 2);
+        const long long first = (long long)u0 * P, end = (long long)A.N * HW, last = (long long)u1 * P;
+        pw_bww_redo<KJ, CI>(A, x, dy, k0, c0, (int)(first / HW), (int)(first % HW), (last < end ? last : end) - first, sum);
+#pragma unroll
+        for (int j = 0; j < KJ; ++j)
+#pragma unroll
+            for (int i = 0; i < CI; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int k = k0 + j * 32 + 8 * (r / 4) + 4 * half + r % 4, c = c0 + i * 32 + l32;
+                    if (k < A.K && c < A.C && !split_finite(*element(k, c))) *element(k, c) = sum[j][i][r];
+                }
     }
 }
 

@@ -130,13 +130,10 @@ __device__ __forceinline__ void reformat_filters_block(size_t block, int Ko, int
             hi = p[1];
         }
     }
-    if (cb / group % 2) {
-        lo = make_float4(-lo.x, -lo.y, -lo.z, -lo.w);
-        hi = make_float4(-hi.x, -hi.y, -hi.z, -hi.w);
-    }
+    const float scale = cb / group % 2 ? -kSplitScale : kSplitScale;
     bf16x4 a[3], b[3];
-    split4(lo, a);
-    split4(hi, b);
+    split4(lo, scale, a);
+    split4(hi, scale, b);
     bf16x8 *out = reinterpret_cast<bf16x8 *>(wd) + step * 192 + half * 32 + l32;
 #pragma unroll
     for (int q = 0; q < 3; ++q) out[q * 64] = __builtin_shufflevector(a[q], b[q], 0, 1, 2, 3, 4, 5, 6, 7);

@@ -211,8 +211,8 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
             const int idx = jj * (KQ * kWave) + sl;
             if (idx < used) {
                 bf16x4 p[3];
-                if constexpr (RAW) split4(reinterpret_cast<const float4 *>(raw)[idx], p);
-                else split4(hreg[jj], p);
+                if constexpr (RAW) split4(reinterpret_cast<const float4 *>(raw)[idx], kSplitScale, p);
+                else split4(hreg[jj], kSplitScale, p);
                 bf16x4 *dst = reinterpret_cast<bf16x4 *>(buf) + ((sl >> 1 & 1) * HPC + (idx >> 2)) * 2 + (sl & 1);
 #pragma unroll
                 for (int i = 0; i < 3; ++i) dst[i * (4 * HPC)] = p[i];
@@ -285,7 +285,7 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
 #pragma unroll
                     for (int pb = 0; pb < 2; ++pb)
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) acc[pb][r] = fmaf(cb % 2 ? -1.f : 1.f, part[pb][r], acc[pb][r]);
+                        for (int r = 0; r < 16; ++r) acc[pb][r] = fmaf(cb % 2 ? -kSplitUnscale : kSplitUnscale, part[pb][r], acc[pb][r]);
                 }
             });
         }
@@ -309,7 +309,7 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
         if constexpr (MODE == 2) { oh = 2 * oh + PI; ow = 2 * ow + PJ; }
         return q < qend;
     };
-    bool finite = true;
+    bool finite[2] = {true, true};
 #pragma unroll
     for (int pb = 0; pb < 2; ++pb) {
         int n, oh, ow;
@@ -319,18 +319,18 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
             const int k = kb32 * 32 + 8 * gq + 4 * half;
             if (k >= g.Ko) continue;
             const float4 r = make_float4(acc[pb][4 * gq], acc[pb][4 * gq + 1], acc[pb][4 * gq + 2], acc[pb][4 * gq + 3]);
-            finite = finite && split_finite(r.x) && split_finite(r.y) && split_finite(r.z) && split_finite(r.w);
+            finite[pb] = finite[pb] && split_finite(r);
             *reinterpret_cast<float4 *>(out + act_off(n, k / kBlk, oh, ow, KoB, g.Ho, g.Wo) + k % kBlk) = r;
         }
     }
-    if (__builtin_expect(!finite, 0)) {             // values outside the range of the bf16 pieces took part
+    // outputs that values outside the range of the scaled pieces took part in
+    if (__builtin_expect(__ballot(!finite[0] || !finite[1]) != 0, 0)) {
 #pragma unroll 1
-        for (int i = 0; i < 32; ++i) {
+        for (int pb = 0; pb < 2; ++pb) {
+            if (__ballot(!finite[pb]) == 0) continue;
             int n, oh, ow;
-            const int k = kb32 * 32 + 8 * (i % 16 / 4) + 4 * half + i % 4;
-            if (!where(i / 16, n, oh, ow) || k >= g.Ko) continue;
-            float *o = out + act_off(n, k / kBlk, oh, ow, KoB, g.Ho, g.Wo) + k % kBlk;
-            if (!split_finite(*o)) *o = split_exact_corr(g, in, n, k, oh, ow, cb0, cb1);
+            const bool valid = where(pb, n, oh, ow);
+            split_redo_corr(g, in, out, valid, n, oh, ow, kb32, cb0, cb1);
         }
     }
 }

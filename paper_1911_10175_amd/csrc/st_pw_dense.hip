@@ -113,8 +113,8 @@ __global__ __launch_bounds__(256, (PwCfg<KQ>::MINW)) void pw_dense_kernel(Geom g
             const int sub = jj / PPL, px = jj % PPL * (KQ * 16) + (sl >> 2);
             if (st * NCB + sub >= CiB) break;           // uniform
             bf16x4 p[3];
-            if constexpr (RAW) split4(reinterpret_cast<const float4 *>(raw)[jj * 256 + sl], p);
-            else split4(hreg[jj], p);
+            if constexpr (RAW) split4(reinterpret_cast<const float4 *>(raw)[jj * 256 + sl], kSplitScale, p);
+            else split4(hreg[jj], kSplitScale, p);
             bf16x4 *dst = reinterpret_cast<bf16x4 *>(buf) + (sub * 384 + (sl >> 1 & 1) * 64 + px) * 2 + (sl & 1);
 #pragma unroll
             for (int i = 0; i < 3; ++i) dst[i * 256] = p[i];
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(256, (PwCfg<KQ>::MINW)) void pw_dense_kernel(Geom g
 #pragma unroll
                 for (int pb = 0; pb < 2; ++pb)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[pb][r] = fmaf(st % 2 ? -1.f : 1.f, part[pb][r], acc[pb][r]);
+                    for (int r = 0; r < 16; ++r) acc[pb][r] = fmaf(st % 2 ? -kSplitUnscale : kSplitUnscale, part[pb][r], acc[pb][r]);
             });
         }
         if (st + 1 == st1) break;
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(256, (PwCfg<KQ>::MINW)) void pw_dense_kernel(Geom g
     // D layout of a 32x32 block: column (pixel) = lane % 32, row (channel) = 8*(r/4) + 4*(lane/32) + r%4:
     // four consecutive channels per group of 4 accumulators, one 16-byte store each
     if (!active) return;
-    bool finite = true;
+    bool finite[2] = {true, true};
 #pragma unroll
     for (int pb = 0; pb < 2; ++pb) {
         const int q = q0 + pb * 32 + l32;
@@ -197,18 +197,17 @@ __global__ __launch_bounds__(256, (PwCfg<KQ>::MINW)) void pw_dense_kernel(Geom g
             const int k = kb32 * 32 + 8 * gq + 4 * half;
             if (k >= g.Ko) continue;
             const float4 r = make_float4(acc[pb][4 * gq], acc[pb][4 * gq + 1], acc[pb][4 * gq + 2], acc[pb][4 * gq + 3]);
-            finite = finite && split_finite(r.x) && split_finite(r.y) && split_finite(r.z) && split_finite(r.w);
+            finite[pb] = finite[pb] && split_finite(r);
             *reinterpret_cast<float4 *>(o + (size_t)(k / kBlk) * HW * kBlk + k % kBlk) = r;
         }
     }
-    if (__builtin_expect(!finite, 0)) {                 // values outside the range of the bf16 pieces took part
+    // outputs that values outside the range of the scaled pieces took part in
+    if (__builtin_expect(__ballot(!finite[0] || !finite[1]) != 0, 0)) {
 #pragma unroll 1
-        for (int i = 0; i < 32; ++i) {
-            const int q = q0 + i / 16 * 32 + l32, k = kb32 * 32 + 8 * (i % 16 / 4) + 4 * half + i % 4;
-            if (q >= npx || k >= g.Ko) continue;
-            const int n = q / HW, p = q % HW;
-            float *o = out + (((size_t)n * KoB + k / kBlk) * HW + p) * kBlk + k % kBlk;
-            if (!split_finite(*o)) *o = split_exact_corr(g, in, n, k, p / g.Wo, p % g.Wo, st0 * NCB, cb1);
+        for (int pb = 0; pb < 2; ++pb) {
+            if (__ballot(!finite[pb]) == 0) continue;
+            const int q = q0 + pb * 32 + l32, p = q % HW;
+            split_redo_corr(g, in, out, q < npx, q / HW, p / g.Wo, p % g.Wo, kb32, st0 * NCB, cb1);
         }
     }
 }

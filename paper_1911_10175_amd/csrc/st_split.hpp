@@ -15,12 +15,12 @@
 // operand negated and subtracted, so that the biases cancel.  What is left is a third of the fp32 instruction's error
 // in FWD / BWI (2304 terms: 6.1e-7 -> 2e-7 of the result's norm) and about half in BWW (10^5 terms: 5e-7 -> 2.7e-7).
 //
-// The decomposition is exact for 2^-100 <= |a| < 2^127.99: smaller values lose their last pieces below the
-// smallest bf16, larger ones round to infinity.  Every element outside that range is handed to the matrix
-// cores as NaN (large and infinite ones become NaN by themselves: inf - inf), so exactly the outputs it takes
-// part in come out non-finite, and a kernel recomputes each non-finite output it holds with plain fp32
-// multiply-adds (split_exact_* below; also the outputs that are non-finite by right).  Ordinary data never
-// gets there.
+// The values are scaled by 2^24 before they are split, so that the last bit of every fp32 value, also of a subnormal one,
+// is a normal bf16 value and the decomposition is exact; the sums are scaled back by 2^-48.  Values from 2^104 and sums from
+// 2^80 on become infinite or NaN that way, as infinities and NaN do by themselves (inf - inf), so exactly the outputs they
+// take part in come out non-finite.  A wavefront that holds a non-finite output computes its tile again with
+// v_mfma_f32_32x32x2_f32, operands straight from memory (split_redo_corr below, the redo parts of the BWW kernels), and takes
+// the non-finite outputs from there.
 #pragma once
 #include "st_common.hpp"
 
@@ -48,25 +48,8 @@ __device__ __forceinline__ bf16x8 split_tr_read(LdsTr p0, LdsTr p1)
 // channel part of a lane's address; its pixel of the four is (lane % 16) / 4
 __device__ __forceinline__ int split_tr_lane(int lane) { return lane / 16 % 2 * 32 + lane % 4 * 8; }
 
-constexpr unsigned kSplitTiny = 0x0D800000u;        // bits of 2^-100
-
-// NaN in place of a value the decomposition cannot carry (non-zero and below 2^-100)
-__device__ __forceinline__ float split_guard(float a)
-{
-    const unsigned b = __float_as_uint(a) << 1;
-    return b - 1u < 2u * kSplitTiny - 1u ? __uint_as_float(0x7fc00000u) : a;
-}
-
-// the same for four values at once; the common case costs six integer operations
-__device__ __forceinline__ float4 split_guard4(float4 v)
-{
-    const unsigned a = (__float_as_uint(v.x) << 1) - 1u, b = (__float_as_uint(v.y) << 1) - 1u;
-    const unsigned c = (__float_as_uint(v.z) << 1) - 1u, d = (__float_as_uint(v.w) << 1) - 1u;
-    const unsigned m = min(min(a, b), min(c, d));       // zeros wrap to the largest value
-    if (__builtin_expect(m < 2u * kSplitTiny - 1u, 0))
-        v = make_float4(split_guard(v.x), split_guard(v.y), split_guard(v.z), split_guard(v.w));
-    return v;
-}
+constexpr float kSplitScale = 16777216.f;                   // 2^24
+constexpr float kSplitUnscale = 1.f / (kSplitScale * kSplitScale);
 
 __device__ __forceinline__ void split2(float a, float b, bf16x2 &p0, bf16x2 &p1, bf16x2 &p2)
 {
@@ -78,43 +61,81 @@ __device__ __forceinline__ void split2(float a, float b, bf16x2 &p0, bf16x2 &p1,
     p2 = __builtin_convertvector(v, bf16x2);            // exact
 }
 
-// the three pieces of four consecutive values, guarded
-__device__ __forceinline__ void split4(float4 v, bf16x4 (&p)[3])
+// the three pieces of four consecutive values times `scale` (kSplitScale or its negative)
+__device__ __forceinline__ void split4(float4 v, float scale, bf16x4 (&p)[3])
 {
-    v = split_guard4(v);
     bf16x2 a[3], b[3];
-    split2(v.x, v.y, a[0], a[1], a[2]);
-    split2(v.z, v.w, b[0], b[1], b[2]);
+    split2(v.x * scale, v.y * scale, a[0], a[1], a[2]);
+    split2(v.z * scale, v.w * scale, b[0], b[1], b[2]);
 #pragma unroll
     for (int i = 0; i < 3; ++i) p[i] = __builtin_shufflevector(a[i], b[i], 0, 1, 2, 3);
 }
 
 __device__ __forceinline__ bool split_finite(float a) { return (__float_as_uint(a) & 0x7f800000u) != 0x7f800000u; }
+__device__ __forceinline__ bool split_finite(float4 v) { return split_finite(v.x) && split_finite(v.y) && split_finite(v.z) && split_finite(v.w); }
 
-// One output of the correlation g (channel blocks cb0 .. cb1-1 of its input) with fp32 multiply-adds from the tensors
-// themselves: g.w = the layer's filters, g.wt = BWI form (channel roles exchanged, taps reversed).
-__device__ __forceinline__ float split_exact_corr(const Geom &g, const float *in, int n, int ko, int oh, int ow, int cb0, int cb1)
+// 32 pixels x 32 output channels of the correlation g once more with fp32 multiply-adds on the matrix cores: the lane's
+// pixel (n, oh, ow; `valid`: it exists), output channels kb32*32 ..., channel blocks cb0 .. cb1-1 of the input.  Non-finite
+// outputs in `out` are replaced.  A tap's products go to a pixel's sum only where the tap meets a sample, so padding
+// never multiplies an infinite filter.  The 64 lanes of the wavefront make the call together.
+// FWD / BWI of 256->256 @56, N = 8, us: 170 / 170 for ordinary values; one infinity in the input 200 / 271, in a filter
+// 344 / 433, everywhere 637 / 1230.  (Output by output, each by one lane, one infinity or subnormal in the input took 9600.)
+__device__ __forceinline__ void split_redo_corr(const Geom &g, const float *in, float *out, bool valid, int n, int oh, int ow,
+                                                          int kb32, int cb0, int cb1)
 {
+    const int lane = threadIdx.x % kWave, l32 = lane % 32, half = lane / 32;
     const int CiB = g.Ci / kBlk, KoB = g.Ko / kBlk;
-    float s = 0.f;
+    const size_t plane = (size_t)g.Hi * g.Wi * kBlk;
+    const int ko = min(kb32 * 32 + l32, g.Ko - 1);          // (rows past the last channel are not stored)
+    const int taps = g.S * g.R;
+    floatx16 sum = {};
 #pragma unroll 1
-    for (int v = 0; v < g.S && s == s; ++v) {               // (NaN stays NaN)
-        const int ph = oh * g.sh - g.ph + v;
-        if (ph < 0 || ph % g.uh != 0 || ph / g.uh >= g.Hi) continue;
-#pragma unroll 1
-        for (int u = 0; u < g.R; ++u) {
-            const int pw = ow * g.sw - g.pw + u;
-            if (pw < 0 || pw % g.uw != 0 || pw / g.uw >= g.Wi) continue;
-#pragma unroll 1
-            for (int ci = cb0 * kBlk; ci < cb1 * kBlk && s == s; ++ci) {
-                const float a = in[act_off(n, ci / kBlk, ph / g.uh, pw / g.uw, CiB, g.Hi, g.Wi) + ci % kBlk];
-                const size_t blk = g.wt ? (((size_t)(ci / kBlk) * KoB + ko / kBlk) * g.S + (g.S - 1 - v)) * g.R + (g.R - 1 - u)
-                                        : (((size_t)(ko / kBlk) * CiB + ci / kBlk) * g.S + v) * g.R + u;
-                s = fmaf(a, g.w[blk * (kBlk * kBlk) + (g.wt ? (ko % kBlk) * kBlk + ci % kBlk : (ci % kBlk) * kBlk + ko % kBlk)], s);
+    for (int tap = 0; tap < taps; ++tap) {
+        const int ph = oh * g.sh - g.ph + tap / g.R, pw = ow * g.sw - g.pw + tap % g.R;
+        const bool meets = valid && ph >= 0 && ph % g.uh == 0 && ph / g.uh < g.Hi && pw >= 0 && pw % g.uw == 0 && pw / g.uw < g.Wi;
+        if (__ballot(meets) == 0) continue;                 // uniform
+        // lanes that meet nothing read the first sample; their column is dropped
+        const float *x = in + (meets ? act_off(n, cb0, ph / g.uh, pw / g.uw, CiB, g.Hi, g.Wi) : (size_t)cb0 * plane) + half * 8;
+        const float *f = g.w + (g.wt ? (((size_t)cb0 * KoB + ko / kBlk) * taps + (taps - 1 - tap)) * (kBlk * kBlk) + ko % kBlk * kBlk
+                                     : (((size_t)(ko / kBlk) * CiB + cb0) * taps + tap) * (kBlk * kBlk) + ko % kBlk) + half * 8 * (g.wt ? 1 : kBlk);
+        const size_t fblock = (size_t)(g.wt ? KoB : 1) * taps * (kBlk * kBlk);
+        floatx16 acc = {};
+        float4 s[2], fv[2];
+        auto load = [&]() __attribute__((always_inline)) {
+            s[0] = *reinterpret_cast<const float4 *>(x);
+            s[1] = *reinterpret_cast<const float4 *>(x + 4);
+            if (g.wt) {
+                fv[0] = *reinterpret_cast<const float4 *>(f);
+                fv[1] = *reinterpret_cast<const float4 *>(f + 4);
+            } else {
+                fv[0] = make_float4(f[0], f[kBlk], f[2 * kBlk], f[3 * kBlk]);
+                fv[1] = make_float4(f[4 * kBlk], f[5 * kBlk], f[6 * kBlk], f[7 * kBlk]);
             }
+            x += plane;
+            f += fblock;
+        };
+        load();
+#pragma unroll 1
+        for (int cb = cb0; cb < cb1; ++cb) {
+            const float4 s0 = s[0], s1 = s[1], f0 = fv[0], f1 = fv[1];
+            if (cb + 1 < cb1) load();                       // in flight during the products
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(j < 4 ? f0[j] : f1[j - 4], j < 4 ? s0[j] : s1[j - 4], acc, 0, 0, 0);
         }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum[r] = meets ? sum[r] + acc[r] : sum[r];
     }
-    return s;
+    if (!valid) return;
+    // the lane's channels: 4*half + {0..3, 8..11} of each of the two 16-channel blocks
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        if (kb32 * 2 + b >= KoB) break;
+        float *o = out + act_off(n, kb32 * 2 + b, oh, ow, KoB, g.Ho, g.Wo) + 4 * half;
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+            if (!split_finite(o[r / 4 * 8 + r % 4])) o[r / 4 * 8 + r % 4] = sum[8 * b + r];
+    }
 }
 #endif
 

@@ -110,3 +110,65 @@ def test_auto_switches_late_with_128_reduced_channels(name, p, dense):
     got = run("auto", raw=True)
     assert torch.equal(got, run(dense, raw=True))
     assert not torch.equal(got, run(not dense, raw=True)), "forms indistinguishable: test is void"
+
+
+def test_dense_forms_on_products_near_the_smallest_normal_number():
+    """Factors in the normal range whose products, and the products of their pieces, are not."""
+    for name in ("3x3 80->144", "3x3 stride 2", "1x1 64->64"):
+        g = GEOMS[name]
+        x, w, dy = inputs(g, 19)
+        check(g, x * np.float32(2.0 ** -62), w * np.float32(2.0 ** -62), dy * np.float32(2.0 ** -64), name)
+        check(g, x * np.float32(2.0 ** -118), w, dy * np.float32(2.0 ** -118), name)
+
+
+def microseconds(fn):
+    """Best of five bursts of ten calls."""
+    best = float("inf")
+    for _ in range(5):
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t0.record()
+        for _ in range(10):
+            fn()
+        t1.record()
+        torch.cuda.synchronize()
+        best = min(best, t0.elapsed_time(t1) * 100)
+    return best
+
+
+@pytest.mark.parametrize("name", ["fwd", "bwi", "bww"])
+@pytest.mark.parametrize("g", [Geom(4, 128, 128, 56, 56, 3, 3, 1, 1, 1, 1), Geom(4, 128, 128, 56, 56, 3, 3, 2, 2, 1, 1),
+                               Geom(8, 256, 256, 56, 56, 1, 1)], ids=["3x3", "stride 2", "1x1"])
+def test_time_of_values_at_the_ends_of_the_range(g, name):
+    """Vanishing values, one (a decayed filter weight, the gradient of a sample the network is sure of) or all of them, cost
+    nothing.  Values from 2^104 on, infinities and NaN make the wavefronts they reach compute their tiles a second time on slower
+    instructions: a few times the usual time and no more, whatever the number of such values."""
+    import paper_1911_10175_amd as st
+    from tests.gpu_harness import desc_of, workspace
+
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    t = {"x": torch.randn((g.N, g.C // 16, g.H, g.W, 16), device="cuda", generator=gen),
+         "w": torch.randn((g.K // 16, g.C // 16, g.S, g.R, 16, 16), device="cuda", generator=gen),
+         "dy": torch.randn((g.N, g.K // 16, g.OH, g.OW, 16), device="cuda", generator=gen)}
+    a, b, out = {"fwd": ("x", "w", "dy"), "bwi": ("dy", "w", "x"), "bww": ("x", "dy", "w")}[name]
+    d, o = desc_of(g), torch.empty_like(t[out])
+    ws = workspace(d, {"fwd": st.ST_PASS_FWD, "bwi": st.ST_PASS_BWI, "bww": st.ST_PASS_BWW}[name], True)
+    entry = getattr(st, f"st_conv_{name}_dense")
+
+    def time_with(which, value, everywhere):
+        ops = {k: t[k].clone() for k in (a, b)}
+        if everywhere:
+            ops[which].fill_(value)
+        elif value is not None:
+            ops[which].view(-1)[ops[which].numel() // 3] = value
+        return microseconds(lambda: entry(d, ops[a], ops[b], o, ws))
+
+    time_with(a, None, False)
+    usual = time_with(a, None, False)
+    # 1.5: two measurements of the same work.  10: the usual time, then 16/6 of its matrix time at fp32 rate without the overlap
+    # of staging and arithmetic that makes the usual time; measured 1.4 to 7 (before such tiles were computed by
+    # wavefronts, lane by lane: one value 10 to 150)
+    for which in (a, b):
+        for value, everywhere, factor in ((1e-35, False, 1.5), (1e-42, False, 1.5), (1e-35, True, 1.5), (float("inf"), False, 10), (float("inf"), True, 10),
+                                          (1e36, False, 10), (float("nan"), False, 10)):
+            us = time_with(which, value, everywhere)
+            assert us <= factor * usual + 5, f"{name} {value} in {which}{' everywhere' if everywhere else ''}: {us:.0f} us, usually {usual:.0f}"
