@@ -71,7 +71,7 @@ bool pick_pair(const Geom &g, Pair *p)
     if (g.R != 3 || g.S != 3 || g.sw != 1 || g.sh != 1 || g.uw != 1 || g.uh != 1) return false;
     if (!fwd_sparse_supported(g) || !fwd_dense_supported(g)) return false;
     if (dense_channel_split(g) != 1) return false;
-    if (g.Ci <= kBlk) return false;                // the dense form adds these up in another order (CHAIN)
+    if (g.Ci <= kBlk) return false;                // one channel block: left to the separate kernels, as it always has been
     // one channel per lane (64 produced channels) is left to the separate kernels: next to the dense body it
     // loses its fifth wavefront per SIMD and runs 14-21 % slower (measured on 64->64 @224 and the BWI of 64->128 @112)
     if (g.Ko % 128 != 0) return false;

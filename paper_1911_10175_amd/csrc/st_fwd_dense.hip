@@ -64,14 +64,14 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const float4 *__restr
     }
 }
 
-template <int KQ, int HPC, bool DEEP, int CHAIN, int MODE>
+template <int KQ, int HPC, bool DEEP, int MODE>
 hipError_t launch_cfg(const Geom &g, const FlatGrid &fq, int cs, const float *in, const float *wd, float *out, float *parts, hipStream_t s)
 {
     constexpr int TQ = 4 / KQ;
     const int kgroups = ceil_div(g.Ko, 32 * KQ);
     const long long blocks = ((long long)fq.tiles + TQ - 1) / TQ * kgroups;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((fwd_dense_kernel<KQ, HPC, DEEP, CHAIN, MODE>), dim3((unsigned)blocks, cs), dim3(256), 0, s, g, in, wd, out, parts, fq, kgroups,
+    hipLaunchKernelGGL((fwd_dense_kernel<KQ, HPC, DEEP, MODE>), dim3((unsigned)blocks, cs), dim3(256), 0, s, g, in, wd, out, parts, fq, kgroups,
                        cs, (size_t)g.N * g.Ko * g.Ho * g.Wo);
     return hipGetLastError();
 }
@@ -84,16 +84,10 @@ hipError_t launch_flat(const Geom &g, int cs, const float *in, const float *wd, 
     int kq;
     long long blocks;
     const FlatGrid q = dense_tiling(g, &kq, &blocks);
-    if (g.Ci == kBlk) {                             // one channel block: filter row by filter row (CHAIN)
-        if (g.sw == 2) return launch_cfg<4, kHaloS2, false, 3, 1>(g, q, cs, in, wd, out, parts, s);
-        if (kq == 4) return launch_cfg<4, kHalo, true, 3, 0>(g, q, cs, in, wd, out, parts, s);
-        if (kq == 2) return launch_cfg<2, kHalo, false, 3, 0>(g, q, cs, in, wd, out, parts, s);
-        return launch_cfg<1, kHalo, false, 3, 0>(g, q, cs, in, wd, out, parts, s);
-    }
-    if (g.sw == 2) return launch_cfg<4, kHaloS2, true, 0, 1>(g, q, cs, in, wd, out, parts, s);
-    if (kq == 4) return launch_cfg<4, kHalo, true, 0, 0>(g, q, cs, in, wd, out, parts, s);
-    if (kq == 2) return launch_cfg<2, kHalo, false, 0, 0>(g, q, cs, in, wd, out, parts, s);
-    return launch_cfg<1, kHalo, false, 0, 0>(g, q, cs, in, wd, out, parts, s);
+    if (g.sw == 2) return launch_cfg<4, kHaloS2, true, 1>(g, q, cs, in, wd, out, parts, s);
+    if (kq == 4) return launch_cfg<4, kHalo, true, 0>(g, q, cs, in, wd, out, parts, s);
+    if (kq == 2) return launch_cfg<2, kHalo, false, 0>(g, q, cs, in, wd, out, parts, s);
+    return launch_cfg<1, kHalo, false, 0>(g, q, cs, in, wd, out, parts, s);
 }
 
 // BWI of a stride-2 layer: the four parity classes of the dx positions in one launch, the longest (4 taps) first.  As
@@ -114,7 +108,7 @@ __global__ __launch_bounds__(256, (FlatLds<KQ, kHalo>::MINW)) void fwd_dense_s2_
     static_for<0, 4>([&](auto I) __attribute__((always_inline)) {
         constexpr int i = decltype(I)::value, PI = (3 - i) / 2, PJ = (3 - i) % 2;
         if (blockIdx.x >= q.first[i] && blockIdx.x < q.first[i + 1])            // uniform over the workgroup
-            fwd_dense_body<KQ, kHalo, false, 0, 2, PI, PJ>(g, in, wd, out, nullptr, q.q[i], kgroups, 1, 0, (int)(blockIdx.x - q.first[i]), 0, lds, raw);
+            fwd_dense_body<KQ, kHalo, false, 2, PI, PJ>(g, in, wd, out, nullptr, q.q[i], kgroups, 1, 0, (int)(blockIdx.x - q.first[i]), 0, lds, raw);
     });
 }
 

@@ -105,11 +105,7 @@ static __device__ __attribute__((aligned(16))) float kSplitZeros[4] = {0.f, 0.f,
 // wg = index of the workgroup among those of the launch, cshare = its share of the channel split;
 // lds, raw: FlatLds::FLOATS and RAWFLOATS floats, 16-byte aligned.  Every thread of
 // the workgroup makes the call (the body contains barriers).
-// CHAIN: taps added up in the matrix cores' accumulators before they join the fp32 sum: all of a channel block (0), or a
-// filter row where the whole reduction is one channel block and its rounding is all there is (16 channels: error 1.7e-7 of the norm
-// with 9 taps, 1.2e-7 with 3, 1.4e-7 with v_mfma_f32_32x32x2_f32; with more channels 9 taps are below the fp32 instruction
-// too, and 3 cost 4 % and the combined kernel of st_fwd_auto.hip 15 % in spilled registers).
-template <int KQ, int HPC, bool DEEP = false, int CHAIN = 0, int MODE = 0, int PI = 0, int PJ = 0>
+template <int KQ, int HPC, bool DEEP = false, int MODE = 0, int PI = 0, int PJ = 0>
 __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__restrict__ in, const float *__restrict__ wd,
                                                float *__restrict__ out, float *__restrict__ parts, const FlatGrid &fq, int kgroups,
                                                int csplit, size_t part_stride, int wg, int cshare, float *lds_base, float *raw)
@@ -118,7 +114,6 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
     using Lds = FlatLds<KQ, HPC>;
     constexpr int TAPS = 9, TQ = Lds::TQ, NT = Cfg::NT, PSTEP = Cfg::PSTEP, NV = Cfg::NV, NU = Cfg::NU;
     constexpr bool RAW = Lds::RAW;
-    constexpr int CH = CHAIN && CHAIN < NT ? CHAIN : NT;
     constexpr int D = !DEEP ? 1 : (NT == 9 ? 3 : NT);            // taps the filters are requested ahead; divides NT
     constexpr int NLD = (HPC * 4 + KQ * 64 - 1) / (KQ * 64);     // 16-byte pieces per lane and block
 
@@ -154,7 +149,7 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
     const bool k_ok = kb32 * 32 < g.Ko;
     const bool active = tile_ok && k_ok;
 
-    // running sums of the two pixel blocks, and the matrix cores' own accumulators of the current chain
+    // sums of the two pixel blocks: the large products of the pieces, and the small ones of the current channel block
     floatx16 acc[2], part[2];
 #pragma unroll
     for (int pb = 0; pb < 2; ++pb)
@@ -258,36 +253,33 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
                 constexpr int ft = wrap ? tp + D - NT : tp + D;
                 const int nstep = (wrap ? min(cb + 1, cb1 - 1) : cb) * TAPS + Cfg::ftap(ft);
                 bf16x8 (&fc)[3] = f[tp % D];
-                auto mul = [&](const bf16x8 &w8, const bf16x8 (&x)[2], bool first) __attribute__((always_inline)) {
+                auto mul = [&](const bf16x8 &w8, const bf16x8 (&x)[2], floatx16 (&to)[2], bool first) __attribute__((always_inline)) {
 #pragma unroll
                     for (int pb = 0; pb < 2; ++pb)              // rows = output channels, columns = pixels
-                        part[pb] = first ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(w8, x[pb], floatx16{}, 0, 0, 0)
-                                         : __builtin_amdgcn_mfma_f32_32x32x16_bf16(w8, x[pb], part[pb], 0, 0, 0);
+                        to[pb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w8, x[pb], first ? floatx16{} : to[pb], 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
                 };
                 bf16x8 f0n;
                 if constexpr (D == 1) f0n = filters(nstep, 0);
-                mul(fc[0], x0, tp % CH == 0);
-                mul(fc[2], x0, false);
+                mul(fc[0], x0, acc, false);
+                mul(fc[2], x0, part, tp == 0);
                 fc[2] = filters(nstep, 2);
-                mul(fc[1], x0, false);
+                mul(fc[1], x0, part, false);
                 if constexpr (!last) { x0[0] = input(nt, 0, 0); x0[1] = input(nt, 1, 0); }
-                mul(fc[1], x1, false);
+                mul(fc[1], x1, part, false);
                 fc[1] = filters(nstep, 1);
-                mul(fc[0], x1, false);
+                mul(fc[0], x1, part, false);
                 if constexpr (!last) { x1[0] = input(nt, 0, 1); x1[1] = input(nt, 1, 1); }
-                mul(fc[0], x2, false);
+                mul(fc[0], x2, part, false);
                 if constexpr (!last) { x2[0] = input(nt, 0, 2); x2[1] = input(nt, 1, 2); }
                 if constexpr (D == 1) fc[0] = f0n;
                 else fc[0] = filters(nstep, 0);
-                // (odd channel blocks have their filters negated: st_split.hpp)
-                if constexpr (tp % CH == CH - 1) {
-#pragma unroll
-                    for (int pb = 0; pb < 2; ++pb)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) acc[pb][r] = fmaf(cb % 2 ? -kSplitUnscale : kSplitUnscale, part[pb][r], acc[pb][r]);
-                }
             });
+            // the small products join the sum, which changes sign: odd channel blocks have their filters negated (st_split.hpp)
+#pragma unroll
+            for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[pb][r] = -acc[pb][r] - part[pb][r];
         }
         if (cb + 1 == cb1) break;
         __syncthreads();                            // every wavefront is done with this block
@@ -309,6 +301,7 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
         if constexpr (MODE == 2) { oh = 2 * oh + PI; ow = 2 * ow + PJ; }
         return q < qend;
     };
+    const float scale = cb1 % 2 ? -kSplitUnscale : kSplitUnscale;
     bool finite[2] = {true, true};
 #pragma unroll
     for (int pb = 0; pb < 2; ++pb) {
@@ -318,7 +311,8 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
         for (int gq = 0; gq < 4; ++gq) {
             const int k = kb32 * 32 + 8 * gq + 4 * half;
             if (k >= g.Ko) continue;
-            const float4 r = make_float4(acc[pb][4 * gq], acc[pb][4 * gq + 1], acc[pb][4 * gq + 2], acc[pb][4 * gq + 3]);
+            const float4 r = make_float4(acc[pb][4 * gq] * scale, acc[pb][4 * gq + 1] * scale, acc[pb][4 * gq + 2] * scale,
+                                         acc[pb][4 * gq + 3] * scale);
             finite[pb] = finite[pb] && split_finite(r);
             *reinterpret_cast<float4 *>(out + act_off(n, k / kBlk, oh, ow, KoB, g.Ho, g.Wo) + k % kBlk) = r;
         }
@@ -335,7 +329,7 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
     }
 }
 
-template <int KQ, int HPC, bool DEEP, int CHAIN, int MODE>
+template <int KQ, int HPC, bool DEEP, int MODE>
 __global__ __launch_bounds__(256, (FlatLds<KQ, HPC, DEEP>::MINW)) void fwd_dense_kernel(
     Geom g, const float *__restrict__ in, const float *__restrict__ wd, float *__restrict__ out, float *__restrict__ parts,
     FlatGrid fq, int kgroups, int csplit, size_t part_stride)
@@ -343,7 +337,7 @@ __global__ __launch_bounds__(256, (FlatLds<KQ, HPC, DEEP>::MINW)) void fwd_dense
     if (form_deselected(g.sel, g.want, g.thr)) return;
     __shared__ __attribute__((aligned(16))) float lds[FlatLds<KQ, HPC>::FLOATS];
     __shared__ __attribute__((aligned(16))) float raw[FlatLds<KQ, HPC>::RAWFLOATS];
-    fwd_dense_body<KQ, HPC, DEEP, CHAIN, MODE>(g, in, wd, out, parts, fq, kgroups, csplit, part_stride, (int)blockIdx.x, (int)blockIdx.y, lds, raw);
+    fwd_dense_body<KQ, HPC, DEEP, MODE>(g, in, wd, out, parts, fq, kgroups, csplit, part_stride, (int)blockIdx.x, (int)blockIdx.y, lds, raw);
 }
 
 // Column blocks per workgroup, tiles and number of workgroups of a 3x3 launch (MODE 0 or 1 of g)

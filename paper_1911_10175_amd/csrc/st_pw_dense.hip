@@ -146,33 +146,31 @@ __global__ __launch_bounds__(256, (PwCfg<KQ>::MINW)) void pw_dense_kernel(Geom g
                 constexpr int ns = last ? 0 : sub + 1;
                 const int cb = st * NCB + sub, ncb = min(cb + 1, cb1 - 1);
                 if (cb >= cb1) return;                  // uniform: the last stage may be short
-                auto mul = [&](const bf16x8 &f, const bf16x8 (&x)[2], bool first) __attribute__((always_inline)) {
+                auto mul = [&](const bf16x8 &f, const bf16x8 (&x)[2], floatx16 (&to)[2], bool first) __attribute__((always_inline)) {
 #pragma unroll
                     for (int pb = 0; pb < 2; ++pb)          // rows = output channels, columns = pixels
-                        part[pb] = first ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, x[pb], floatx16{}, 0, 0, 0)
-                                         : __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, x[pb], part[pb], 0, 0, 0);
+                        to[pb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, x[pb], first ? floatx16{} : to[pb], 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
                 };
                 const bf16x8 f0n = filters(ncb, 0);
-                mul(f0, x0, true);
-                mul(f2, x0, false);
+                mul(f0, x0, acc, false);
+                mul(f2, x0, part, sub == 0);
                 f2 = filters(ncb, 2);
-                mul(f1, x0, false);
+                mul(f1, x0, part, false);
                 if constexpr (!last) { x0[0] = input(ns, 0, 0); x0[1] = input(ns, 1, 0); }
-                mul(f1, x1, false);
+                mul(f1, x1, part, false);
                 f1 = filters(ncb, 1);
-                mul(f0, x1, false);
+                mul(f0, x1, part, false);
                 if constexpr (!last) { x1[0] = input(ns, 0, 1); x1[1] = input(ns, 1, 1); }
-                mul(f0, x2, false);
+                mul(f0, x2, part, false);
                 if constexpr (!last) { x2[0] = input(ns, 0, 2); x2[1] = input(ns, 1, 2); }
                 f0 = f0n;
-                // (a channel block is one chain of the matrix cores' accumulators: with a whole stage in a chain the
-                // short reductions, 64 channels, have 1.3e-7 of the norm as error, with one block 1.0e-7)
-#pragma unroll
-                for (int pb = 0; pb < 2; ++pb)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[pb][r] = fmaf(st % 2 ? -kSplitUnscale : kSplitUnscale, part[pb][r], acc[pb][r]);
             });
+            // the small products join the sum, which changes sign: odd stages have their filters negated (st_split.hpp)
+#pragma unroll
+            for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[pb][r] = -acc[pb][r] - part[pb][r];
         }
         if (st + 1 == st1) break;
         __syncthreads();                                // every wavefront is done with this stage
@@ -186,6 +184,7 @@ __global__ __launch_bounds__(256, (PwCfg<KQ>::MINW)) void pw_dense_kernel(Geom g
     // D layout of a 32x32 block: column (pixel) = lane % 32, row (channel) = 8*(r/4) + 4*(lane/32) + r%4:
     // four consecutive channels per group of 4 accumulators, one 16-byte store each
     if (!active) return;
+    const float scale = st1 % 2 ? -kSplitUnscale : kSplitUnscale;
     bool finite[2] = {true, true};
 #pragma unroll
     for (int pb = 0; pb < 2; ++pb) {
@@ -196,7 +195,8 @@ __global__ __launch_bounds__(256, (PwCfg<KQ>::MINW)) void pw_dense_kernel(Geom g
         for (int gq = 0; gq < 4; ++gq) {
             const int k = kb32 * 32 + 8 * gq + 4 * half;
             if (k >= g.Ko) continue;
-            const float4 r = make_float4(acc[pb][4 * gq], acc[pb][4 * gq + 1], acc[pb][4 * gq + 2], acc[pb][4 * gq + 3]);
+            const float4 r = make_float4(acc[pb][4 * gq] * scale, acc[pb][4 * gq + 1] * scale, acc[pb][4 * gq + 2] * scale,
+                                         acc[pb][4 * gq + 3] * scale);
             finite[pb] = finite[pb] && split_finite(r);
             *reinterpret_cast<float4 *>(o + (size_t)(k / kBlk) * HW * kBlk + k % kBlk) = r;
         }

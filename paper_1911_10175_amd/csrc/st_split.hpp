@@ -1,19 +1,28 @@
-// fp32 products on the bf16 matrix cores without giving up fp32 accuracy, shared by the dense kernels.
+// fp32 products on the bf16 matrix cores without giving up fp32 accuracy, shared by the dense kernels.  Splitting a value
+// into pieces of a shorter type whose products a matrix unit forms exactly is a published method (Markidis et al.,
+// "NVIDIA Tensor Core Programmability, Performance & Precision", 2018; Henry, Tang and Heinecke, "Leveraging the bfloat16
+// Artificial Intelligence Datatype For Higher-Precision Computations", 2019: three bf16 pieces of an fp32 value).
 //
 // An fp32 value is the exact sum of three bf16 values (8 significant bits each, rounded to nearest, so the
 // remainders carry their own sign): a = a0 + a1 + a2.  Of the nine products of two such sums the six largest
 //   a0 b0, a0 b1, a1 b0, a1 b1, a0 b2, a2 b0
-// are formed; the three left out are below 2^-24 of |a b| together (at most 2^-8 * 2^-16 each for two of them), at the
-// rounding of one fp32 product.  v_mfma_f32_32x32x16_bf16 does 16 multiply-adds per element in the time
-// v_mfma_f32_32x32x2_f32 does one, so six of them cost 6/16 of the fp32 instruction's time per product.
+// are formed; the three left out are below 2^-24 of |a b| together (at most 2^-8 * 2^-17 each for two of them), and
+// 5e-9 of it in the root mean square, a fifth of what rounding one fp32 product costs.  v_mfma_f32_32x32x16_bf16 does 16
+// multiply-adds per element in the time v_mfma_f32_32x32x2_f32 does one, so six of them cost 6/16 of the fp32
+// instruction's time per product.
 //
-// The matrix core adds the 16 products of an instruction to the accumulator at the accumulator's own precision,
-// small terms cut off towards minus infinity rather than rounded (measured: 1 + 16 * 2^-27 returns 1).  Over a long
-// reduction that is 10-20 % more error than the fp32 instruction has, and a bias that grows with the number of terms.
-// Two measures take both away: the kernels start a fresh accumulator per block of the reduction (16 channels x 9
-// taps, 3 where the layer has no more than 16 channels; 16 channels of a 1x1; 16 or 32 pixels) and add it to the running fp32 sum on the vector ALUs, and every other block is computed with one
-// operand negated and subtracted, so that the biases cancel.  What is left is a third of the fp32 instruction's error
-// in FWD / BWI (2304 terms: 6.1e-7 -> 2e-7 of the result's norm) and about half in BWW (10^5 terms: 5e-7 -> 2.7e-7).
+// How the sums are taken decides the error.  v_mfma_f32_32x32x2_f32 is a chain of fused multiply-adds (measured: bit for
+// bit).  v_mfma_f32_32x32x16_bf16 adds 8 products, then 8 more, each group to the accumulator with one rounding to
+// nearest; within a group whatever lies 24 bits below the largest product is cut off, also of an accumulator smaller than the
+// products.  So the large products a0 b0 (16 bits, a group of them is nearly exact) and the five small ones have accumulators
+// of their own: the small ones' roundings are 2^-8 of a rounding of the sum, the large ones round twice per 16 products
+// where fp32 instructions round once per non-zero product, and the two meet in an fp32 addition.  With one accumulator for
+// all six products the sum was rounded twelve times per 16 products: with 80 % zeros that was 1.2 to 1.9 times the fp32
+// instruction's error.
+//
+// What is cut off leaves a small bias, which over 10^5 terms would outgrow the roundings (256->256 @56, N = 32, BWW: error
+// 7.8e-7 of the norm with one sign, 2.7e-7 with both): every other block of the reduction is computed with one operand
+// negated, so that the biases cancel.
 //
 // The values are scaled by 2^24 before they are split, so that the last bit of every fp32 value, also of a subnormal one,
 // is a normal bf16 value and the decomposition is exact; the sums are scaled back by 2^-48.  Values from 2^104 and sums from
