@@ -535,7 +535,8 @@ __device__ __forceinline__ void bww_redo(const BwwArgs &A, const float *x, const
     }
 }
 
-template <int R, int S, int TH, int TW, int PSTEP = 1>
+// SHORT: for workgroups of few tiles, see the products below.
+template <int R, int S, int TH, int TW, int PSTEP, bool SHORT>
 __global__ __launch_bounds__(256, 2) void bww_dense_kernel(BwwArgs A, const float *__restrict__ x,
                                                            const float *__restrict__ dy, float *__restrict__ part)
 {
@@ -600,8 +601,8 @@ __global__ __launch_bounds__(256, 2) void bww_dense_kernel(BwwArgs A, const floa
                 sx[i] = *reinterpret_cast<const float4 *>(x + act_off(n, cb, ih, iw, CB, A.H, A.W) + (q & 3) * 4);
         }
     };
-    // Every other step of 16 pixels is added up with the opposite sign (its dy negated here, its sum subtracted): the
-    // matrix cores cut off towards minus infinity, and over 10^5 pixels that bias would outgrow the rounding errors
+    // Every other step of 16 pixels is added up with the opposite sign (its dy negated here, its sum subtracted): what the
+    // matrix cores cut off leaves a small bias, which over 10^5 pixels would outgrow the rounding errors
     // (256->256 @56, N = 32: error 7.8e-7 of the norm with one sign, 2.7e-7 with both).
     constexpr int NS = P / 16;
     auto flipped = [&](int unit, int s) __attribute__((always_inline)) { return NS % 2 == 0 ? s % 2 != 0 : (unit + s) % 2 != 0; };
@@ -663,12 +664,28 @@ __global__ __launch_bounds__(256, 2) void bww_dense_kernel(BwwArgs A, const floa
                 bf16x8 fn[3];
                 if constexpr (tap + 1 < S * R) input(tap + 1, fn);
                 __builtin_amdgcn_sched_barrier(0);              // the next tap's reads go ahead of this tap's products
-                floatx16 t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[2], f[0], floatx16{}, 0, 0, 0);
+                floatx16 t = {};
+                if constexpr (SHORT) {                          // two of the products usually left out
+                    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[2], f[1], t, 0, 0, 0);
+                    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[1], f[2], t, 0, 0, 0);
+                }
+                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[2], f[0], t, 0, 0, 0);
                 t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[0], f[2], t, 0, 0, 0);
                 t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[1], f[1], t, 0, 0, 0);
                 t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[1], f[0], t, 0, 0, 0);
                 t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[0], f[1], t, 0, 0, 0);
-                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[0], f[0], t, 0, 0, 0);
+                // The products of the leading pieces on top of the others cut the others off at their own last bit.  Beside the
+                // rounding of a sum over many steps that is nothing; in a launch of few tiles the two meet in an fp32 addition
+                // instead, and two more of the small products are formed (SHORT).  (16 to 162 pixels with 4 % non-zero
+                // products: 1.13-1.34 -> 1.00-1.04 times the fp32 instruction's error; it takes 5 % longer on long sums, whose
+                // error it does not change.)
+                if constexpr (SHORT) {
+                    const floatx16 h = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[0], f[0], floatx16{}, 0, 0, 0);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) t[r] += h[r];
+                } else {
+                    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[0], f[0], t, 0, 0, 0);
+                }
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[tap][r] = flipped(unit, s) ? acc[tap][r] - t[r] : acc[tap][r] + t[r];
                 if constexpr (tap + 1 < S * R) {
@@ -769,8 +786,10 @@ __device__ __forceinline__ void pw_bww_redo(const BwwArgs &A, const float *x, co
 // registers while the current one is multiplied.  128 x 128 uses a staged pixel for four blocks; layers with only 64
 // channels on a side get the narrower tile (no padded blocks) and chunks of 64 pixels, so that there are as many
 // matrix instructions between two barriers.  Between two barriers one team multiplies while the other splits and stashes
-// its next chunk, so the matrix cores and the vector ALUs work at the same time.  The matrix cores' accumulators are
-// joined to the fp32 sums every 32 pixels, with a sign that alternates by chunk.
+// its next chunk, so the matrix cores and the vector ALUs work at the same time.  The products of the leading pieces go straight
+// to the sums; the others have accumulators of their own, which join the sums once per chunk, and the sums change sign
+// there.  (6x56x56 pixels, 4 % non-zero products, 16 and 64 channels, error: 1.2e-7 of the norm with one accumulator for all
+// products and the partial sums added up in 32 bits, 6e-8 to 7e-8 now.)
 template <int CW, int KW, int P>
 __global__ __launch_bounds__(512, 2) void pw_bww_dense_kernel(BwwArgs A, const float *__restrict__ x,
                                                               const float *__restrict__ dy, float *__restrict__ part)
@@ -859,8 +878,7 @@ __global__ __launch_bounds__(512, 2) void pw_bww_dense_kernel(BwwArgs A, const f
         } else if (unit < u1) {
             if (unit + 2 < u1) fetch();                 // in flight during the MFMAs below
             if (active) {
-                const float sg = flip(it) ? -1.f : 1.f;
-                floatx16 acc[KJ][CI];
+                floatx16 small[KJ][CI];
 #pragma unroll
                 for (int s = 0; s < P / 16; ++s) {
                     bf16x8 d[KJ][3], f[CI][3];
@@ -878,30 +896,36 @@ __global__ __launch_bounds__(512, 2) void pw_bww_dense_kernel(BwwArgs A, const f
                             const int off = (i * (P * 64) + q * XB + s * 1024) / 8;
                             f[i][q] = split_tr_read(xp + off, xp + off + 32);
                         }
-                    constexpr int ta[6] = {2, 0, 1, 1, 0, 0}, tb[6] = {0, 2, 1, 0, 1, 0};      // smallest products first
+                    constexpr int ta[5] = {2, 0, 1, 1, 0}, tb[5] = {0, 2, 1, 0, 1};
 #pragma unroll
-                    for (int t = 0; t < 6; ++t)
-#pragma unroll
-                        for (int j = 0; j < KJ; ++j)
-#pragma unroll
-                            for (int i = 0; i < CI; ++i)
-                                acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[j][ta[t]], f[i][tb[t]],
-                                                                                    s % 2 == 0 && t == 0 ? floatx16{} : acc[j][i], 0, 0, 0);
-                    if (s % 2 == 1) {
+                    for (int t = 0; t < 5; ++t)
 #pragma unroll
                         for (int j = 0; j < KJ; ++j)
 #pragma unroll
                             for (int i = 0; i < CI; ++i)
+                                small[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[j][ta[t]], f[i][tb[t]],
+                                                                                      s == 0 && t == 0 ? floatx16{} : small[j][i], 0, 0, 0);
+                    // (left to itself the compiler moves these up and the next step's reads down: 256->64 @56 36.6 -> 37.5)
+                    if constexpr (KJ * CI > 1) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                                for (int r = 0; r < 16; ++r) sum[j][i][r] = fmaf(sg, acc[j][i][r], sum[j][i][r]);
-                    }
+                    for (int j = 0; j < KJ; ++j)
+#pragma unroll
+                        for (int i = 0; i < CI; ++i) sum[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[j][0], f[i][0], sum[j][i], 0, 0, 0);
                 }
+                // the small products join the sum, which changes sign (with the dy of the team's next chunk)
+#pragma unroll
+                for (int j = 0; j < KJ; ++j)
+#pragma unroll
+                    for (int i = 0; i < CI; ++i)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) sum[j][i][r] = -sum[j][i][r] - small[j][i][r];
             }
         }
         __syncthreads();
     }
 
     // the second team's sums join the first's: [register][thread of the team]
+    const float scale = flip((u1 - u0 - team + 1) / 2) ? -kSplitUnscale : kSplitUnscale;       // (after that many chunks)
     float *red = reinterpret_cast<float *>(pw_lds) + t256;
     if (team == 1) {
 #pragma unroll
@@ -909,7 +933,7 @@ __global__ __launch_bounds__(512, 2) void pw_bww_dense_kernel(BwwArgs A, const f
 #pragma unroll
             for (int i = 0; i < CI; ++i)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) red[((j * CI + i) * 16 + r) * 256] = sum[j][i][r];
+                for (int r = 0; r < 16; ++r) red[((j * CI + i) * 16 + r) * 256] = sum[j][i][r] * scale;
     }
     __syncthreads();
     if (team == 1 || !active) return;
@@ -933,7 +957,7 @@ __global__ __launch_bounds__(512, 2) void pw_bww_dense_kernel(BwwArgs A, const f
                 float v[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    v[r] = (sum[j][i][4 * gq + r] + red[((j * CI + i) * 16 + 4 * gq + r) * 256]) * kSplitUnscale;
+                    v[r] = fmaf(sum[j][i][4 * gq + r], scale, red[((j * CI + i) * 16 + 4 * gq + r) * 256]);
                     finite = finite && split_finite(v[r]);
                 }
                 *reinterpret_cast<float4 *>(element(k, c)) = make_float4(v[0], v[1], v[2], v[3]);
@@ -1130,18 +1154,22 @@ __global__ __launch_bounds__(512, 4) void pw_bww_sparse_kernel(BwwArgs A, const 
 // belongs to the form `want` and does nothing when another one was selected.
 struct Splits3 { int f[3]; };
 constexpr int kAnyForm = -2;
-// 0 + part[first] + part[first + step] + ... below `splits` (n4 float4 apart), eight loads in flight at a time
-__device__ __forceinline__ float4 add_partials(const float4 *part, size_t n4, int first, int splits, int step)
+// part[first] + part[first + step] + ... below `splits` (n4 float4 apart), eight loads in flight at a time: each eight in
+// pairs, their sums in 64 bits.  Added up one after the other in 32 bits, hundreds of partial sums round more often than
+// the products in them (3x3 64->64, 4 x 30 x 28 pixels, 105 partial sums, 4 % non-zero products: error 9.9e-8 of the norm one
+// after the other, 5.7e-8 here; v_mfma_f32_32x32x2_f32 and its 34 partial sums 9.6e-8).
+struct Sum4 { double x, y, z, w; };
+__device__ __forceinline__ Sum4 add_partials(const float4 *part, size_t n4, int first, int splits, int step)
 {
     constexpr int BATCH = 8;
-    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    Sum4 s = {0., 0., 0., 0.};
     int p = first;
     for (; p + (BATCH - 1) * step < splits; p += BATCH * step) {
         float4 v[BATCH];
 #pragma unroll
         for (int b = 0; b < BATCH; ++b) v[b] = part[(size_t)(p + b * step) * n4];
-#pragma unroll
-        for (int b = 0; b < BATCH; ++b) { s.x += v[b].x; s.y += v[b].y; s.z += v[b].z; s.w += v[b].w; }
+        const float4 t = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+        s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
     }
     for (; p < splits; p += step) {
         const float4 v = part[(size_t)p * n4];
@@ -1161,27 +1189,28 @@ __global__ __launch_bounds__(1024) void bww_reduce_kernel(const float4 *part, fl
     const int splits = form == 0 ? sp.f[0] : form == 1 ? sp.f[1] : sp.f[2];
     // few splits: a thread per output (the order of the sum is the same)
     if (splits <= 16) {
-        for (size_t i = (size_t)blockIdx.x * 1024 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 1024)
-            dw[i] = add_partials(part + i, n4, 0, splits, 1);
+        for (size_t i = (size_t)blockIdx.x * 1024 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 1024) {
+            const Sum4 s = add_partials(part + i, n4, 0, splits, 1);
+            dw[i] = make_float4((float)s.x, (float)s.y, (float)s.z, (float)s.w);
+        }
         return;
     }
-    __shared__ float4 red[16][64];
+    __shared__ Sum4 red[16][64];
     const int o = threadIdx.x % 64, sl = threadIdx.x / 64;
     const size_t nblk = (n4 + 63) / 64;
     for (size_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {       // uniform trip count per workgroup
         const size_t i = blk * 64 + o;
-        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+        Sum4 s = {0., 0., 0., 0.};
         if (i < n4)
             s = add_partials(part + i, n4, sl, splits, 16);
         red[sl][o] = s;
         __syncthreads();
         if (sl == 0 && i < n4) {
-            const int lanes = splits < 16 ? splits : 16;
-            for (int q = 1; q < lanes; ++q) {
-                const float4 v = red[q][o];
+            for (int q = 1; q < 16; ++q) {
+                const Sum4 v = red[q][o];
                 s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
             }
-            dw[i] = s;
+            dw[i] = make_float4((float)s.x, (float)s.y, (float)s.z, (float)s.w);
         }
         __syncthreads();                                    // red is rewritten by the next round
     }
@@ -1222,6 +1251,9 @@ constexpr int kDenseTH = 4, kDenseTW = 8, kDenseWideTH = 2, kDenseWideTW = 14;
 constexpr int kS2TH = 4, kS2TW = 8, kDenseS2TH = 2, kDenseS2TW = 8;
 
 constexpr int kBwwTargetWorkgroups = 512;
+// dense launches of at most this many tiles, one or two for a workgroup, take the SHORT form (with a workgroup's time in its
+// tiles it would cost 10 %: 512->512 @14, N = 4, 48 -> 53)
+constexpr int kBwwShortUnits = 16;
 
 BwwArgs make_args(const st_conv_desc &d, int TH, int TW, bool tiles_over_input)
 {
@@ -1257,6 +1289,24 @@ BwwArgs dense_args(const st_conv_desc &d)
 {
     if (bww_s2(d)) return make_args(d, kDenseS2TH, kDenseS2TW, false);
     return dense_wide(d) ? make_args(d, kDenseWideTH, kDenseWideTW, false) : make_args(d, kDenseTH, kDenseTW, false);
+}
+
+template <int TH, int TW, int PSTEP>
+void launch_bww_dense_tiles(const BwwArgs &A, const float *x, const float *dy, float *part, hipStream_t s)
+{
+    const dim3 grid(A.splits, ceil_div(A.K, 64) * A.cgroups);
+    if (A.units <= kBwwShortUnits && A.units <= 2 * A.splits)
+        hipLaunchKernelGGL((bww_dense_kernel<3, 3, TH, TW, PSTEP, true>), grid, dim3(256), 0, s, A, x, dy, part);
+    else hipLaunchKernelGGL((bww_dense_kernel<3, 3, TH, TW, PSTEP, false>), grid, dim3(256), 0, s, A, x, dy, part);
+}
+
+// the 3x3 dense kernel with A = dense_args(d)
+hipError_t launch_bww_dense_3x3(const st_conv_desc &d, const BwwArgs &A, const float *x, const float *dy, float *part, hipStream_t s)
+{
+    if (bww_s2(d)) launch_bww_dense_tiles<kDenseS2TH, kDenseS2TW, 2>(A, x, dy, part, s);
+    else if (dense_wide(d)) launch_bww_dense_tiles<kDenseWideTH, kDenseWideTW, 1>(A, x, dy, part, s);
+    else launch_bww_dense_tiles<kDenseTH, kDenseTW, 1>(A, x, dy, part, s);
+    return hipGetLastError();
 }
 
 // tiles of the zero-skipping 3x3 kernel that tests the input of layer d
@@ -1500,9 +1550,7 @@ hipError_t launch_bww_auto_merged(const st_conv_desc &d, const float *x, const f
     hipLaunchKernelGGL((bww_sparse_either_kernel<3, 3, kSparseTH, kSparseTW>), grid, dim3(512), kSparseLds, s, A0, A1, x, dy, ws);
     err = hipGetLastError();
     if (err != hipSuccess) return err;
-    if (dense_wide(d)) hipLaunchKernelGGL((bww_dense_kernel<3, 3, kDenseWideTH, kDenseWideTW>), dim3(A2.splits, ygroups), dim3(256), 0, s, A2, x, dy, ws);
-    else hipLaunchKernelGGL((bww_dense_kernel<3, 3, kDenseTH, kDenseTW>), dim3(A2.splits, ygroups), dim3(256), 0, s, A2, x, dy, ws);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
+    if ((err = launch_bww_dense_3x3(d, A2, x, dy, ws, s)) != hipSuccess) return err;
     const size_t n4 = (size_t)d.K * d.C * d.S * d.R / 4;
     const size_t nblk = (n4 + 63) / 64;
     Splits3 sp = {{A0.splits, A1.splits, A2.splits}};
@@ -1514,15 +1562,6 @@ hipError_t launch_bww_auto_merged(const st_conv_desc &d, const float *x, const f
 hipError_t launch_bww_dense(const st_conv_desc &d, const float *x, const float *dy, float *dw,
                             float *ws, hipStream_t s, const unsigned *sel)
 {
-    if (bww_s2(d)) {
-        BwwArgs A2 = dense_args(d);
-        A2.sel = sel; A2.want = 2;
-        dim3 grid2(A2.splits, ceil_div(d.K, 64) * A2.cgroups);
-        hipLaunchKernelGGL((bww_dense_kernel<3, 3, kDenseS2TH, kDenseS2TW, 2>), grid2, dim3(256), 0, s, A2, x, dy,
-                           A2.splits == 1 ? dw : ws);
-        hipError_t err = hipGetLastError();
-        return err != hipSuccess ? err : reduce(d, A2, ws, dw, s);
-    }
     if (d.R == 1) {
         BwwArgs A1 = make_args_pw_dense(d);
         A1.sel = sel; A1.want = 2;
@@ -1546,10 +1585,7 @@ hipError_t launch_bww_dense(const st_conv_desc &d, const float *x, const float *
     BwwArgs A = dense_args(d);
     A.sel = sel; A.want = 2;
     float *part = A.splits == 1 ? dw : ws;
-    dim3 grid(A.splits, ceil_div(d.K, 64) * A.cgroups);
-    if (dense_wide(d)) hipLaunchKernelGGL((bww_dense_kernel<3, 3, kDenseWideTH, kDenseWideTW>), grid, dim3(256), 0, s, A, x, dy, part);
-    else hipLaunchKernelGGL((bww_dense_kernel<3, 3, kDenseTH, kDenseTW>), grid, dim3(256), 0, s, A, x, dy, part);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_bww_dense_3x3(d, A, x, dy, part, s);
     if (e != hipSuccess) return e;
     return reduce(d, A, part, dw, s);
 }

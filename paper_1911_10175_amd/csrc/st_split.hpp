@@ -18,7 +18,8 @@
 // of their own: the small ones' roundings are 2^-8 of a rounding of the sum, the large ones round twice per 16 products
 // where fp32 instructions round once per non-zero product, and the two meet in an fp32 addition.  With one accumulator for
 // all six products the sum was rounded twelve times per 16 products: with 80 % zeros that was 1.2 to 1.9 times the fp32
-// instruction's error.
+// instruction's error.  (The 3x3 BWW has no registers for two accumulators beside its 144 sums: it starts a fresh one every 16
+// pixels, small products first, and adds it to the sum.)
 //
 // What is cut off leaves a small bias, which over 10^5 terms would outgrow the roundings (256->256 @56, N = 32, BWW: error
 // 7.8e-7 of the norm with one sign, 2.7e-7 with both): every other block of the reduction is computed with one operand

@@ -160,6 +160,14 @@ SHORT = {
     "3x3 256->256 split": Geom(1, 256, 256, 7, 7, 3, 3, 1, 1, 1, 1),
     "3x3 stride 2 32->16": Geom(4, 32, 16, 28, 28, 3, 3, 2, 2, 1, 1),
     "3x3 stride 2 16->80": Geom(4, 16, 80, 28, 28, 3, 3, 2, 2, 1, 1),
+    # BWW over 16 to 196 pixels: every number of tiles around the limit of the short form, one and several partial sums
+    "3x3 64->64 one tile": Geom(1, 64, 64, 4, 4, 3, 3, 1, 1, 1, 1),
+    "3x3 512->256 one image": Geom(1, 512, 256, 7, 7, 3, 3, 1, 1, 1, 1),
+    "3x3 64->80 @14": Geom(1, 64, 80, 14, 14, 3, 3, 1, 1, 1, 1),
+    "3x3 80->64 two images": Geom(2, 80, 64, 8, 16, 3, 3, 1, 1, 1, 1),
+    "3x3 stride 2 64->64 @14": Geom(1, 64, 64, 14, 14, 3, 3, 2, 2, 1, 1),
+    "1x1 144->64 @7": Geom(1, 144, 64, 7, 7, 1, 1),
+    "1x1 64->144 nine images": Geom(9, 64, 144, 14, 14, 1, 1),
 }
 
 
@@ -169,18 +177,20 @@ def test_short_reductions_err_no_more_than_fp32_instructions(name, zeros):
     """Few non-zero products per output, where every rounding counts and no averaging over a long reduction helps: the error
     against 64 bits is no larger than that of a chain of fp32 multiply-adds over the same terms.  5 %: the products of pieces
     that are left out (root mean square 5e-9 of a product) beside one rounding of it (2.4e-8) are 3 % where an output has one
-    product, and the two errors are those of 5000 outputs and more, 2 % of chance."""
+    product, and the two errors are those of 5000 outputs and more, 2 % of chance.  BWW with 4 % non-zero products has that few
+    of them (16 pixels: none or one), so that the 3 % and what the products of one step cut off of each other (2^-24 of the largest,
+    up to a rounding where two of them meet) are all there is beside the chain's own rounding: 10 %."""
     g = SHORT[name]
     x = stgen.relu_sparse(g.x_shape, zeros, 31) if zeros else stgen.normal(31, int(np.prod(g.x_shape))).reshape(g.x_shape).astype(np.float32)
     w = stgen.he_normal(g.w_shape, 32)
     dy = stgen.bernoulli_masked(g.y_shape, zeros, 33, 34)
     L = DeviceLayer(g, x, w, dy)
-    for p in ("fwd", "bwi"):
+    for p in ("fwd", "bwi", "bww"):
         a, b, shape = as_products(g, x, w, dy, p)
         exact = a @ b
         got = torch.from_numpy(shape(getattr(L, p)(True)).astype(np.float64))
         err, chain = norm_error(got, exact), norm_error(fma_chain(a, b), exact)
-        assert err <= 1.05 * chain, f"{name} {p} {zeros}: {err:.3g}, fp32 instructions {chain:.3g}"
+        assert err <= (1.1 if p == "bww" else 1.05) * chain, f"{name} {p} {zeros}: {err:.3g}, fp32 instructions {chain:.3g}"
 
 
 def microseconds(fn):
