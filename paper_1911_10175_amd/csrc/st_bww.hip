@@ -1287,8 +1287,15 @@ bool dense_wide(const st_conv_desc &d)
 }
 BwwArgs dense_args(const st_conv_desc &d)
 {
-    if (bww_s2(d)) return make_args(d, kDenseS2TH, kDenseS2TW, false);
-    return dense_wide(d) ? make_args(d, kDenseWideTH, kDenseWideTW, false) : make_args(d, kDenseTH, kDenseTW, false);
+    BwwArgs A = bww_s2(d) ? make_args(d, kDenseS2TH, kDenseS2TW, false)
+              : dense_wide(d) ? make_args(d, kDenseWideTH, kDenseWideTW, false) : make_args(d, kDenseTH, kDenseTW, false);
+    // As many partial gradients as the workgroup with the most tiles calls for: with 512 for 784 tiles half of the workgroups
+    // take two and the others write 18 MB of partial sums for nothing (64->64 @56, N = 8: 38 -> 35 us, 512->512 @14, N = 4:
+    // 48 -> 45).  Up to three tiles are left to one workgroup where the filters alone fill the chip: no partial sums and no
+    // launch to add them up (one image, 512->512 @7: 22 -> 17).
+    const int each = ceil_div(A.units, A.splits);
+    A.splits = A.units <= 3 && ceil_div(d.K, 64) * A.cgroups >= 32 ? 1 : ceil_div(A.units, each);
+    return A;
 }
 
 template <int TH, int TW, int PSTEP>

@@ -1,0 +1,25 @@
+"""Choices of the dense forms that their workspace queries tell (host side only)."""
+import paper_1911_10175_amd as st
+
+
+def partials(N, C, K, H, W, stride=1):
+    d = st.ConvDesc(N, C, K, H, W, 3, 3, stride, stride, 1, 1)
+    need = st.st_conv_workspace_bytes(d, st.ST_PASS_BWW, True)
+    assert need % (K * C * 9 * 4) == 0
+    return need // (K * C * 9 * 4)
+
+
+def test_no_more_partial_gradients_than_the_longest_workgroup_calls_for():
+    # 784 tiles of 4 x 8 pixels: at most 512 workgroups would take two each, and 392 do
+    assert partials(8, 64, 64, 56, 56) == 392
+    assert partials(32, 64, 64, 56, 56) == 448                  # 3136 tiles, seven each
+    assert partials(32, 256, 256, 56, 56) == 32                 # 16 workgroups for the filters alone
+    # fewer tiles than workgroups: one each
+    assert partials(2, 64, 64, 28, 28) == 56
+    assert partials(2, 112, 48, 8, 214, 2) == 56
+
+
+def test_few_tiles_of_many_filters_go_straight_to_the_gradient():
+    assert partials(1, 512, 512, 7, 7) == 0
+    assert partials(1, 512, 512, 14, 14) == 7                   # seven tiles
+    assert partials(1, 64, 64, 7, 7) == 2                       # the chip would be empty
