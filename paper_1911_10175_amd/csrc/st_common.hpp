@@ -176,7 +176,7 @@ hipError_t launch_pw_dense_direct(const Geom &g, bool transpose, const float *in
 // sign of its filter copy
 hipError_t launch_pw_dense(const Geom &g, int cs, const float *in, const float *wd, float *out, float *parts, hipStream_t s);
 int pw_channel_split(const Geom &g);
-// 1x1 launches of few workgroups stay on fp32 instructions, with an fp32 filter copy
+// 1x1 launches of few workgroups or few produced channels stay on fp32 instructions, with an fp32 filter copy
 bool pw_small(const Geom &g);
 hipError_t launch_pw_small(const Geom &g, const float *in, const float *wd, float *out, hipStream_t s);
 int pw_sign_group(const Geom &g);

@@ -201,14 +201,16 @@ int dense_images_per_launch(const Geom &g)
 hipError_t launch_fwd_dense(const Geom &g, const float *in, const float *wd, float *out, hipStream_t s)
 {
     if (!fwd_dense_supported(g)) return hipErrorInvalidValue;
-    if (pw_small(g)) return launch_pw_small(g, in, wd, out, s);
+    const bool small = pw_small(g);                 // (of the whole call: the filter copy is in its layout)
     const int step = dense_images_per_launch(g), cs = step < g.N ? 1 : dense_channel_split(g);
     // partial outputs of the shares after the first sit behind the filter copy in the workspace
     float *parts = cs > 1 ? const_cast<float *>(wd) + (fwd_dense_filter_bytes(g) + 255) / 256 * 256 / sizeof(float) : nullptr;
     for (int n = 0; n < g.N; n += step) {           // (one launch but for tensors of tens of GB)
         Geom h = g;
         h.N = g.N - n < step ? g.N - n : step;
-        const hipError_t e = launch_dense_images(h, cs, in + (size_t)n * g.Ci * g.Hi * g.Wi, wd, out + (size_t)n * g.Ko * g.Ho * g.Wo, parts, s);
+        const float *in_n = in + (size_t)n * g.Ci * g.Hi * g.Wi;
+        float *out_n = out + (size_t)n * g.Ko * g.Ho * g.Wo;
+        const hipError_t e = small ? launch_pw_small(h, in_n, wd, out_n, s) : launch_dense_images(h, cs, in_n, wd, out_n, parts, s);
         if (e != hipSuccess) return e;
     }
     if (cs == 1) return hipSuccess;

@@ -227,7 +227,7 @@ hipError_t launch_pw(const Geom &g, int cs, const float *in, const float *wd, fl
     return hipGetLastError();
 }
 
-// Launches of few pixels and channels (fewer than kPwSmall workgroups of the kernel above): with a workgroup or less per
+// Launches of few pixels and channels (fewer than kPwSmall workgroups of the kernel above; pw_small names others): with a workgroup or less per
 // compute unit nothing hides a stage's two barriers there, about 2 us a stage.  Here every wavefront works by
 // itself on v_mfma_f32_32x32x2_f32: a lane supplies, for its pixel, 8 of the 16 channels of a block, which are 32
 // contiguous bytes of the blocked activation layout, loaded from global memory in the order the instruction consumes
@@ -617,7 +617,17 @@ long long pw_blocks(const Geom &g)
 }
 }  // namespace
 
-bool pw_small(const Geom &g) { return g.R == 1 && g.S == 1 && pw_blocks(g) < kPwSmall; }
+// Also with few produced channels, where both kernels wait for memory and this one, without barriers, has more of it in
+// flight (size, N, us, this kernel : that one): 16->16 .. 64 @112 N = 16 10.8 : 11.2, 11.3 : 13.6, 16.0 : 16.3, 16.6 : 17.8, but
+// 16->128 33.6 : 24.7; 32->16 and 32->32 @112 11.8 : 13.1, 13.6 : 15.8, but 32->48 20.8 : 19.7; 48->32 @112 16.4 : 19.6, 80->32
+// @112 N = 32 35 : 38, 128->32 @80 28 : 31, 160->32 @219 N = 13 101 : 107, 256->32 @80 46 : 52, 512->16 @70 N = 20 38 : 44.
+// With 64 input channels that kernel has its two stages in flight from the start: 64->16 and 64->32 @200 N = 32 89 : 87, 107 : 104.
+bool pw_small(const Geom &g)
+{
+    if (g.R != 1 || g.S != 1) return false;
+    if ((g.Ko <= 64 && g.Ci <= 16) || (g.Ko <= 32 && g.Ci != 64)) return true;
+    return pw_blocks(g) < kPwSmall;
+}
 
 // Shares of the channel reduction of launches with few pixels: enough workgroups for every compute unit and some, at
 // least four whole stages each (fewer cost less than the launch that adds the shares up)

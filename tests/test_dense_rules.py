@@ -23,3 +23,17 @@ def test_few_tiles_of_many_filters_go_straight_to_the_gradient():
     assert partials(1, 512, 512, 7, 7) == 0
     assert partials(1, 512, 512, 14, 14) == 7                   # seven tiles
     assert partials(1, 64, 64, 7, 7) == 2                       # the chip would be empty
+
+
+def bytes_per_filter_element(N, C, K, H, W):
+    """4: the copy of the 1x1 kernel on fp32 instructions, 6: three bf16 pieces (K is padded to whole groups of 128)."""
+    d = st.ConvDesc(N, C, K, H, W, 1, 1)
+    return st.st_conv_workspace_bytes(d, st.ST_PASS_FWD, True) / ((K + 127) // 128 * 128 * C)
+
+
+def test_1x1_layers_of_few_produced_channels_stay_on_fp32_instructions():
+    assert [bytes_per_filter_element(16, 16, k, 112, 112) for k in (16, 32, 48, 64, 80)] == [4, 4, 4, 4, 6]
+    assert [bytes_per_filter_element(16, 32, k, 112, 112) for k in (16, 32, 48)] == [4, 4, 6]
+    assert [bytes_per_filter_element(32, c, 32, 80, 80) for c in (48, 64, 80, 256)] == [4, 6, 4, 4]
+    assert [bytes_per_filter_element(4, c, 256, 56, 56) for c in (16, 256)] == [6, 6]
+    assert bytes_per_filter_element(1, 256, 256, 14, 14) == 4          # few pixels

@@ -244,3 +244,18 @@ def test_time_of_values_at_the_ends_of_the_range(g, name):
                                           (1e36, False, 10), (float("nan"), False, 10)):
             us = time_with(which, value, everywhere)
             assert us <= factor * usual + 5, f"{name} {value} in {which}{' everywhere' if everywhere else ''}: {us:.0f} us, usually {usual:.0f}"
+
+
+@pytest.mark.parametrize("g", [Geom(3, 16, 64, 61, 53, 1, 1), Geom(3, 16, 80, 61, 53, 1, 1), Geom(5, 48, 32, 57, 61, 1, 1), Geom(5, 64, 32, 57, 61, 1, 1),
+                               Geom(2, 80, 16, 203, 151, 1, 1), Geom(2, 32, 48, 203, 151, 1, 1)], ids=lambda g: f"{g.C}to{g.K} {g.H}x{g.W}")
+def test_1x1_layers_of_few_produced_channels(g):
+    """Either side of the lines between the two 1x1 kernels, FWD and, with the roles of the channels exchanged, BWI;
+    ragged ends of the pixel numbering."""
+    x = stgen.relu_sparse(g.x_shape, 0.5, 51)
+    w = stgen.he_normal(g.w_shape, 52)
+    flip = Geom(g.N, g.K, g.C, g.H, g.W, 1, 1)          # its BWI is the same product
+    L, M = DeviceLayer(g, x, w, None), DeviceLayer(flip, None, w.transpose(1, 0, 2, 3), x)
+    ref = np.einsum("kc,nchw->nkhw", w[:, :, 0, 0].astype(np.float64), x.astype(np.float64))
+    mag = np.einsum("kc,nchw->nkhw", np.abs(w[:, :, 0, 0]).astype(np.float64), np.abs(x).astype(np.float64))
+    for got in (L.fwd(True), M.bwi(True)):
+        assert np.all(np.abs(got - ref) <= (g.C + 3) * 2.0 ** -24 * mag)
