@@ -1187,8 +1187,10 @@ __global__ __launch_bounds__(1024) void bww_reduce_kernel(const float4 *part, fl
         if (want != kAnyForm && form != want) return;
     }
     const int splits = form == 0 ? sp.f[0] : form == 1 ? sp.f[1] : sp.f[2];
-    // few splits: a thread per output (the order of the sum is the same)
-    if (splits <= 16) {
+    // Few splits: a thread per output.  With few outputs as well, that many threads would wait for one load after the other;
+    // there the 16 wavefronts of a workgroup share the partial sums (48->48 @12 stride 2, N = 4, 9 partial sums of 5184 float4:
+    // 18.1 -> 16.4 us for the whole call; two partial sums of 576 are faster added up by one thread each, 17.5 : 18.4).
+    if (splits <= 4 || (splits <= 16 && n4 >= 16384)) {
         for (size_t i = (size_t)blockIdx.x * 1024 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 1024) {
             const Sum4 s = add_partials(part + i, n4, 0, splits, 1);
             dw[i] = make_float4((float)s.x, (float)s.y, (float)s.z, (float)s.w);
@@ -1206,7 +1208,7 @@ __global__ __launch_bounds__(1024) void bww_reduce_kernel(const float4 *part, fl
         red[sl][o] = s;
         __syncthreads();
         if (sl == 0 && i < n4) {
-            for (int q = 1; q < 16; ++q) {
+            for (int q = 1; q < 16; ++q) {                  // (slices past the last partial sum are zero)
                 const Sum4 v = red[q][o];
                 s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
             }
