@@ -1291,12 +1291,16 @@ BwwArgs dense_args(const st_conv_desc &d)
 {
     BwwArgs A = bww_s2(d) ? make_args(d, kDenseS2TH, kDenseS2TW, false)
               : dense_wide(d) ? make_args(d, kDenseWideTH, kDenseWideTW, false) : make_args(d, kDenseTH, kDenseTW, false);
-    // As many partial gradients as the workgroup with the most tiles calls for: with 512 for 784 tiles half of the workgroups
-    // take two and the others write 18 MB of partial sums for nothing (64->64 @56, N = 8: 38 -> 35 us, 512->512 @14, N = 4:
-    // 48 -> 45).  Up to three tiles are left to one workgroup where the filters alone fill the chip: no partial sums and no
-    // launch to add them up (one image, 512->512 @7: 22 -> 17).
+    // Two workgroups fit on a compute unit: not one more than that many (nine groups of 64 x 64 filters times 57 are 513, and
+    // the last one took as long as the 512 before it; 320->320 @28, N = 8: 122 -> 89 us).
+    const int groups = ceil_div(d.K, 64) * A.cgroups, resident = kBwwTargetWorkgroups / groups;
+    if (resident >= 1 && A.splits > resident) A.splits = resident;
+    // And no more than the workgroup with the most tiles calls for: with 512 for 784 tiles half of the workgroups take two
+    // and the others write 18 MB of partial sums for nothing (64->64 @56, N = 8: 38 -> 35 us, 512->512 @14, N = 4: 48 -> 45).
+    // Up to three tiles are left to one workgroup where the filters alone fill the chip: no partial sums and no launch to
+    // add them up (one image, 512->512 @7: 22 -> 17).
     const int each = ceil_div(A.units, A.splits);
-    A.splits = A.units <= 3 && ceil_div(d.K, 64) * A.cgroups >= 32 ? 1 : ceil_div(A.units, each);
+    A.splits = A.units <= 3 && groups >= 32 ? 1 : ceil_div(A.units, each);
     return A;
 }
 
@@ -1352,7 +1356,10 @@ constexpr size_t pw_dense_lds(int cw, int kw, int p) { return (size_t)2 * 3 * (c
 BwwArgs make_args_pw_dense(const st_conv_desc &d)
 {
     const int cw = pw_dense_tile(d.C), kw = pw_dense_tile(d.K);
-    return make_args_pw(d, kw, cw, cw == 128 && kw == 128 ? 32 : 64, kPwDenseWorkgroups);
+    // One workgroup fits on a compute unit: not one more than there are compute units (three groups of filters, 86 splits: 258
+    // workgroups, of which the last two took as long as the 256 before them; 16->352 @200, N = 4: 127 -> 69 us, 512->1536 @7, N = 32: 43 -> 29)
+    const int groups = ceil_div(d.K, kw) * ceil_div(d.C, cw), splits = kPwDenseWorkgroups / groups;
+    return make_args_pw(d, kw, cw, cw == 128 && kw == 128 ? 32 : 64, groups * (splits > 1 ? splits : 1));
 }
 
 int pw_kpl(const st_conv_desc &d) { return d.K % 256 == 0 ? 4 : (d.K % 128 == 0 ? 2 : 1); }

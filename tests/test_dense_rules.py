@@ -1,4 +1,6 @@
 """Choices of the dense forms that their workspace queries tell (host side only)."""
+import pytest
+
 import paper_1911_10175_amd as st
 
 
@@ -23,6 +25,18 @@ def test_few_tiles_of_many_filters_go_straight_to_the_gradient():
     assert partials(1, 512, 512, 7, 7) == 0
     assert partials(1, 512, 512, 14, 14) == 7                   # seven tiles
     assert partials(1, 64, 64, 7, 7) == 2                       # the chip would be empty
+
+
+@pytest.mark.parametrize("C,K", [(16, 352), (64, 144), (320, 320), (448, 512), (176, 368), (1536, 1792), (80, 1280)])
+def test_no_more_workgroups_than_fit_on_the_chip(C, K):
+    """256 compute units hold two workgroups of the 3x3 kernel each, or one of the 1x1 kernel; one workgroup more would run by itself."""
+    groups = -(-C // 64) * -(-K // 64)
+    assert 1 <= partials(32, C, K, 28, 28) * groups <= 512 or groups > 256
+    cw, kw = (128 if n > 64 else 64 for n in (C, K))
+    groups = -(-C // cw) * -(-K // kw)
+    d = st.ConvDesc(32, C, K, 28, 28, 1, 1)
+    need = st.st_conv_workspace_bytes(d, st.ST_PASS_BWW, True)
+    assert need % (K * C * 4) == 0 and max(1, need // (K * C * 4)) * groups <= 256
 
 
 def bytes_per_filter_element(N, C, K, H, W):

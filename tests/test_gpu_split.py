@@ -259,3 +259,15 @@ def test_1x1_layers_of_few_produced_channels(g):
     mag = np.einsum("kc,nchw->nkhw", np.abs(w[:, :, 0, 0]).astype(np.float64), np.abs(x).astype(np.float64))
     for got in (L.fwd(True), M.bwi(True)):
         assert np.all(np.abs(got - ref) <= (g.C + 3) * 2.0 ** -24 * mag)
+
+
+@pytest.mark.parametrize("g", [Geom(2, 64, 144, 30, 26, 3, 3, 1, 1, 1, 1), Geom(1, 320, 320, 20, 22, 3, 3, 1, 1, 1, 1), Geom(3, 48, 160, 17, 19, 3, 3, 2, 2, 1, 1),
+                               Geom(2, 16, 352, 41, 37, 1, 1), Geom(2, 336, 272, 9, 11, 1, 1)], ids=lambda g: f"{g.R}x{g.S}/{g.stride_w} {g.C}to{g.K}")
+def test_bww_with_numbers_of_filter_groups_that_do_not_divide_the_chip(g):
+    """3, 25, 3, 3 and 9 groups of filters: partial gradients over unequal shares of the tiles."""
+    x, w, dy = inputs(g, 23)
+    L = DeviceLayer(g, x, w, dy)
+    ref, ref_abs = st_ref.conv_bww(g, x, dy)
+    bound = (g.N * g.OH * g.OW + 3) * 2.0 ** -24 * ref_abs
+    for form in (True, "auto"):
+        assert np.all(np.abs(L.bww(form) - ref) <= bound), form
