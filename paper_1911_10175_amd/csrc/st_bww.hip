@@ -1190,7 +1190,7 @@ __global__ __launch_bounds__(1024) void bww_reduce_kernel(const float4 *part, fl
     // Few splits: a thread per output.  With few outputs as well, that many threads would wait for one load after the other;
     // there the 16 wavefronts of a workgroup share the partial sums (48->48 @12 stride 2, N = 4, 9 partial sums of 5184 float4:
     // 18.1 -> 16.4 us for the whole call; two partial sums of 576 are faster added up by one thread each, 17.5 : 18.4).
-    if (splits <= 4 || (splits <= 16 && n4 >= 16384)) {
+    if (splits <= 2 || (splits <= 16 && n4 >= 16384)) {
         for (size_t i = (size_t)blockIdx.x * 1024 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 1024) {
             const Sum4 s = add_partials(part + i, n4, 0, splits, 1);
             dw[i] = make_float4((float)s.x, (float)s.y, (float)s.z, (float)s.w);
