@@ -220,11 +220,14 @@ st_status st_conv_fwd_static(const st_conv_desc *desc, const float *x, const flo
 size_t st_conv_workspace_bytes(const st_conv_desc *desc, int pass, int dense);
 
 /*
- * The zero fraction of the tested operand, in per mille, from which skipping pays on the fp32 pipes: the
- * zero-skipping form (pass = ST_PASS_FWD or ST_PASS_BWI) against fp32 matrix instructions for this
- * geometry: 0 = always, 1001 = never; -1 for an invalid descriptor or another pass.  The st_conv_*_dense
- * forms reach fp32 accuracy on faster instructions, so st_conv_fwd_auto and st_conv_bwi_auto switch later than
- * this (see there), never earlier.  Host-side, no GPU work.
+ * A zero fraction of the tested operand, in per mille: 0 = always, 1001 = never; -1 for an invalid descriptor or
+ * another pass.  Host-side, no GPU work.
+ *   pass = ST_PASS_FWD_AUTO or ST_PASS_BWI_AUTO: the fraction from which st_conv_fwd_auto / st_conv_bwi_auto run the
+ *     zero-skipping form of this geometry.  A caller that tracks sparsity itself can compare it and call the form
+ *     directly.
+ *   pass = ST_PASS_FWD or ST_PASS_BWI: the fraction from which the zero-skipping form beats fp32 matrix instructions.
+ *     The st_conv_*_dense forms of 3x3 layers reach fp32 accuracy on faster instructions, so this is below the
+ *     fraction above, and not where the faster of the two entry points changes.
  */
 int st_conv_sparse_threshold(const st_conv_desc *desc, int pass);
 

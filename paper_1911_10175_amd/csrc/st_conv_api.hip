@@ -444,7 +444,8 @@ int st_conv_sparse_threshold(const st_conv_desc *desc, int pass)
         return -1;
     }
     if (!st::fwd_sparse_supported(g) || !st::fwd_dense_supported(g)) return 0;
-    return (int)st::fwd_sparse_threshold(g);
+    const bool self_selecting = pass == ST_PASS_FWD_AUTO || pass == ST_PASS_BWI_AUTO;
+    return (int)(self_selecting ? st::fwd_auto_threshold(g) : st::fwd_sparse_threshold(g));
 }
 
 st_status st_conv_kernel_name(const st_conv_desc *desc, int pass, char *buf, size_t len)

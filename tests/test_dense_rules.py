@@ -51,3 +51,22 @@ def test_1x1_layers_of_few_produced_channels_stay_on_fp32_instructions():
     assert [bytes_per_filter_element(32, c, 32, 80, 80) for c in (48, 64, 80, 256)] == [4, 6, 4, 4]
     assert [bytes_per_filter_element(4, c, 256, 56, 56) for c in (16, 256)] == [6, 6]
     assert bytes_per_filter_element(1, 256, 256, 14, 14) == 4          # few pixels
+
+
+def test_the_switching_points_of_the_self_selecting_entry_points_can_be_asked_for():
+    F, B = st.ST_PASS_FWD_AUTO, st.ST_PASS_BWI_AUTO
+    ask = st.st_conv_sparse_threshold
+    vgg = st.ConvDesc(16, 256, 256, 56, 56, 3, 3, 1, 1, 1, 1)
+    assert ask(vgg, F) == 950 and ask(vgg, B) == 950
+    # one main kernel with fewer than 128 reduced channels (FWD: C, BWI: K); two kernels
+    mixed = st.ConvDesc(16, 64, 128, 56, 56, 3, 3, 1, 1, 1, 1)
+    assert ask(mixed, F) == 650 and ask(mixed, B) == 850
+    # never: stride 2, 1x1; always: geometries without a tiled dense form
+    assert ask(st.ConvDesc(8, 128, 128, 56, 56, 3, 3, 2, 2, 1, 1), F) == 1001
+    assert ask(st.ConvDesc(8, 64, 256, 56, 56, 1, 1), B) == 1001
+    assert ask(st.ConvDesc(1, 16, 16, 9, 9, 5, 5, 1, 1, 2, 2), F) == 0
+    assert ask(st.ConvDesc(0, 16, 16, 9, 9, 3, 3), F) == -1 and ask(vgg, st.ST_PASS_BWW_AUTO) == -1
+    # never below what the form itself needs to beat fp32 instructions
+    for d in (vgg, mixed):
+        for auto, direct in ((F, st.ST_PASS_FWD), (B, st.ST_PASS_BWI)):
+            assert ask(d, auto) >= ask(d, direct)
