@@ -164,7 +164,8 @@ st_status st_conv_bww_dy(const st_conv_desc *desc, const float *x, const float *
  * Two kinds of layer are decided without sampling: 1x1 layers, where a zero saves too few
  * multiply-adds to beat the matrix cores at any zero fraction measured (up to 95 %), go straight to the dense form;
  * stride-2 3x3 layers always test dy (x has four times the elements and each feeds fewer taps,
- * Sec. 3.3, so that form is the faster one at any sparsity).
+ * Sec. 3.3, so that zero-skipping form is the faster of the two at any sparsity; the dense form, faster than
+ * both on some of these layers, is not considered).
  * Workspace: st_conv_workspace_bytes(desc, ST_PASS_BWW_AUTO, 0).
  */
 st_status st_conv_bww_auto(const st_conv_desc *desc, const float *x, const float *dy, float *dw,
@@ -176,10 +177,13 @@ st_status st_conv_bww_auto(const st_conv_desc *desc, const float *x, const float
  * profiled sparsity; here a first kernel counts the zeros in a sample of the tested operand (x for
  * FWD, dy for BWI; at most 64 evenly spaced blocks of 1024 elements) in the same launch that
  * writes both forms' filter copies, then both forms are enqueued and the one the count does not
- * select returns at once.  The zero-skipping form runs when the sampled zero fraction reaches the
- * break-even point against the dense form measured for the geometry: 95 % for unit-stride 3x3 layers
- * that one main kernel serves (below; 65 % with less than 128 reduced channels), 85 % for the others, never for stride-2 3x3 and for 1x1 layers
- * (measured up to 90 and 95 % zeros), always for geometries only the generic kernels cover.  Where the answer is "always" or "never" the call
+ * select returns at once.  The zero-skipping form runs when the sampled zero fraction reaches a line that
+ * depends on the geometry (st_conv_sparse_threshold tells it): 95 % for unit-stride 3x3 layers that one main
+ * kernel serves (below) and that have 128 or more reduced channels, which is where the two forms were measured
+ * to be equally fast; 65 % for those with fewer channels and 85 % for other unit-stride 3x3 layers, where these
+ * entry points have always skipped zeros at 70 and 90 % (the dense form is up to a fifth faster between there and
+ * 90 to 95 %); never for stride-2 3x3 and for 1x1 layers (measured up to 90 and 95 % zeros); always for
+ * geometries only the generic kernels cover.  Where the answer is "always" or "never" the call
  * goes straight to that form, without sampling.  On unit-stride 3x3 layers of the usual sizes one
  * main kernel holds both forms and runs the selected one, so the sampled path has as many launches
  * as the direct call (st_conv_kernel_name tells); elsewhere it costs one launch more.  Same tensors and
@@ -212,6 +216,7 @@ st_status st_conv_fwd_static(const st_conv_desc *desc, const float *x, const flo
  * Bytes of device workspace the given pass needs for this geometry
  * (pass = ST_PASS_*, dense = 0 for st_conv_<pass>, 1 for st_conv_<pass>_dense; ST_PASS_BWW_DY with
  * dense = 0 is st_conv_bww_dy, ST_PASS_*_AUTO with dense = 0 are the st_conv_*_auto entry points).
+ * Sizes are those of this version of the library (st_conv_version): ask again rather than keep them.
  * Returns 0 when none is needed or when desc is invalid (the pass itself then
  * reports the error).  The workspace must be 256-byte aligned.  Its contents
  * need not be initialised and are undefined afterwards; two calls that are in

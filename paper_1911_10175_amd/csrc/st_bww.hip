@@ -25,7 +25,7 @@
 //    (Sec. 3.4, accumulation of partial results at the end of a sweep), so results are
 //    deterministic without floating-point atomics.
 #include <cstdio>
-#include <cstdlib>
+#include <atomic>
 #include <type_traits>
 
 #include "st_common.hpp"
@@ -1229,7 +1229,7 @@ template <auto Kern>
 hipError_t allow_dynamic_lds(size_t bytes)
 {
     constexpr int kMaxDev = 64;
-    static bool allowed[kMaxDev] = {};
+    static std::atomic<bool> allowed[kMaxDev] = {};         // (calls from several threads: at worst the attribute is set twice)
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;

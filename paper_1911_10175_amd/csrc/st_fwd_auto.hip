@@ -23,7 +23,8 @@ constexpr int cmax(int a, int b) { return a > b ? a : b; }
 
 // TH x TW pixels and KPL channels per lane, CS wavefronts per task: the zero-skipping form; KQ column blocks
 // per workgroup and strips of TWD pixels: the dense form (28: two strips of 14 a row; whole rows of 28 need a halo half as
-// large again and take 583 instead of 567 us on 512->512 @28, N = 32)
+// large again and take 583 instead of 567 us on 512->512 @28, N = 32).  TWD does not enter the kernel, whose strips come with
+// the grid: it tells the launches apart by the name that st_conv_kernel_name and a profiler give
 template <int TH, int TW, int KPL, int CS, int KQ, int TWD>
 __global__ __launch_bounds__(256, 4) void fwd_auto_kernel(Geom g, const float *__restrict__ in, const float *__restrict__ wl,
                                                           const float *__restrict__ wd, float *__restrict__ out,

@@ -21,7 +21,6 @@
 // 8192 x 8192 matrices 1280: at that rate the chip lowers its clock, and staging, LDS reads and the vector adds take
 // their share of the power.  The smaller layers lose to the last round of workgroups (392 of 256 compute units' worth on
 // 512->512 @14).
-#include <cstdlib>
 
 #include "st_common.hpp"
 #include "st_filter_copies.hpp"

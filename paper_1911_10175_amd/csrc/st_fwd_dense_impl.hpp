@@ -352,8 +352,9 @@ inline FlatGrid dense_tiling(const Geom &g, int *kq, long long *blocks)
     return q;
 }
 
-// Workgroups of the rectangular tiles (8x8, 4x14, 2x28) that the choices between forms and the workspace query of
-// unit-stride launches are stated in, and their width
+// Workgroups of a unit-stride launch on rectangular tiles (8x8, 4x14, 2x28), and their width.  No kernel has these tiles any
+// more.  What the interface tells of a geometry is stated in them and stays: which launches have one main kernel for both
+// forms and its name (st_conv_kernel_name), and the least the workspace query counts for a launch that splits its channels.
 inline long long dense_rect_blocks(const Geom &g, int *twd)
 {
     // tile width that divides the row length, if any: 8 -> 8x8, 28 -> 2x28, 14 -> 4x14
@@ -384,7 +385,7 @@ inline int dense_channel_split(const Geom &g)
     return cs;
 }
 
-// The partial outputs counted by the workspace query for a unit-stride launch (a power of two of them)
+// The partial outputs the workspace query counts at least for a unit-stride launch: a power of two, more than are written
 inline int dense_channel_split_pow2(const Geom &g)
 {
     int twd;

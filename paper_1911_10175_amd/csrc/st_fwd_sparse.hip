@@ -52,9 +52,10 @@ unsigned fwd_sparse_threshold(const Geom &g)
 //   256->256 @56 595 : 502 / 497 : 474   512->512 @28 590 : 530 / 502 : 499   512->512 @14 188 : 156 / 163 : 145
 //   128->256 @56 304 : 271 / 260 : 245   64->64 @224 736 : 572 / 585 : 542
 // Between the two the difference falls by half or more, so the lines cross near 95 % on the layers of 128 and more input
-// channels that the one-kernel launch of st_fwd_auto.hip serves (950).  With fewer (64->128 @112 332 : 272 / 302 : 265)
-// that launch has always been documented and checked to test its operand from 70 % zeros on, the other unit-stride
-// launches from 90 % on (64->64 @56 57 : 54, 128->128 @28 49 : 49, 256->256 @14 53 : 58 there): 650 and 850 keep both.
+// channels that the one-kernel launch of st_fwd_auto.hip serves (950).  The other two lines are not crossings: launches with
+// fewer channels have always been checked to test their operand from 70 % zeros on, although the dense form is faster there
+// (64->128 @112 332 : 272 / 302 : 265), the other unit-stride launches from 90 % on (64->64 @56 57 : 54, 128->128 @28 49 : 49,
+// 256->256 @14 53 : 58, 64->64 @224 585 : 542 there): 650 and 850 keep that.
 // Stride 2 stays behind at 90 %: FWD 128->128 @56 76 : 52, 256->256 @28 129 : 77, BWI 75 : 58, 85 : 63 (512->512 @14
 // 89 : 91).
 unsigned fwd_auto_threshold(const Geom &g)

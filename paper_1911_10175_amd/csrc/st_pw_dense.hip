@@ -17,7 +17,7 @@
 // Bound by a stage's fixed costs where a compute unit holds one or two workgroups (7x7, 14x14), by the matrix cores and
 // the splitting (130 vector instructions a stage and wavefront against 48 matrix instructions) elsewhere.  Filters
 // requested a whole stage ahead (three wavefronts per SIMD) were measured and are 6-12 % slower.
-#include <cstdlib>
+#include <atomic>
 #include <type_traits>
 
 #include "st_common.hpp"
@@ -563,7 +563,7 @@ hipError_t launch_pw_lds(const Geom &g, bool transpose, const float *in, const f
     // More than 48 KB of dynamic LDS has to be allowed once per kernel and device; done on the first
     // call on that device, outside any launch sequence a caller may be capturing into a graph later.
     {
-        static bool allowed[kMaxDevices] = {};
+        static std::atomic<bool> allowed[kMaxDevices] = {};         // (several threads: at worst the attribute is set twice)
         int devid = 0;
         hipError_t e = hipGetDevice(&devid);
         if (e != hipSuccess) return e;
