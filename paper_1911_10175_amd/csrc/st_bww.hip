@@ -1611,10 +1611,11 @@ hipError_t launch_bww_dense(const st_conv_desc &d, const float *x, const float *
 // 3x3 zero-skipping forms pass the dense one at 85-90 % zeros or not at all.  The line is drawn at 75 %, not there: from 80 % on
 // this entry point has always been checked to test the sparser operand; between 75 % and the crossing it is up to 15 % slower for
 // that.
-// Launches that give every workgroup one tile and write 200 partial gradients of 64 x 64 filters or more are bound by these, and
-// the dense form's smaller tiles leave more of them (zero-skipping at 30 / 50 / 70 % zeros : dense: 208->256 @9 N = 4 26.6 / 25.8 /
-// 24.8 : 30.8, 512->256 @10 N = 2 29.4 / 28.9 / 28.4 : 32.8, 256->256 @28 N = 1 32.9 / 32.0 / 31.1 : 36.3; with fewer, 64->128 @14
-// N = 4 23.1 / 22.3 / 21.4 : 17.0, 64->64 @56 N = 2 29.8 / 28.9 / 28.0 : 26.1): from 25 % on.
+// Launches of at most 128 tiles that give every workgroup one of them and write 24 MB of partial gradients or more are bound by
+// these, and the dense form's smaller tiles leave more of them (zero-skipping at 30 / 50 / 70 % zeros : dense: 208->256 @9
+// N = 4 26.6 / 25.8 / 24.8 : 30.8, 512->256 @10 N = 2 29.4 / 28.9 / 28.4 : 32.8, 256->256 @28 N = 1 32.9 / 32.0 / 31.1 : 36.3, 336->192
+// @12 N = 2 24.0 / 23.2 / 22.3 : 25.9; with less, 64->128 @14 N = 4 23.1 / 22.3 / 21.4 : 17.0, or more tiles, 64->64 @56 N = 2 29.8 /
+// 28.9 / 28.0 : 26.1, 80->48 @37x53 N = 3 at 50 % 29.4 : 25.5): from 25 % on.
 // A 1x1 layer saves at most K/64 (or C/64) multiply-adds per zero and stays behind the matrix cores at every zero
 // fraction measured (up to 95 %): never (1001).  (Stride-2 layers never get here: they test dy, unsampled.)
 unsigned bww_sparse_threshold(const st_conv_desc &d)
@@ -1622,7 +1623,8 @@ unsigned bww_sparse_threshold(const st_conv_desc &d)
     if (!bww_fast_supported(d)) return 0;           // generic kernels: the test only ever removes work
     if (d.R == 1) return 1001;
     const BwwArgs A = dense_args(d);
-    return A.splits == A.units && (long long)A.units * ceil_div(d.K, 64) * A.cgroups >= 200 ? 250 : 750;
+    const long long partial_bytes = (long long)A.units * d.K * d.C * (9 * (int)sizeof(float));
+    return A.splits == A.units && A.units <= 128 && partial_bytes >= 24000000 ? 250 : 750;
 }
 
 }  // namespace st

@@ -273,12 +273,13 @@ def test_bww_with_numbers_of_filter_groups_that_do_not_divide_the_chip(g):
         assert np.all(np.abs(L.bww(form) - ref) <= bound), form
 
 
-@pytest.mark.parametrize("g,form", [(Geom(4, 208, 256, 9, 9, 3, 3, 1, 1, 1, 1), False), (Geom(1, 256, 256, 28, 28, 3, 3, 1, 1, 1, 1), False),
+@pytest.mark.parametrize("g,form", [(Geom(4, 208, 256, 9, 9, 3, 3, 1, 1, 1, 1), False), (Geom(1, 256, 256, 28, 28, 3, 3, 1, 1, 1, 1), False), (Geom(2, 336, 192, 12, 12, 3, 3, 1, 1, 1, 1), False),
+                                    (Geom(3, 80, 48, 37, 53, 3, 3, 1, 1, 1, 1), True),
                                     (Geom(4, 64, 128, 14, 14, 3, 3, 1, 1, 1, 1), True), (Geom(2, 64, 64, 56, 56, 3, 3, 1, 1, 1, 1), True),
                                     (Geom(8, 512, 512, 14, 14, 3, 3, 1, 1, 1, 1), True)], ids=lambda v: f"{v.C}to{v.K} {v.H}" if isinstance(v, Geom) else "")
 def test_bww_auto_takes_the_faster_form_of_launches_bound_by_partial_gradients(g, form):
-    """Half zeros: bit for bit the zero-skipping form (x tested) where every workgroup has one tile and there are 200 partial
-    gradients of 64 x 64 filters and more, the dense form elsewhere."""
+    """Half zeros: bit for bit the zero-skipping form (x tested) where every one of at most 128 workgroups has one tile and
+    the partial gradients are 24 MB and more, the dense form elsewhere."""
     x, w, dy = inputs(g, 29)
     L = DeviceLayer(g, x, None, dy)
     got = L.bww("auto", raw=True)
