@@ -868,9 +868,67 @@ __global__ __launch_bounds__(512, 2) void pw_bww_dense_kernel(BwwArgs A, const f
     // Phases of team 0: multiply chunk 0, stash 1, multiply 1, ...; of team 1, one behind: stash 0, multiply 0, ...
     const int rounds = (u1 - u0 + 1) / 2;               // the same for both teams (barriers); the last may be one team's only
     auto flip = [&](int it) __attribute__((always_inline)) { return (it + split + team) % 2 != 0; };
+    const bool apart = rounds * P <= kSplitApartPixels;
     if (u0 + team < u1) fetch();
     if (team == 0) stash(flip(0));                      // (a workgroup has at least one chunk)
     __syncthreads();
+    auto multiply = [&](auto A) __attribute__((always_inline)) {
+        constexpr bool APART = decltype(A)::value;
+        floatx16 block[KJ][CI];
+#pragma unroll
+        for (int s = 0; s < P / 16; ++s) {
+            bf16x8 d[KJ][3], f[CI][3];
+#pragma unroll
+            for (int j = 0; j < KJ; ++j)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const int off = (j * (P * 64) + q * DB + s * 1024) / 8;
+                    d[j][q] = split_tr_read(dp + off, dp + off + 32);
+                }
+#pragma unroll
+            for (int i = 0; i < CI; ++i)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const int off = (i * (P * 64) + q * XB + s * 1024) / 8;
+                    f[i][q] = split_tr_read(xp + off, xp + off + 32);
+                }
+            if (s > 0 && s % 2 == 0 && !APART) {            // a block is 32 pixels
+#pragma unroll
+                for (int j = 0; j < KJ; ++j)
+#pragma unroll
+                    for (int i = 0; i < CI; ++i) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) sum[j][i][r] += block[j][i][r];
+                    }
+            }
+            constexpr int ta[5] = {2, 0, 1, 1, 0}, tb[5] = {0, 2, 1, 0, 1};            // smallest products first
+#pragma unroll
+            for (int t = 0; t < 5; ++t)
+#pragma unroll
+                for (int j = 0; j < KJ; ++j)
+#pragma unroll
+                    for (int i = 0; i < CI; ++i)
+                        block[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[j][ta[t]], f[i][tb[t]],
+                                                                              (APART ? s == 0 : s % 2 == 0) && t == 0 ? floatx16{} : block[j][i], 0, 0, 0);
+            // (left to itself the compiler moves these up and the next step's reads down: 256->64 @56 36.6 -> 37.5)
+            if constexpr (KJ * CI > 1) __builtin_amdgcn_sched_barrier(0);
+            auto leading = [&](floatx16 (&to)[KJ][CI]) __attribute__((always_inline)) {
+#pragma unroll
+                for (int j = 0; j < KJ; ++j)
+#pragma unroll
+                    for (int i = 0; i < CI; ++i) to[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[j][0], f[i][0], to[j][i], 0, 0, 0);
+            };
+            if constexpr (APART) leading(sum);
+            else leading(block);
+        }
+        // the block joins the sum, which changes sign (with the dy of the team's next chunk)
+#pragma unroll
+        for (int j = 0; j < KJ; ++j)
+#pragma unroll
+            for (int i = 0; i < CI; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sum[j][i][r] = -sum[j][i][r] - block[j][i][r];
+    };
     for (int ph = 0; ph < 2 * rounds; ++ph) {
         const int it = (ph + (team == 0 ? ph % 2 : 0)) / 2, unit = u0 + 2 * it + team;
         if (ph % 2 != team) {
@@ -878,47 +936,8 @@ __global__ __launch_bounds__(512, 2) void pw_bww_dense_kernel(BwwArgs A, const f
         } else if (unit < u1) {
             if (unit + 2 < u1) fetch();                 // in flight during the MFMAs below
             if (active) {
-                floatx16 small[KJ][CI];
-#pragma unroll
-                for (int s = 0; s < P / 16; ++s) {
-                    bf16x8 d[KJ][3], f[CI][3];
-#pragma unroll
-                    for (int j = 0; j < KJ; ++j)
-#pragma unroll
-                        for (int q = 0; q < 3; ++q) {
-                            const int off = (j * (P * 64) + q * DB + s * 1024) / 8;
-                            d[j][q] = split_tr_read(dp + off, dp + off + 32);
-                        }
-#pragma unroll
-                    for (int i = 0; i < CI; ++i)
-#pragma unroll
-                        for (int q = 0; q < 3; ++q) {
-                            const int off = (i * (P * 64) + q * XB + s * 1024) / 8;
-                            f[i][q] = split_tr_read(xp + off, xp + off + 32);
-                        }
-                    constexpr int ta[5] = {2, 0, 1, 1, 0}, tb[5] = {0, 2, 1, 0, 1};
-#pragma unroll
-                    for (int t = 0; t < 5; ++t)
-#pragma unroll
-                        for (int j = 0; j < KJ; ++j)
-#pragma unroll
-                            for (int i = 0; i < CI; ++i)
-                                small[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[j][ta[t]], f[i][tb[t]],
-                                                                                      s == 0 && t == 0 ? floatx16{} : small[j][i], 0, 0, 0);
-                    // (left to itself the compiler moves these up and the next step's reads down: 256->64 @56 36.6 -> 37.5)
-                    if constexpr (KJ * CI > 1) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int j = 0; j < KJ; ++j)
-#pragma unroll
-                        for (int i = 0; i < CI; ++i) sum[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[j][0], f[i][0], sum[j][i], 0, 0, 0);
-                }
-                // the small products join the sum, which changes sign (with the dy of the team's next chunk)
-#pragma unroll
-                for (int j = 0; j < KJ; ++j)
-#pragma unroll
-                    for (int i = 0; i < CI; ++i)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) sum[j][i][r] = -sum[j][i][r] - small[j][i][r];
+                if (apart) multiply(std::true_type{});              // uniform
+                else multiply(std::false_type{});
             }
         }
         __syncthreads();

@@ -41,7 +41,9 @@ __global__ __launch_bounds__(256, 4) void fwd_auto_kernel(Geom g, const float *_
                                                sq.kt_major, lds);
     } else {
         if ((long long)blockIdx.x >= dq.blocks) return;
-        fwd_dense_body<KQ, HPC>(g, in, wd, out, nullptr, dq.q, dq.kgroups, 1, 0, (int)blockIdx.x, 0, lds, raw);
+        if (g.Ci / kBlk <= kSplitApart)
+            fwd_dense_body<KQ, HPC, false, true>(g, in, wd, out, nullptr, dq.q, dq.kgroups, 1, 0, (int)blockIdx.x, 0, lds, raw);
+        else fwd_dense_body<KQ, HPC, false, false>(g, in, wd, out, nullptr, dq.q, dq.kgroups, 1, 0, (int)blockIdx.x, 0, lds, raw);
     }
 }
 

@@ -63,16 +63,24 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const float4 *__restr
     }
 }
 
-template <int KQ, int HPC, bool DEEP, int MODE>
-hipError_t launch_cfg(const Geom &g, const FlatGrid &fq, int cs, const float *in, const float *wd, float *out, float *parts, hipStream_t s)
+template <int KQ, int HPC, bool DEEP, int MODE, bool APART>
+hipError_t launch_form(const Geom &g, const FlatGrid &fq, int cs, const float *in, const float *wd, float *out, float *parts, hipStream_t s)
 {
     constexpr int TQ = 4 / KQ;
     const int kgroups = ceil_div(g.Ko, 32 * KQ);
     const long long blocks = ((long long)fq.tiles + TQ - 1) / TQ * kgroups;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((fwd_dense_kernel<KQ, HPC, DEEP, MODE>), dim3((unsigned)blocks, cs), dim3(256), 0, s, g, in, wd, out, parts, fq, kgroups,
+    hipLaunchKernelGGL((fwd_dense_kernel<KQ, HPC, DEEP, APART, MODE>), dim3((unsigned)blocks, cs), dim3(256), 0, s, g, in, wd, out, parts, fq, kgroups,
                        cs, (size_t)g.N * g.Ko * g.Ho * g.Wo);
     return hipGetLastError();
+}
+
+// (the shares of a channel split differ by one block at most)
+template <int KQ, int HPC, bool DEEP, int MODE>
+hipError_t launch_cfg(const Geom &g, const FlatGrid &fq, int cs, const float *in, const float *wd, float *out, float *parts, hipStream_t s)
+{
+    if (ceil_div(g.Ci / kBlk, cs) <= kSplitApart) return launch_form<KQ, HPC, DEEP, MODE, true>(g, fq, cs, in, wd, out, parts, s);
+    return launch_form<KQ, HPC, DEEP, MODE, false>(g, fq, cs, in, wd, out, parts, s);
 }
 
 // FWD at either stride and unit-stride BWI.  With whole column blocks the filters are requested three taps ahead at three
@@ -97,7 +105,7 @@ struct ParityGrid {
     unsigned first[5];                              // first workgroup of each class
 };
 
-template <int KQ>
+template <int KQ, bool APART>
 __global__ __launch_bounds__(256, (FlatLds<KQ, kHalo>::MINW)) void fwd_dense_s2_bwi_kernel(
     Geom g, const float *__restrict__ in, const float *__restrict__ wd, float *__restrict__ out, ParityGrid q, int kgroups)
 {
@@ -107,7 +115,7 @@ __global__ __launch_bounds__(256, (FlatLds<KQ, kHalo>::MINW)) void fwd_dense_s2_
     static_for<0, 4>([&](auto I) __attribute__((always_inline)) {
         constexpr int i = decltype(I)::value, PI = (3 - i) / 2, PJ = (3 - i) % 2;
         if (blockIdx.x >= q.first[i] && blockIdx.x < q.first[i + 1])            // uniform over the workgroup
-            fwd_dense_body<KQ, kHalo, false, 2, PI, PJ>(g, in, wd, out, nullptr, q.q[i], kgroups, 1, 0, (int)(blockIdx.x - q.first[i]), 0, lds, raw);
+            fwd_dense_body<KQ, kHalo, false, APART, 2, PI, PJ>(g, in, wd, out, nullptr, q.q[i], kgroups, 1, 0, (int)(blockIdx.x - q.first[i]), 0, lds, raw);
     });
 }
 
@@ -126,7 +134,8 @@ hipError_t launch_s2_bwi(const Geom &g, const float *in, const float *wd, float 
         if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     }
     q.first[4] = (unsigned)blocks;
-    hipLaunchKernelGGL((fwd_dense_s2_bwi_kernel<KQ>), dim3((unsigned)blocks), dim3(256), 0, s, g, in, wd, out, q, kgroups);
+    if (g.Ci / kBlk <= kSplitApart) hipLaunchKernelGGL((fwd_dense_s2_bwi_kernel<KQ, true>), dim3((unsigned)blocks), dim3(256), 0, s, g, in, wd, out, q, kgroups);
+    else hipLaunchKernelGGL((fwd_dense_s2_bwi_kernel<KQ, false>), dim3((unsigned)blocks), dim3(256), 0, s, g, in, wd, out, q, kgroups);
     return hipGetLastError();
 }
 

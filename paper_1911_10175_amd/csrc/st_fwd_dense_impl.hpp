@@ -105,7 +105,8 @@ static __device__ __attribute__((aligned(16))) float kSplitZeros[4] = {0.f, 0.f,
 // wg = index of the workgroup among those of the launch, cshare = its share of the channel split;
 // lds, raw: FlatLds::FLOATS and RAWFLOATS floats, 16-byte aligned.  Every thread of
 // the workgroup makes the call (the body contains barriers).
-template <int KQ, int HPC, bool DEEP = false, int MODE = 0, int PI = 0, int PJ = 0>
+// APART: the form of short reductions (kSplitApart)
+template <int KQ, int HPC, bool DEEP, bool APART, int MODE = 0, int PI = 0, int PJ = 0>
 __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__restrict__ in, const float *__restrict__ wd,
                                                float *__restrict__ out, float *__restrict__ parts, const FlatGrid &fq, int kgroups,
                                                int csplit, size_t part_stride, int wg, int cshare, float *lds_base, float *raw)
@@ -149,7 +150,7 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
     const bool k_ok = kb32 * 32 < g.Ko;
     const bool active = tile_ok && k_ok;
 
-    // sums of the two pixel blocks: the large products of the pieces, and the small ones of the current channel block
+    // sums of the two pixel blocks, and those of the current channel block; with APART the large products go straight to the former
     floatx16 acc[2], part[2];
 #pragma unroll
     for (int pb = 0; pb < 2; ++pb)
@@ -261,8 +262,8 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
                 };
                 bf16x8 f0n;
                 if constexpr (D == 1) f0n = filters(nstep, 0);
-                mul(fc[0], x0, acc, false);
-                mul(fc[2], x0, part, tp == 0);
+                mul(fc[0], x0, APART ? acc : part, !APART && tp == 0);
+                mul(fc[2], x0, part, APART && tp == 0);
                 fc[2] = filters(nstep, 2);
                 mul(fc[1], x0, part, false);
                 if constexpr (!last) { x0[0] = input(nt, 0, 0); x0[1] = input(nt, 1, 0); }
@@ -275,7 +276,8 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
                 if constexpr (D == 1) fc[0] = f0n;
                 else fc[0] = filters(nstep, 0);
             });
-            // the small products join the sum, which changes sign: odd channel blocks have their filters negated (st_split.hpp)
+            // the block's products (all or the small ones) join the sum, which changes sign: odd channel blocks have their
+            // filters negated (st_split.hpp)
 #pragma unroll
             for (int pb = 0; pb < 2; ++pb)
 #pragma unroll
@@ -329,7 +331,7 @@ __device__ __forceinline__ void fwd_dense_body(const Geom &g, const float *__res
     }
 }
 
-template <int KQ, int HPC, bool DEEP, int MODE>
+template <int KQ, int HPC, bool DEEP, bool APART, int MODE>
 __global__ __launch_bounds__(256, (FlatLds<KQ, HPC, DEEP>::MINW)) void fwd_dense_kernel(
     Geom g, const float *__restrict__ in, const float *__restrict__ wd, float *__restrict__ out, float *__restrict__ parts,
     FlatGrid fq, int kgroups, int csplit, size_t part_stride)
@@ -337,7 +339,7 @@ __global__ __launch_bounds__(256, (FlatLds<KQ, HPC, DEEP>::MINW)) void fwd_dense
     if (form_deselected(g.sel, g.want, g.thr)) return;
     __shared__ __attribute__((aligned(16))) float lds[FlatLds<KQ, HPC>::FLOATS];
     __shared__ __attribute__((aligned(16))) float raw[FlatLds<KQ, HPC>::RAWFLOATS];
-    fwd_dense_body<KQ, HPC, DEEP, MODE>(g, in, wd, out, parts, fq, kgroups, csplit, part_stride, (int)blockIdx.x, (int)blockIdx.y, lds, raw);
+    fwd_dense_body<KQ, HPC, DEEP, APART, MODE>(g, in, wd, out, parts, fq, kgroups, csplit, part_stride, (int)blockIdx.x, (int)blockIdx.y, lds, raw);
 }
 
 // Column blocks per workgroup, tiles and number of workgroups of a 3x3 launch (MODE 0 or 1 of g)

@@ -42,7 +42,8 @@ typedef const __attribute__((address_space(1))) void *PwGlobalPtr;
 typedef __attribute__((address_space(3))) void *PwLdsPtr;
 static __device__ __attribute__((aligned(16))) float kPwZeros[4] = {0.f, 0.f, 0.f, 0.f};
 
-template <int KQ>
+// APART: the form of short reductions (kSplitApart1x1)
+template <int KQ, bool APART>
 __global__ __launch_bounds__(256, (PwCfg<KQ>::MINW)) void pw_dense_kernel(Geom g, const float *__restrict__ in,
                                                                           const float *__restrict__ wd, float *__restrict__ out,
                                                                           float *__restrict__ parts, int kgroups, int csplit,
@@ -153,8 +154,8 @@ __global__ __launch_bounds__(256, (PwCfg<KQ>::MINW)) void pw_dense_kernel(Geom g
                     __builtin_amdgcn_sched_barrier(0);
                 };
                 const bf16x8 f0n = filters(ncb, 0);
-                mul(f0, x0, acc, false);
-                mul(f2, x0, part, sub == 0);
+                mul(f0, x0, APART ? acc : part, !APART);
+                mul(f2, x0, part, APART && sub == 0);
                 f2 = filters(ncb, 2);
                 mul(f1, x0, part, false);
                 if constexpr (!last) { x0[0] = input(ns, 0, 0); x0[1] = input(ns, 1, 0); }
@@ -165,8 +166,15 @@ __global__ __launch_bounds__(256, (PwCfg<KQ>::MINW)) void pw_dense_kernel(Geom g
                 mul(f0, x2, part, false);
                 if constexpr (!last) { x2[0] = input(ns, 0, 2); x2[1] = input(ns, 1, 2); }
                 f0 = f0n;
+                if (!APART && cb + 1 < min(st * NCB + NCB, cb1)) {
+#pragma unroll
+                    for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[pb][r] += part[pb][r];
+                }
             });
-            // the small products join the sum, which changes sign: odd stages have their filters negated (st_split.hpp)
+            // the stage's small products, or its last block's products, join the sum, which changes sign: odd stages have their
+            // filters negated (st_split.hpp)
 #pragma unroll
             for (int pb = 0; pb < 2; ++pb)
 #pragma unroll
@@ -222,8 +230,14 @@ hipError_t launch_pw(const Geom &g, int cs, const float *in, const float *wd, fl
     const int kgroups = ceil_div(g.Ko, 32 * KQ);
     const long long blocks = (tiles + TQ - 1) / TQ * kgroups;
     if (blocks > 0x7fffffffLL || tiles * kPwPx > 0x7fff0000LL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((pw_dense_kernel<KQ>), dim3((unsigned)blocks, cs), dim3(256), 0, s, g, in, wd, out, parts, kgroups, cs,
-                       (size_t)g.N * g.Ko * g.Ho * g.Wo);
+    // (the shares of a channel split are whole stages and differ by one at most)
+    const int nst = ceil_div(g.Ci / kBlk, PwCfg<KQ>::NCB);
+    if (ceil_div(nst, cs) * PwCfg<KQ>::NCB <= kSplitApart1x1)
+        hipLaunchKernelGGL((pw_dense_kernel<KQ, true>), dim3((unsigned)blocks, cs), dim3(256), 0, s, g, in, wd, out, parts, kgroups, cs,
+                           (size_t)g.N * g.Ko * g.Ho * g.Wo);
+    else
+        hipLaunchKernelGGL((pw_dense_kernel<KQ, false>), dim3((unsigned)blocks, cs), dim3(256), 0, s, g, in, wd, out, parts, kgroups, cs,
+                           (size_t)g.N * g.Ko * g.Ho * g.Wo);
     return hipGetLastError();
 }
 

@@ -14,12 +14,14 @@
 // How the sums are taken decides the error.  v_mfma_f32_32x32x2_f32 is a chain of fused multiply-adds (measured: bit for
 // bit).  v_mfma_f32_32x32x16_bf16 adds 8 products, then 8 more, each group to the accumulator with one rounding to
 // nearest; within a group whatever lies 24 bits below the largest product is cut off, also of an accumulator smaller than the
-// products.  So the large products a0 b0 (16 bits, a group of them is nearly exact) and the five small ones have accumulators
-// of their own: the small ones' roundings are 2^-8 of a rounding of the sum, the large ones round twice per 16 products
-// where fp32 instructions round once per non-zero product, and the two meet in an fp32 addition.  With one accumulator for
-// all six products the sum was rounded twelve times per 16 products: with 80 % zeros that was 1.2 to 1.9 times the fp32
-// instruction's error.  (The 3x3 BWW has no registers for two accumulators beside its 144 sums: it starts a fresh one every 16
-// pixels, small products first, and adds it to the sum.)
+// products.  With all six products on one accumulator that is twelve roundings per 16 products, of a sum that should stay
+// small: a fresh accumulator for every block of the reduction (16 channels x 9 taps; 16 channels of a 1x1; 16 or 32 pixels) joins
+// the running sum in an fp32 addition.  Over many blocks a quarter of the fp32 instruction's error is left (2304 terms: 8.6e-7 ->
+// 2.0e-7 of the norm).  Over a few blocks the accumulator is as large as the sum, and with many zeros, where fp32 instructions
+// round only for the non-zero products, the error was 1.2 to 1.9 times theirs.  There the large products a0 b0 (16 bits, a
+// group of them is nearly exact) go straight to the running sum, two roundings per 16 products, and only the five small ones,
+// whose roundings are 2^-8 of one of the sum, have the block's accumulator (kSplitApart below; the 3x3 BWW has no registers for
+// it and starts a fresh accumulator every 16 pixels, small products first).
 //
 // What is cut off leaves a small bias, which over 10^5 terms would outgrow the roundings (256->256 @56, N = 32, BWW: error
 // 7.8e-7 of the norm with one sign, 2.7e-7 with both): every other block of the reduction is computed with one operand
@@ -60,6 +62,14 @@ __device__ __forceinline__ int split_tr_lane(int lane) { return lane / 16 % 2 * 
 
 constexpr float kSplitScale = 16777216.f;                   // 2^24
 constexpr float kSplitUnscale = 1.f / (kSplitScale * kSplitScale);
+
+// The longest reductions whose large products have the running sum for an accumulator: channel blocks of a 3x3 and of a 1x1
+// correlation, pixels of a 1x1 filter gradient.  In units of half a rounding of the final sum, B blocks of T taps take 12 T + B
+// with one accumulator per block, or 2 T B + B: equal at B = 6 without
+// zeros, later with many; a 1x1, whose blocks of one tap join stage by stage, at 8 to 10.
+// (Error of the norm with one accumulator : apart: 256 and 512 channels without zeros 2.0e-7 : 2.9e-7 and 2.1e-7 : 4.2e-7, 32
+// channels with 80 % zeros 1.7e-7 : 6e-8; v_mfma_f32_32x32x2_f32 8.6e-7 on the first and 1.4e-7 on the last.)
+constexpr int kSplitApart = 6, kSplitApart1x1 = 8, kSplitApartPixels = 128;
 
 __device__ __forceinline__ void split2(float a, float b, bf16x2 &p0, bf16x2 &p1, bf16x2 &p2)
 {
