@@ -28,6 +28,10 @@ GEOMS = {
     "3x3 stride 2 16->80": Geom(2, 16, 80, 9, 12, 3, 3, 2, 2, 1, 1),
     "1x1 64->64": Geom(3, 64, 64, 53, 53, 1, 1),
     "1x1 80->48": Geom(2, 80, 48, 5, 7, 1, 1),
+    # enough pixels for the 1x1 kernel on pieces: 1, 2 and 4 column blocks per workgroup, short and long reductions
+    "1x1 64->32": Geom(8, 64, 32, 65, 64, 1, 1),
+    "1x1 32->48": Geom(8, 32, 48, 64, 65, 1, 1),
+    "1x1 144->80": Geom(4, 144, 80, 65, 64, 1, 1),
 }
 
 
@@ -65,7 +69,8 @@ def check(g, x, w, dy, label):
 
 @pytest.mark.parametrize("name", GEOMS)
 def test_dense_forms_keep_fp32_accuracy(name):
-    """Values of very different size side by side: every bit of each of them counts somewhere."""
+    """Values of very different size side by side, each output within the bound of an fp32 sum.  (The bound grows with the number
+    of terms, so a lost third piece need not break it: test_short_reductions_err_no_more_than_fp32_instructions sees that.)"""
     g = GEOMS[name]
     x, w, dy = inputs(g, 11)
     rng = np.random.default_rng(5)
@@ -155,6 +160,10 @@ def norm_error(got, ref):
 
 SHORT = {
     "1x1 16->48": Geom(8, 16, 48, 64, 64, 1, 1),
+    "1x1 64->32": Geom(8, 64, 32, 64, 64, 1, 1),
+    "1x1 32->48": Geom(8, 32, 48, 64, 64, 1, 1),
+    "1x1 16->80": Geom(4, 16, 80, 64, 64, 1, 1),
+    "1x1 144->80": Geom(4, 144, 80, 64, 64, 1, 1),
     "3x3 16->32": Geom(2, 16, 32, 20, 14, 3, 3, 1, 1, 1, 1),
     "3x3 64->144": Geom(2, 64, 144, 14, 14, 3, 3, 1, 1, 1, 1),
     "3x3 256->256 split": Geom(1, 256, 256, 7, 7, 3, 3, 1, 1, 1, 1),
