@@ -145,40 +145,32 @@ __device__ __forceinline__ void reformat_filters_block(size_t block, int Ko, int
 // at the sampled blocks part, part + 4, ... with all its 16 loads per thread in flight at once (one memory
 // round trip, whatever the tensor size) and WRITES {zeros, elements looked at} to out[2 * part], out[2 * part + 1]:
 // nothing is accumulated across workgroups, so no counter has to be cleared first and no atomics are involved;
-// the readers add the four pairs (sample_zeros / sample_seen).  red: 8 unsigned of LDS.  Every thread of the
-// workgroup must make the call.
+// the readers add the four pairs (sample_zeros / sample_seen).  n is a multiple of 16 (whole channel blocks), so a float4
+// lies inside the tensor or outside; the loads are made unconditionally, from the tensor's start where there is nothing to
+// look at: under a condition each waited for itself, sixteen round trips one after the
+// other (sample of x and dy, 80->48 @37x53, N = 3: 8.4 -> 3.9 us; its FWD, BWI and BWW together 82 -> 68).
+// red: 8 unsigned of LDS.  Every thread of the workgroup must make the call.
 constexpr int kSampleBlocks = 64, kSampleParts = 4;
 __device__ __forceinline__ void zero_sample_block(const float *__restrict__ t, size_t n, int part, unsigned *__restrict__ out,
                                                   unsigned *red)
 {
-    const size_t blocks = (n + 1023) / 1024;
-    const size_t stride = (blocks + kSampleBlocks - 1) / kSampleBlocks;
-    const size_t sampled = (blocks + stride - 1) / stride;
-    unsigned zeros = 0, seen = 0;
+    const size_t stride = ((n + 1023) / 1024 + kSampleBlocks - 1) / kSampleBlocks, n4 = n / 4;
     constexpr int UN = kSampleBlocks / kSampleParts;
+    const float4 *t4 = reinterpret_cast<const float4 *>(t);
     float4 v[UN];
-    bool full[UN];
 #pragma unroll
     for (int i = 0; i < UN; ++i) {
-        const size_t sb = (size_t)i * kSampleParts + part;
-        const size_t base = sb * stride * 1024 + threadIdx.x * 4;
-        full[i] = sb < sampled && base + 3 < n;             // tensors are 64-byte aligned: one 16-byte load
-        v[i] = full[i] ? *reinterpret_cast<const float4 *>(t + base) : make_float4(1.f, 1.f, 1.f, 1.f);
+        const size_t at = (size_t)(i * kSampleParts + part) * stride * 256 + threadIdx.x;
+        v[i] = t4[at < n4 ? at : 0];
     }
+    __builtin_amdgcn_sched_barrier(0);
+    unsigned zeros = 0, seen = 0;
 #pragma unroll
     for (int i = 0; i < UN; ++i) {
-        const size_t sb = (size_t)i * kSampleParts + part;
-        const size_t base = sb * stride * 1024 + threadIdx.x * 4;
-        if (full[i]) {
-            zeros += (v[i].x == 0.f ? 1u : 0u) + (v[i].y == 0.f ? 1u : 0u) + (v[i].z == 0.f ? 1u : 0u) + (v[i].w == 0.f ? 1u : 0u);
-            seen += 4u;
-        } else if (sb < sampled) {
-            for (int j = 0; j < 4; ++j)
-                if (base + j < n) {
-                    zeros += t[base + j] == 0.f ? 1u : 0u;
-                    seen += 1u;
-                }
-        }
+        const size_t at = (size_t)(i * kSampleParts + part) * stride * 256 + threadIdx.x;
+        const unsigned z = (v[i].x == 0.f ? 1u : 0u) + (v[i].y == 0.f ? 1u : 0u) + (v[i].z == 0.f ? 1u : 0u) + (v[i].w == 0.f ? 1u : 0u);
+        zeros += at < n4 ? z : 0u;
+        seen += at < n4 ? 4u : 0u;
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
