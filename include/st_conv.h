@@ -185,8 +185,9 @@ st_status st_conv_bww_auto(const st_conv_desc *desc, const float *x, const float
  * 90 to 95 %); never for stride-2 3x3 and for 1x1 layers (measured up to 90 and 95 % zeros); always for
  * geometries only the generic kernels cover.  Where the answer is "always" or "never" the call
  * goes straight to that form, without sampling.  On unit-stride 3x3 layers of the usual sizes one
- * main kernel holds both forms and runs the selected one, so the sampled path has as many launches
- * as the direct call (st_conv_kernel_name tells); elsewhere it costs one launch more.  Same tensors and
+ * main kernel holds both forms (st_conv_kernel_name tells) and runs the selected one, so the sampled path has as many
+ * launches as the direct call, unless the dense form of the layer has a faster kernel of its own (64 and more reduced
+ * channels in whole 32s); there and elsewhere it costs one launch more.  Same tensors and
  * layouts as st_conv_fwd / st_conv_bwi, same result to rounding, no host synchronisation.
  * Workspace: st_conv_workspace_bytes(desc, ST_PASS_FWD_AUTO or ST_PASS_BWI_AUTO, 0).
  */
@@ -245,7 +246,8 @@ int st_conv_sparse_threshold(const st_conv_desc *desc, int pass);
  * With pass = ST_PASS_FWD_AUTO or ST_PASS_BWI_AUTO: the single main kernel of st_conv_fwd_auto /
  * st_conv_bwi_auto that holds both forms ("fwd_auto_kernel<4, 8, 2, 4, 4, 8>": tile height, width,
  * channels per lane and wavefronts per tile of the zero-skipping form, column blocks and tile width of
- * the dense one), ST_ERR_UNSUPPORTED where the two forms are launched separately.  For matching
+ * the dense one; the dense form may run in a kernel of its own all the same, see above), ST_ERR_UNSUPPORTED where
+ * there is no such kernel.  For matching
  * profiler output and timings to calls; host side only, launches nothing.  buf receives at most len
  * bytes including the terminating NUL.  ST_ERR_UNSUPPORTED for other passes and for geometries the
  * generic kernels serve.

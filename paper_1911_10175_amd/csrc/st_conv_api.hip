@@ -255,13 +255,15 @@ st_status run_fwd_bwi_auto(const st_conv_desc *d, const float *act, const float 
     hipError_t e;
     if (fast_sparse && fast_dense && !st::pw_dense_direct_supported(g)) {
         // both forms tiled: sample and both filter copies in one launch, then one main kernel that holds both
-        // forms, or, for the shapes that have none, the two main kernels, of which the one the count does not
-        // select returns at once
+        // forms, or the two main kernels, of which the one the count does not select returns at once: for the
+        // shapes that have no such kernel, and where the dense form takes 32 channels at a time
         if (st::launch_auto_prepare(g, bwi, act, n_act, w, ws_sparse, ws_dense, sel, s) != hipSuccess) return ST_ERR_DEVICE;
         g.sel = sel;
         g.want = 0;
-        if (st::fwd_auto_combined_supported(g)) return dev(st::launch_fwd_auto_combined(g, act, ws_sparse, ws_dense, out, s));
-        if (st::launch_fwd_sparse(g, act, ws_sparse, out, s) != hipSuccess) return ST_ERR_DEVICE;
+        const bool combined = st::fwd_auto_combined_supported(g);
+        e = combined ? st::launch_fwd_auto_combined(g, act, ws_sparse, ws_dense, out, s) : st::launch_fwd_sparse(g, act, ws_sparse, out, s);
+        if (e != hipSuccess) return ST_ERR_DEVICE;
+        if (combined && !st::fwd_dense_wide(g)) return ST_OK;
         g.want = 1;
         return dev(st::launch_fwd_dense(g, act, ws_dense, out, s));
     }

@@ -139,6 +139,45 @@ __device__ __forceinline__ void reformat_filters_block(size_t block, int Ko, int
     for (int q = 0; q < 3; ++q) out[q * 64] = __builtin_shufflevector(a[q], b[q], 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
+// The same for the 3x3 kernel that takes 32 reduced channels at a time and 16 produced ones (Ci a multiple of 32): [Ko/32][Ci/32][tap]
+// [3 pieces][2 halves of the 32 k][4 groups of 8 c][16 k][8 c] bf16; every second 32 reduced channels are negated.
+__device__ __forceinline__ void stage_filters_block(size_t block, int Ko, int Ci, int S, int R, int transpose, const float *__restrict__ w,
+                                                    float *__restrict__ wd, size_t total)
+{
+    const size_t i = block * 256 + threadIdx.x;
+    if (i >= total) return;
+    const int TAPS = S * R, CiB = Ci / kBlk, KoB = Ko / kBlk, NS = CiB / 2;
+    size_t t = i;
+    const int l16 = t % 16; t /= 16;
+    const int grp = t % 4; t /= 4;
+    const int kh = t % 2; t /= 2;
+    const size_t step = t;                              // (kb32 * NS + stage) * TAPS + tap
+    const int tap = t % TAPS; t /= TAPS;
+    const int st = t % NS, kb = (int)(t / NS) * 2 + kh, cb = st * 2 + grp / 2, c0 = grp % 2 * 8;
+    float4 lo = make_float4(0.f, 0.f, 0.f, 0.f), hi = lo;
+    if (kb < KoB) {
+        if (!transpose) {
+            // w[K = Ko][C = Ci]: element [kb][cb][tap][ci%16][ko%16], eight of them 16 apart
+            const float *p = w + (((size_t)kb * CiB + cb) * TAPS + tap) * (kBlk * kBlk) + c0 * kBlk + l16;
+            lo = make_float4(p[0], p[kBlk], p[2 * kBlk], p[3 * kBlk]);
+            hi = make_float4(p[4 * kBlk], p[5 * kBlk], p[6 * kBlk], p[7 * kBlk]);
+        } else {
+            // w[K = Ci][C = Ko]: element [cb][kb][reversed tap][ko%16][ci%16], eight in a row
+            const float4 *p = reinterpret_cast<const float4 *>(
+                w + (((size_t)cb * KoB + kb) * TAPS + (TAPS - 1 - tap)) * (kBlk * kBlk) + l16 * kBlk + c0);
+            lo = p[0];
+            hi = p[1];
+        }
+    }
+    const float scale = st % 2 ? -kSplitScale : kSplitScale;
+    bf16x4 a[3], b[3];
+    split4(lo, scale, a);
+    split4(hi, scale, b);
+    bf16x8 *out = reinterpret_cast<bf16x8 *>(wd) + step * 384 + kh * 64 + grp * 16 + l16;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) out[q * 128] = __builtin_shufflevector(a[q], b[q], 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
 // Zero statistics of one tensor: the elements equal to zero in a sample of the tensor, one block of 1024
 // consecutive floats out of every `stride` blocks, kSampleBlocks (64) blocks at most, 65 536 elements: enough to
 // fix a zero fraction to 0.2 %.  kSampleParts (4) workgroups of 256 threads share the sample; part `part` looks

@@ -5,6 +5,12 @@
 // the two forms' grids; workgroups beyond the selected form's own leave at once.  Both bodies use the
 // same 256 threads and the same LDS allocation, and compute exactly what the separate kernels compute,
 // in the same order: the result is bit-identical to the direct call of the selected form.
+//
+// Layers whose dense form takes 32 channels at a time (fwd_dense_wide) need 220 to 256 registers for it, which would leave the
+// zero-skipping body two wavefronts per SIMD instead of four: here this kernel computes the zero-skipping form only and
+// leaves at once otherwise, and the dense kernel follows in a launch of its own.  That launch costs 2 to 5 us and the
+// faster kernel saves more, down to the smallest of these layers (us, both bodies in one : two launches, half zeros: 64->128 @112 N = 2
+// 28.3 : 28.4, N = 4 48.7 : 47.6, N = 32 293 : 270; 128->128 @56 N = 8 48.2 : 44.0; 512->512 @28 N = 8 163 : 142).
 #include <cstdio>
 
 #include "st_fwd_dense_impl.hpp"
@@ -56,7 +62,7 @@ hipError_t launch_pair(const Geom &g, const float *in, const float *wl, const fl
     dq.q = flat_grid(g.N, g.Ho, g.Wo, 1, 3, 3, kHalo, TWD > 16 ? TWD / 2 : TWD);
     dq.kgroups = ceil_div(g.Ko, 32 * KQ);
     constexpr int TQ = 4 / KQ;
-    dq.blocks = ((long long)dq.q.tiles + TQ - 1) / TQ * dq.kgroups;
+    dq.blocks = fwd_dense_wide(g) ? 0 : ((long long)dq.q.tiles + TQ - 1) / TQ * dq.kgroups;      // (a launch of its own)
     if (!sq.ok || dq.blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const long long blocks = sq.blocks > dq.blocks ? sq.blocks : dq.blocks;
     hipLaunchKernelGGL((fwd_auto_kernel<TH, TW, KPL, CS, KQ, TWD>), dim3((unsigned)blocks), dim3(256), 0, s, g, in, wl, wd, out, sq, dq);
@@ -73,7 +79,7 @@ bool pick_pair(const Geom &g, Pair *p)
 {
     if (g.R != 3 || g.S != 3 || g.sw != 1 || g.sh != 1 || g.uw != 1 || g.uh != 1) return false;
     if (!fwd_sparse_supported(g) || !fwd_dense_supported(g)) return false;
-    if (dense_channel_split(g) != 1) return false;
+    if (dense_channel_split_blocks(g) != 1) return false;
     if (g.Ci <= kBlk) return false;                // one channel block: left to the separate kernels, as it always has been
     // one channel per lane (64 produced channels) is left to the separate kernels: next to the dense body it
     // loses its fifth wavefront per SIMD and runs 14-21 % slower (measured on 64->64 @224 and the BWI of 64->128 @112)

@@ -25,6 +25,7 @@
 #include "st_common.hpp"
 #include "st_filter_copies.hpp"
 #include "st_fwd_dense_impl.hpp"
+#include "st_fwd_dense_wide.hpp"
 
 namespace st {
 namespace {
@@ -37,6 +38,13 @@ __global__ __launch_bounds__(256) void reformat_filters_kernel(int Ko, int Ci, i
 {
     if (form_deselected(sel, 1, thr)) return;       // the copy of a form that will not run is not written
     reformat_filters_block(blockIdx.x, Ko, Ci, S, R, transpose, group, w, wd, total);
+}
+
+__global__ __launch_bounds__(256) void stage_filters_kernel(int Ko, int Ci, int S, int R, int transpose, const float *__restrict__ w,
+                                                            float *__restrict__ wd, size_t total, const unsigned *sel, unsigned thr)
+{
+    if (form_deselected(sel, 1, thr)) return;
+    stage_filters_block(blockIdx.x, Ko, Ci, S, R, transpose, w, wd, total);
 }
 
 __global__ __launch_bounds__(256) void pw_filters_kernel(int Ko, int Ci, int transpose, const float *__restrict__ w,
@@ -83,13 +91,72 @@ hipError_t launch_cfg(const Geom &g, const FlatGrid &fq, int cs, const float *in
     return launch_form<KQ, HPC, DEEP, MODE, false>(g, fq, cs, in, wd, out, parts, s);
 }
 
-// FWD at either stride and unit-stride BWI.  With whole column blocks the filters are requested three taps ahead at three
+template <int KQ, int HPC, int MODE>
+hipError_t launch_wide(const Geom &g, const FlatGrid &fq, int cs, const float *in, const float *wd, float *out, float *parts, hipStream_t s)
+{
+    const int kgroups = ceil_div(g.Ko, 32 * KQ);
+    const long long blocks = (long long)fq.tiles * kgroups;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks, cs);
+    const size_t stride = (size_t)g.N * g.Ko * g.Ho * g.Wo;
+    // (the shares of a channel split differ by one stage at most)
+    if (2 * ceil_div(g.Ci / kStageC, cs) <= kSplitApart)
+        hipLaunchKernelGGL((fwd_dense_wide_kernel<KQ, HPC, true, MODE>), grid, dim3(256), 0, s, g, in, wd, out, parts, fq, kgroups, cs, stride);
+    else
+        hipLaunchKernelGGL((fwd_dense_wide_kernel<KQ, HPC, false, MODE>), grid, dim3(256), 0, s, g, in, wd, out, parts, fq, kgroups, cs, stride);
+    return hipGetLastError();
+}
+
+int wide_column_blocks(const Geom &g) { return g.Ko > 64 ? 4 : 2; }
+
+template <int KQ, int HPC>
+FlatGrid wide_grid(const Geom &g)
+{
+    return flat_grid(g.N, g.Ho, g.Wo, g.sw, 3, 3, HPC, 0, WideLds<KQ, HPC>::PX);
+}
+
+// Workgroups of an unsplit launch, give or take the ragged ends of strips
+long long wide_blocks(const Geom &g)
+{
+    const int kq = wide_column_blocks(g), tile = kWavePx * (4 / kq);
+    return ((long long)g.N * g.Ho * g.Wo + tile - 1) / tile * ceil_div(g.Ko, 32 * kq);
+}
+
+// Shares of the stages of launches that would leave compute units idle
+int wide_channel_split(const Geom &g)
+{
+    if ((long long)g.N * g.Ho * g.Wo > 1 << 20) return 1;
+    const long long blocks = wide_blocks(g);
+    const int NS = g.Ci / kStageC;
+    int cs = 1;
+    while (cs < 8 && blocks * cs < 288 && cs < NS) ++cs;
+    // short shares (kSplitApart) of equal length where the chip takes them: the longest one has the largest error
+    if (2 * ceil_div(NS, cs) <= kSplitApart)
+        for (int c = cs; c <= 8 && blocks * c <= 512; ++c)
+            if (NS % c == 0) return c;
+    return cs;
+}
+
+int dense_channel_split(const Geom &g)
+{
+    if (pointwise(g)) return pw_channel_split(g);
+    return fwd_dense_wide(g) ? wide_channel_split(g) : dense_channel_split_blocks(g);
+}
+
+// FWD at either stride and unit-stride BWI.  16 channels at a time: with whole column blocks the filters are requested three taps ahead at three
 // wavefronts per SIMD instead of one tap at four (N = 32, us: 256->256 @56 541 -> 532, 512->512 @14 167 -> 158, one image
 // 512->512 @14 35 -> 30); with 64 produced channels, where that costs a third wavefront, it is 4 % slower.
 hipError_t launch_flat(const Geom &g, int cs, const float *in, const float *wd, float *out, float *parts, hipStream_t s)
 {
     int kq;
     long long blocks;
+    if (fwd_dense_wide(g)) {
+        if (g.sw == 2) return launch_wide<4, kWideHaloS2, 1>(g, wide_grid<4, kWideHaloS2>(g), cs, in, wd, out, parts, s);
+        if (wide_column_blocks(g) == 4) return launch_wide<4, kWideHalo, 0>(g, wide_grid<4, kWideHalo>(g), cs, in, wd, out, parts, s);
+        const FlatGrid q = wide_grid<2, kWideHalo2>(g), m = wide_grid<2, kWideHalo2Max>(g);
+        if (q.tiles * 10LL <= m.tiles * 11LL) return launch_wide<2, kWideHalo2, 0>(g, q, cs, in, wd, out, parts, s);
+        return launch_wide<2, kWideHalo2Max, 0>(g, m, cs, in, wd, out, parts, s);
+    }
     const FlatGrid q = dense_tiling(g, &kq, &blocks);
     if (g.sw == 2) return launch_cfg<4, kHaloS2, true, 1>(g, q, cs, in, wd, out, parts, s);
     if (kq == 4) return launch_cfg<4, kHalo, true, 0>(g, q, cs, in, wd, out, parts, s);
@@ -163,6 +230,21 @@ bool fwd_dense_supported(const Geom &g)
     return false;
 }
 
+// 32 channels at a time from 64 reduced channels on, where they come in whole 32s and the launch, its channels split if need be,
+// has a workgroup for every compute unit.  us, 16 channels at a time : 32 at a time (two wavefronts per SIMD instead of three or
+// four, so what comes before and after the channel loop is covered less): 64->128 @112, N = 32 285 : 268, 64->64 @224 577 : 552,
+// 96->48 @64 N = 16 38.2 : 35.0, but 16->128 @112 N = 16 53 : 77, 48->128 @56 40 : 44, 144->144 @56 136 : 145 (an odd last 16 as
+// pairs of taps), 96->32 @64 33.5 : 34.1, one image 512->512 @14 (128 workgroups) 29.5 : 30.0.  The BWI of stride-2 layers, with 1 to 4 taps
+// a stage, is the same either way (128->128 @56 55.0 : 55.2) and slower with odd blocks.  Short shares of unequal length would err
+// more than those of 16 channels at a time (320->96 @20x33, N = 4, seven shares: 1.07e-7 of the norm against 1.04e-7).
+bool fwd_dense_wide(const Geom &g)
+{
+    if (!fwd_dense_supported(g) || g.R != 3 || g.uw != 1 || g.Ci % kStageC != 0 || g.Ci < 2 * kStageC) return false;
+    if (g.Ko <= (g.sw == 2 ? 64 : 32)) return false;
+    const int cs = wide_channel_split(g), NS = g.Ci / kStageC;
+    return wide_blocks(g) * cs >= 256 && (NS % cs == 0 || 2 * ceil_div(NS, cs) > kSplitApart);
+}
+
 size_t fwd_dense_filter_bytes(const Geom &g)
 {
     // output channels padded to a multiple of 128 so that every column block a workgroup touches exists
@@ -191,17 +273,22 @@ hipError_t launch_reformat_filters(const Geom &g, bool transpose, const float *w
         return hipGetLastError();
     }
     const size_t total = fwd_dense_filter_bytes(g) / 48;                 // 8 elements per thread
+    if (fwd_dense_wide(g)) {
+        hipLaunchKernelGGL(stage_filters_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, g.Ko, g.Ci, g.S, g.R,
+                           transpose ? 1 : 0, w, wd, total, g.sel, g.thr);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(reformat_filters_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, g.Ko, g.Ci,
                        g.S, g.R, transpose ? 1 : 0, pointwise(g) ? pw_sign_group(g) : 1, w, wd, total, g.sel, g.thr);
     return hipGetLastError();
 }
 
-// Images a launch can take at once: its pixel numbers, and the samples of the images a 3x3 tile of 64 pixels can span
-// (strips are at least 7 pixels wide where images are), are kept in int
+// Images a launch can take at once: its pixel numbers, and the samples of the images a 3x3 tile of 64 pixels, or 128 with 33 to 64
+// produced channels, can span (strips are at least 7 pixels wide where images are), are kept in int
 int dense_images_per_launch(const Geom &g)
 {
     const long long px = (long long)g.Ho * g.Wo;
-    if (!pointwise(g) && (g.Ho / (g.uw == 2 ? 2 : 1) >= 10 ? 3LL : 66LL) * (g.Ci / kBlk) * g.Hi * g.Wi > 0x7fffffffLL) return 1;
+    if (!pointwise(g) && (g.Ho / (g.uw == 2 ? 2 : 1) >= 10 ? 3LL : g.Ko > 32 && g.Ko <= 64 ? 130LL : 66LL) * (g.Ci / kBlk) * g.Hi * g.Wi > 0x7fffffffLL) return 1;
     const long long n = 0x3fffffffLL / px;
     return n < 1 ? 1 : (n < g.N ? (int)n : g.N);
 }

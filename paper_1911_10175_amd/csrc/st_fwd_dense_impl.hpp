@@ -39,7 +39,7 @@ constexpr int kHalo = 160, kHaloS2 = 320;
 
 struct FlatGrid {
     int rows, cols;                         // output grid (of the parity class)
-    int strips, tpx;                        // vertical strips; pixels per tile (64, fewer where the halo would not fit)
+    int strips, tpx;                        // vertical strips; pixels per tile (fewer than asked for where the halo would not fit)
     int per_strip, tiles;                   // tiles of a strip, of all
 };
 
@@ -55,7 +55,7 @@ inline long long flat_halo(int N, int rows, int w, int tpx, int pstep, int nv, i
 
 // Strips and tile size for a grid: among strips of 7 to 16 pixels (or `width`, if given, or the whole row where it is
 // shorter) the one with the smallest halo.  N * rows * cols must fit an int.
-inline FlatGrid flat_grid(int N, int rows, int cols, int pstep, int nv, int nu, int cap, int width = 0)
+inline FlatGrid flat_grid(int N, int rows, int cols, int pstep, int nv, int nu, int cap, int width = 0, int px = kTilePx)
 {
     FlatGrid q;
     q.rows = rows; q.cols = cols; q.strips = 1; q.tpx = 0; q.per_strip = q.tiles = 0;
@@ -65,7 +65,7 @@ inline FlatGrid flat_grid(int N, int rows, int cols, int pstep, int nv, int nu, 
     for (int ns = lo; ns <= hi; ++ns) {
         if (ns > lo + 16) break;                                    // (rows of hundreds of pixels: enough choice)
         const int w = ceil_div(cols, ns), w1 = cols / ns;           // widths differ by at most one
-        int tpx = kTilePx;
+        int tpx = px;
         long long need;
         for (;; --tpx) {
             need = flat_halo(N, rows, w, tpx, pstep, nv, nu);
@@ -73,7 +73,7 @@ inline FlatGrid flat_grid(int N, int rows, int cols, int pstep, int nv, int nu, 
             if (n1 > need) need = n1;
             if (need <= cap || tpx == 1) break;
         }
-        const long long score = (long long)(kTilePx - tpx) * 100000 + need;         // whole tiles first, then the halo
+        const long long score = (long long)(px - tpx) * 100000 + need;         // whole tiles first, then the halo
         if (q.tpx == 0 || score < best) { best = score; q.strips = ns; q.tpx = tpx; }
     }
     q.per_strip = (int)(((long long)N * rows * ceil_div(cols, q.strips) + q.tpx - 1) / q.tpx);
@@ -372,9 +372,8 @@ inline long long dense_rect_blocks(const Geom &g, int *twd)
 // layers: a workgroup per 64 pixels and 128 output channels gives 100 workgroups for 512 -> 512 @7,
 // N = 32, each walking all 512 input channels): up to 8 shares of at least two channel blocks, enough for a
 // workgroup per compute unit and some.  Depends on the geometry only, so that the workspace query and the launch agree.
-inline int dense_channel_split(const Geom &g)
+inline int dense_channel_split_blocks(const Geom &g)
 {
-    if (g.R == 1) return pw_channel_split(g);
     if (g.uw != 1) return 1;
     int kq, twd;
     if (g.sw == 1 && dense_rect_blocks(g, &twd) >= 384) return 1;

@@ -202,6 +202,35 @@ def test_short_reductions_err_no_more_than_fp32_instructions(name, zeros):
         assert err <= (1.1 if p == "bww" else 1.05) * chain, f"{name} {p} {zeros}: {err:.3g}, fp32 instructions {chain:.3g}"
 
 
+WIDE = {
+    # 3x3 kernels that take 32 reduced channels at a time: 2, 3, 4 and 8 stages, split among workgroups and not, wavefronts without
+    # channels of their own (80, 48), tiles of 64 and 128 pixels with ragged ends, tiles over many images, the larger halo, stride 2
+    "64->80 33x31": Geom(8, 64, 80, 33, 31, 3, 3, 1, 1, 1, 1),
+    "96->144 @14": Geom(24, 96, 144, 14, 14, 3, 3, 1, 1, 1, 1),
+    "128->48 17x57": Geom(16, 128, 48, 17, 57, 3, 3, 1, 1, 1, 1),
+    "64->64 3x5": Geom(1100, 64, 64, 3, 5, 3, 3, 1, 1, 1, 1),
+    "128->128 @56": Geom(6, 128, 128, 56, 56, 3, 3, 1, 1, 1, 1),
+    "256->64 @28 pad 2": Geom(12, 256, 64, 28, 28, 3, 3, 1, 1, 2, 2),
+    "stride 2 128->96 45x27": Geom(16, 128, 96, 45, 27, 3, 3, 2, 2, 1, 1),
+}
+
+
+@pytest.mark.parametrize("value", [None, np.inf])
+@pytest.mark.parametrize("name", WIDE)
+def test_dense_forms_of_32_channels_at_a_time(name, value):
+    """Values of very different size side by side, or a few infinities: each output within the bound of an fp32 sum."""
+    g = WIDE[name]
+    x, w, dy = inputs(g, 37)
+    if value is None:
+        rng = np.random.default_rng(7)
+        for t in (x, w, dy):
+            t *= np.float32(2.0) ** rng.integers(-20, 21, t.shape).astype(np.float32)
+    else:
+        w[w == 0] = 0.25
+        x[-1, -1, -1, -1] = x[0, 17, 1, 2] = dy[0, 0, 0, 0] = value
+    check(g, x, w, dy, name)
+
+
 @pytest.mark.parametrize("name", ["fwd", "bwi"])
 def test_long_reductions_err_far_less_than_fp32_instructions(name):
     """2304 terms, reduced by one workgroup: a chain of fp32 multiply-adds rounds the running sum once per term, the dense form
