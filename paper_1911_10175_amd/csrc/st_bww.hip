@@ -480,9 +480,8 @@ __global__ __launch_bounds__(512, 4) void bww_sparse_either_kernel(BwwArgs A, Bw
 // Tiles have at most 32 pixels: 144 sums, two short accumulators, the operands of a tap and the next tile's loads then
 // fit the 256 registers of two wavefronts per SIMD, and two workgroups share a compute unit, so that one's staging
 // (two barriers per 108 matrix instructions of a wavefront) meets the other's arithmetic.  Measured (N = 32, the same
-// structure on v_mfma_f32_32x32x2_f32 and 98-pixel tiles -> now): 256->256 @56 987 -> 580 us (204 TFLOP/s), 512->512
-// @28 991 -> 650, 512->512 @14 268 -> 185, 128->128 @28 88 -> 64 (of which 20 are the sum of the partial gradients),
-// stride 2 128->128 @56 98 -> 82.
+// structure on v_mfma_f32_32x32x2_f32 and 98-pixel tiles -> now): stride 2 128->128 @56 98 -> 82 us.  (At unit stride, before the
+// kernel below, 256->256 @56 987 -> 554.)
 // ------------------------------------------------------------------------------------------
 template <int R, int S, int TH, int TW, int PSTEP>
 struct BwwDenseCfg {
@@ -728,6 +727,221 @@ __global__ __launch_bounds__(256, 2) void bww_dense_kernel(BwwArgs A, const floa
             for (int r = 0; r < 16; ++r) {
                 const int k = k32 + 8 * (r / 4) + 4 * half + r % 4;
                 if (k < A.K && !split_finite(*element(k, tap))) *element(k, tap) = acc[tap][r];
+            }
+    }
+}
+
+// The same for unit stride (the kernel above serves stride 2) with v_mfma_f32_16x16x32_bf16, 32 pixels (a whole tile) at a
+// time: it reaches 2050 TFLOP/s where 32x32x16 reaches 1760 (st_fwd_dense_wide.hpp), and its sum joins the running one once per
+// tile instead of once per 16 pixels.  A wavefront's 32 x 32 channels are 2 x 2 blocks of 16 x 16.  The registers are full (144 sums,
+// 16 of a tap, 48 operands, 24 of the next tile), so every x operand is read again for the next tap as soon as its last product
+// has been issued.  N = 32, us, 32x32x16 -> now (both with the final sum): 256->256 @56 554 -> 490 (242 TFLOP/s), 512->512 @28
+// 607 -> 542, @14 170 -> 154, 64->64 @224 614 -> 540, 128->128 @28 63.5 -> 61.6, one image 64->64 @14 14.4 -> 12.5; error against
+// 64 bits 2.55e-7 -> 1.86e-7, 2.72e-7 -> 2.03e-7, 1.46e-7 -> 1.15e-7, 2.62e-7 -> 1.95e-7, 9.3e-8 -> 8.2e-8, 4.5e-8 -> 3.8e-8.
+// Bound: power (see there) and, beside the products, splitting and stashing the next tile.
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+template <int R, int S, int TH, int TW, bool SHORT>
+__global__ __launch_bounds__(256, 2) void bww_dense_wide_kernel(BwwArgs A, const float *__restrict__ x,
+                                                                const float *__restrict__ dy, float *__restrict__ part)
+{
+    using Cfg = BwwDenseCfg<R, S, TH, TW, 1>;
+    if (deselected(A.sel, A.want)) return;              // uniform over the grid, before any barrier
+    constexpr int HW = Cfg::Halo::HW, HP = Cfg::Halo::HP, TP = Cfg::TP, P = 32, XB = Cfg::XB, DB = Cfg::DB;
+    static_assert(Cfg::P == P, "a tile is one step");
+    __shared__ __attribute__((aligned(16))) char lds[2 * Cfg::LDS];     // tiles take turns
+
+    // the wavefront index is the same in every lane: kept in a scalar register, and with it every tile coordinate
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+    const int l16 = lane % 16, grp = lane / 16;
+    const int kh = wave % 2, ch = wave / 2;
+    const int split = blockIdx.x;
+    const int kt = blockIdx.y / A.cgroups, cg = blockIdx.y % A.cgroups;
+    const int CB = A.C / kBlk, KB = A.K / kBlk;
+    const bool active = kt * 64 + kh * 32 < A.K && cg * 64 + ch * 32 < A.C;
+
+    floatx4 acc[S * R][2][2];                           // [tap][16 k][16 c]
+#pragma unroll
+    for (int t = 0; t < S * R; ++t)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) acc[t][kb][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    const int u0 = (int)((long long)A.units * split / A.splits);
+    const int u1 = (int)((long long)A.units * (split + 1) / A.splits);
+
+    // staging as above: asked for while the previous tile is being multiplied, split and written to LDS after it, into the other
+    // buffer: one barrier a tile (256->256 @56 502 -> 490; a piece after each of the last taps has no registers, 76 spilled, 514)
+    constexpr int ND = (P * 16 + 255) / 256, NXH = (HP * 16 + 255) / 256;
+    float4 sd[ND], sx[NXH];
+    auto fetch = [&](int unit) __attribute__((always_inline)) {
+        int t = unit;
+        const int tw = t % A.tiles_w; t /= A.tiles_w;
+        const int th = t % A.tiles_h;
+        const int n = t / A.tiles_h;
+        const int oh0 = th * TH, ow0 = tw * TW, ih0 = oh0 - A.ph, iw0 = ow0 - A.pw;
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+#pragma unroll
+        for (int i = 0; i < ND; ++i) {
+            const int idx = tid + i * 256;
+            const int pix = idx >> 4, q = idx & 15;
+            const int oh = oh0 + pix / TW, ow = ow0 + pix % TW;
+            const int kb = kt * 4 + (q >> 2);
+            sd[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (pix < TP && oh < A.OH && ow < A.OW && kb < KB)
+                sd[i] = *reinterpret_cast<const float4 *>(dy + act_off(n, kb, oh, ow, KB, A.OH, A.OW) + (q & 3) * 4);
+        }
+#pragma unroll
+        for (int i = 0; i < NXH; ++i) {
+            const int idx = tid + i * 256;
+            const int pix = idx >> 4, q = idx & 15;
+            const int ih = ih0 + pix / HW, iw = iw0 + pix % HW;
+            const int cb = cg * 4 + (q >> 2);
+            sx[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (pix < HP && ih >= 0 && ih < A.H && iw >= 0 && iw < A.W && cb < CB)
+                sx[i] = *reinterpret_cast<const float4 *>(x + act_off(n, cb, ih, iw, CB, A.H, A.W) + (q & 3) * 4);
+        }
+    };
+    // every other tile is added up with the opposite sign (its dy negated, its sum subtracted), as every other step is above
+    auto sign = [&](int unit) __attribute__((always_inline)) { return unit % 2 ? -1.f : 1.f; };
+    auto stash = [&](int unit, char *buf) __attribute__((always_inline)) {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+#pragma unroll
+        for (int i = 0; i < ND + NXH; ++i) {
+            const bool isx = i >= ND;
+            const int idx = tid + (isx ? i - ND : i) * 256, pix = idx >> 4, q = idx & 15, bytes = isx ? XB : DB;
+            if (pix >= (isx ? HP : P)) continue;
+            bf16x4 p[3];
+            split4(isx ? sx[isx ? i - ND : 0] : sd[isx ? 0 : i], isx ? kSplitScale : sign(unit) * kSplitScale, p);
+            char *dst = buf + (isx ? 6 * DB : 0) + (q >> 3) * bytes + pix * 64 + (q & 7) * 8;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) *reinterpret_cast<bf16x4 *>(dst + j * 2 * bytes) = p[j];
+        }
+    };
+
+    // operands: lane l takes channel l % 16 of a block and pixels 8*(l/16) .. +7 of the tile, four per transposing read, for which
+    // it supplies the address of 8 bytes of pixel (l % 16) / 4 of the four
+    int dp, xp[2];
+    {
+        const int px = grp * 8 + l16 / 4, chan = l16 % 4 * 8;
+        dp = kh * DB + px * 64 + chan;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int p = min(px + i * 4, TP - 1);              // (the padding's dy is zero)
+            xp[i] = 6 * DB + ch * XB + (p / TW * HW + p % TW) * 64 + chan;
+        }
+    }
+
+    fetch(u0);                                               // (a split has at least one tile)
+    stash(u0, lds);
+    __syncthreads();
+    for (int unit = u0; unit < u1; ++unit) {
+        char *const buf = lds + (unit - u0) % 2 * Cfg::LDS;
+        if (unit + 1 < u1) fetch(unit + 1);                  // in flight during this tile's MFMAs
+        if (active) {
+            const float sg = sign(unit);
+            auto at = [&](int offset) __attribute__((always_inline)) { return (LdsTr)(buf + offset); };
+            bf16x8 d[3][2];
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) d[q][kb] = split_tr_read(at(dp + q * 2 * DB + kb * 32), at(dp + q * 2 * DB + kb * 32 + 256));
+            auto input = [&](int tap, int q, bf16x8 (&f)[2]) __attribute__((always_inline)) {
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb) {
+                    const int off = q * 2 * XB + (tap / R * HW + tap % R) * 64 + cb * 32;
+                    f[cb] = split_tr_read(at(xp[0] + off), at(xp[1] + off));
+                }
+            };
+            bf16x8 f[3][2];
+            input(0, 2, f[2]);
+            input(0, 1, f[1]);
+            input(0, 0, f[0]);
+            static_for<0, S * R>([&](auto T) __attribute__((always_inline)) {
+                constexpr int tap = decltype(T)::value;
+                constexpr bool last = tap + 1 == S * R;
+                floatx4 t[2][2];
+                auto mul = [&](int qd, int qf, bool first) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                        for (int cb = 0; cb < 2; ++cb)
+                            t[kb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d[qd][kb], f[qf][cb], first ? floatx4{0.f, 0.f, 0.f, 0.f} : t[kb][cb], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                // the small products first: beside the leading pieces' only their sum is rounded
+                if constexpr (SHORT) {                              // two of the products usually left out
+                    mul(1, 2, true);
+                    mul(2, 1, false);
+                }
+                mul(0, 2, !SHORT);
+                if constexpr (!last) input(tap + 1, 2, f[2]);
+                mul(1, 1, false);
+                mul(0, 1, false);
+                if constexpr (!last) input(tap + 1, 1, f[1]);
+                mul(2, 0, false);
+                mul(1, 0, false);
+                // (SHORT: the two meet in an fp32 addition, as above)
+                if constexpr (SHORT) {
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                        for (int cb = 0; cb < 2; ++cb)
+                            t[kb][cb] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(d[0][kb], f[0][cb], floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                } else {
+                    mul(0, 0, false);
+                }
+                if constexpr (!last) input(tap + 1, 0, f[0]);
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) acc[tap][kb][cb][r] = __builtin_fmaf(t[kb][cb][r], sg, acc[tap][kb][cb][r]);
+            });
+        }
+        if (unit + 1 == u1) break;
+        stash(unit + 1, lds + (unit + 1 - u0) % 2 * Cfg::LDS);
+        __syncthreads();
+    }
+    if (!active) return;
+
+    // D layout of a 16x16 block: column (c) = lane % 16, row (k) = 4*(lane/16) + r: four consecutive output channels, one 16-byte store,
+    // the lanes' side by side
+    const int k32 = kt * 64 + kh * 32, c32 = cg * 64 + ch * 32;
+    float *pbase = part + (size_t)split * A.K * A.C * (S * R);
+    auto element = [&](int k, int c, int tap) __attribute__((always_inline)) {
+        return pbase + (((size_t)(k / kBlk) * CB + c / kBlk) * (S * R) + tap) * (kBlk * kBlk) + (c % kBlk) * kBlk + k % kBlk;
+    };
+    bool finite = true;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+            const int k = k32 + kb * 16 + 4 * grp, c = c32 + cb * 16 + l16;
+            if (k >= A.K || c >= A.C) continue;
+#pragma unroll
+            for (int tap = 0; tap < S * R; ++tap) {
+                const floatx4 a = acc[tap][kb][cb];
+                const float4 v = make_float4(a[0] * kSplitUnscale, a[1] * kSplitUnscale, a[2] * kSplitUnscale, a[3] * kSplitUnscale);
+                finite = finite && split_finite(v);
+                *reinterpret_cast<float4 *>(element(k, c, tap)) = v;
+            }
+        }
+    // sums that values outside the range of the scaled pieces took part in
+    if (__builtin_expect(__ballot(!finite) != 0, 0)) {
+        floatx16 redo[S * R];
+        bww_redo<R, S, TH, TW, 1>(A, x, dy, k32, c32, u0, u1, redo);
+        const int c = c32 + lane % 32;
+        if (c >= A.C) return;
+#pragma unroll
+        for (int tap = 0; tap < S * R; ++tap)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int k = k32 + 8 * (r / 4) + 4 * (lane / 32) + r % 4;
+                if (k < A.K && !split_finite(*element(k, c, tap))) *element(k, c, tap) = redo[tap][r];
             }
     }
 }
@@ -1323,6 +1537,15 @@ BwwArgs dense_args(const st_conv_desc &d)
     return A;
 }
 
+template <int TH, int TW>
+void launch_bww_dense_wide(const BwwArgs &A, const float *x, const float *dy, float *part, hipStream_t s)
+{
+    const dim3 grid(A.splits, ceil_div(A.K, 64) * A.cgroups);
+    if (A.units <= kBwwShortUnits && A.units <= 2 * A.splits)
+        hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, true>), grid, dim3(256), 0, s, A, x, dy, part);
+    else hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, false>), grid, dim3(256), 0, s, A, x, dy, part);
+}
+
 template <int TH, int TW, int PSTEP>
 void launch_bww_dense_tiles(const BwwArgs &A, const float *x, const float *dy, float *part, hipStream_t s)
 {
@@ -1336,8 +1559,8 @@ void launch_bww_dense_tiles(const BwwArgs &A, const float *x, const float *dy, f
 hipError_t launch_bww_dense_3x3(const st_conv_desc &d, const BwwArgs &A, const float *x, const float *dy, float *part, hipStream_t s)
 {
     if (bww_s2(d)) launch_bww_dense_tiles<kDenseS2TH, kDenseS2TW, 2>(A, x, dy, part, s);
-    else if (dense_wide(d)) launch_bww_dense_tiles<kDenseWideTH, kDenseWideTW, 1>(A, x, dy, part, s);
-    else launch_bww_dense_tiles<kDenseTH, kDenseTW, 1>(A, x, dy, part, s);
+    else if (dense_wide(d)) launch_bww_dense_wide<kDenseWideTH, kDenseWideTW>(A, x, dy, part, s);
+    else launch_bww_dense_wide<kDenseTH, kDenseTW>(A, x, dy, part, s);
     return hipGetLastError();
 }
 
