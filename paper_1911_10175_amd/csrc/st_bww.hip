@@ -1697,7 +1697,8 @@ hipError_t launch_pw_sparse(const st_conv_desc &d, const st_conv_desc &e, const 
 // name of the kernel instance launch_bww_sparse runs for d (requires bww_fast_supported(d))
 void bww_sparse_kernel_name(const st_conv_desc &d, char *buf, size_t len)
 {
-    if (d.R == 1) snprintf(buf, len, "pw_bww_sparse_kernel<%d>", pw_kpl(d));
+    if (bww_direct(d)) snprintf(buf, len, "bww_direct_kernel<%d>", d.R);
+    else if (d.R == 1) snprintf(buf, len, "pw_bww_sparse_kernel<%d>", pw_kpl(d));
     else if (bww_s2(d)) snprintf(buf, len, "bww_sparse_kernel<3, 3, %d, %d, 1>", kSparseS2TH, kSparseS2TW);
     else snprintf(buf, len, "bww_sparse_kernel<3, 3, %d, %d, 0>", kSparseTH, kSparseTW);
 }
@@ -1705,6 +1706,7 @@ void bww_sparse_kernel_name(const st_conv_desc &d, char *buf, size_t len)
 hipError_t launch_bww_sparse(const st_conv_desc &d, const float *x, const float *dy, float *dw,
                              float *ws, hipStream_t s, const unsigned *sel)
 {
+    if (!sel && bww_direct(d)) return launch_bww_direct(d, x, dy, dw, 0, nullptr, s);
     if (d.R == 1) return launch_pw_sparse(d, d, x, dy, dw, ws, false, s, sel);
     BwwArgs A = sparse_args(d);
     A.sel = sel; A.want = 0;
@@ -1761,6 +1763,7 @@ size_t bww_sparse_dy_workspace(const st_conv_desc &d)
 hipError_t launch_bww_sparse_dy(const st_conv_desc &d, const float *x, const float *dy, float *dw,
                                 float *ws, hipStream_t s, const unsigned *sel)
 {
+    if (!sel && bww_direct(d)) return launch_bww_direct(d, x, dy, dw, 1, nullptr, s);
     if (bww_s2(d)) {
         BwwArgs A = make_args_s2_dy(d);
         A.sel = sel; A.want = 1; A.swapped = 1;
@@ -1801,19 +1804,25 @@ hipError_t launch_bww_auto_merged(const st_conv_desc &d, const float *x, const f
     BwwArgs A2 = dense_args(d);
     A0.sel = A1.sel = A2.sel = sel;
     A0.want = kEitherOperand; A1.want = kEitherOperand; A1.swapped = 1; A2.want = 2;
-    const int ygroups = ceil_div(d.K, 64) * ceil_div(d.C, 64);      // the same for both operand roles
-    dim3 grid(A0.splits > A1.splits ? A0.splits : A1.splits, ygroups);
-    hipError_t err = allow_dynamic_lds<bww_sparse_either_kernel<3, 3, kSparseTH, kSparseTW>>(kSparseLds);
-    if (err != hipSuccess) return err;
-    hipLaunchKernelGGL((bww_sparse_either_kernel<3, 3, kSparseTH, kSparseTW>), grid, dim3(512), kSparseLds, s, A0, A1, x, dy, ws);
-    err = hipGetLastError();
-    if (err != hipSuccess) return err;
+    const bool direct = bww_direct(d);                              // small layers: writes dw itself
+    hipError_t err;
+    if (direct) {
+        if ((err = launch_bww_direct(d, x, dy, dw, 0, sel, s)) != hipSuccess) return err;
+    } else {
+        const int ygroups = ceil_div(d.K, 64) * ceil_div(d.C, 64);  // the same for both operand roles
+        dim3 grid(A0.splits > A1.splits ? A0.splits : A1.splits, ygroups);
+        err = allow_dynamic_lds<bww_sparse_either_kernel<3, 3, kSparseTH, kSparseTW>>(kSparseLds);
+        if (err != hipSuccess) return err;
+        hipLaunchKernelGGL((bww_sparse_either_kernel<3, 3, kSparseTH, kSparseTW>), grid, dim3(512), kSparseLds, s, A0, A1, x, dy, ws);
+        err = hipGetLastError();
+        if (err != hipSuccess) return err;
+    }
     if ((err = launch_bww_dense_3x3(d, A2, x, dy, ws, s)) != hipSuccess) return err;
     const size_t n4 = (size_t)d.K * d.C * d.S * d.R / 4;
     const size_t nblk = (n4 + 63) / 64;
     Splits3 sp = {{A0.splits, A1.splits, A2.splits}};
     hipLaunchKernelGGL(bww_reduce_kernel, dim3((unsigned)(nblk < kReduceGrid ? nblk : kReduceGrid)), dim3(1024), 0, s,
-                       reinterpret_cast<const float4 *>(ws), reinterpret_cast<float4 *>(dw), n4, sp, sel, kAnyForm);
+                       reinterpret_cast<const float4 *>(ws), reinterpret_cast<float4 *>(dw), n4, sp, sel, direct ? 2 : kAnyForm);
     return hipGetLastError();
 }
 

@@ -183,6 +183,13 @@ bool pw_small(const Geom &g);
 hipError_t launch_pw_small(const Geom &g, const float *in, const float *wd, float *out, hipStream_t s);
 int pw_sign_group(const Geom &g);
 
+// small unit-stride layers: the zero-skipping forms in one launch on the library's layouts (st_direct.hip); the launchers of
+// these forms go there by themselves.  bww: want = 0 tests x, 1 tests dy; sel set: whichever is selected, none for the dense form
+bool fwd_direct(const Geom &g);
+hipError_t launch_fwd_direct(const Geom &g, const float *in, float *out, hipStream_t s);
+bool bww_direct(const st_conv_desc &d);
+hipError_t launch_bww_direct(const st_conv_desc &d, const float *x, const float *dy, float *dw, int want, const unsigned *sel, hipStream_t s);
+
 bool bww_fast_supported(const st_conv_desc &d);
 size_t bww_sparse_workspace(const st_conv_desc &d);
 hipError_t launch_bww_sparse(const st_conv_desc &d, const float *x, const float *dy, float *dw,

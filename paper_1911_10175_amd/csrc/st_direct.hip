@@ -1,0 +1,250 @@
+// Zero-skipping FWD / BWI and BWW of small unit-stride 3x3 and 1x1 layers, each in one launch on the library's own layouts.
+//
+// The tiled kernels (st_fwd_sparse_impl.hpp, st_bww.hip) walk a tile's channels or pixels one after the other, read the filters
+// from a copy that a launch of its own writes, and leave partial gradients to another launch.  Where a layer has little work, their time
+// is these launches and that walk.  Here a lane takes one produced channel (FWD / BWI) or one output channel (BWW) and four
+// tested channels, requests everything a step needs at once, and skips the products of a zero by a lane-wise select; nothing is staged.
+// The price is a load for every 3 to 8 multiply-adds and two to three instructions for each of them: the work limits are below.
+#include <cstdio>
+
+#include "st_common.hpp"
+
+namespace st {
+namespace {
+
+constexpr int kRun = 4;                                 // neighbouring pixels of a row a wavefront takes together
+static __device__ __attribute__((aligned(16))) float kDirectZeros[4] = {0.f, 0.f, 0.f, 0.f};    // source of padding
+
+// ROWS x COLS samples from (ih0, iw0) of image n on, four channels of block cb; zeros outside the image
+template <int ROWS, int COLS>
+__device__ __forceinline__ void direct_window(const float *__restrict__ in, int n, int cb, int CB, int H, int W, int ih0, int iw0, int c4,
+                                              float4 (&x)[ROWS][COLS])
+{
+#pragma unroll
+    for (int v = 0; v < ROWS; ++v)
+#pragma unroll
+        for (int j = 0; j < COLS; ++j) {
+            const int ih = ih0 + v, iw = iw0 + j;
+            const bool ok = ih >= 0 && ih < H && iw >= 0 && iw < W;         // (the same in every lane)
+            x[v][j] = *reinterpret_cast<const float4 *>(ok ? in + act_off(n, cb, ih, iw, CB, H, W) + c4 : kDirectZeros);
+        }
+}
+
+__device__ __forceinline__ float direct_lane(const float4 &v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
+
+// FWD, or BWI with the roles of the channels exchanged and the taps reversed (WT).  Workgroup = 16 produced channels x one run of
+// pixels, its NW wavefronts share the blocks of the reduced channels; lane = produced channel lane % 16, reduced
+// channels 4 * (lane / 16) .. +3 of a block.
+template <int R, bool WT, int NW>
+__global__ __launch_bounds__(64 * NW) void fwd_direct_kernel(Geom g, const float *__restrict__ in, const float *__restrict__ w,
+                                                             float *__restrict__ out, int runs)
+{
+    if (form_deselected(g.sel, 0, g.thr)) return;
+    constexpr int T = R * R;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave, k = lane % 16, grp = lane / 16;
+    const int KoB = g.Ko / kBlk, CiB = g.Ci / kBlk;
+    const int kb = blockIdx.x % KoB, run = blockIdx.x / KoB;
+    const int ow0 = run % runs * kRun, oh = run / runs % g.Ho, n = run / runs / g.Ho;
+
+    float acc[2][kRun];                                 // (two chains a pixel)
+#pragma unroll
+    for (int p = 0; p < kRun; ++p) acc[0][p] = acc[1][p] = 0.f;
+#pragma unroll 1
+    for (int cb = CiB * wave / NW; cb < CiB * (wave + 1) / NW; ++cb) {
+        float4 x[R][kRun + R - 1], f[T];                // f: the four channels of each tap
+        direct_window<R, kRun + R - 1>(in, n, cb, CiB, g.Hi, g.Wi, oh - g.ph, ow0 - g.pw, 4 * grp, x);
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            if constexpr (WT) {
+                f[t] = *reinterpret_cast<const float4 *>(w + (((size_t)cb * KoB + kb) * T + (T - 1 - t)) * (kBlk * kBlk) + k * kBlk + 4 * grp);
+            } else {
+                const float *p = w + (((size_t)kb * CiB + cb) * T + t) * (kBlk * kBlk) + 4 * grp * kBlk + k;
+                f[t] = make_float4(p[0], p[kBlk], p[2 * kBlk], p[3 * kBlk]);
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < R; ++v)
+#pragma unroll
+            for (int j = 0; j < kRun + R - 1; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float xv = direct_lane(x[v][j], i);
+                    const bool nz = xv != 0.f;
+#pragma unroll
+                    for (int u = 0; u < R; ++u)
+                        if (j - u >= 0 && j - u < kRun)
+                            acc[i % 2][j - u] = __builtin_fmaf(xv, nz ? direct_lane(f[v * R + u], i) : 0.f, acc[i % 2][j - u]);
+                }
+    }
+    // the four channel groups of the wavefront, then the wavefronts, in 64 bits (with many zeros the chains are short and these
+    // sums would round as often); lane group p stores pixel p
+    double mine = 0.;
+#pragma unroll
+    for (int p = 0; p < kRun; ++p) {
+        double s = (double)acc[0][p] + (double)acc[1][p];
+        s += __shfl_xor(s, 16);
+        s += __shfl_xor(s, 32);
+        mine = grp == p ? s : mine;
+    }
+    if constexpr (NW > 1) {
+        __shared__ double red[NW][kWave];
+        red[wave][lane] = mine;
+        __syncthreads();
+        if (wave != 0) return;
+        mine = red[0][lane];
+#pragma unroll
+        for (int q = 1; q < NW; ++q) mine += red[q][lane];
+    }
+    if (ow0 + grp < g.Wo) out[act_off(n, kb, oh, ow0 + grp, KoB, g.Ho, g.Wo) + k] = (float)mine;
+}
+
+// BWW: workgroup = 16 x 16 channels and one row of taps (blockIdx.y); its eight wavefronts share the runs of pixels of the minibatch, the
+// next run's operands in flight during a run.  Lane = output channel lane % 16, input channels 4 * (lane / 16) .. +3.  want: 0 tests
+// x, 1 tests dy; with sel set whichever the sampled counts select.
+struct DirectBww {
+    int N, C, K, H, W, OH, OW, ph, pw;
+    const unsigned *sel;
+    int want;
+};
+constexpr int kBwwWaves = 8;
+
+template <int R>
+__global__ __launch_bounds__(64 * kBwwWaves) void bww_direct_kernel(DirectBww a, const float *__restrict__ x, const float *__restrict__ dy,
+                                                                    float *__restrict__ dw)
+{
+    int form = a.want;
+    if (a.sel) {
+        form = selected_form(a.sel);
+        if (form == 2) return;                          // uniform over the grid, before any barrier
+    }
+    __shared__ double red[kBwwWaves][R * 4][kWave];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave, k = lane % 16, grp = lane / 16;
+    const int CB = a.C / kBlk, KB = a.K / kBlk, kb = blockIdx.x / CB, cb = blockIdx.x % CB, v = blockIdx.y;
+    const int rpr = (a.OW + kRun - 1) / kRun, runs = a.N * a.OH * rpr;
+
+    // in 64 bits: with many zeros an element has one or two products, and eight wavefronts' sums to add up (16->16 @8, 85 % zeros: error 3.3e-8
+    // of the norm with 32-bit sums, 3.2e-8 in the tiled form); the launch waits for memory
+    double acc[R][4];
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[u][i] = 0.;
+    float4 xw[2][1][kRun + R - 1];
+    float d[2][kRun];
+    auto request = [&](int run, int slot) __attribute__((always_inline)) {
+        const int ow0 = run % rpr * kRun, oh = run / rpr % a.OH, n = run / rpr / a.OH;
+        direct_window<1, kRun + R - 1>(x, n, cb, CB, a.H, a.W, oh - a.ph + v, ow0 - a.pw, 4 * grp, xw[slot]);
+        const float *dp = dy + act_off(n, kb, oh, ow0, KB, a.OH, a.OW) + k;
+#pragma unroll
+        for (int p = 0; p < kRun; ++p) d[slot][p] = dp[ow0 + p < a.OW ? p * kBlk : 0];
+    };
+    auto add = [&](int run, int slot) __attribute__((always_inline)) {
+        const int np = min(a.OW - run % rpr * kRun, kRun);
+#pragma unroll
+        for (int p = 0; p < kRun; ++p) {
+            if (p >= np) break;                         // (the same in every lane)
+            const float dv = d[slot][p];
+            if (form == 0) {
+#pragma unroll
+                for (int u = 0; u < R; ++u)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float xv = direct_lane(xw[slot][0][p + u], i);
+                        acc[u][i] = __builtin_fma((double)xv, (double)(xv != 0.f ? dv : 0.f), acc[u][i]);
+                    }
+            } else {
+                const bool nz = dv != 0.f;
+#pragma unroll
+                for (int u = 0; u < R; ++u)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[u][i] = __builtin_fma((double)(nz ? direct_lane(xw[slot][0][p + u], i) : 0.f), (double)dv, acc[u][i]);
+            }
+        }
+    };
+    if (wave < runs) request(wave, 0);
+#pragma unroll 1
+    for (int run = wave; run < runs; run += 2 * kBwwWaves) {
+        if (run + kBwwWaves < runs) request(run + kBwwWaves, 1);
+        add(run, 0);
+        if (run + 2 * kBwwWaves < runs) request(run + 2 * kBwwWaves, 0);
+        if (run + kBwwWaves < runs) add(run + kBwwWaves, 1);
+    }
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) red[wave][u * 4 + i][lane] = acc[u][i];
+    __syncthreads();
+    float *o = dw + (((size_t)kb * CB + cb) * R + v) * R * (kBlk * kBlk);
+    for (int e = threadIdx.x; e < R * kBlk * kBlk; e += 64 * kBwwWaves) {
+        const int u = e / (kBlk * kBlk), c = e / kBlk % kBlk, row = u * 4 + c % 4, col = c / 4 * 16 + e % kBlk;
+        double s = 0.;
+#pragma unroll
+        for (int q = 0; q < kBwwWaves; ++q) s += red[q][row][col];
+        o[e] = (float)s;
+    }
+}
+
+template <int R, bool WT, int NW>
+hipError_t launch_fwd(const Geom &g, const float *in, float *out, hipStream_t s)
+{
+    const int runs = ceil_div(g.Wo, kRun);
+    if (g.describe) {
+        snprintf(g.describe, (size_t)g.describe_len, "fwd_direct_kernel<%d, %s, %d>", R, WT ? "true" : "false", NW);
+        return hipSuccess;
+    }
+    hipLaunchKernelGGL((fwd_direct_kernel<R, WT, NW>), dim3((unsigned)((long long)g.N * g.Ho * runs * (g.Ko / kBlk))), dim3(64 * NW), 0, s, g, in, g.w, out, runs);
+    return hipGetLastError();
+}
+
+template <int R, bool WT>
+hipError_t launch_fwd(const Geom &g, const float *in, float *out, hipStream_t s)
+{
+    const int CiB = g.Ci / kBlk;
+    if (CiB >= 16) return launch_fwd<R, WT, 16>(g, in, out, s);
+    if (CiB >= 8) return launch_fwd<R, WT, 8>(g, in, out, s);
+    if (CiB >= 4) return launch_fwd<R, WT, 4>(g, in, out, s);
+    if (CiB >= 2) return launch_fwd<R, WT, 2>(g, in, out, s);
+    return launch_fwd<R, WT, 1>(g, in, out, s);
+}
+
+}  // namespace
+
+// Up to 120 million multiply-adds before skipping (3x3), 25 million (1x1, where a load feeds fewer of them): this form needs about
+// 6 us and 0.12 us (0.3) for every million, whatever the zeros; the other has its launches and its channel walk.  At 50 / 90 % zeros : here,
+// us per call (8 of them are what a call from Python takes): 16->16 @8 15.0 / - : 8.4, 64->64 @28 24.8 / - : 8.3, 256->256 @7 40.7 / - :
+// 8.2, 64->64 @56 (116 M) 24.8 / 21.8 : 16.3, 512->512 @7 (116 M) 66.5 / 52.9 : 21, but 64->64 @28 N = 8 (231 M) 26.4 / 20.9 : 27.5, 64->64 @112 (462 M)
+// 39.8 / 28.2 : 49; 1x1 64->256 @28 (13 M) 14.8 / - : 8.3, 512->2048 @7 (51 M) 45 / - : 12, but 64->256 @56 N = 8 (411 M) 28.7 / 24.6 : 138.
+bool fwd_direct(const Geom &g)
+{
+    if (!fwd_sparse_supported(g) || g.sw != 1 || g.uw != 1) return false;
+    return (double)g.N * g.Ho * g.Wo * g.Ko * g.Ci * g.R * g.S <= (g.R == 1 ? 25e6 : 120e6);
+}
+
+hipError_t launch_fwd_direct(const Geom &g, const float *in, float *out, hipStream_t s)
+{
+    if (g.R == 3) return g.wt ? launch_fwd<3, true>(g, in, out, s) : launch_fwd<3, false>(g, in, out, s);
+    return g.wt ? launch_fwd<1, true>(g, in, out, s) : launch_fwd<1, false>(g, in, out, s);
+}
+
+// One workgroup for each compute unit and up to 56 runs of pixels (3x3), 64 (1x1), 0.8 us for every eight.  The other form leaves partial
+// gradients to a second launch.  50 / 90 % zeros : here, us: 16->16 @8 17.8 / 13.6 : 8.3, 64->64 @8x16 - / 15.8 : 9.9, @14 (56 runs) 19.7 /
+// 15.9 : 15.2, 128->128 @14 (192 workgroups) 20.6 / 17.0 : 15.6; 1x1 256->256 @10 N = 2 (256, 60 runs) 13.7 / 12.5 : 10.1; but 256->256 @7 (768
+// workgroups) 16.3 / 12.6 : 16.3, and beyond 56 runs (with 32-bit sums, a quarter faster) 16->16 @20 (100) 18.9 / 14.8 : 17.7, 64->64 @28 (196)
+// 20.4 / 16.9 : 33.
+bool bww_direct(const st_conv_desc &d)
+{
+    if (!bww_fast_supported(d) || !bww_dy_fast_supported(d) || d.stride_w != 1) return false;
+    const int oh = d.H + 2 * d.pad_h - d.S + 1, ow = d.W + 2 * d.pad_w - d.R + 1;
+    return (double)(d.C / kBlk) * (d.K / kBlk) * d.S <= 256 && (double)d.N * oh * ceil_div(ow, kRun) <= (d.R == 1 ? 64 : 56);
+}
+
+hipError_t launch_bww_direct(const st_conv_desc &d, const float *x, const float *dy, float *dw, int want, const unsigned *sel, hipStream_t s)
+{
+    const DirectBww a = {d.N, d.C, d.K, d.H, d.W, d.H + 2 * d.pad_h - d.S + 1, d.W + 2 * d.pad_w - d.R + 1, d.pad_h, d.pad_w, sel, want};
+    const dim3 grid((unsigned)(d.C / kBlk) * (d.K / kBlk), d.S);
+    if (d.R == 3) hipLaunchKernelGGL(bww_direct_kernel<3>, grid, dim3(64 * kBwwWaves), 0, s, a, x, dy, dw);
+    else hipLaunchKernelGGL(bww_direct_kernel<1>, grid, dim3(64 * kBwwWaves), 0, s, a, x, dy, dw);
+    return hipGetLastError();
+}
+
+}  // namespace st

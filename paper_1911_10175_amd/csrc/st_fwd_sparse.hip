@@ -93,6 +93,7 @@ hipError_t launch_wave_filters(const Geom &g, bool transpose, const float *w, fl
 {
     const int KB = (transpose ? g.Ci : g.Ko) / kBlk, CB = (transpose ? g.Ko : g.Ci) / kBlk;     // of the layer
     const long long blocks = (long long)KB * CB;
+    if (fwd_direct(g)) return hipSuccess;               // reads the layer's filters themselves
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const int paired = fwd_sparse_filters_paired(g) ? 1 : 0;
     if (transpose)
@@ -112,6 +113,7 @@ bool fwd_sparse_filters_paired(const Geom &g)
 
 hipError_t launch_fwd_sparse(const Geom &g, const float *in, const float *f, float *out, hipStream_t s)
 {
+    if (fwd_direct(g)) return launch_fwd_direct(g, in, out, s);
     if (g.sw == 2) return fs::launch_s2_fwd(g, in, f, out, s);
     if (g.uw == 2) return fs::launch_s2_bwi(g, in, f, out, s);
     if (g.R == 3 && g.S == 3) {

@@ -288,7 +288,7 @@ hipError_t launch_auto_prepare(const Geom &g, bool transpose, const float *act, 
     a.S = g.S; a.R = g.R; a.Ko = g.Ko; a.Ci = g.Ci; a.transpose = transpose ? 1 : 0;
     a.paired = fwd_sparse_filters_paired(g) ? 1 : 0;
     a.wide = fwd_dense_wide(g) ? 1 : 0;
-    const long long n_wave = (long long)a.KB * a.CB;
+    const long long n_wave = fwd_direct(g) ? 0 : (long long)a.KB * a.CB;
     a.total_dense = fwd_dense_filter_bytes(g) / 48;
     const long long n_dense = (long long)((a.total_dense + 255) / 256);
     if (n_wave + n_dense + kSampleParts > 0x7fffffffLL) return hipErrorInvalidValue;

@@ -1,15 +1,17 @@
 """Zero-skipping launches with few tiles: the wavefronts of a workgroup share a tile's input channels, also shares that
 are no whole channel blocks.  Every test here needs an MI355X."""
+import numpy as np
 import pytest
 import torch
 
 import stgen
+from oracle import st_ref
 from oracle.st_ref import Geom
 
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
-    from tests.gpu_harness import check_all_passes_full
+    from tests.gpu_harness import DeviceLayer, check_all_passes_full
 
 # channel counts around the shares of 8 and 16 wavefronts: two channels each, uneven ones, one block split over several
 # shares, shares that end inside a block; 1x1 with fewer, as many and more blocks than shares; stride 2
@@ -27,3 +29,40 @@ def test_channel_shares_of_small_launches(g, dead):
     if dead:
         x, dy = stgen.dead_channels(x, dead, 408), stgen.dead_channels(dy, dead, 409)
     check_all_passes_full(g, x, w, dy, "shares", variants=(False,))
+
+
+# the kernels of small unit-stride layers: every number of wavefronts that share the channel blocks (1, 2, 3, 5, 9 and 17 of them), rows that
+# are no multiple of four pixels, padding 0 to 2, several images, 1x1; then layers just above their limits
+DIRECT = [Geom(1, 16, 16, 1, 1, 3, 3, 1, 1, 1, 1), Geom(1, 16, 32, 3, 4, 3, 3, 1, 1, 0, 0), Geom(2, 32, 16, 5, 7, 3, 3, 1, 1, 2, 2),
+          Geom(3, 48, 80, 4, 6, 3, 3, 1, 1, 1, 0), Geom(1, 80, 48, 9, 5, 3, 3, 1, 1, 1, 1), Geom(1, 144, 272, 6, 6, 3, 3, 1, 1, 1, 1),
+          Geom(1, 272, 144, 5, 9, 3, 3, 1, 1, 1, 1), Geom(1, 16, 16, 7, 3, 1, 1), Geom(2, 272, 80, 3, 5, 1, 1), Geom(1, 48, 144, 1, 13, 1, 1),
+          Geom(1, 64, 64, 16, 16, 3, 3, 1, 1, 1, 1), Geom(1, 64, 64, 16, 17, 3, 3, 1, 1, 1, 1), Geom(2, 192, 192, 14, 13, 3, 3, 1, 1, 1, 1),
+          Geom(1, 512, 64, 27, 29, 1, 1)]
+
+
+@pytest.mark.parametrize("g", DIRECT, ids=[f"{g.R}x{g.S} {g.N}x{g.C}to{g.K} {g.H}x{g.W} pad {g.pad_h}" for g in DIRECT])
+def test_small_layers_in_one_launch(g):
+    """All zero-skipping passes, either operand tested in BWW, against the oracle; an infinite filter or sample behind zeros is never
+    multiplied."""
+    x = stgen.relu_sparse(g.x_shape, 0.5, 414)
+    w = stgen.he_normal(g.w_shape, 415)
+    dy = stgen.bernoulli_masked(g.y_shape, 0.5, 416, 417)
+    check_all_passes_full(g, x, w, dy, "direct", variants=(False,))
+    L = DeviceLayer(g, x, None, dy)
+    ref, ref_abs = st_ref.conv_bww(g, x, dy)
+    got = L.bww("dy")
+    assert np.all(np.abs(got - ref) <= 1e-6 * ref_abs)
+    x[:, 3], dy[:, 5] = 0.0, 0.0
+    bad = w.copy()
+    bad[:, 3] = np.inf
+    assert np.array_equal(DeviceLayer(g, x, bad, None).fwd(False), DeviceLayer(g, x, w, None).fwd(False))
+    bad = w.copy()
+    bad[5] = np.inf
+    assert np.array_equal(DeviceLayer(g, None, bad, dy).bwi(False), DeviceLayer(g, None, w, dy).bwi(False))
+    # BWW: zeros in the tested operand meet infinities in the other
+    bad = np.zeros_like(dy)
+    bad[:, 7] = np.inf
+    only = np.zeros_like(x)
+    assert not DeviceLayer(g, only, None, bad).bww(False).any()
+    bad = np.full_like(x, np.inf)
+    assert not DeviceLayer(g, bad, None, np.zeros_like(dy)).bww("dy").any()
