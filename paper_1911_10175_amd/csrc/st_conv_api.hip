@@ -307,13 +307,17 @@ st_status run_bww_auto(const st_conv_desc *d, const float *x, const float *dy, f
     hipStream_t s = static_cast<hipStream_t>(stream);
     unsigned *sel = static_cast<unsigned *>(ws);
     float *part = reinterpret_cast<float *>(static_cast<char *>(ws) + kCounterBytes);
-    // Stride-2 3x3 layers: x has four times the elements of dy and each feeds 2.25 taps on average
+    // Stride-2 3x3 layers, unsampled: x has four times the elements of dy and each feeds 2.25 taps on average
     // (Sec. 3.3 of the paper), so of the two zero-skipping forms the dy-testing one is the faster whatever the
-    // two sparsities (132 us with no zeros in dy against 157 us with 90 % zeros in x on 256->256 @28); it is
-    // taken without sampling.  The dense form is not a candidate here, although on 128->128 @56 it takes 78 us
-    // against 98 at 50 % zeros.
-    if (d->stride_w == 2 && d->stride_h == 2 && st::bww_dy_fast_supported(*d))
+    // two sparsities (132 us with no zeros in dy against 157 us with 90 % zeros in x on 256->256 @28).  From 750 million
+    // multiply-adds on the dense form is faster than that as well (us, dy-testing at 50 or 30 / 90 % zeros in dy : dense: 128->128
+    // @56 N = 32 103 / 84 : 78, 512->512 @14 108 / 90 : 85, 64->64 @56 55 / 50.5 : 40.5, 96->160 @33x41 N = 16, the smallest, 59 /
+    // 46 : 44); in smaller launches its shorter tiles leave more partial gradients (64->64 @56 N = 8 31.5 / 28.1 : 32.8, 256->256
+    // @28 N = 1 25.6 / 23.7 : 27).
+    if (d->stride_w == 2 && d->stride_h == 2 && st::bww_dy_fast_supported(*d)) {
+        if ((double)d->N * o.OH * o.OW * d->C * d->K * d->R * d->S >= 750e6) return dev(st::launch_bww_dense(*d, x, dy, dw, part, s));
         return dev(st::launch_bww_sparse_dy(*d, x, dy, dw, part, s));
+    }
     const size_t nx = (size_t)d->N * d->C * d->H * d->W, ny = (size_t)d->N * d->K * o.OH * o.OW;
     // the dense form takes part in the choice where tiled kernels exist for all three
     const bool tiled = st::bww_fast_supported(*d) && st::bww_dy_fast_supported(*d);

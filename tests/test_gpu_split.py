@@ -342,3 +342,14 @@ def test_bww_auto_takes_the_faster_form_of_launches_bound_by_partial_gradients(g
     got = L.bww("auto", raw=True)
     assert torch.equal(got, L.bww(form, raw=True))
     assert not torch.equal(got, L.bww(not form, raw=True)), "forms indistinguishable: test is void"
+
+
+@pytest.mark.parametrize("g,form", [(Geom(8, 64, 64, 56, 56, 3, 3, 2, 2, 1, 1), "dy"), (Geom(15, 96, 160, 33, 41, 3, 3, 2, 2, 1, 1), "dy"),
+                                    (Geom(16, 96, 160, 33, 41, 3, 3, 2, 2, 1, 1), True)], ids=lambda v: f"{v.N}x{v.C}to{v.K}" if isinstance(v, Geom) else "")
+def test_bww_auto_of_stride_2_layers(g, form):
+    """Bit for bit the dense form from 750 million multiply-adds on (740 and 790 million here), the dy-testing one below."""
+    x, w, dy = inputs(g, 43)
+    L = DeviceLayer(g, x, None, dy)
+    got = L.bww("auto", raw=True)
+    assert torch.equal(got, L.bww(form, raw=True))
+    assert not torch.equal(got, L.bww("dy" if form is True else True, raw=True)), "forms indistinguishable: test is void"
