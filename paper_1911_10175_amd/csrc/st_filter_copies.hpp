@@ -140,8 +140,8 @@ __device__ __forceinline__ void reformat_filters_block(size_t block, int Ko, int
 }
 
 // The same for the 3x3 kernel that takes 32 reduced channels at a time and 16 produced ones (Ci a multiple of 32): [Ko/32][Ci/32][tap]
-// [3 pieces][2 halves of the 32 k][4 groups of 8 c][16 k][8 c] bf16; every second 32 reduced channels are negated.
-__device__ __forceinline__ void stage_filters_block(size_t block, int Ko, int Ci, int S, int R, int transpose, const float *__restrict__ w,
+// [3 pieces][2 halves of the 32 k][4 groups of 8 c][16 k][8 c] bf16; every second group of 32 * `group` reduced channels is negated.
+__device__ __forceinline__ void stage_filters_block(size_t block, int Ko, int Ci, int S, int R, int transpose, int group, const float *__restrict__ w,
                                                     float *__restrict__ wd, size_t total)
 {
     const size_t i = block * 256 + threadIdx.x;
@@ -169,7 +169,7 @@ __device__ __forceinline__ void stage_filters_block(size_t block, int Ko, int Ci
             hi = p[1];
         }
     }
-    const float scale = st % 2 ? -kSplitScale : kSplitScale;
+    const float scale = st / group % 2 ? -kSplitScale : kSplitScale;
     bf16x4 a[3], b[3];
     split4(lo, scale, a);
     split4(hi, scale, b);

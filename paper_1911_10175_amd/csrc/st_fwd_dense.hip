@@ -40,11 +40,11 @@ __global__ __launch_bounds__(256) void reformat_filters_kernel(int Ko, int Ci, i
     reformat_filters_block(blockIdx.x, Ko, Ci, S, R, transpose, group, w, wd, total);
 }
 
-__global__ __launch_bounds__(256) void stage_filters_kernel(int Ko, int Ci, int S, int R, int transpose, const float *__restrict__ w,
+__global__ __launch_bounds__(256) void stage_filters_kernel(int Ko, int Ci, int S, int R, int transpose, int group, const float *__restrict__ w,
                                                             float *__restrict__ wd, size_t total, const unsigned *sel, unsigned thr)
 {
     if (form_deselected(sel, 1, thr)) return;
-    stage_filters_block(blockIdx.x, Ko, Ci, S, R, transpose, w, wd, total);
+    stage_filters_block(blockIdx.x, Ko, Ci, S, R, transpose, group, w, wd, total);
 }
 
 __global__ __launch_bounds__(256) void pw_filters_kernel(int Ko, int Ci, int transpose, const float *__restrict__ w,
@@ -273,9 +273,9 @@ hipError_t launch_reformat_filters(const Geom &g, bool transpose, const float *w
         return hipGetLastError();
     }
     const size_t total = fwd_dense_filter_bytes(g) / 48;                 // 8 elements per thread
-    if (fwd_dense_wide(g)) {
+    if (fwd_dense_wide(g) || pw_wide(g)) {
         hipLaunchKernelGGL(stage_filters_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, g.Ko, g.Ci, g.S, g.R,
-                           transpose ? 1 : 0, w, wd, total, g.sel, g.thr);
+                           transpose ? 1 : 0, pointwise(g) ? 2 : 1, w, wd, total, g.sel, g.thr);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(reformat_filters_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, g.Ko, g.Ci,

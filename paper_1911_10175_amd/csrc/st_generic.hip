@@ -209,7 +209,7 @@ __global__ __launch_bounds__(256) void auto_prepare_kernel(PrepareArgs a)
         if (a.transpose) wave_filters_block<true>((int)(b - kSampleParts), a.KB, a.CB, a.S, a.R, a.w, a.wl, tile, a.paired);
         else wave_filters_block<false>((int)(b - kSampleParts), a.KB, a.CB, a.S, a.R, a.w, a.wl, tile, a.paired);
     } else {
-        if (a.wide) stage_filters_block(b - kSampleParts - a.n_wave, a.Ko, a.Ci, a.S, a.R, a.transpose, a.w, a.wd, a.total_dense);
+        if (a.wide) stage_filters_block(b - kSampleParts - a.n_wave, a.Ko, a.Ci, a.S, a.R, a.transpose, 1, a.w, a.wd, a.total_dense);
         else reformat_filters_block(b - kSampleParts - a.n_wave, a.Ko, a.Ci, a.S, a.R, a.transpose, 1, a.w, a.wd, a.total_dense);
     }
 }

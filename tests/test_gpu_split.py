@@ -203,7 +203,7 @@ def test_short_reductions_err_no_more_than_fp32_instructions(name, zeros):
 
 
 WIDE = {
-    # 3x3 kernels that take 32 reduced channels at a time: 2, 3, 4 and 8 stages, split among workgroups and not, wavefronts without
+    # kernels that take 32 reduced channels at a time, 3x3: 2, 3, 4 and 8 stages, split among workgroups and not, wavefronts without
     # channels of their own (80, 48), tiles of 64 and 128 pixels with ragged ends, tiles over many images, the larger halo, stride 2
     "64->80 33x31": Geom(8, 64, 80, 33, 31, 3, 3, 1, 1, 1, 1),
     "96->144 @14": Geom(24, 96, 144, 14, 14, 3, 3, 1, 1, 1, 1),
@@ -212,6 +212,12 @@ WIDE = {
     "128->128 @56": Geom(6, 128, 128, 56, 56, 3, 3, 1, 1, 1, 1),
     "256->64 @28 pad 2": Geom(12, 256, 64, 28, 28, 3, 3, 1, 1, 2, 2),
     "stride 2 128->96 45x27": Geom(16, 128, 96, 45, 27, 3, 3, 2, 2, 1, 1),
+    # 1x1 kernel: 1, 2, 3 and 8 stages of 64 channels, split and not, wavefronts without channels, ragged ends of the pixel numbering
+    "1x1 64->128": Geom(4, 64, 128, 47, 45, 1, 1),
+    "1x1 128->160": Geom(3, 128, 160, 41, 43, 1, 1),
+    "1x1 192->144": Geom(4, 192, 144, 37, 29, 1, 1),
+    "1x1 512->272 split": Geom(2, 512, 272, 39, 41, 1, 1),
+    "1x1 1024->256 split, few workgroups": Geom(1, 1024, 256, 47, 45, 1, 1),
 }
 
 
