@@ -56,18 +56,27 @@ __global__ __launch_bounds__(256) void pw_filters_kernel(int Ko, int Ci, int tra
 
 bool pointwise(const Geom &g) { return g.R == 1 && g.S == 1; }      // served by the pixel-wise kernels (st_pw_dense.hip)
 
-// out += part[0] + part[1] + ... (splits - 1 of them, in that order), float4 at a time, on a capped grid
+// out += part[0] + part[1] + ... (splits - 1 of them, in that order, in 64 bits), float4 at a time, on a capped grid; eight loads in flight
+// (one after the other they cost a round trip each), four where there are no more
+template <int BATCH>
 __global__ __launch_bounds__(256) void sum_partials_kernel(const float4 *__restrict__ part, float4 *__restrict__ out,
                                                            size_t n4, int splits, const unsigned *sel, unsigned thr)
 {
     if (form_deselected(sel, 1, thr)) return;
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 256) {
-        float4 a = out[i];
-        for (int p = 1; p < splits; ++p) {
-            const float4 v = part[(size_t)(p - 1) * n4 + i];
-            a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
+        const float4 a = out[i];
+        double x = a.x, y = a.y, z = a.z, w = a.w;
+        for (int p = 1; p < splits; p += BATCH) {
+            float4 v[BATCH];
+#pragma unroll
+            for (int b = 0; b < BATCH; ++b) v[b] = part[(size_t)(min(p + b, splits - 1) - 1) * n4 + i];
+#pragma unroll
+            for (int b = 0; b < BATCH; ++b) {
+                const bool in = p + b < splits;
+                x += in ? v[b].x : 0.f; y += in ? v[b].y : 0.f; z += in ? v[b].z : 0.f; w += in ? v[b].w : 0.f;
+            }
         }
-        out[i] = a;
+        out[i] = make_float4((float)x, (float)y, (float)z, (float)w);
     }
 }
 
@@ -129,10 +138,10 @@ int wide_channel_split(const Geom &g)
     const long long blocks = wide_blocks(g);
     const int NS = g.Ci / kStageC;
     int cs = 1;
-    while (cs < 8 && blocks * cs < 288 && cs < NS) ++cs;
+    while (cs < kMaxShares && blocks * cs < 288 && cs < NS) ++cs;
     // short shares (kSplitApart) of equal length where the chip takes them: the longest one has the largest error
     if (2 * ceil_div(NS, cs) <= kSplitApart)
-        for (int c = cs; c <= 8 && blocks * c <= 512; ++c)
+        for (int c = cs; c <= kMaxShares && blocks * c <= 512; ++c)
             if (NS % c == 0) return c;
     return cs;
 }
@@ -310,8 +319,11 @@ hipError_t launch_fwd_dense(const Geom &g, const float *in, const float *wd, flo
     }
     if (cs == 1) return hipSuccess;
     const size_t n4 = (size_t)g.N * g.Ko * g.Ho * g.Wo / 4;
-    hipLaunchKernelGGL(sum_partials_kernel, dim3((unsigned)(n4 / 256 + 1 < 1024 ? n4 / 256 + 1 : 1024)), dim3(256), 0, s,
-                       reinterpret_cast<const float4 *>(parts), reinterpret_cast<float4 *>(out), n4, cs, g.sel, g.thr);
+    const dim3 grid((unsigned)(n4 / 256 + 1 < 1024 ? n4 / 256 + 1 : 1024));
+    const float4 *p4 = reinterpret_cast<const float4 *>(parts);
+    float4 *o4 = reinterpret_cast<float4 *>(out);
+    if (cs <= 5) hipLaunchKernelGGL(sum_partials_kernel<4>, grid, dim3(256), 0, s, p4, o4, n4, cs, g.sel, g.thr);
+    else hipLaunchKernelGGL(sum_partials_kernel<8>, grid, dim3(256), 0, s, p4, o4, n4, cs, g.sel, g.thr);
     return hipGetLastError();
 }
 

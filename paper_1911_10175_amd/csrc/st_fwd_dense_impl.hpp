@@ -370,8 +370,12 @@ inline long long dense_rect_blocks(const Geom &g, int *twd)
 
 // Channel split of the 3x3 launches that would leave most of the chip idle (7x7 and 14x14
 // layers: a workgroup per 64 pixels and 128 output channels gives 100 workgroups for 512 -> 512 @7,
-// N = 32, each walking all 512 input channels): up to 8 shares of at least two channel blocks, enough for a
-// workgroup per compute unit and some.  Depends on the geometry only, so that the workspace query and the launch agree.
+// N = 32, each walking all 512 input channels): up to 16 shares, enough for a workgroup per compute unit and some.  A block costs about 2.5 us in a launch that leaves compute units idle, a share its partial output: shares
+// of two blocks at least (10 blocks, 160->160 @20 N = 2: five shares 16.4 us, ten 17.4; 8 blocks, 128->128 @56 N = 1: four 17.8, six
+// 22.4), of one where there are fewer than eight blocks, if two of two can be had at all (5 blocks, 80->48 @37x53 N = 3: two shares 22.6, five 18.7; 7
+// blocks, 112->48 @40 N = 2: three 19.8, seven 15.5).  Sixteen shares of one image 512->512 @14 24.6 us, eight 29.5.  Depends on
+// the geometry only, so that the workspace query and the launch agree.
+constexpr int kMaxShares = 16;
 inline int dense_channel_split_blocks(const Geom &g)
 {
     if (g.uw != 1) return 1;
@@ -382,7 +386,9 @@ inline int dense_channel_split_blocks(const Geom &g)
     dense_tiling(g, &kq, &blocks);
     const int CiB = g.Ci / kBlk;
     int cs = 1;
-    while (cs < 8 && blocks * cs < 288 && CiB / (cs + 1) >= 2) ++cs;
+    while (cs < kMaxShares && blocks * cs < 288 && CiB / (cs + 1) >= (cs == 1 || CiB >= 8 ? 2 : 1)) ++cs;
+    // (more than eight only as far as they shorten the longest one: 25 blocks, 400->400 @11x17 N = 1, eight 28.4, nine 25.6, twelve 29.6)
+    while (cs > 8 && ceil_div(CiB, cs - 1) == ceil_div(CiB, cs)) --cs;
     return cs;
 }
 
