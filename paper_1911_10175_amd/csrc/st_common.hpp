@@ -183,7 +183,7 @@ bool pw_small(const Geom &g);
 hipError_t launch_pw_small(const Geom &g, const float *in, const float *wd, float *out, hipStream_t s);
 int pw_sign_group(const Geom &g);
 // 1x1 layers whose dense form takes 32 channels at a time (not those that pw_small or pw_dense_direct_supported name); their filter copy is
-// stage_filters_block's with stages of 64 channels
+// stage_filters_block's, in stages of 64 channels (more than 64 produced ones) or 32
 bool pw_wide(const Geom &g);
 
 // small unit-stride layers: the zero-skipping forms in one launch on the library's layouts (st_direct.hip); the launchers of

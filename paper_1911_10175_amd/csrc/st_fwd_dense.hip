@@ -284,7 +284,7 @@ hipError_t launch_reformat_filters(const Geom &g, bool transpose, const float *w
     const size_t total = fwd_dense_filter_bytes(g) / 48;                 // 8 elements per thread
     if (fwd_dense_wide(g) || pw_wide(g)) {
         hipLaunchKernelGGL(stage_filters_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, g.Ko, g.Ci, g.S, g.R,
-                           transpose ? 1 : 0, pointwise(g) ? 2 : 1, w, wd, total, g.sel, g.thr);
+                           transpose ? 1 : 0, pointwise(g) && g.Ko > 64 ? 2 : 1, w, wd, total, g.sel, g.thr);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(reformat_filters_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, g.Ko, g.Ci,

@@ -220,9 +220,8 @@ __global__ __launch_bounds__(256, (PwCfg<KQ>::MINW)) void pw_dense_kernel(Geom g
     }
 }
 
-// The same with v_mfma_f32_16x16x32_bf16 (2050 TFLOP/s against 1760, st_fwd_dense_wide.hpp) for layers with more than 64 produced channels
-// and whole stages of 64 reduced ones: a stage is two steps of 32 channels, a wavefront's 64 pixels x 32 channels are 4 x 2 blocks
-// of 16 x 16.  Two LDS buffers: the next stage is split and written while the current one is multiplied, one barrier a stage.
+// The same with v_mfma_f32_16x16x32_bf16 (2050 TFLOP/s against 1760, st_fwd_dense_wide.hpp), 32 reduced channels a step; a
+// wavefront's 64 pixels x 32 channels are 4 x 2 blocks of 16 x 16.  Two LDS buffers: the next stage is split and written while the current one is multiplied, one barrier a stage.
 // Each step has an accumulator of its own, the small products first, so only the four roundings of the leading pieces' sums and the
 // join count (error of the norm, half zeros, 16 channels at a time or, below 128 workgroups, fp32 instructions -> now: 192->144
 // 1.04e-7 -> 6.0e-8, 1024->512 4.0e-7 -> 8.0e-8, 2048->512 5.7e-7 -> 1.02e-7).
@@ -230,13 +229,14 @@ constexpr int kPwWideC = 64;
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 // APART: the form of short reductions (kSplitApart1x1), the leading pieces' products straight on the sum.
-template <bool APART>
+// KQ = 4: 64 pixels x 128 produced channels and stages of 64 reduced ones; KQ = 2: 128 x 64, stages of 32.
+template <int KQ, bool APART>
 __global__ __launch_bounds__(256, 2) void pw_dense_wide_kernel(Geom g, const float *__restrict__ in, const float *__restrict__ wd,
                                                                float *__restrict__ out, float *__restrict__ parts, int kgroups,
                                                                int csplit, size_t part_stride)
 {
     if (form_deselected(g.sel, 1, g.thr)) return;
-    constexpr int SB = kPwWideC / kBlk, BUF = SB * kPwPx * 24;      // channel blocks of a stage; floats of a buffer
+    constexpr int TQ = 4 / KQ, PX = TQ * kPwPx, SB = KQ, STEPS = SB / 2, BUF = SB * PX * 24;  // channel blocks of a stage; floats of a buffer
     __shared__ __attribute__((aligned(16))) float lds[2 * BUF];     // [step][piece][4 groups of 8 channels][pixel][8 channels] bf16
 
     // the wavefront index is the same in every lane: kept in a scalar register, and with it every tile coordinate
@@ -244,13 +244,14 @@ __global__ __launch_bounds__(256, 2) void pw_dense_wide_kernel(Geom g, const flo
     const int l16 = lane % 16, grp = lane / 16;
     const int kg = blockIdx.x % kgroups, tile = blockIdx.x / kgroups;
     const int CiB = g.Ci / kBlk, KoB = g.Ko / kBlk, HW = g.Ho * g.Wo, npx = g.N * HW;
-    const int q0 = tile * kPwPx;                        // (the host keeps npx + a tile in int range)
+    const int kqi = wave % KQ, tqi = wave / KQ;
+    const int q0 = tile * PX, qs = q0 + tqi * kPwPx;    // (the host keeps npx + a tile in int range)
     // shares of the channel split are whole stages; share 0 writes the output, the others partial outputs
     const int NST = CiB / SB, cshare = blockIdx.y;
     const int st0 = NST * cshare / csplit, st1 = NST * (cshare + 1) / csplit;
     if (cshare > 0) out = parts + (cshare - 1) * part_stride;
-    const int kb32 = kg * 4 + wave;                     // this wavefront's column block
-    const bool active = kb32 * 32 < g.Ko;
+    const int kb32 = kg * KQ + kqi;                     // this wavefront's column block
+    const bool active = kb32 * 32 < g.Ko && qs < npx;
 
     floatx4 acc[2][4], part[2][4];
 #pragma unroll
@@ -259,34 +260,45 @@ __global__ __launch_bounds__(256, 2) void pw_dense_wide_kernel(Geom g, const flo
         for (int pb = 0; pb < 4; ++pb) acc[kb][pb] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     // filters: 16-byte unit (kb32 * steps + step)*384 + piece*128 + kb*64 + lane of the copy
-    const bf16x8 *bbase = reinterpret_cast<const bf16x8 *>(wd) + (size_t)(active ? kb32 : 0) * NST * 2 * 384;
+    const bf16x8 *bbase = reinterpret_cast<const bf16x8 *>(wd) + (size_t)(active ? kb32 : 0) * NST * STEPS * 384;
     auto filters = [&](int step, int q, bf16x8 (&f)[2]) __attribute__((always_inline)) {
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) f[kb] = (bbase + (size_t)step * 384 + q * 128 + kb * 64)[lane];
     };
 
-    // staging: a lane's pieces are one quarter of its pixel's channels in each block of the stage; pixels past the end are zeros
-    const int sq = threadIdx.x % 4, spx = threadIdx.x / 4, q = q0 + spx;
-    const float *src = q < npx ? in + ((size_t)(q / HW) * CiB * HW + q % HW) * kBlk + sq * 4 : kPwZeros;
-    const size_t plane = q < npx ? (size_t)HW * kBlk : 0;
-    float4 hreg[SB];
+    // staging: a lane's pieces are one quarter of its TQ pixels' channels in each block of the stage; pixels past the end are zeros
+    const int sq = threadIdx.x % 4, spx = threadIdx.x / 4;
+    const float *src[TQ];
+    size_t plane[TQ];
+#pragma unroll
+    for (int i = 0; i < TQ; ++i) {
+        const int q = q0 + i * kPwPx + spx;
+        src[i] = q < npx ? in + ((size_t)(q / HW) * CiB * HW + q % HW) * kBlk + sq * 4 : kPwZeros;
+        plane[i] = q < npx ? (size_t)HW * kBlk : 0;
+    }
+    float4 hreg[SB][TQ];
     auto fetch = [&](int st) __attribute__((always_inline)) {
 #pragma unroll
-        for (int b = 0; b < SB; ++b) hreg[b] = *reinterpret_cast<const float4 *>(src + (size_t)(st * SB + b) * plane);
+        for (int b = 0; b < SB; ++b)
+#pragma unroll
+            for (int i = 0; i < TQ; ++i) hreg[b][i] = *reinterpret_cast<const float4 *>(src[i] + (size_t)(st * SB + b) * plane[i]);
     };
     auto stash1 = [&](int st, int b) __attribute__((always_inline)) {
-        bf16x4 p[3];
-        split4(hreg[b], kSplitScale, p);
-        bf16x4 *dst = reinterpret_cast<bf16x4 *>(lds + (st - st0) % 2 * BUF) + ((b / 2 * 12 + b % 2 * 2 + sq / 2) * kPwPx + spx) * 2 + sq % 2;
 #pragma unroll
-        for (int i = 0; i < 3; ++i) dst[i * (8 * kPwPx)] = p[i];
+        for (int i = 0; i < TQ; ++i) {
+            bf16x4 p[3];
+            split4(hreg[b][i], kSplitScale, p);
+            bf16x4 *dst = reinterpret_cast<bf16x4 *>(lds + (st - st0) % 2 * BUF) + ((b / 2 * 12 + b % 2 * 2 + sq / 2) * PX + i * kPwPx + spx) * 2 + sq % 2;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) dst[q * (8 * PX)] = p[q];
+        }
     };
 
     fetch(st0);
     bf16x8 f0[2], f1[2], f2[2];
-    filters(st0 * 2, 0, f0);
-    filters(st0 * 2, 1, f1);
-    filters(st0 * 2, 2, f2);
+    filters(st0 * STEPS, 0, f0);
+    filters(st0 * STEPS, 1, f1);
+    filters(st0 * STEPS, 2, f2);
 #pragma unroll
     for (int b = 0; b < SB; ++b) stash1(st0, b);
     __syncthreads();
@@ -295,18 +307,19 @@ __global__ __launch_bounds__(256, 2) void pw_dense_wide_kernel(Geom g, const flo
         constexpr bool more = decltype(More)::value;
         if constexpr (more) fetch(st + 1);
         if (active) {
-            const bf16x8 *xin = reinterpret_cast<const bf16x8 *>(lds + (st - st0) % 2 * BUF) + grp * kPwPx + l16;
+            const bf16x8 *xin = reinterpret_cast<const bf16x8 *>(lds + (st - st0) % 2 * BUF) + grp * PX + tqi * kPwPx + l16;
             auto input = [&](int step, int piece, bf16x8 (&x)[4]) __attribute__((always_inline)) {
 #pragma unroll
-                for (int pb = 0; pb < 4; ++pb) x[pb] = xin[(step * 3 + piece) * (4 * kPwPx) + pb * 16];
+                for (int pb = 0; pb < 4; ++pb) x[pb] = xin[(step * 3 + piece) * (4 * PX) + pb * 16];
             };
             bf16x8 x0[4], x1[4], x2[4];
             input(0, 2, x2);
             input(0, 1, x1);
             input(0, 0, x0);
-            static_for<0, 2>([&](auto T) __attribute__((always_inline)) {
+            static_for<0, STEPS>([&](auto T) __attribute__((always_inline)) {
                 constexpr int sub = decltype(T)::value;
-                const int next = sub == 0 || more ? st * 2 + sub + 1 : st * 2 + sub;
+                constexpr bool last = sub + 1 == STEPS;
+                const int next = st * STEPS + sub + (!last || more ? 1 : 0);
                 auto mul = [&](const bf16x8 (&f)[2], const bf16x8 (&x)[4], floatx4 (&to)[2][4], bool first) __attribute__((always_inline)) {
 #pragma unroll
                     for (int kb = 0; kb < 2; ++kb)
@@ -318,25 +331,25 @@ __global__ __launch_bounds__(256, 2) void pw_dense_wide_kernel(Geom g, const flo
                 bf16x8 f0n[2];
                 filters(next, 0, f0n);
                 mul(f0, x2, part, !APART || sub == 0);
-                if constexpr (sub == 0) input(1, 2, x2);
+                if constexpr (!last) input(sub + 1, 2, x2);
                 mul(f1, x1, part, false);
                 mul(f0, x1, part, false);
-                if constexpr (sub == 0) input(1, 1, x1);
+                if constexpr (!last) input(sub + 1, 1, x1);
                 mul(f2, x0, part, false);
                 filters(next, 2, f2);
                 mul(f1, x0, part, false);
                 filters(next, 1, f1);
                 mul(f0, x0, APART ? acc : part, false);
-                if constexpr (sub == 0) input(1, 0, x0);
+                if constexpr (!last) input(sub + 1, 0, x0);
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb) f0[kb] = f0n[kb];
                 if constexpr (more) { stash1(st + 1, 2 * sub); stash1(st + 1, 2 * sub + 1); }
                 // joined; after the stage's last step the sum changes sign: odd stages have their filters negated
-                if constexpr (!APART || sub == 1) {
+                if constexpr (!APART || last) {
 #pragma unroll
                     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                        for (int pb = 0; pb < 4; ++pb) acc[kb][pb] = sub == 0 ? acc[kb][pb] + part[kb][pb] : -acc[kb][pb] - part[kb][pb];
+                        for (int pb = 0; pb < 4; ++pb) acc[kb][pb] = !last ? acc[kb][pb] + part[kb][pb] : -acc[kb][pb] - part[kb][pb];
                 }
                 __builtin_amdgcn_sched_barrier(0);
             });
@@ -355,7 +368,7 @@ __global__ __launch_bounds__(256, 2) void pw_dense_wide_kernel(Geom g, const flo
     bool finite[2] = {true, true};
 #pragma unroll
     for (int pb = 0; pb < 4; ++pb) {
-        const int p = q0 + pb * 16 + l16;
+        const int p = qs + pb * 16 + l16;
         if (p >= npx) continue;
         float *o = out + ((size_t)(p / HW) * KoB * HW + p % HW) * kBlk + 4 * grp;
 #pragma unroll
@@ -372,13 +385,32 @@ __global__ __launch_bounds__(256, 2) void pw_dense_wide_kernel(Geom g, const flo
 #pragma unroll 1
         for (int pb = 0; pb < 2; ++pb) {
             if (__ballot(!finite[pb]) == 0) continue;
-            const int p = q0 + pb * 32 + lane % 32, r = p % HW;
+            const int p = qs + pb * 32 + lane % 32, r = p % HW;
             split_redo_corr(g, in, out, p < npx, p / HW, r / g.Wo, r % g.Wo, kb32, st0 * SB, st1 * SB);
         }
     }
 }
 
 inline int pw_column_blocks(const Geom &g) { return g.Ko > 64 ? 4 : (g.Ko > 32 ? 2 : 1); }
+
+template <int KQ>
+hipError_t launch_pw_wide(const Geom &g, int cs, const float *in, const float *wd, float *out, float *parts, hipStream_t s)
+{
+    constexpr int PX = kPwPx * (4 / KQ), SB = KQ;
+    const long long tiles = ((long long)g.N * g.Ho * g.Wo + PX - 1) / PX;
+    const int kgroups = ceil_div(g.Ko, 32 * KQ);
+    const long long blocks = tiles * kgroups;
+    if (blocks > 0x7fffffffLL || tiles * PX > 0x7fff0000LL) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks, cs);
+    const size_t stride = (size_t)g.N * g.Ko * g.Ho * g.Wo;
+    if constexpr (KQ == 4)
+        if (ceil_div(g.Ci / kPwWideC, cs) * SB <= kSplitApart1x1) {
+            hipLaunchKernelGGL((pw_dense_wide_kernel<KQ, true>), grid, dim3(256), 0, s, g, in, wd, out, parts, kgroups, cs, stride);
+            return hipGetLastError();
+        }
+    hipLaunchKernelGGL((pw_dense_wide_kernel<KQ, false>), grid, dim3(256), 0, s, g, in, wd, out, parts, kgroups, cs, stride);
+    return hipGetLastError();
+}
 
 template <int KQ>
 hipError_t launch_pw(const Geom &g, int cs, const float *in, const float *wd, float *out, float *parts, hipStream_t s)
@@ -756,8 +788,8 @@ hipError_t launch_pw_lds(const Geom &g, bool transpose, const float *in, const f
 
 // 1x1 layers whose filters fit in 64 KB of LDS, with 64 or (64 input channels) 128 output channels, and that have enough
 // pixels to occupy the chip: computed straight from the library filter layout.  With more products per pixel the
-// kernel on bf16 pieces is ahead in spite of its filter copy (56x56, N = 32, us, this form : that one: 64->64 13 : 18, 256->64
-// 34 : 40, 128->64 20 : 26, 64->128 23 : 24, 128->128 35 : 33, 64->256 41 : 36).
+// kernel on bf16 pieces is ahead in spite of its filter copy (56x56, N = 32, us, this form : that one: 64->64 13 : 16, 256->64
+// 34 : 33, at N = 8 12.7 : 20.1, 128->64 20 : 22, 64->128 23 : 24, 128->128 35 : 33, 64->256 41 : 36).
 bool pw_dense_direct_supported(const Geom &g)
 {
     if (g.R != 1 || g.S != 1 || g.sw != 1 || g.sh != 1 || g.uw != 1 || g.uh != 1 || g.pw != 0 || g.ph != 0) return false;
@@ -797,9 +829,13 @@ long long pw_blocks(const Geom &g)
 // us, 16 channels at a time : 32 at a time: 512->2048 @7 N = 32 33.1 : 28.3, 1024->512 @14 53.6 : 44.4, 512->128 @28 30.8 : 26.1, 1024->256 @14
 // 36.2 : 31.4, 128->256 @56 57.0 : 51.8, 64->256 @56 38.4 : 36.9, 256->128 @56, 128->512 @28 and
 // 256->1024 @14, bound by memory, the same; a single stage and wavefronts without channels of their own, 64->192 @112 N = 8, 33.2 : 34.0.
+// 33 to 64 produced channels: 512->64 @56 65.3 : 55.6, 320->64 @40 24.3 : 22.7; not short reductions there, whose stages of 32 would round the
+// running sum twice as often (64->48 4.1e-8 : 4.8e-8).
 bool pw_wide(const Geom &g)
 {
-    if (g.R != 1 || g.S != 1 || g.sw != 1 || g.Ci % kPwWideC != 0) return false;
+    if (g.R != 1 || g.S != 1 || g.sw != 1) return false;
+    if (g.Ko > 32 && g.Ko <= 64) return g.Ci % 32 == 0 && g.Ci > kSplitApart1x1 * kBlk;
+    if (g.Ci % kPwWideC != 0) return false;
     return g.Ci > kPwWideC ? g.Ko > 64 : g.Ko % 128 == 0;
 }
 
@@ -847,18 +883,7 @@ hipError_t launch_pw_small(const Geom &g, const float *in, const float *wd, floa
 // filter copy of launch_reformat_filters; parts = the partial outputs of the cs - 1 shares after the first
 hipError_t launch_pw_dense(const Geom &g, int cs, const float *in, const float *wd, float *out, float *parts, hipStream_t s)
 {
-    if (pw_wide(g)) {
-        const long long tiles = ((long long)g.N * g.Ho * g.Wo + kPwPx - 1) / kPwPx;
-        const int kgroups = ceil_div(g.Ko, 128);
-        const long long blocks = tiles * kgroups;
-        if (blocks > 0x7fffffffLL || tiles * kPwPx > 0x7fff0000LL) return hipErrorInvalidValue;
-        const dim3 grid((unsigned)blocks, cs);
-        const size_t stride = (size_t)g.N * g.Ko * g.Ho * g.Wo;
-        if (ceil_div(g.Ci / kPwWideC, cs) * (kPwWideC / kBlk) <= kSplitApart1x1)
-            hipLaunchKernelGGL(pw_dense_wide_kernel<true>, grid, dim3(256), 0, s, g, in, wd, out, parts, kgroups, cs, stride);
-        else hipLaunchKernelGGL(pw_dense_wide_kernel<false>, grid, dim3(256), 0, s, g, in, wd, out, parts, kgroups, cs, stride);
-        return hipGetLastError();
-    }
+    if (pw_wide(g)) return pw_column_blocks(g) == 4 ? launch_pw_wide<4>(g, cs, in, wd, out, parts, s) : launch_pw_wide<2>(g, cs, in, wd, out, parts, s);
     switch (pw_column_blocks(g)) {
     case 4: return launch_pw<4>(g, cs, in, wd, out, parts, s);
     case 2: return launch_pw<2>(g, cs, in, wd, out, parts, s);
