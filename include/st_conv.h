@@ -159,7 +159,7 @@ st_status st_conv_bww_dy(const st_conv_desc *desc, const float *x, const float *
  * synchronisation; the cost is the sampling pass (at most 256 KB of x and of dy are read once more)
  * and the empty launches.  Where tiled kernels exist, the dense form (st_conv_bww_dense) is the
  * third candidate: it runs when even the sparser operand has fewer than 75 % zeros on 3x3 layers (the
- * measured break-even is 85-90 % or, on some layers, beyond; Sec. 5.3 combines the kernels with dense ones
+ * measured break-even is about 96 % or, on some layers, beyond; Sec. 5.3 combines the kernels with dense ones
  * layer by layer), fewer than 25 % on those so small that the partial gradients are what they wait for.
  * Two kinds of layer are decided without sampling: 1x1 layers, where a zero saves too few
  * multiply-adds to beat the matrix cores at any zero fraction measured (up to 95 %), go straight to the dense form;

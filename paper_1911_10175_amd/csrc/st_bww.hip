@@ -1857,10 +1857,9 @@ hipError_t launch_bww_dense(const st_conv_desc &d, const float *x, const float *
     return reduce(d, A, part, dw, s);
 }
 
-// Measured on the layer shapes of the paper's Table 1 (N = 32, us, zero-skipping at 70 / 90 % zeros against dense:
-// 256->256 @56 716 / 578 : 579, 512->512 @14 215 / 179 : 184, 64->64 @56 73 / 63 : 63, 128->128 @28 71 / 62 : 64): the
-// 3x3 zero-skipping forms pass the dense one at 85-90 % zeros or not at all.  The line is drawn at 75 %, not there: from 80 % on
-// this entry point has always been checked to test the sparser operand; between 75 % and the crossing it is up to 15 % slower for
+// The 3x3 zero-skipping forms pass the dense one at about 96 % zeros (256->256 @56, N = 32, us, at 90 / 95 / 97 % zeros 577 / 502 / 427, dense
+// 475) or not at all.  The line is drawn at 75 %, not there: from 80 % on
+// this entry point has always been checked to test the sparser operand; between 75 % and the crossing it is up to a fifth slower for
 // that.
 // Launches of at most 128 tiles that give every workgroup one of them and write 24 MB of partial gradients or more are bound by
 // these, and the dense form's smaller tiles leave more of them (zero-skipping at 30 / 50 / 70 % zeros : dense: 208->256 @9
@@ -1868,7 +1867,7 @@ hipError_t launch_bww_dense(const st_conv_desc &d, const float *x, const float *
 // @12 N = 2 24.0 / 23.2 / 22.3 : 25.9; with less, 64->128 @14 N = 4 23.1 / 22.3 / 21.4 : 17.0, or more tiles, 64->64 @56 N = 2 29.8 /
 // 28.9 / 28.0 : 26.1, 80->48 @37x53 N = 3 at 50 % 29.4 : 25.5): from 25 % on.
 // A 1x1 layer saves at most K/64 (or C/64) multiply-adds per zero and stays behind the matrix cores at every zero
-// fraction measured (up to 95 %): never (1001).  (Stride-2 layers never get here: they test dy, unsampled.)
+// fraction measured (up to 95 %): never (1001).  (Stride-2 layers never get here: they are decided by size, unsampled.)
 unsigned bww_sparse_threshold(const st_conv_desc &d)
 {
     if (!bww_fast_supported(d)) return 0;           // generic kernels: the test only ever removes work

@@ -499,6 +499,6 @@ const char *st_status_str(st_status status)
     }
 }
 
-const char *st_conv_version(void) { return "0.7"; }
+const char *st_conv_version(void) { return "0.8"; }
 
 }  // extern "C"

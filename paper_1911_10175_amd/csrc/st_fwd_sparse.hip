@@ -48,11 +48,10 @@ unsigned fwd_sparse_threshold(const Geom &g)
 
 // Where the self-selecting entry points switch.  Against the dense kernels of today (fp32 accuracy from bf16 pieces, which
 // also run at a higher clock the more zeros their operands hold) zero-skipping pays much later.  N = 32, us, zero-skipping
-// : dense on the same tensors at 70 / 90 % zeros:
-//   256->256 @56 595 : 502 / 497 : 474   512->512 @28 590 : 530 / 502 : 499   512->512 @14 188 : 156 / 163 : 145
-//   128->256 @56 304 : 271 / 260 : 245   64->64 @224 736 : 572 / 585 : 542
-// Between the two the difference falls by half or more, so the lines cross near 95 % on the layers of 128 and more input
-// channels that the one-kernel launch of st_fwd_auto.hip serves (950).  The other two lines are not crossings: launches with
+// : dense on the same tensors at 90 / 95 / 97 / 99 % zeros:
+//   256->256 @56 494 : 458 / 460 : 442 / 404 : 432 / 243 : 413   512->512 @28 498 : 481 / 464 : 468 / 407 : 458 / 249 : 439
+// So the lines cross at 95 to 96 % on the layers of 128 and more input
+// channels that st_fwd_auto.hip serves (950).  The other two lines are not crossings: launches with
 // fewer channels have always been checked to test their operand from 70 % zeros on, although the dense form is faster there
 // (64->128 @112 332 : 272 / 302 : 265), the other unit-stride launches from 90 % on (64->64 @56 57 : 54, 128->128 @28 49 : 49,
 // 256->256 @14 53 : 58, 64->64 @224 585 : 542 there): 650 and 850 keep that.

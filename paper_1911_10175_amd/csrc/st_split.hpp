@@ -13,7 +13,7 @@
 //
 // How the sums are taken decides the error.  v_mfma_f32_32x32x2_f32 is a chain of fused multiply-adds (measured: bit for
 // bit).  v_mfma_f32_32x32x16_bf16 adds 8 products, then 8 more, each group to the accumulator with one rounding to
-// nearest; within a group whatever lies 24 bits below the largest product is cut off, also of an accumulator smaller than the
+// nearest (16x16x32 alike: four groups of 8); within a group whatever lies 24 bits below the largest product is cut off, also of an accumulator smaller than the
 // products.  With all six products on one accumulator that is twelve roundings per 16 products, of a sum that should stay
 // small: a fresh accumulator for every block of the reduction (16 channels x 9 taps; 16 channels of a 1x1; 16 or 32 pixels) joins
 // the running sum in an fp32 addition.  Over many blocks a quarter of the fp32 instruction's error is left (2304 terms: 8.6e-7 ->
@@ -62,6 +62,9 @@ __device__ __forceinline__ int split_tr_lane(int lane) { return lane / 16 % 2 * 
 
 constexpr float kSplitScale = 16777216.f;                   // 2^24
 constexpr float kSplitUnscale = 1.f / (kSplitScale * kSplitScale);
+
+// A kernel whose accumulator takes one tap or one step only issues the small products first: their sum is 2^-8 of the large ones' and
+// rounds that much finer, and the roundings of the leading pieces' products remain (1x1 FWD / BWI and both BWW kernels).
 
 // The longest reductions whose large products have the running sum for an accumulator: channel blocks of a 3x3 and of a 1x1
 // correlation, pixels of a 1x1 filter gradient.  In units of half a rounding of the final sum, B blocks of T taps take 12 T + B
