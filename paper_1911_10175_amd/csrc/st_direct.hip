@@ -213,11 +213,14 @@ hipError_t launch_fwd(const Geom &g, const float *in, float *out, hipStream_t s)
 // 6 us and 0.12 us (0.3) for every million, whatever the zeros; the other has its launches and its channel walk.  At 50 / 90 % zeros : here,
 // us per call (8 of them are what a call from Python takes): 16->16 @8 15.0 / - : 8.4, 64->64 @28 24.8 / - : 8.3, 256->256 @7 40.7 / - :
 // 8.2, 64->64 @56 (116 M) 24.8 / 21.8 : 16.3, 512->512 @7 (116 M) 66.5 / 52.9 : 21, but 64->64 @28 N = 8 (231 M) 26.4 / 20.9 : 27.5, 64->64 @112 (462 M)
-// 39.8 / 28.2 : 49; 1x1 64->256 @28 (13 M) 14.8 / - : 8.3, 512->2048 @7 (51 M) 45 / - : 12, but 64->256 @56 N = 8 (411 M) 28.7 / 24.6 : 138.
+// 39.8 / 28.2 : 49.  Half of that where one or two channel blocks go into more than four, which is little to walk for the other form (90 % zeros,
+// 116 to 118 M: 16->512 @40 14.6 : 15.7, 16->256 @56 13.7 : 15.5, but 16->64 @56 N = 4 16.1 : 15.8, 32->32 @112 20.1 : 16.4, 512->16 @40 61 : 20).
+// 1x1: 64->256 @28 (13 M) 14.8 / - : 8.3, 512->2048 @7 (51 M) 45 / - : 12, but 64->256 @56 N = 8 (411 M) 28.7 / 24.6 : 138.
 bool fwd_direct(const Geom &g)
 {
     if (!fwd_sparse_supported(g) || g.sw != 1 || g.uw != 1) return false;
-    return (double)g.N * g.Ho * g.Wo * g.Ko * g.Ci * g.R * g.S <= (g.R == 1 ? 25e6 : 120e6);
+    const double most = g.R == 1 ? 25e6 : 120e6;
+    return (double)g.N * g.Ho * g.Wo * g.Ko * g.Ci * g.R * g.S <= (g.Ci <= 32 && g.Ko > 64 ? most / 2 : most);
 }
 
 hipError_t launch_fwd_direct(const Geom &g, const float *in, float *out, hipStream_t s)
