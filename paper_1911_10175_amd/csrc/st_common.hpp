@@ -169,6 +169,8 @@ size_t fwd_dense_filter_bytes(const Geom &g);
 size_t fwd_dense_workspace_bytes(const Geom &g);
 // whether the dense form runs in the kernel that takes 32 reduced channels at a time (st_fwd_dense_wide.hpp)
 bool fwd_dense_wide(const Geom &g);
+// whether that kernel multiplies f16 pieces; its filter copy is half_filters_block's then
+bool fwd_dense_half(const Geom &g);
 hipError_t launch_reformat_filters(const Geom &g, bool transpose, const float *w, float *wd, hipStream_t s);
 int dense_images_per_launch(const Geom &g);
 hipError_t launch_fwd_dense(const Geom &g, const float *in, const float *wd, float *out, hipStream_t s);

@@ -178,6 +178,63 @@ __device__ __forceinline__ void stage_filters_block(size_t block, int Ko, int Ci
     for (int q = 0; q < 3; ++q) out[q * 128] = __builtin_shufflevector(a[q], b[q], 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
+// The same in two f16 pieces (st_split.hpp: layout and scale).  128 threads write one step of 32 produced channels; all that write
+// one of these 32 look at the same 1024 of their filters for the scale.  red: 8 unsigned of LDS; every thread of the workgroup must make the call
+__device__ __forceinline__ void half_filters_block(size_t block, int Ko, int Ci, int S, int R, int transpose, const float *__restrict__ w,
+                                                   float *__restrict__ wd, unsigned *red)
+{
+    const int TAPS = S * R, CiB = Ci / kBlk, KoB = Ko / kBlk, NS = CiB / 2;
+    const int l16 = threadIdx.x % 16, grp = threadIdx.x / 16 % 4, kh = threadIdx.x / kWave % 2;
+    const size_t step = block * 2 + threadIdx.x / 128;  // (kb32 * NS + stage) * TAPS + tap: 4 blocks of 32 k, an even number
+    size_t t = step;
+    const int tap = t % TAPS; t /= TAPS;
+    const int st = t % NS, kb32 = (int)(t / NS), kb = kb32 * 2 + kh, cb = st * 2 + grp / 2, c0 = grp % 2 * 8;
+    // 16 x 16 filters of blocks b (produced) and c (reduced) of a tap of the layer's own order
+    auto filters_of = [&](int b, int c, int tp) __attribute__((always_inline)) {
+        return w + ((transpose ? (size_t)c * KoB + b : (size_t)b * CiB + c) * TAPS + tp) * (kBlk * kBlk);
+    };
+    float4 lo = make_float4(0.f, 0.f, 0.f, 0.f), hi = lo, sample[2] = {lo, lo};
+    if (kb < KoB) {
+        if (!transpose) {
+            const float *p = filters_of(kb, cb, tap) + c0 * kBlk + l16;
+            lo = make_float4(p[0], p[kBlk], p[2 * kBlk], p[3 * kBlk]);
+            hi = make_float4(p[4 * kBlk], p[5 * kBlk], p[6 * kBlk], p[7 * kBlk]);
+        } else {
+            const float4 *p = reinterpret_cast<const float4 *>(filters_of(kb, cb, TAPS - 1 - tap) + l16 * kBlk + c0);
+            lo = p[0];
+            hi = p[1];
+        }
+        // evenly spaced over the reduced blocks and taps of the produced block (64 threads each of two blocks)
+        const int j = grp * 16 + l16;
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            const int at = (int)((long long)(2 * j + a) * (CiB * TAPS) / 128);
+            sample[a] = reinterpret_cast<const float4 *>(filters_of(kb, at / TAPS, at % TAPS))[(j * 2 + a) * 29 % 64];
+        }
+    }
+    const unsigned m = wave_max(max(half_magnitude(sample[0]), half_magnitude(sample[1])));
+    const int wave = threadIdx.x / kWave;
+    if (threadIdx.x % kWave == 0) red[wave] = m;
+    __syncthreads();
+    const int e = half_exponent(max(red[wave & 2], red[wave | 1]));
+    const unsigned key = half_low_key(e);
+    const unsigned lows = __popcll(__ballot(half_low(lo, key) != 0)) + __popcll(__ballot(half_low(hi, key) != 0));
+    if (threadIdx.x % kWave == 0) red[4 + wave] = lows;
+    __syncthreads();
+    int *notes = reinterpret_cast<int *>(wd) + half_notes(Ko, Ci * TAPS);
+    if (threadIdx.x % 128 == 0) {
+        notes[kb32] = e;                                // (the same value from every step)
+        notes[half_blocks(Ko) + step] = (int)(red[4 + wave] + red[5 + wave]);
+    }
+    const float scale = st % 2 ? -half_scale(e) : half_scale(e);
+    f16x4 a[2], b[2];
+    half4(lo, scale, scale * kHalfLow, a);
+    half4(hi, scale, scale * kHalfLow, b);
+    f16x8 *out = reinterpret_cast<f16x8 *>(wd) + step * 256 + kh * 64 + grp * 16 + l16;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) out[q * 128] = __builtin_shufflevector(a[q], b[q], 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
 // Zero statistics of one tensor: the elements equal to zero in a sample of the tensor, one block of 1024
 // consecutive floats out of every `stride` blocks, kSampleBlocks (64) blocks at most, 65 536 elements: enough to
 // fix a zero fraction to 0.2 %.  kSampleParts (4) workgroups of 256 threads share the sample; part `part` looks

@@ -1,23 +1,24 @@
 // The dense matrix-core kernel of the 3x3 correlations with an even number of input channel blocks as a template: 32 channels
-// at a time through v_mfma_f32_16x16x32_bf16.
+// at a time through v_mfma_f32_16x16x32_f16 (three products of two f16 pieces, HALF) or _bf16 (six of three bf16 pieces); st_split.hpp has both.
 //
 // Why another instruction than st_fwd_dense_impl.hpp uses: with two operands of random values in registers and nothing else to
 // do, v_mfma_f32_32x32x16_bf16 runs at 1760 TFLOP/s from two wavefronts per SIMD and at 1580 from four, and
-// v_mfma_f32_16x16x32_bf16 at 2050 from either (half the accumulator traffic per product, so less power, which is what holds
-// the clock down: 2.4 GHz on zeros, 1.9 on ordinary values).  It rounds alike: groups of 8 products, each with one rounding of
-// the accumulator.  A fresh accumulator for every 3 taps of 32 channels errs less than one for 9 taps of 16 (256 channels, half zeros:
-// 1.87e-7 of the norm against 1.94e-7; for 4 and 5 taps 2.02e-7), short reductions (APART) join as often as there, twice per 32.
+// v_mfma_f32_16x16x32_bf16 at 2080, _f16 at 1950 from either (half the accumulator traffic per product, so less power, which is what holds
+// the clock down).  It rounds alike: groups of 8 products, each with one rounding of the accumulator.  Errors of the norm against 64 bits,
+// half zeros: 256 channels 1.87e-7 (bf16) -> 1.4e-7 (f16), 128 1.8e-7 -> 1.2e-7, at 90 % zeros 1.4e-7 -> 1.15e-7.  The f16 form takes a fresh
+// accumulator for every 3 taps of 32 channels (9 taps: 1 % faster, error 1.6e-7).  Reductions of up to kSplitApart blocks stay on
+// bf16 pieces, whose error is the smaller one there from 50 % zeros on (64 channels, 50 / 80 %: 1.06e-7 : 1.13e-7, 7.4e-8 : 1.10e-7).
 //
 // Wavefront = 64 pixels x 32 output channels (2 x 4 blocks of 16 x 16), workgroup = KQ column blocks x 4/KQ parts of one run of
 // pixels, which share its halo.  With two wavefronts per SIMD there are registers for the next stage's samples on their way
 // (loads land there while the current stage is multiplied) and LDS for a second buffer: a piece is split and written after each of
-// the last taps, beside the matrix instructions, and a stage costs one barrier.  256->256 @56, N = 32: 525 -> 470 us (252
-// TFLOP/s), 512->512 @28 568 -> 503, @14 159 -> 142, 128->128 @28 47 -> 42, 64->64 @224 575 -> 533.
-// What it spends its time on (256->256 @56, us; parts left out in a trial, results wrong): without the stream of filters from
-// L2 (6 GB a launch) 411, without the input reads from LDS 440, without staging 444, without all three 371; on zeros, where the
-// clock stays up, 389.  Matrix pipe busy 75 % of the cycles at 1.9 GHz.  Tried: 128 pixels x 64 channels per workgroup (the two
-// pixel parts share filter lines in L1) 488, 128 x 128 with eight wavefronts (one workgroup per compute unit: nothing covers
-// its first loads and its stores) 528; input rows at other distances in LDS (fewer bank conflicts) no change.
+// the last taps, beside the matrix instructions, and a stage costs one barrier.  N = 32, us, bf16 pieces -> f16 pieces: 256->256 @56
+// 462 -> 295 (402 TFLOP/s), 512->512 @28 485 -> 308, @14 139 -> 89, 128->128 @28 41 -> 30, stride 2 128->128 @56 46 -> 35; and on bf16 64->64 @224 533.
+// What it spends its time on (256->256 @56, f16, us; parts left out in a trial, results wrong): without staging 271, without
+// the stream of filters from L2 (4 GB a launch) some 30 less, without the input reads from LDS some 35 less, without all three 222; the bare
+// instructions take 182.  A vector instruction beside the products costs its issue time: computing what the paths that stash have in
+// common ahead of them all, where the loads are waited for, took 330, counting small values by itself 20.  Tried before: 128 pixels x
+// 64 channels per workgroup, 128 x 128 with eight wavefronts, input rows at other distances in LDS (no gain).
 #pragma once
 #include "st_fwd_dense_impl.hpp"
 
@@ -30,31 +31,38 @@ constexpr int kStageC = 32, kWavePx = 64;       // channels of a stage, pixels o
 // pixels, kWideHaloS2 at stride 2, and with 64 output channels, where a tile has 128 pixels, kWideHalo2 (six pieces a lane) where at most a
 // tenth more tiles come of it, else kWideHalo2Max (seven, and a dozen spilled registers: 64->64 @224, N = 32 535 : 547 us, 256->64 @56
 // 145 : 155; but 128->64 @31x57, N = 16, where a halo of 192 samples would hold 98 pixels, 40 : 33)
-constexpr int kWideHalo = 160, kWideHaloS2 = 320, kWideHalo2 = 192, kWideHalo2Max = 212;
-template <int KQ, int HPC>
+// (f16 pieces take less of LDS: 224, whole rounds of the 256 lanes; at stride 2 two buffers of 304 would fit, but ten pieces of
+// staging beside nine taps spill 40 registers, 128->128 @56 35.7 : 42.4)
+constexpr int kWideHalo = 160, kWideHaloS2 = 320, kWideHalo2 = 192, kWideHalo2Max = 212, kWideHalo2MaxHalf = 224;
+template <int KQ, int HPC, bool HALF = false>
 struct WideLds {
     static constexpr int TQ = 4 / KQ, PX = TQ * kWavePx;
     static constexpr int BUFS = HPC == kWideHaloS2 ? 1 : 2;         // two buffers where both fit twice on a compute unit
-    // pieces: [3 pieces][4 groups of 8 channels][sample][8 channels] bf16, i.e. 16 bytes per sample and group,
+    // pieces: [3 or 2 pieces][4 groups of 8 channels][sample][8 channels] of 16 bits, i.e. 16 bytes per sample and group,
     // so that neighbouring lanes (pixels) of an operand read are 16 bytes apart
-    static constexpr int BUF = HPC * 48, FLOATS = BUFS * BUF;
+    static constexpr int NP = HALF ? 2 : 3, BUF = HPC * 16 * NP;
+    // then, HALF: the largest magnitudes the four wavefronts have sampled, and the fours they have staged with one below the pieces' range
+    static constexpr int MISC = BUFS * BUF, FLOATS = MISC + (HALF ? 8 : 0);
 };
 
 
 // wg = index of the workgroup among those of the launch, cshare = its share of the channel split; lds: WideLds::FLOATS floats, 16-byte
 // aligned.  Every thread of the workgroup makes the call (the body contains barriers).
-// APART: the form of short reductions (kSplitApart)
-template <int KQ, int HPC, bool APART, int MODE>
+// HALF: products from two f16 pieces, else, for short reductions (kSplitApart), from three bf16 pieces
+template <int KQ, int HPC, bool HALF, int MODE>
 __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *__restrict__ in, const float *__restrict__ wd,
                                                float *__restrict__ out, float *__restrict__ parts, const FlatGrid &fq, int kgroups,
                                                int csplit, size_t part_stride, int wg, int cshare, float *lds_base)
 {
     using Cfg = FlatCfg<MODE>;
-    using Lds = WideLds<KQ, HPC>;
+    using Lds = WideLds<KQ, HPC, HALF>;
+    using Op = std::conditional_t<HALF, f16x8, bf16x8>;
+    constexpr int NP = Lds::NP, UNITS = NP * 128;                // 16-byte units of a tap's filters
     constexpr int TAPS = 9, NT = Cfg::NT, PSTEP = Cfg::PSTEP, NV = Cfg::NV, NU = Cfg::NU;
     constexpr int NLD = (HPC * 8 + 255) / 256;                   // 16-byte pieces per lane and stage
-    constexpr int NJ = APART ? 4 : 3;                            // taps between joins (APART: 4, then 5)
+    constexpr int NJ = HALF ? 3 : 4;                             // taps between joins (4, then 5)
     constexpr bool DB = Lds::BUFS == 2;
+    static_assert(!DB || NLD <= NT, "a piece a tap");
 
     // the wavefront index is the same in every lane: kept in a scalar register, and with it every tile coordinate
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
@@ -85,20 +93,20 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
     const int kb32 = kg * KQ + kqi;                 // this wavefront's column block
     const bool active = kb32 * 32 < g.Ko && qs < qend;
 
-    // sums of 2 x 16 channels times 4 x 16 pixels, and those of the current taps; with APART the large products go straight
-    // to the former
-    floatx4 acc[2][4], part[2][4];
+    // sums of 2 x 16 channels times 4 x 16 pixels, and those of the current taps: of the large products with HALF, whose small ones
+    // have sums of their own (`low`, 2^11 times as large), else of the small ones, while the large ones go straight to the former
+    floatx4 acc[2][4], part[2][4], low[2][4];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int pb = 0; pb < 4; ++pb) acc[kb][pb] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int pb = 0; pb < 4; ++pb) acc[kb][pb] = low[kb][pb] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     // filter operand: lane supplies the pieces of element (k = kb32*32 + kb*16 + l16, c = grp*8 .. grp*8+7 of the stage) from
-    // the reformatted copy: 16-byte unit ((kb32*NS + stage)*TAPS + tap)*384 + piece*128 + kb*64 + lane
-    const bf16x8 *bbase = reinterpret_cast<const bf16x8 *>(wd) + (size_t)(active ? kb32 : 0) * NS * TAPS * 384;
-    auto filters = [&](int step, int q, bf16x8 (&f)[2]) __attribute__((always_inline)) {
+    // the reformatted copy: 16-byte unit ((kb32*NS + stage)*TAPS + tap)*UNITS + piece*128 + kb*64 + lane
+    const Op *bbase = reinterpret_cast<const Op *>(wd) + (size_t)(active ? kb32 : 0) * NS * TAPS * UNITS;
+    auto filters = [&](int step, int q, Op (&f)[2]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) f[kb] = (bbase + (size_t)step * 384 + q * 128 + kb * 64)[lane];
+        for (int kb = 0; kb < 2; ++kb) f[kb] = (bbase + (size_t)step * UNITS + q * 128 + kb * 64)[lane];
     };
     // input operand: lane supplies pixel pb*16 + l16 of its 64, channels grp*8 .. grp*8+7 of the stage
     int apix[4];
@@ -108,19 +116,19 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
         apix[pb] = grp * HPC + (vrow(q) - v0) * pitch + q % w * PSTEP;
     }
 
-    // halo staging: the 16-byte pieces of a stage, first those of its first 16 channels, are split among the 256 lanes.
+    // halo staging: the 16-byte pieces of a stage, eight for a sample, are split among the 256 lanes, so that a lane's are 32 samples apart.
     // poff: the piece's pixel relative to the stage's first plane of image n0, -1 for padding
     int poff[NLD];
-    auto unit = [&](int jj) __attribute__((always_inline)) { return (jj * 256 + (int)threadIdx.x) >> 2; };
+    const int sample0 = (int)threadIdx.x / 8, sblock = (int)threadIdx.x / 4 % 2;
     const int HW = g.Hi * g.Wi;
 #pragma unroll
     for (int jj = 0; jj < NLD; ++jj) {
-        const int b = unit(jj) >= HPC ? 1 : 0, hp = unit(jj) - b * HPC;
+        const int hp = jj * 32 + sample0;
         const int vr = v0 + hp / pitch, n = vr / VR;
         const int ih = vr % VR - g.ph;
         const int iw = c0 * PSTEP + hp % pitch - g.pw;
         const bool ok = hp < used && n < g.N && ih >= 0 && ih < g.Hi && iw >= 0 && iw < g.Wi;
-        poff[jj] = ok ? ((n - n0) * CiB + b) * HW + ih * g.Wi + iw : -1;
+        poff[jj] = ok ? ((n - n0) * CiB + sblock) * HW + ih * g.Wi + iw : -1;
     }
     const size_t plane = (size_t)HW * kBlk;
     const float *in0 = in + (size_t)n0 * CiB * plane + threadIdx.x % 4 * 4;
@@ -134,27 +142,63 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
             hreg[jj] = *reinterpret_cast<const float4 *>(src);
         }
     };
+    float xscale = 0.f, xscale_low = 0.f;                        // HALF: of the input's pieces h and l
+    unsigned low_key = 0, lows = 0;
+    const int stash_at = ((sblock * 2 + ((int)threadIdx.x >> 1 & 1)) * HPC + sample0) * 2 + (threadIdx.x & 1);
     auto stash1 = [&](char *buf, int jj) __attribute__((always_inline)) {
-        int tid = threadIdx.x;
-        asm volatile("" : "+v"(tid));
-        const int u = (jj * 256 + tid) >> 2, b = u >= HPC ? 1 : 0;
-        if ((jj + 1) * 64 > 2 * HPC && u >= 2 * HPC) return;
-        bf16x4 p[3];
-        split4(hreg[jj], kSplitScale, p);
-        bf16x4 *dst = reinterpret_cast<bf16x4 *>(buf) + (u + (b + (threadIdx.x >> 1 & 1)) * HPC) * 2 + (threadIdx.x & 1);
+        if ((jj + 1) * 32 > HPC && jj * 32 + sample0 >= HPC) return;
+        // (the paths that stash are many, and what they share must not be computed ahead of them all, where the loads would be waited for)
+        float4 v = hreg[jj];
+        asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+        if constexpr (HALF) {
+            f16x4 p[2];
+            half4(v, xscale, xscale_low, p);
+            lows += half_low(v, low_key);
+            f16x4 *dst = reinterpret_cast<f16x4 *>(buf) + stash_at + jj * 64;
 #pragma unroll
-        for (int i = 0; i < 3; ++i) dst[i * (8 * HPC)] = p[i];
+            for (int i = 0; i < 2; ++i) dst[i * (8 * HPC)] = p[i];
+        } else {
+            bf16x4 p[3];
+            split4(v, kSplitScale, p);
+            bf16x4 *dst = reinterpret_cast<bf16x4 *>(buf) + stash_at + jj * 64;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) dst[i * (8 * HPC)] = p[i];
+        }
     };
     char *const lds0 = reinterpret_cast<char *>(lds_base);
     auto buffer = [&](int st) __attribute__((always_inline)) { return lds0 + (DB && (st - st0) % 2 ? Lds::BUF * 4 : 0); };
 
+    unsigned *const misc = reinterpret_cast<unsigned *>(lds_base) + Lds::MISC;
+    // (the stage's barrier comes before anyone reads it)
+    auto note_lows = [&]() __attribute__((always_inline)) {
+        unsigned c = 0;
+        if (__ballot(lows != 0) != 0)
+            for (int l = 0; l < kWave; ++l) c += (unsigned)__builtin_amdgcn_readlane((int)lows, l);
+        if (lane == 0) misc[4 + wave] = c;
+    };
     fetch(st0);
-    bf16x8 f0[2], f1[2], f2[2];
-    filters(st0 * TAPS + Cfg::ftap(0), 0, f0);
-    filters(st0 * TAPS + Cfg::ftap(0), 1, f1);
-    filters(st0 * TAPS + Cfg::ftap(0), 2, f2);
+    Op f[NP][2];
+#pragma unroll
+    for (int q = 0; q < NP; ++q) filters(st0 * TAPS + Cfg::ftap(0), q, f[q]);
+    int xe = 0;                                                  // exponent of the input's scale
+    if constexpr (HALF) {
+        // the first stage and, spread over the others, a piece of each lane
+        const int st = st0 + (int)((threadIdx.x / 4u) % (unsigned)(st1 - st0));
+        const float *src = poff[0] < 0 ? kSplitZeros : in0 + 2 * st * plane + (size_t)(unsigned)poff[0] * kBlk;
+        unsigned m = half_magnitude(*reinterpret_cast<const float4 *>(src));
+#pragma unroll
+        for (int jj = 0; jj < NLD; ++jj) m = max(m, half_magnitude(hreg[jj]));
+        m = wave_max(m);
+        if (lane == 0) misc[wave] = m;
+        __syncthreads();
+        xe = __builtin_amdgcn_readfirstlane(half_exponent(max(max(misc[0], misc[1]), max(misc[2], misc[3]))));
+        xscale = half_scale(xe);
+        xscale_low = half_scale(xe + 11);
+        low_key = half_low_key(xe);
+    }
 #pragma unroll
     for (int jj = 0; jj < NLD; ++jj) stash1(buffer(st0), jj);
+    if constexpr (HALF) note_lows();
     __syncthreads();
 
     // one stage; More: another one follows (the last one is compiled by itself: the staging of the next under a condition costs
@@ -162,18 +206,16 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
     auto stage = [&](int st, auto More) __attribute__((always_inline)) {
         constexpr bool more = decltype(More)::value;
         if constexpr (more) fetch(st + 1);
-        const bf16x8 *lds = reinterpret_cast<const bf16x8 *>(buffer(st));
+        const Op *lds = reinterpret_cast<const Op *>(buffer(st));
         char *const next = buffer(st + 1);
-        auto input = [&](int tp, int q, bf16x8 (&x)[4]) __attribute__((always_inline)) {
+        auto input = [&](int tp, int q, Op (&x)[4]) __attribute__((always_inline)) {
 #pragma unroll
             for (int pb = 0; pb < 4; ++pb) x[pb] = lds[apix[pb] + Cfg::dv(tp) * pitch + Cfg::du(tp) + q * 4 * HPC];
         };
         if (active) {
-            bf16x8 x0[4], x1[4], x2[4];
-            input(0, 0, x0);
-            input(0, 1, x1);
-            input(0, 2, x2);
-            // One tap = six products of 2 x 4 blocks.  Every operand register is refilled for the next tap as soon as its last
+            Op x[NP][4];
+            static_for<0, NP>([&](auto Q) __attribute__((always_inline)) { input(0, decltype(Q)::value, x[decltype(Q)::value]); });
+            // One tap = three or six products of 2 x 4 blocks.  Every operand register is refilled for the next tap as soon as its last
             // product of this one has been issued (filter piece 0, used first and last, has a second set).  The last tap requests
             // the filters of the next stage's first one.
             static_for<0, NT>([&](auto T) __attribute__((always_inline)) {
@@ -181,30 +223,42 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
                 constexpr bool last = tp + 1 == NT;
                 constexpr int nt = last ? 0 : tp + 1;
                 const int nstep = (last && more ? st + 1 : st) * TAPS + Cfg::ftap(nt);
-                auto mul = [&](const bf16x8 (&f)[2], const bf16x8 (&x)[4], floatx4 (&to)[2][4], bool first) __attribute__((always_inline)) {
+                auto mul = [&](const Op (&fk)[2], const Op (&xp)[4], floatx4 (&to)[2][4], bool first) __attribute__((always_inline)) {
 #pragma unroll
                     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                        for (int pb = 0; pb < 4; ++pb)              // rows = output channels, columns = pixels
-                            to[kb][pb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[kb], x[pb], first ? floatx4{0.f, 0.f, 0.f, 0.f} : to[kb][pb], 0, 0, 0);
+                        for (int pb = 0; pb < 4; ++pb) {            // rows = output channels, columns = pixels
+                            const floatx4 c = first ? floatx4{0.f, 0.f, 0.f, 0.f} : to[kb][pb];
+                            if constexpr (HALF) to[kb][pb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fk[kb], xp[pb], c, 0, 0, 0);
+                            else to[kb][pb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fk[kb], xp[pb], c, 0, 0, 0);
+                        }
                     __builtin_amdgcn_sched_barrier(0);
                 };
                 constexpr bool fresh = tp % NJ == 0 && tp < 8;
-                bf16x8 f0n[2];
+                Op f0n[2];
                 filters(nstep, 0, f0n);
-                mul(f0, x0, APART ? acc : part, !APART && fresh);
-                mul(f2, x0, part, APART && fresh);
-                filters(nstep, 2, f2);
-                mul(f1, x0, part, false);
-                if constexpr (!last) input(nt, 0, x0);
-                mul(f1, x1, part, false);
-                filters(nstep, 1, f1);
-                mul(f0, x1, part, false);
-                if constexpr (!last) input(nt, 1, x1);
-                mul(f0, x2, part, false);
-                if constexpr (!last) input(nt, 2, x2);
+                if constexpr (HALF) {
+                    mul(f[0], x[0], part, fresh);
+                    mul(f[1], x[0], low, false);
+                    filters(nstep, 1, f[1]);
+                    if constexpr (!last) input(nt, 0, x[0]);
+                    mul(f[0], x[1], low, false);
+                    if constexpr (!last) input(nt, 1, x[1]);
+                } else {
+                    mul(f[0], x[0], acc, false);
+                    mul(f[NP - 1], x[0], part, fresh);
+                    filters(nstep, 2, f[NP - 1]);
+                    mul(f[1], x[0], part, false);
+                    if constexpr (!last) input(nt, 0, x[0]);
+                    mul(f[1], x[1], part, false);
+                    filters(nstep, 1, f[1]);
+                    mul(f[0], x[1], part, false);
+                    if constexpr (!last) input(nt, 1, x[1]);
+                    mul(f[0], x[NP - 1], part, false);
+                    if constexpr (!last) input(nt, 2, x[NP - 1]);
+                }
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb) f0[kb] = f0n[kb];
+                for (int kb = 0; kb < 2; ++kb) f[0][kb] = f0n[kb];
                 if constexpr (DB && more && tp >= NT - NLD) stash1(next, tp - (NT - NLD));
                 if constexpr ((tp + 1) % NJ == 0 && tp + 1 < 8) {
 #pragma unroll
@@ -214,12 +268,14 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
                     __builtin_amdgcn_sched_barrier(0);          // (else the next tap's products get registers of their own)
                 }
             });
-            // the products of the last taps (all or the small ones) join the sum, which changes sign: odd stages have their
-            // filters negated (st_split.hpp)
+            // the products of the last taps join the sum, which changes sign: odd stages have their filters negated (st_split.hpp)
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                for (int pb = 0; pb < 4; ++pb) acc[kb][pb] = -acc[kb][pb] - part[kb][pb];
+                for (int pb = 0; pb < 4; ++pb) {
+                    acc[kb][pb] = -acc[kb][pb] - part[kb][pb];
+                    if constexpr (HALF) low[kb][pb] = -low[kb][pb];
+                }
         } else if (DB && more) {
 #pragma unroll
             for (int jj = 0; jj < NLD; ++jj) stash1(next, jj);
@@ -230,6 +286,7 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
 #pragma unroll
                 for (int jj = 0; jj < NLD; ++jj) stash1(next, jj);
             }
+            if constexpr (HALF) if (st + 2 == st1) note_lows();
             __syncthreads();
         }
     };
@@ -246,7 +303,31 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
         ow = c0 + q % w;
         return q < qend;
     };
-    const float scale = st1 % 2 ? -kSplitUnscale : kSplitUnscale;
+    const float scale = (st1 % 2 ? -1.f : 1.f) * (HALF ? 1.f : kSplitUnscale);
+    int exponent = 0;
+    float safe = 0.f;                                   // HALF: smaller outputs do not count
+    if constexpr (HALF) {
+        const int *notes = reinterpret_cast<const int *>(wd) + half_notes(g.Ko, g.Ci * TAPS);
+        exponent = -(xe + notes[kb32]);
+        float least = kHalfSafe;
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int pb = 0; pb < 4; ++pb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    acc[kb][pb][r] = __builtin_fmaf(low[kb][pb][r], 1.f / kHalfLow, acc[kb][pb][r]);
+                    least = fminf(least, fabsf(acc[kb][pb][r]));
+                }
+        if (__ballot(least < kHalfSafe) != 0) {
+            unsigned c = lane < 4 ? misc[4 + lane] : 0;
+            for (int i = st0 * TAPS + lane; i < st1 * TAPS; i += kWave) c += (unsigned)notes[half_blocks(g.Ko) + kb32 * (NS * TAPS) + i];
+            unsigned sum = 0;
+            if (__ballot(c != 0) != 0)
+                for (int l = 0; l < kWave; ++l) sum += (unsigned)__builtin_amdgcn_readlane((int)c, l);
+            safe = kHalfSafe * fminf(4.f * (float)sum / (float)((st1 - st0) * (kStageC * TAPS)), 1.f);
+        }
+    }
     bool finite[2] = {true, true};
 #pragma unroll
     for (int pb = 0; pb < 4; ++pb) {
@@ -256,7 +337,11 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
         for (int kb = 0; kb < 2; ++kb) {
             if (kb32 * 2 + kb >= KoB) continue;
             const floatx4 a = acc[kb][pb];
-            const float4 r = make_float4(a[0] * scale, a[1] * scale, a[2] * scale, a[3] * scale);
+            float4 r = make_float4(a[0] * scale, a[1] * scale, a[2] * scale, a[3] * scale);
+            if constexpr (HALF) {
+                auto finish = [&](float v) __attribute__((always_inline)) { return fabsf(v) < safe ? __builtin_nanf("") : ldexpf(v, exponent); };
+                r = make_float4(finish(r.x), finish(r.y), finish(r.z), finish(r.w));
+            }
             finite[pb / 2] = finite[pb / 2] && split_finite(r);
             *reinterpret_cast<float4 *>(out + act_off(n, kb32 * 2 + kb, oh, ow, KoB, g.Ho, g.Wo) + 4 * grp) = r;
         }
@@ -274,14 +359,14 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
     }
 }
 
-template <int KQ, int HPC, bool APART, int MODE>
+template <int KQ, int HPC, bool HALF, int MODE>
 __global__ __launch_bounds__(256, 2) void fwd_dense_wide_kernel(
     Geom g, const float *__restrict__ in, const float *__restrict__ wd, float *__restrict__ out, float *__restrict__ parts,
     FlatGrid fq, int kgroups, int csplit, size_t part_stride)
 {
     if (form_deselected(g.sel, g.want, g.thr)) return;
-    __shared__ __attribute__((aligned(16))) float lds[WideLds<KQ, HPC>::FLOATS];
-    fwd_dense_wide_body<KQ, HPC, APART, MODE>(g, in, wd, out, parts, fq, kgroups, csplit, part_stride, (int)blockIdx.x, (int)blockIdx.y, lds);
+    __shared__ __attribute__((aligned(16))) float lds[WideLds<KQ, HPC, HALF>::FLOATS];
+    fwd_dense_wide_body<KQ, HPC, HALF, MODE>(g, in, wd, out, parts, fq, kgroups, csplit, part_stride, (int)blockIdx.x, (int)blockIdx.y, lds);
 }
 
 }  // namespace

@@ -193,7 +193,7 @@ struct PrepareArgs {
     int Ko, Ci;                 // produced / reduced channels of the correlation the kernels run
     int transpose;              // BWI
     int paired;                 // layout of the first copy (fwd_sparse_filters_paired)
-    int wide;                   // layout of the second (fwd_dense_wide)
+    int wide, half;             // layout of the second (fwd_dense_wide, fwd_dense_half)
     unsigned n_wave;            // workgroups of the first copy
     size_t total_dense;         // pieces of 8 elements of the second copy
 };
@@ -209,7 +209,8 @@ __global__ __launch_bounds__(256) void auto_prepare_kernel(PrepareArgs a)
         if (a.transpose) wave_filters_block<true>((int)(b - kSampleParts), a.KB, a.CB, a.S, a.R, a.w, a.wl, tile, a.paired);
         else wave_filters_block<false>((int)(b - kSampleParts), a.KB, a.CB, a.S, a.R, a.w, a.wl, tile, a.paired);
     } else {
-        if (a.wide) stage_filters_block(b - kSampleParts - a.n_wave, a.Ko, a.Ci, a.S, a.R, a.transpose, 1, a.w, a.wd, a.total_dense);
+        if (a.half) half_filters_block(b - kSampleParts - a.n_wave, a.Ko, a.Ci, a.S, a.R, a.transpose, a.w, a.wd, red);
+        else if (a.wide) stage_filters_block(b - kSampleParts - a.n_wave, a.Ko, a.Ci, a.S, a.R, a.transpose, 1, a.w, a.wd, a.total_dense);
         else reformat_filters_block(b - kSampleParts - a.n_wave, a.Ko, a.Ci, a.S, a.R, a.transpose, 1, a.w, a.wd, a.total_dense);
     }
 }
@@ -288,6 +289,7 @@ hipError_t launch_auto_prepare(const Geom &g, bool transpose, const float *act, 
     a.S = g.S; a.R = g.R; a.Ko = g.Ko; a.Ci = g.Ci; a.transpose = transpose ? 1 : 0;
     a.paired = fwd_sparse_filters_paired(g) ? 1 : 0;
     a.wide = fwd_dense_wide(g) ? 1 : 0;
+    a.half = fwd_dense_half(g) ? 1 : 0;
     const long long n_wave = fwd_direct(g) ? 0 : (long long)a.KB * a.CB;
     a.total_dense = fwd_dense_filter_bytes(g) / 48;
     const long long n_dense = (long long)((a.total_dense + 255) / 256);

@@ -108,6 +108,90 @@ __device__ __forceinline__ void split_lanes_fence()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// ---- two f16 pieces of an fp32 value (long reductions: st_fwd_dense_wide.hpp says where) ----------------------------------
+// a = h + l 2^-11 with h = a rounded to f16 (11 significant bits) and l = the remainder times 2^11, rounded: 23 bits and more, three
+// quarters of all values exactly.  Of the four products of two such sums three are formed, h h on one accumulator, h l + l h on
+// another that is 2^11 times as large: half the matrix work of the six bf16 products (v_mfma_f32_16x16x32_f16 runs at 1950 TFLOP/s on
+// random operands where the bf16 one runs at 2080, and rounds alike, groups of 8; subnormal f16 operands are kept) and 4 bytes of operands a
+// value instead of 6.  What is left out of a product and of the values is 7.5e-8 of it in the root mean square (5e-9 with bf16 pieces),
+// but the leading pieces' accumulator takes half the roundings: over 128 reduced channels of a 3x3 and more the sum errs less.
+// The method is published (Ootomo and Yokota, "Recovering single precision accuracy from Tensor Cores while surpassing the FP32
+// theoretical peak performance", 2022: the remainder scaled by 2^11).
+//
+// f16 has 5 exponent bits, so values are scaled by a power of two.  A workgroup takes the one that puts the largest of some
+// thousand of the values it will read into [2^11, 2^12), a block of 32 rows of filters likewise: larger ones may be
+// 16 times as large before h is infinite (such outputs come out non-finite and are computed again, as above), and from 2^-14 on, 2^25 below the
+// largest, all bits are kept.  Of a smaller value what lies below 2^-36 is lost, 2^-36 2^16 of a product at most.  An fp32 sum of n terms may
+// be off by n 2^-24 of their magnitudes, so c such values are within it in outputs of 2^5 c / n and more.  Smaller outputs (twice as large, with what else is left
+// out) are computed again, as above, where c is not zero: half_low counts the values a workgroup meets, the copy of the filters tells theirs.
+// In normal layers one value in 2^24 is as small as that and an output in 2^30 is smaller than 2^6 / n.  (Without the count, any output below
+// 2^6 where there is one such value: 512->512 @28 345 -> 445 us with one such filter.)
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+// The copy of the filters: [Ko/32][Ci/32][tap][2 pieces][2 halves of the 32 k][4 groups of 8 c][16 k][8 c] f16 (Ko padded to whole
+// groups of 128), then an int per 32 produced channels, the exponent of their scale, then one per 32 produced channels and step
+// (stage and tap), how many fours of its values hold one below the pieces' range
+__host__ __device__ __forceinline__ int half_blocks(int Ko) { return (Ko + 127) / 128 * 4; }
+__host__ __device__ __forceinline__ size_t half_notes(int Ko, int terms) { return (size_t)half_blocks(Ko) * 32 * terms; }      // in 4 bytes
+
+constexpr float kHalfLow = 2048.f;                          // scale of l beside h
+constexpr float kHalfSafe = 64.f;                           // times c / n: outputs from here on need no second look
+
+// exponent of the scale for the largest magnitude `bits` (of a finite fp32 value; 0: nothing but zeros seen)
+__device__ __forceinline__ int half_exponent(unsigned bits)
+{
+    const int e = (int)(bits >> 23);
+    return bits == 0 ? 0 : min(138 - max(e, 1), 116);       // (2^(e + 11), the scale of l, is finite)
+}
+__device__ __forceinline__ float half_scale(int e) { return __uint_as_float((unsigned)(e + 127) << 23); }
+__device__ __forceinline__ unsigned half_magnitude(float v)
+{
+    const unsigned b = __float_as_uint(v) & 0x7fffffffu;
+    return b < 0x7f800000u ? b : 0u;
+}
+__device__ __forceinline__ unsigned half_magnitude(float4 v)
+{
+    return max(max(half_magnitude(v.x), half_magnitude(v.y)), max(half_magnitude(v.z), half_magnitude(v.w)));
+}
+// the largest m of the wavefront's lanes
+__device__ __forceinline__ unsigned wave_max(unsigned m)
+{
+    m = max(m, (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, 0x111, 0xf, 0xf, false));          // row_shr 1, 2, 4, 8: lane 15 of each row
+    m = max(m, (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, 0x112, 0xf, 0xf, false));
+    m = max(m, (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, 0x114, 0xf, 0xf, false));
+    m = max(m, (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, 0x118, 0xf, 0xf, false));
+    m = max(m, (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, 0x142, 0xa, 0xf, false));          // row_bcast 15, 31: lane 63
+    m = max(m, (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, 0x143, 0xc, 0xf, false));
+    return (unsigned)__builtin_amdgcn_readlane((int)m, 63);
+}
+// magnitudes below 2^-14 of the scale 2^e, zero not among them, have keys below this one
+__device__ __forceinline__ unsigned half_key(float a) { return (__float_as_uint(a) << 1) - 1u; }
+__device__ __forceinline__ unsigned half_low_key(int e)
+{
+    const unsigned bits = e < 113 ? (unsigned)(113 - e) << 23 : 1u << (135 - e);        // of 2^(-14 - e), subnormal from e = 113 on
+    return (bits << 1) - 1u;
+}
+// 1 if there are any among four values (counted as four)
+__device__ __forceinline__ unsigned half_low(float4 v, unsigned low_key)
+{
+    return min(min(half_key(v.x), half_key(v.y)), min(half_key(v.z), half_key(v.w))) < low_key ? 1u : 0u;
+}
+// the two pieces of four consecutive values times s; low = s * kHalfLow
+__device__ __forceinline__ void half4(float4 v, float s, float low, f16x4 (&p)[2])
+{
+    auto pair = [&](floatx2 a, f16x2 &h, f16x2 &l) __attribute__((always_inline)) {
+        h = __builtin_convertvector(a * s, f16x2);
+        const floatx2 r = {__builtin_fmaf((float)h[0], -kHalfLow, a[0] * low), __builtin_fmaf((float)h[1], -kHalfLow, a[1] * low)};      // exact
+        l = __builtin_convertvector(r, f16x2);
+    };
+    f16x2 h[2], l[2];
+    pair(floatx2{v.x, v.y}, h[0], l[0]);
+    pair(floatx2{v.z, v.w}, h[1], l[1]);
+    p[0] = __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3);
+    p[1] = __builtin_shufflevector(l[0], l[1], 0, 1, 2, 3);
+}
+
 // 32 pixels x 32 output channels of the correlation g once more with fp32 multiply-adds on the matrix cores: the lane's
 // pixel (n, oh, ow; `valid`: it exists), output channels kb32*32 ..., channel blocks cb0 .. cb1-1 of the input.  Non-finite
 // outputs in `out` are replaced.  A tap's products go to a pixel's sum only where the tap meets a sample, so padding

@@ -20,13 +20,22 @@ def _ask(name, g):
     return f(ctypes.byref(g))
 
 
+def _correlation(d, bwi):
+    if bwi:
+        return _Geom(N=d.N, Ci=d.K, Ko=d.C, Hi=d.OH, Wi=d.OW, Ho=d.H, Wo=d.W, R=d.R, S=d.S, sw=1, sh=1, pw=d.R - 1 - d.pad_w, ph=d.S - 1 - d.pad_h,
+                     uw=d.stride_w, uh=d.stride_h, wt=1)
+    return _Geom(N=d.N, Ci=d.C, Ko=d.K, Hi=d.H, Wi=d.W, Ho=d.OH, Wo=d.OW, R=d.R, S=d.S, sw=d.stride_w, sh=d.stride_h, pw=d.pad_w, ph=d.pad_h, uw=1, uh=1)
+
+
+def f16_pieces(d, bwi=False):
+    """Whether that kernel forms its products from two f16 pieces (else from three bf16 ones)."""
+    return _ask("fwd_dense_half", _correlation(d, bwi))
+
+
 def dense_kernel(d, bwi=False):
     """ "32" or "16": channels that the kernel on bf16 pieces takes at a time; for 1x1 layers also "lds", whole filters in LDS, and "fp32",
     both on fp32 matrix instructions."""
-    g = _Geom(N=d.N, Ci=d.C, Ko=d.K, Hi=d.H, Wi=d.W, Ho=d.OH, Wo=d.OW, R=d.R, S=d.S, sw=d.stride_w, sh=d.stride_h, pw=d.pad_w, ph=d.pad_h, uw=1, uh=1)
-    if bwi:
-        g = _Geom(N=d.N, Ci=d.K, Ko=d.C, Hi=d.OH, Wi=d.OW, Ho=d.H, Wo=d.W, R=d.R, S=d.S, sw=1, sh=1, pw=d.R - 1 - d.pad_w, ph=d.S - 1 - d.pad_h,
-                  uw=d.stride_w, uh=d.stride_h, wt=1)
+    g = _correlation(d, bwi)
     if d.R == 3:
         return "32" if _ask("fwd_dense_wide", g) else "16"
     if _ask("pw_dense_direct_supported", g):

@@ -1,0 +1,133 @@
+"""Dense kernels that form fp32 products from two f16 pieces (long reductions): the error of an ordinary layer, and values of the sizes
+where the pieces' five exponent bits end.  Every test here needs an MI355X."""
+import numpy as np
+import pytest
+import torch
+
+import stgen
+from oracle import st_ref
+from oracle.st_ref import Geom
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from tests.gpu_harness import DeviceLayer, desc_of
+    from tests.kernel_choice import f16_pieces
+    from tests.test_gpu_split import as_products, check, fma_chain, inputs, norm_error
+
+# whole launches of 4 and 5 stages, two shares, tiles of 64 and 128 pixels (the larger halo too), tiles over many images, stride 2
+GEOMS = {
+    "128->128 @56": Geom(6, 128, 128, 56, 56, 3, 3, 1, 1, 1, 1),
+    "160->80 33x31": Geom(18, 160, 80, 33, 31, 3, 3, 1, 1, 1, 1),
+    "256->144 @14": Geom(44, 256, 144, 14, 14, 3, 3, 1, 1, 1, 1),
+    "128->64 @57x61": Geom(11, 128, 64, 57, 61, 3, 3, 1, 1, 1, 1),
+    "192->48 3x5": Geom(2600, 192, 48, 3, 5, 3, 3, 1, 1, 1, 1),
+    "stride 2 160->160 45x27": Geom(32, 160, 160, 45, 27, 3, 3, 2, 2, 1, 1),
+}
+
+
+def half_passes(g):
+    d = desc_of(g)
+    return [p for p, bwi in (("fwd", False), ("bwi", True)) if f16_pieces(d, bwi)]
+
+
+def corr(g, x, w, dy, p):
+    return st_ref.conv_fwd(g, x, w) if p == "fwd" else st_ref.conv_bwi(g, dy, w)
+
+
+def within_fp32_sum(g, x, w, dy, label):
+    L = DeviceLayer(g, x, w, dy)
+    passes = half_passes(g)
+    assert passes, "another kernel: test is void"
+    for p in passes:
+        ref, mag = corr(g, x, w, dy, p)
+        n = (g.C if p == "fwd" else g.K) * g.R * g.S
+        off, bound = np.abs(getattr(L, p)(True).astype(np.float64) - ref), (n + 3) * 2.0 ** -24 * mag + n * 2.0 ** -150
+        assert np.all(off <= bound), f"{label} {p}: {np.max(off / np.maximum(bound, 1e-300))} of the bound"
+
+
+@pytest.mark.parametrize("small", [2.0 ** -13, 2.0 ** -27, 2.0 ** -33, 2.0 ** -60, 2.0 ** -120])
+@pytest.mark.parametrize("name", GEOMS)
+def test_images_and_filters_of_very_different_scale(name, small):
+    """Every other image (its outputs share tiles with those of its neighbours), then every other filter, then every other reduced channel is
+    smaller by a factor on either side of what the pieces hold beside the larger ones.  Each output within the bound of an fp32 sum: those
+    that only small values take part in are as exact as the others."""
+    g = GEOMS[name]
+    x, w, dy = inputs(g, 71)
+    s = np.float32(small)
+    scaled = x.copy(), dy.copy()
+    for t in scaled:
+        t[1::2] *= s
+    within_fp32_sum(g, scaled[0], w, scaled[1], f"{name} images {small}")
+    w2 = w.copy()
+    w2[1::2, ::2] *= s
+    w2[::2, 1::2] *= s
+    xs, dys = x.copy(), dy.copy()
+    xs[:, 1::2] = 0                                     # even rows: the large filters only; odd rows: the small ones only
+    dys[:, 1::2] = 0
+    within_fp32_sum(g, xs, w2, dys, f"{name} filters {small}")
+    xs[:, 1::2] = x[:, 1::2] * s                        # and with factors that make up for it
+    dys[:, 1::2] = dy[:, 1::2] * s
+    within_fp32_sum(g, xs, w2 / s if small > 2.0 ** -100 else w2, dys, f"{name} both {small}")
+
+
+@pytest.mark.parametrize("name", ["128->128 @56", "stride 2 160->160 45x27"])
+def test_zeros_and_tensors_of_extreme_scale(name):
+    g = GEOMS[name]
+    x, w, dy = inputs(g, 73)
+    within_fp32_sum(g, 0 * x, w, 0 * dy, "zeros")
+    within_fp32_sum(g, x, 0 * w, dy, "zero filters")
+    one = np.zeros_like(x), np.zeros_like(dy)
+    for t in one:
+        t[-1, 5, 1, 1] = 2.0 ** -126                    # nothing else: hardly any sample sees it
+    within_fp32_sum(g, one[0], w, one[1], "one value")
+    for a, b in ((2.0 ** 100, 2.0 ** -90), (2.0 ** -110, 2.0 ** 90), (2.0 ** -128, 2.0 ** 110)):
+        within_fp32_sum(g, x * np.float32(a), w * np.float32(b), dy * np.float32(a), f"{a} {b}")
+
+
+@pytest.mark.parametrize("name", GEOMS)
+def test_values_far_above_the_sampled_ones(name):
+    """A few values that no sample is likely to see, 2^4 to 2^60 times the others: h is infinite from 2^5 on and such outputs are computed
+    again."""
+    g = GEOMS[name]
+    for big in (2.0 ** 4, 2.0 ** 9, 2.0 ** 60):
+        x, w, dy = inputs(g, 75)
+        for t in (x, dy):
+            t.reshape(-1)[[7, t.size // 2, t.size - 3]] = np.float32(5 * big)
+        within_fp32_sum(g, x, w, dy, f"{name} {big}")
+        x, w, dy = inputs(g, 75)
+        w[0, 0, 0, 0] = w[-1, -1, -1, -1] = np.float32(big)
+        within_fp32_sum(g, x, w, dy, f"{name} filter {big}")
+
+
+def test_infinities_and_nan():
+    for name in ("128->64 @57x61", "256->144 @14"):
+        g = GEOMS[name]
+        for value in (np.inf, np.nan):
+            x, w, dy = inputs(g, 77)
+            w[w == 0] = 0.25
+            x[-1, 3, 2, 2] = dy[0, 1, 0, 1] = value
+            check(g, x, w, dy, f"{name} {value}")
+
+
+@pytest.mark.parametrize("zeros", [0.0, 0.5, 0.9])
+@pytest.mark.parametrize("channels", [128, 256])
+def test_error_of_ordinary_layers(channels, zeros):
+    """Beside a chain of fp32 multiply-adds, which rounds the running sum once per non-zero term.  In units of half a squared rounding of
+    the whole sum: three taps' 12 roundings (a group of 8 products each) of a sum that is 1/T of the whole, T of them, and T joins, T = 9 C /
+    96, so 12 + T against 9 C (1 - zeros); what the pieces leave out adds 7.5e-8, three roundings of a product (2.4e-8).  A fifth more for what
+    products cut off of each other."""
+    N = {128: 6, 256: 6}[channels]
+    g, one = Geom(N, channels, 128, 56, 56, 3, 3, 1, 1, 1, 1), Geom(1, channels, 128, 56, 56, 3, 3, 1, 1, 1, 1)
+    assert f16_pieces(desc_of(g)), "another kernel: test is void"
+    w = stgen.he_normal(g.w_shape, 82)
+    x = stgen.relu_sparse(g.x_shape, zeros, 81) if zeros else stgen.normal(81, int(np.prod(g.x_shape))).reshape(g.x_shape).astype(np.float32)
+    L = DeviceLayer(g, x, w, None)
+    a, b, flat = as_products(one, x[:1], w, x[:1], "fwd")
+    rows = slice(0, 16)                                 # a block of produced channels
+    exact = (a @ b)[rows]
+    got = torch.from_numpy(flat(L.fwd(True)[:1]).astype(np.float64))[rows]
+    err, chain = norm_error(got, exact), norm_error(fma_chain(a[rows], b), exact)
+    T = 9 * channels / 96
+    bound = 1.2 * np.hypot(np.sqrt((12 + T) / (9 * channels * (1 - zeros))) * chain, 7.5e-8)
+    assert err <= bound, f"{err:.3g}, bound {bound:.3g}, fp32 instructions {chain:.3g}"
