@@ -735,6 +735,88 @@ __global__ __launch_bounds__(256, 2) void bww_dense_kernel(BwwArgs A, const floa
     }
 }
 
+// Staging of the unit-stride kernel: as above, with the vector instructions that cost the matrix cores their issue slots taken out (203 -> 92 to ask for a
+// tile, 191 -> 167 to split and write it: 256->256 @56, N = 32, 494 -> 478 us, 512->512 @28 547 -> 529, 64->64 @224 536 -> 518).  Addresses are 32 bits behind a buffer descriptor per image, whose range check returns the zeros of channels past
+// the end; pixels outside the image ask beyond it.  A row and a column are compared as one packed pair.  Layout of a buffer: [pieces][2 halves of the 64
+// channels][32 pixels][32 channels] of dy, the same of x with kHaloRows pixels.
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+// BIG: images of any size (bww_big_image), with 64-bit addresses.
+template <int TH, int TW, bool BIG = false>
+struct BwwWideStage {
+    static constexpr int HW = TW + 2, HP = (TH + 2) * HW, XPX = 64, DPX = 32;       // (halos of 60 and 64 samples)
+    static constexpr int XB = XPX * 64, DB = DPX * 64;
+    static_assert(HP <= XPX && HP > XPX - 16 && TH * TW <= DPX && TH * TW > DPX - 16, "whole rounds of 256 threads");
+    static constexpr int bytes(int pieces) { return pieces * 2 * (XB + DB); }
+    float4 sd[2], sx[4];
+    int n, th, tw;                                           // the tile to ask for next
+
+    __device__ __forceinline__ void start(const BwwArgs &A, int unit)
+    {
+        tw = unit % A.tiles_w;
+        th = unit / A.tiles_w % A.tiles_h;
+        n = unit / A.tiles_w / A.tiles_h;
+    }
+
+    // 16-byte pieces of channel blocks cb .. cb+3 of image n of a tensor (CB blocks of H x W): a block of samples of COLS columns whose first one is
+    // (h0, w0); PX of them, zeros for those outside the image
+    template <int COLS, int PX, int NP>
+    static __device__ __forceinline__ void ask(const float *t, int n, int cb, int CB, int h0, int w0, int H, int W, float4 (&to)[NP])
+    {
+        // (thread index the compiler cannot see through: see above)
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int q = tid & 15, pix0 = tid >> 4;
+        const float *base = t + ((size_t)n * CB + cb) * H * W * kBlk;
+        if constexpr (BIG) {
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                const int pix = pix0 + i * 16, h = h0 + pix / COLS, w = w0 + pix % COLS;
+                to[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (pix < PX && h >= 0 && h < H && w >= 0 && w < W && cb + (q >> 2) < CB)
+                    to[i] = *reinterpret_cast<const float4 *>(base + ((size_t)(q >> 2) * H * W + (size_t)h * W + w) * kBlk + (q & 3) * 4);
+            }
+        } else {
+            const __amdgpu_buffer_rsrc_t from =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base), 0, min(4, CB - cb) * (H * W) * (kBlk * 4), 0x00020000);
+            const unsigned at = (unsigned)((h0 * W + w0) * (kBlk * 4) + (q >> 2) * (H * W * (kBlk * 4)) + (q & 3) * 16);
+            const u16x2 first = {(unsigned short)h0, (unsigned short)w0}, last = {(unsigned short)(H - 1), (unsigned short)(W - 1)};
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                const unsigned pix = pix0 + i * 16, r = pix / COLS, c = pix % COLS;
+                const u16x2 hw = __builtin_bit_cast(u16x2, r | c << 16) + first, in = __builtin_elementwise_min(hw, last);
+                const bool ok = __builtin_bit_cast(unsigned, in) == __builtin_bit_cast(unsigned, hw) && ((i + 1) * 16 <= PX || (int)pix < PX);
+                const unsigned off = ok ? at + r * (W * (kBlk * 4)) + c * (kBlk * 4) : 0x80000000u;
+                to[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(from, (int)off, 0, 0));
+            }
+        }
+    }
+    // the next tile
+    __device__ __forceinline__ void fetch(const BwwArgs &A, const float *__restrict__ x, const float *__restrict__ dy, int kt, int cg)
+    {
+        ask<TW, TH * TW>(dy, n, kt * 4, A.K / kBlk, th * TH, tw * TW, A.OH, A.OW, sd);
+        ask<HW, HP>(x, n, cg * 4, A.C / kBlk, th * TH - A.ph, tw * TW - A.pw, A.H, A.W, sx);
+        if (++tw == A.tiles_w) {
+            tw = 0;
+            if (++th == A.tiles_h) { th = 0; ++n; }
+        }
+    }
+    __device__ __forceinline__ void stash(float sign, char *buf) const
+    {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int q = tid & 15, pix0 = tid >> 4, at = pix0 * 64 + (q & 7) * 8;
+        char *d = buf + (q >> 3) * DB + at, *h = buf + 6 * DB + (q >> 3) * XB + at;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            bf16x4 p[3];
+            split4(i < 2 ? sd[i < 2 ? i : 0] : sx[i < 2 ? 0 : i - 2], i < 2 ? sign * kSplitScale : kSplitScale, p);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) *reinterpret_cast<bf16x4 *>(i < 2 ? d + i * 1024 + j * 2 * DB : h + (i - 2) * 1024 + j * 2 * XB) = p[j];
+        }
+    }
+};
+
 // The same for unit stride (the kernel above serves stride 2) with v_mfma_f32_16x16x32_bf16, 32 pixels (a whole tile) at a
 // time: it reaches 2050 TFLOP/s where 32x32x16 reaches 1760 (st_fwd_dense_wide.hpp), and its sum joins the running one once per
 // tile instead of once per 16 pixels.  A wavefront's 32 x 32 channels are 2 x 2 blocks of 16 x 16.  The registers are full (144 sums,
@@ -743,15 +825,14 @@ __global__ __launch_bounds__(256, 2) void bww_dense_kernel(BwwArgs A, const floa
 // 607 -> 542, @14 170 -> 154, 64->64 @224 614 -> 540, 128->128 @28 63.5 -> 61.6, one image 64->64 @14 14.4 -> 12.5; error against
 // 64 bits 2.55e-7 -> 1.86e-7, 2.72e-7 -> 2.03e-7, 1.46e-7 -> 1.15e-7, 2.62e-7 -> 1.95e-7, 9.3e-8 -> 8.2e-8, 4.5e-8 -> 3.8e-8.
 // Bound: power (see there) and, beside the products, splitting and stashing the next tile.
-template <int R, int S, int TH, int TW, bool SHORT>
+template <int R, int S, int TH, int TW, bool SHORT, bool BIG>
 __global__ __launch_bounds__(256, 2) void bww_dense_wide_kernel(BwwArgs A, const float *__restrict__ x,
                                                                 const float *__restrict__ dy, float *__restrict__ part)
 {
-    using Cfg = BwwDenseCfg<R, S, TH, TW, 1>;
+    using Stage = BwwWideStage<TH, TW, BIG>;
     if (deselected(A.sel, A.want)) return;              // uniform over the grid, before any barrier
-    constexpr int HW = Cfg::Halo::HW, TP = Cfg::TP, XB = Cfg::XB, DB = Cfg::DB;
-    static_assert(Cfg::P == 32, "a tile is the reduction of one instruction");
-    __shared__ __attribute__((aligned(16))) char lds[2 * Cfg::LDS];     // tiles take turns
+    constexpr int HW = Stage::HW, TP = TH * TW, XB = Stage::XB, DB = Stage::DB;
+    __shared__ __attribute__((aligned(16))) char lds[2 * Stage::bytes(3)];      // tiles take turns
 
     // the wavefront index is the same in every lane: kept in a scalar register, and with it every tile coordinate
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
@@ -775,7 +856,9 @@ __global__ __launch_bounds__(256, 2) void bww_dense_wide_kernel(BwwArgs A, const
 
     // the next tile is written into the other buffer: one barrier a tile (256->256 @56 502 -> 490; a piece after each of the last taps
     // has no registers, 76 spilled, 514)
-    BwwDenseStage<R, S, TH, TW, 1> stage;
+    Stage stage;
+    stage.start(A, u0);
+    auto sign = [](int unit) __attribute__((always_inline)) { return unit % 2 ? -1.f : 1.f; };        // (BwwDenseStage)
 
     // operands: lane l takes channel l % 16 of a block and pixels 8*(l/16) .. +7 of the tile, four per transposing read, for which
     // it supplies the address of 8 bytes of pixel (l % 16) / 4 of the four
@@ -790,14 +873,14 @@ __global__ __launch_bounds__(256, 2) void bww_dense_wide_kernel(BwwArgs A, const
         }
     }
 
-    stage.fetch(A, x, dy, kt, cg, u0);                       // (a split has at least one tile)
-    stage.stash(u0, lds);
+    stage.fetch(A, x, dy, kt, cg);                       // (a split has at least one tile)
+    stage.stash(sign(u0), lds);
     __syncthreads();
     for (int unit = u0; unit < u1; ++unit) {
-        char *const buf = lds + (unit - u0) % 2 * Cfg::LDS;
-        if (unit + 1 < u1) stage.fetch(A, x, dy, kt, cg, unit + 1);                  // in flight during this tile's MFMAs
+        char *const buf = lds + (unit - u0) % 2 * Stage::bytes(3);
+        if (unit + 1 < u1) stage.fetch(A, x, dy, kt, cg);                  // in flight during this tile's MFMAs
         if (active) {
-            const float sg = stage.sign(unit);
+            const float sg = sign(unit);
             auto at = [&](int offset) __attribute__((always_inline)) { return (LdsTr)(buf + offset); };
             bf16x8 d[3][2];
 #pragma unroll
@@ -859,7 +942,7 @@ __global__ __launch_bounds__(256, 2) void bww_dense_wide_kernel(BwwArgs A, const
             });
         }
         if (unit + 1 == u1) break;
-        stage.stash(unit + 1, lds + (unit + 1 - u0) % 2 * Cfg::LDS);
+        stage.stash(sign(unit + 1), lds + (unit + 1 - u0) % 2 * Stage::bytes(3));
         __syncthreads();
     }
     if (!active) return;
@@ -1494,13 +1577,21 @@ BwwArgs dense_args(const st_conv_desc &d)
     return A;
 }
 
+// Images whose offsets within four channel blocks, or whose sides, are too large for the 32 and 16 bits of BwwWideStage
+bool bww_big_image(const BwwArgs &A)
+{
+    auto big = [](int H, int W) { return (long long)H * W >= 1 << 22 || H > 32000 || W > 32000; };
+    return big(A.H, A.W) || big(A.OH, A.OW);
+}
+
 template <int TH, int TW>
 void launch_bww_dense_wide(const BwwArgs &A, const float *x, const float *dy, float *part, hipStream_t s)
 {
     const dim3 grid(A.splits, ceil_div(A.K, 64) * A.cgroups);
-    if (A.units <= kBwwShortUnits && A.units <= 2 * A.splits)
-        hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, true>), grid, dim3(256), 0, s, A, x, dy, part);
-    else hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, false>), grid, dim3(256), 0, s, A, x, dy, part);
+    if (bww_big_image(A)) hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, false, true>), grid, dim3(256), 0, s, A, x, dy, part);
+    else if (A.units <= kBwwShortUnits && A.units <= 2 * A.splits)
+        hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, true, false>), grid, dim3(256), 0, s, A, x, dy, part);
+    else hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, false, false>), grid, dim3(256), 0, s, A, x, dy, part);
 }
 
 template <int TH, int TW, int PSTEP>

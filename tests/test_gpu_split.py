@@ -425,3 +425,13 @@ def test_error_of_bww_auto_of_stride_2_layers(zeros):
     assert err["auto"] <= 1.1 * np.hypot(err["dy"], 2.4e-8), err
     if zeros[1] <= 0.7:
         assert err["auto"] <= err["dy"], err
+
+
+@pytest.mark.parametrize("g", [Geom(1, 16, 32, 3, 32100, 3, 3, 1, 1, 1, 1), Geom(1, 32, 16, 32100, 2, 3, 3, 1, 1, 1, 1), Geom(2, 80, 48, 2, 31999, 3, 3, 1, 1, 1, 1)],
+                         ids=lambda g: f"{g.H}x{g.W}")
+def test_bww_of_images_with_long_sides(g):
+    """Either side of the line from which rows and columns are no longer compared as packed pairs of 16 bits."""
+    x, w, dy = inputs(g, 47)
+    ref, ref_abs = st_ref.conv_bww(g, x, dy)
+    off = np.abs(DeviceLayer(g, x, None, dy).bww(True) - ref)
+    assert np.all(off <= (g.N * g.OH * g.OW + 3) * 2.0 ** -24 * ref_abs)
