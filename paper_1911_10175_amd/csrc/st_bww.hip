@@ -748,15 +748,22 @@ struct BwwWideStage {
     static constexpr int XB = XPX * 64, DB = DPX * 64;
     static_assert(HP <= XPX && HP > XPX - 16 && TH * TW <= DPX && TH * TW > DPX - 16, "whole rounds of 256 threads");
     static constexpr int bytes(int pieces) { return pieces * 2 * (XB + DB); }
-    float4 sd[2], sx[4];
-    int n, th, tw;                                           // the tile to ask for next
-
-    __device__ __forceinline__ void start(const BwwArgs &A, int unit)
-    {
-        tw = unit % A.tiles_w;
-        th = unit / A.tiles_w % A.tiles_h;
-        n = unit / A.tiles_w / A.tiles_h;
-    }
+    struct Tile {
+        int n, th, tw;
+        __device__ __forceinline__ void start(const BwwArgs &A, int unit)
+        {
+            tw = unit % A.tiles_w;
+            th = unit / A.tiles_w % A.tiles_h;
+            n = unit / A.tiles_w / A.tiles_h;
+        }
+        __device__ __forceinline__ void step(const BwwArgs &A)
+        {
+            if (++tw == A.tiles_w) {
+                tw = 0;
+                if (++th == A.tiles_h) { th = 0; ++n; }
+            }
+        }
+    };
 
     // 16-byte pieces of channel blocks cb .. cb+3 of image n of a tensor (CB blocks of H x W): a block of samples of COLS columns whose first one is
     // (h0, w0); PX of them, zeros for those outside the image
@@ -791,17 +798,16 @@ struct BwwWideStage {
             }
         }
     }
-    // the next tile
-    __device__ __forceinline__ void fetch(const BwwArgs &A, const float *__restrict__ x, const float *__restrict__ dy, int kt, int cg)
+    static __device__ __forceinline__ void fetch_dy(const BwwArgs &A, const float *__restrict__ dy, int kt, const Tile &t, float4 (&sd)[2])
     {
-        ask<TW, TH * TW>(dy, n, kt * 4, A.K / kBlk, th * TH, tw * TW, A.OH, A.OW, sd);
-        ask<HW, HP>(x, n, cg * 4, A.C / kBlk, th * TH - A.ph, tw * TW - A.pw, A.H, A.W, sx);
-        if (++tw == A.tiles_w) {
-            tw = 0;
-            if (++th == A.tiles_h) { th = 0; ++n; }
-        }
+        ask<TW, TH * TW>(dy, t.n, kt * 4, A.K / kBlk, t.th * TH, t.tw * TW, A.OH, A.OW, sd);
     }
-    __device__ __forceinline__ void stash(float sign, char *buf) const
+    static __device__ __forceinline__ void fetch_x(const BwwArgs &A, const float *__restrict__ x, int cg, const Tile &t, float4 (&sx)[4])
+    {
+        ask<HW, HP>(x, t.n, cg * 4, A.C / kBlk, t.th * TH - A.ph, t.tw * TW - A.pw, A.H, A.W, sx);
+    }
+    // three bf16 pieces of a tile
+    static __device__ __forceinline__ void stash(const float4 (&sd)[2], const float4 (&sx)[4], float sign, char *buf)
     {
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
@@ -815,6 +821,28 @@ struct BwwWideStage {
             for (int j = 0; j < 3; ++j) *reinterpret_cast<bf16x4 *>(i < 2 ? d + i * 1024 + j * 2 * DB : h + (i - 2) * 1024 + j * 2 * XB) = p[j];
         }
     }
+    // two f16 pieces of one operand's part of a tile (halves of the channels BYTES apart), scale sign 2^e; returns how many of its fours hold a value
+    // below the pieces' range
+    template <int BYTES, int NP>
+    static __device__ __forceinline__ unsigned stash_half(const float4 (&v)[NP], float sign, int e, char *buf)
+    {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int q = tid & 15, pix0 = tid >> 4;
+        char *d = buf + (q >> 3) * BYTES + pix0 * 64 + (q & 7) * 8;
+        const float scale = sign * half_scale(e), low = sign * half_scale(e + 11);
+        unsigned lows = 0;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            f16x4 p[2];
+            half4(v[i], scale, low, p);
+            lows += half_low(v[i], half_low_key(e));
+#pragma unroll
+            for (int j = 0; j < 2; ++j) *reinterpret_cast<f16x4 *>(d + i * 1024 + j * 2 * BYTES) = p[j];
+            __builtin_amdgcn_sched_barrier(0);                  // a piece at a time: there are no registers for several
+        }
+        return lows;
+    }
 };
 
 // The same for unit stride (the kernel above serves stride 2) with v_mfma_f32_16x16x32_bf16, 32 pixels (a whole tile) at a
@@ -825,14 +853,12 @@ struct BwwWideStage {
 // 607 -> 542, @14 170 -> 154, 64->64 @224 614 -> 540, 128->128 @28 63.5 -> 61.6, one image 64->64 @14 14.4 -> 12.5; error against
 // 64 bits 2.55e-7 -> 1.86e-7, 2.72e-7 -> 2.03e-7, 1.46e-7 -> 1.15e-7, 2.62e-7 -> 1.95e-7, 9.3e-8 -> 8.2e-8, 4.5e-8 -> 3.8e-8.
 // Bound: power (see there) and, beside the products, splitting and stashing the next tile.
+// lds: two buffers of three pieces, which take turns
 template <int R, int S, int TH, int TW, bool SHORT, bool BIG>
-__global__ __launch_bounds__(256, 2) void bww_dense_wide_kernel(BwwArgs A, const float *__restrict__ x,
-                                                                const float *__restrict__ dy, float *__restrict__ part)
+__device__ __forceinline__ void bww_dense_wide_body(const BwwArgs &A, const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part, char *lds)
 {
     using Stage = BwwWideStage<TH, TW, BIG>;
-    if (deselected(A.sel, A.want)) return;              // uniform over the grid, before any barrier
     constexpr int HW = Stage::HW, TP = TH * TW, XB = Stage::XB, DB = Stage::DB;
-    __shared__ __attribute__((aligned(16))) char lds[2 * Stage::bytes(3)];      // tiles take turns
 
     // the wavefront index is the same in every lane: kept in a scalar register, and with it every tile coordinate
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
@@ -856,8 +882,14 @@ __global__ __launch_bounds__(256, 2) void bww_dense_wide_kernel(BwwArgs A, const
 
     // the next tile is written into the other buffer: one barrier a tile (256->256 @56 502 -> 490; a piece after each of the last taps
     // has no registers, 76 spilled, 514)
-    Stage stage;
-    stage.start(A, u0);
+    typename Stage::Tile next;
+    next.start(A, u0);
+    float4 sd[2], sx[4];
+    auto fetch = [&]() __attribute__((always_inline)) {
+        Stage::fetch_dy(A, dy, kt, next, sd);
+        Stage::fetch_x(A, x, cg, next, sx);
+        next.step(A);
+    };
     auto sign = [](int unit) __attribute__((always_inline)) { return unit % 2 ? -1.f : 1.f; };        // (BwwDenseStage)
 
     // operands: lane l takes channel l % 16 of a block and pixels 8*(l/16) .. +7 of the tile, four per transposing read, for which
@@ -873,12 +905,12 @@ __global__ __launch_bounds__(256, 2) void bww_dense_wide_kernel(BwwArgs A, const
         }
     }
 
-    stage.fetch(A, x, dy, kt, cg);                       // (a split has at least one tile)
-    stage.stash(sign(u0), lds);
+    fetch();                                                 // (a split has at least one tile)
+    Stage::stash(sd, sx, sign(u0), lds);
     __syncthreads();
     for (int unit = u0; unit < u1; ++unit) {
         char *const buf = lds + (unit - u0) % 2 * Stage::bytes(3);
-        if (unit + 1 < u1) stage.fetch(A, x, dy, kt, cg);                  // in flight during this tile's MFMAs
+        if (unit + 1 < u1) fetch();                  // in flight during this tile's MFMAs
         if (active) {
             const float sg = sign(unit);
             auto at = [&](int offset) __attribute__((always_inline)) { return (LdsTr)(buf + offset); };
@@ -942,7 +974,7 @@ __global__ __launch_bounds__(256, 2) void bww_dense_wide_kernel(BwwArgs A, const
             });
         }
         if (unit + 1 == u1) break;
-        stage.stash(sign(unit + 1), lds + (unit + 1 - u0) % 2 * Stage::bytes(3));
+        Stage::stash(sd, sx, sign(unit + 1), lds + (unit + 1 - u0) % 2 * Stage::bytes(3));
         __syncthreads();
     }
     if (!active) return;
@@ -978,6 +1010,255 @@ __global__ __launch_bounds__(256, 2) void bww_dense_wide_kernel(BwwArgs A, const
         if (c >= A.C) return;
 #pragma unroll
         for (int tap = 0; tap < S * R; ++tap)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int k = k32 + 8 * (r / 4) + 4 * (lane / 32) + r % 4;
+                if (k < A.K && !split_finite(*element(k, c, tap))) *element(k, c, tap) = redo[tap][r];
+            }
+    }
+}
+
+template <int R, int S, int TH, int TW, bool SHORT, bool BIG>
+__global__ __launch_bounds__(256, 2) void bww_dense_wide_kernel(BwwArgs A, const float *__restrict__ x,
+                                                                const float *__restrict__ dy, float *__restrict__ part)
+{
+    if (deselected(A.sel, A.want)) return;              // uniform over the grid, before any barrier
+    __shared__ __attribute__((aligned(16))) char lds[2 * BwwWideStage<TH, TW>::bytes(3)];
+    bww_dense_wide_body<R, S, TH, TW, SHORT, BIG>(A, x, dy, part, lds);
+}
+
+// The same with two f16 pieces (st_split.hpp) where a workgroup has many tiles (kBwwHalfTiles): three products instead of six.  N = 32, half zeros, us:
+// 256->256 @56 478 -> 353 (335 TFLOP/s), 512->512 @28 529 -> 375, 128->256 @56 246 -> 191, 64->64 @224 518 -> 425.  Bound: issue, half of it vector
+// instructions (800 beside the 216 matrix instructions of a pair of tiles: splitting them, their addresses, joining the sums).  Workgroups take two tiles
+// at a time, 64 pixels a sum, so that sums join half as often: what the pieces leave out (7.5e-8 of the norm) is less than what that saves.
+// The registers are full (144 sums, 32 of a tap, 48 operands), so a pair is staged in three steps of 16 registers, each asked for three taps before
+// it is split: the halo of its first tile into the third of three buffers that take turns, both dy tiles into the second pair of buffers, the halo
+// of the second tile into the first buffer when this pair is done (two barriers a pair).  (24 registers, two steps: 20 spilled, 345 -> 372 us.)
+// A tap of a tile is three groups of four instructions; the large and the small products have a sum each.
+template <int TH, int TW>
+__global__ __launch_bounds__(256, 2) void bww_dense_half_kernel(BwwArgs A, const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part)
+{
+    constexpr int R = 3, S = 3, TAPS = R * S;
+    using Stage = BwwWideStage<TH, TW>;
+    if (deselected(A.sel, A.want)) return;              // uniform over the grid, before any barrier
+    constexpr int HW = Stage::HW, TP = TH * TW, XB = Stage::XB, DB = Stage::DB, XBUF = 4 * XB, DBUF = 4 * DB, LDS = 3 * XBUF + 4 * DBUF;
+    static_assert(LDS >= 2 * Stage::bytes(3) && 2 * LDS <= 160 * 1024, "either form in one array, two workgroups a compute unit");
+    __shared__ __attribute__((aligned(16))) char lds[LDS];
+    unsigned *misc = reinterpret_cast<unsigned *>(lds);         // before the first tile and after the last
+
+    // the wavefront index is the same in every lane: kept in a scalar register, and with it every tile coordinate
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+    const int l16 = lane % 16, grp = lane / 16;
+    const int kh = wave % 2, ch = wave / 2;
+    const int split = blockIdx.x;
+    const int kt = blockIdx.y / A.cgroups, cg = blockIdx.y % A.cgroups;
+    const int CB = A.C / kBlk, KB = A.K / kBlk;
+    const bool active = kt * 64 + kh * 32 < A.K && cg * 64 + ch * 32 < A.C;
+
+    const int u0 = (int)((long long)A.units * split / A.splits);
+    const int u1 = (int)((long long)A.units * (split + 1) / A.splits);
+
+    // a sample for the scales: the first pixels of 16 tiles
+    int xe, de;
+    {
+        const int slot = threadIdx.x / 16, q = threadIdx.x % 16;
+        const int u = u0 + (int)((long long)(u1 - u0) * slot / 16);
+        const int tw = u % A.tiles_w, th = u / A.tiles_w % A.tiles_h, n = u / A.tiles_w / A.tiles_h;
+        const int cb = min(cg * 4 + q / 4, CB - 1), kb = min(kt * 4 + q / 4, KB - 1);
+        const float4 vx = *reinterpret_cast<const float4 *>(x + act_off(n, cb, min(th * TH, A.H - 1), min(tw * TW, A.W - 1), CB, A.H, A.W) + q % 4 * 4);
+        const float4 vd = *reinterpret_cast<const float4 *>(dy + act_off(n, kb, th * TH, tw * TW, KB, A.OH, A.OW) + q % 4 * 4);
+        const unsigned mx = wave_max(half_magnitude(vx)), md = wave_max(half_magnitude(vd));
+        auto filled = [](float4 v) __attribute__((always_inline)) {             // values of the wavefront that are not zero
+            return (unsigned)(__popcll(__ballot(v.x != 0.f)) + __popcll(__ballot(v.y != 0.f)) + __popcll(__ballot(v.z != 0.f)) + __popcll(__ballot(v.w != 0.f)));
+        };
+        const unsigned fx = filled(vx), fd = filled(vd);
+        if (lane == 0) { misc[wave] = mx; misc[4 + wave] = md; misc[8 + wave] = fx; misc[12 + wave] = fd; }
+        __syncthreads();
+        const unsigned products = (misc[8] + misc[9] + misc[10] + misc[11]) * (misc[12] + misc[13] + misc[14] + misc[15]);
+        const unsigned bits_x = max(max(misc[0], misc[1]), max(misc[2], misc[3])), bits_d = max(max(misc[4], misc[5]), max(misc[6], misc[7]));
+        xe = __builtin_amdgcn_readfirstlane(half_exponent(bits_x));
+        de = __builtin_amdgcn_readfirstlane(half_exponent(bits_d));
+        __syncthreads();                                        // (misc is overwritten from here on)
+        if ((unsigned)__builtin_amdgcn_readfirstlane((int)products) < (1u << 20) / 20) {        // of 1024 x 1024
+            bww_dense_wide_body<R, S, TH, TW, false, false>(A, x, dy, part, lds);
+            return;
+        }
+    }
+    floatx4 acc[TAPS][2][2];                            // [tap][16 k][16 c]
+#pragma unroll
+    for (int t = 0; t < TAPS; ++t)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) acc[t][kb][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // (every other pair with the opposite sign: BwwDenseStage)
+    auto sign = [](int pair) __attribute__((always_inline)) { return pair % 2 ? -1.f : 1.f; };
+    typename Stage::Tile ta, tb;                                // the two tiles to ask for next
+    ta.start(A, u0);
+    tb = ta;
+    // a second tile that does not exist: rows that no image of these sizes has, all zeros
+    auto second = [&](int unit) __attribute__((always_inline)) {
+        tb = ta;
+        tb.step(A);
+        if (unit >= u1) { tb.n = 0; tb.th = 40000 / TH; }
+    };
+    auto first = [&](int unit) __attribute__((always_inline)) {
+        ta = tb;
+        ta.step(A);
+        if (unit >= u1) { ta.n = 0; ta.th = 40000 / TH; }
+    };
+    float4 sx[4], sda[2], sdb[2];
+    unsigned lows = 0;
+    char *const xlds = lds, *const dlds = lds + 3 * XBUF;
+    Stage::fetch_x(A, x, cg, ta, sx);                           // (a split has at least one tile)
+    lows += Stage::template stash_half<XB>(sx, 1.f, xe, xlds);
+    second(u0 + 1);
+    Stage::fetch_dy(A, dy, kt, ta, sda);
+    Stage::fetch_dy(A, dy, kt, tb, sdb);
+    Stage::fetch_x(A, x, cg, tb, sx);
+    lows += Stage::template stash_half<DB>(sda, 1.f, de, dlds);
+    lows += Stage::template stash_half<DB>(sdb, 1.f, de, dlds + DBUF);
+    lows += Stage::template stash_half<XB>(sx, 1.f, xe, xlds + XBUF);
+    __syncthreads();
+
+    // operands: lane l takes channel l % 16 of a block and pixels 8*(l/16) .. +7 of the tile, four per transposing read, for which
+    // it supplies the address of 8 bytes of pixel (l % 16) / 4 of the four
+    int dp, xp[2];
+    {
+        const int px = grp * 8 + l16 / 4, chan = l16 % 4 * 8;
+        dp = kh * DB + px * 64 + chan;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int p = min(px + i * 4, TP - 1);              // (the padding's dy is zero)
+            xp[i] = ch * XB + (p / TW * HW + p % TW) * 64 + chan;
+        }
+    }
+    int slot = 0;                                               // buffer of the pair's first tile; the second one's is the next
+    for (int unit = u0, pair = 0;; unit += 2, ++pair) {
+        const bool more = unit + 2 < u1;
+        char *const tile[2] = {xlds + slot * XBUF, xlds + (slot + 1) % 3 * XBUF}, *const spare = xlds + (slot + 2) % 3 * XBUF;
+        char *const dtile = dlds + pair % 2 * (2 * DBUF), *const dspare = dlds + (1 - pair % 2) * (2 * DBUF);
+        // (no branches around what follows, also not for a last pair's successor or for wavefronts without channels of their own, which multiply
+        // zeros: with them 20 to 40 registers are spilled)
+        first(unit + 2);
+        second(unit + 3);
+        Stage::fetch_x(A, x, cg, ta, sx);                       // in flight during the first taps
+        __builtin_amdgcn_sched_barrier(0);
+        const float sg = sign(pair), nsg = sign(pair + 1);
+        auto at = [&](int t, int offset) __attribute__((always_inline)) { return (LdsTr)(tile[t] + offset); };
+        auto dat = [&](int t, int offset) __attribute__((always_inline)) { return (LdsTr)(dtile + t * DBUF + offset); };
+        auto read = [&](LdsTr p0, LdsTr p1) __attribute__((always_inline)) { return __builtin_bit_cast(f16x8, split_tr_read(p0, p1)); };
+        auto input = [&](int t, int tap, int q, f16x8 (&f)[2]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) {
+                const int off = q * 2 * XB + (tap / R * HW + tap % R) * 64 + cb * 32;
+                f[cb] = read(at(t, xp[0] + off), at(t, xp[1] + off));
+            }
+        };
+        f16x8 d[2][2][2], f[2][2];                              // [tile][piece][16 k], [piece][16 c]
+        auto taps = [&](auto First, auto Last) __attribute__((always_inline)) {
+            static_for<decltype(First)::value, decltype(Last)::value>([&](auto T) __attribute__((always_inline)) {
+                constexpr int tap = decltype(T)::value;
+                floatx4 large[2][2], small[2][2];
+                static_for<0, 2>([&](auto Tile) __attribute__((always_inline)) {
+                    constexpr int t = decltype(Tile)::value;
+                    constexpr int nt = 1 - t, ntap = t == 0 ? tap : tap + 1;            // whose input replaces this one's
+                    auto mul = [&](int qd, int qf, floatx4 (&to)[2][2], bool first) __attribute__((always_inline)) {
+#pragma unroll
+                        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                            for (int cb = 0; cb < 2; ++cb)
+                                to[kb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(d[t][qd][kb], f[qf][cb], first ? floatx4{0.f, 0.f, 0.f, 0.f} : to[kb][cb], 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                    };
+                    mul(0, 0, large, t == 0);
+                    mul(1, 0, small, t == 0);
+                    if constexpr (ntap < TAPS) input(nt, ntap, 0, f[0]);
+                    mul(0, 1, small, false);
+                    if constexpr (ntap < TAPS) input(nt, ntap, 1, f[1]);
+                });
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            acc[tap][kb][cb][r] = __builtin_fmaf(__builtin_fmaf(small[kb][cb][r], 1.f / kHalfLow, large[kb][cb][r]), sg, acc[tap][kb][cb][r]);
+                // (here, not behind the loop's end where the compiler would take it with 256 registers in scratch memory)
+                asm volatile("" : "+v"(acc[tap][0][0]), "+v"(acc[tap][0][1]), "+v"(acc[tap][1][0]), "+v"(acc[tap][1][1]));
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        };
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) d[t][q][kb] = read(dat(t, dp + q * 2 * DB + kb * 32), dat(t, dp + q * 2 * DB + kb * 32 + 256));
+        input(0, 0, 0, f[0]);
+        input(0, 0, 1, f[1]);
+        taps(std::integral_constant<int, 0>{}, std::integral_constant<int, 3>{});
+        lows += Stage::template stash_half<XB>(sx, 1.f, xe, spare);
+        Stage::fetch_dy(A, dy, kt, ta, sda);
+        Stage::fetch_dy(A, dy, kt, tb, sdb);
+        __builtin_amdgcn_sched_barrier(0);
+        taps(std::integral_constant<int, 3>{}, std::integral_constant<int, 6>{});
+        lows += Stage::template stash_half<DB>(sda, nsg, de, dspare);
+        lows += Stage::template stash_half<DB>(sdb, nsg, de, dspare + DBUF);
+        Stage::fetch_x(A, x, cg, tb, sx);
+        __builtin_amdgcn_sched_barrier(0);
+        taps(std::integral_constant<int, 6>{}, std::integral_constant<int, TAPS>{});
+        if (!more) break;
+        __syncthreads();                                        // every wavefront is done with the pair
+        lows += Stage::template stash_half<XB>(sx, 1.f, xe, tile[0]);
+        __syncthreads();
+        slot = (slot + 2) % 3;
+    }
+
+    // values below the pieces' range that the workgroup has met
+    misc = reinterpret_cast<unsigned *>(xlds + (slot + 2) % 3 * XBUF);          // (no one reads the third buffer now)
+    {
+        unsigned c = 0;
+        if (__ballot(lows != 0) != 0)
+            for (int l = 0; l < kWave; ++l) c += (unsigned)__builtin_amdgcn_readlane((int)lows, l);
+        if (lane == 0) misc[wave] = c;
+        __syncthreads();
+    }
+    if (!active) return;
+    const float safe = kHalfSafe * fminf(4.f * (float)(misc[0] + misc[1] + misc[2] + misc[3]) / (float)((u1 - u0) * TP), 1.f);
+
+    // D layout of a 16x16 block: column (c) = lane % 16, row (k) = 4*(lane/16) + r: four consecutive output channels, one 16-byte store,
+    // the lanes' side by side
+    const int k32 = kt * 64 + kh * 32, c32 = cg * 64 + ch * 32, exponent = -(xe + de);
+    float *pbase = part + (size_t)split * A.K * A.C * TAPS;
+    auto element = [&](int k, int c, int tap) __attribute__((always_inline)) {
+        return pbase + (((size_t)(k / kBlk) * CB + c / kBlk) * TAPS + tap) * (kBlk * kBlk) + (c % kBlk) * kBlk + k % kBlk;
+    };
+    auto finish = [&](float v) __attribute__((always_inline)) { return fabsf(v) < safe ? __builtin_nanf("") : ldexpf(v, exponent); };
+    bool finite = true;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+            const int k = k32 + kb * 16 + 4 * grp, c = c32 + cb * 16 + l16;
+            if (k >= A.K || c >= A.C) continue;
+#pragma unroll
+            for (int tap = 0; tap < TAPS; ++tap) {
+                const floatx4 a = acc[tap][kb][cb];
+                const float4 v = make_float4(finish(a[0]), finish(a[1]), finish(a[2]), finish(a[3]));
+                finite = finite && split_finite(v);
+                *reinterpret_cast<float4 *>(element(k, c, tap)) = v;
+            }
+        }
+    // sums that values outside the range of the pieces took part in
+    if (__builtin_expect(__ballot(!finite) != 0, 0)) {
+        split_lanes_fence();
+        floatx16 redo[TAPS];
+        bww_redo<R, S, TH, TW, 1>(A, x, dy, k32, c32, u0, u1, redo);
+        const int c = c32 + lane % 32;
+        if (c >= A.C) return;
+#pragma unroll
+        for (int tap = 0; tap < TAPS; ++tap)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int k = k32 + 8 * (r / 4) + 4 * (lane / 32) + r % 4;
@@ -1529,6 +1810,11 @@ constexpr int kBwwTargetWorkgroups = 512;
 // dense launches of at most this many tiles, one or two for a workgroup, take the SHORT form (with a workgroup's time in its
 // tiles it would cost 10 %: 512->512 @14, N = 4, 48 -> 53)
 constexpr int kBwwShortUnits = 16;
+// Unit-stride dense launches with this many tiles for a workgroup multiply f16 pieces.  In units of (1e-8 of the norm) squared T tiles err 54 + 2.9 T with
+// bf16 pieces, whose sums join once a tile, and 130 + 1.3 T with f16 ones (256->256 @56, N = 32, half zeros, T = 98, 1.85e-7 : 1.61e-7, at 50 / 90 %
+// 1.69e-7 : 1.62e-7, 128->256 @56, T = 49, 1.37e-7 : 1.36e-7, 512->512 @14, T = 28, 1.17e-7 : 1.28e-7).  Where fewer than 5 % of the products are not
+// zero sums have few terms to round, and a workgroup that samples that stays on bf16 pieces (90 / 90 %: 1.06e-7 : 1.17e-7)
+constexpr long long kBwwHalfTiles = 48;
 
 BwwArgs make_args(const st_conv_desc &d, int TH, int TW, bool tiles_over_input)
 {
@@ -1584,6 +1870,8 @@ bool bww_big_image(const BwwArgs &A)
     return big(A.H, A.W) || big(A.OH, A.OW);
 }
 
+bool bww_half_tiles(const BwwArgs &A) { return A.units >= kBwwHalfTiles * A.splits && !bww_big_image(A); }
+
 template <int TH, int TW>
 void launch_bww_dense_wide(const BwwArgs &A, const float *x, const float *dy, float *part, hipStream_t s)
 {
@@ -1591,6 +1879,7 @@ void launch_bww_dense_wide(const BwwArgs &A, const float *x, const float *dy, fl
     if (bww_big_image(A)) hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, false, true>), grid, dim3(256), 0, s, A, x, dy, part);
     else if (A.units <= kBwwShortUnits && A.units <= 2 * A.splits)
         hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, true, false>), grid, dim3(256), 0, s, A, x, dy, part);
+    else if (bww_half_tiles(A)) hipLaunchKernelGGL((bww_dense_half_kernel<TH, TW>), grid, dim3(256), 0, s, A, x, dy, part);
     else hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, false, false>), grid, dim3(256), 0, s, A, x, dy, part);
 }
 
@@ -1714,6 +2003,11 @@ size_t bww_sparse_workspace(const st_conv_desc &d)
 {
     if (d.R == 1 && d.S == 1) return partial_bytes(d, make_args_pw(d, 64 * pw_kpl(d), 64));
     return partial_bytes(d, sparse_args(d));
+}
+
+bool bww_dense_half(const st_conv_desc &d)
+{
+    return d.R == 3 && d.stride_w == 1 && bww_fast_supported(d) && bww_half_tiles(dense_args(d));
 }
 
 size_t bww_dense_workspace(const st_conv_desc &d)

@@ -209,6 +209,8 @@ size_t bww_sparse_dy_workspace(const st_conv_desc &d);
 hipError_t launch_bww_sparse_dy(const st_conv_desc &d, const float *x, const float *dy, float *dw,
                                 float *ws, hipStream_t s, const unsigned *sel = nullptr);
 size_t bww_dense_workspace(const st_conv_desc &d);
+// whether the dense 3x3 form multiplies f16 pieces
+bool bww_dense_half(const st_conv_desc &d);
 // st_conv_bww_auto in three launches (zero-skipping with either operand tested, dense, sum of the partials):
 // unit-stride 3x3 layers; ws holds max(splits) * K*C*S*R floats, at least one set
 bool bww_auto_merged_supported(const st_conv_desc &d);

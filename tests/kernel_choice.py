@@ -32,6 +32,13 @@ def f16_pieces(d, bwi=False):
     return _ask("fwd_dense_half", _correlation(d, bwi))
 
 
+def bww_f16_pieces(d):
+    """Whether the dense BWW forms its products from two f16 pieces."""
+    f = ctypes.CDLL(st.lib_path())["_ZN2st14bww_dense_halfERK12st_conv_desc"]
+    f.restype = ctypes.c_bool
+    return f(ctypes.byref(d._c()))
+
+
 def dense_kernel(d, bwi=False):
     """ "32" or "16": channels that the kernel on bf16 pieces takes at a time; for 1x1 layers also "lds", whole filters in LDS, and "fp32",
     both on fp32 matrix instructions."""

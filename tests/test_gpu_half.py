@@ -11,8 +11,9 @@ from oracle.st_ref import Geom
 pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
-    from tests.gpu_harness import DeviceLayer, desc_of
-    from tests.kernel_choice import f16_pieces
+    import paper_1911_10175_amd as st
+    from tests.gpu_harness import DeviceLayer, desc_of, workspace
+    from tests.kernel_choice import bww_f16_pieces, f16_pieces
     from tests.test_gpu_split import as_products, check, fma_chain, inputs, norm_error
 
 # whole launches of 4 and 5 stages, two shares, tiles of 64 and 128 pixels (the larger halo too), tiles over many images, stride 2
@@ -131,3 +132,103 @@ def test_error_of_ordinary_layers(channels, zeros):
     T = 9 * channels / 96
     bound = 1.2 * np.hypot(np.sqrt((12 + T) / (9 * channels * (1 - zeros))) * chain, 7.5e-8)
     assert err <= bound, f"{err:.3g}, bound {bound:.3g}, fp32 instructions {chain:.3g}"
+
+
+# BWW: (N, C, K, H, W, pad), 48 and more tiles for a workgroup.  Even and odd numbers of tiles, 4 x 8 and 2 x 14 pixels, ragged ends, channels that
+# fill no whole group of 64, shares of unequal length
+BWW = {
+    "1024->1024 @56x55, 49 tiles": (1, 1024, 1024, 56, 55, 1),
+    "1040->528 @14, 56": (24, 1040, 528, 14, 14, 1),
+    "528->1040 37x41 pad 2": (3, 528, 1040, 37, 41, 2),
+    "768->784 @31x29 pad 0": (5, 768, 784, 31, 29, 0),
+}
+
+
+def bww_inputs(N, C, K, H, W, pad, seed):
+    d = st.ConvDesc(N, C, K, H, W, 3, 3, 1, 1, pad, pad)
+    assert bww_f16_pieces(d), "another kernel: test is void"
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    x = torch.relu(torch.randn((N, C // 16, H, W, 16), device="cuda", generator=gen))
+    dy = torch.randn((N, K // 16, d.OH, d.OW, 16), device="cuda", generator=gen)
+    dy *= torch.rand(dy.shape, device="cuda", generator=gen) >= 0.5
+    return d, x, dy
+
+
+def bww_result(d, x, dy):
+    dw = torch.full((d.K // 16, d.C // 16, 3, 3, 16, 16), float("nan"), device="cuda")
+    st.st_conv_bww_dense(d, x, dy, dw, workspace(d, st.ST_PASS_BWW, True))
+    torch.cuda.synchronize()
+    return dw.permute(2, 3, 0, 5, 1, 4).reshape(3, 3, d.K, d.C).double()
+
+
+def bww_exact(d, x, dy):
+    """Result and sum of magnitudes in 64 bits, [v][u][k][c]."""
+    def plain(t):
+        return t.double().permute(1, 4, 0, 2, 3).reshape(t.shape[1] * 16, t.shape[0], t.shape[2], t.shape[3])
+    xp = torch.nn.functional.pad(plain(x), (d.pad_w, d.pad_w, d.pad_h, d.pad_h))
+    dyf = plain(dy).reshape(d.K, -1)
+    ref, mag = (torch.empty((3, 3, d.K, d.C), dtype=torch.float64, device="cuda") for _ in range(2))
+    for v in range(3):
+        for u in range(3):
+            cols = xp[:, :, v:v + d.OH, u:u + d.OW].reshape(d.C, -1).t()
+            ref[v, u], mag[v, u] = dyf @ cols, dyf.abs() @ cols.abs()
+    return ref, mag
+
+
+def bww_within_fp32_sum(d, x, dy, label):
+    got, (ref, mag) = bww_result(d, x, dy), bww_exact(d, x, dy)
+    n = d.N * d.OH * d.OW
+    off, bound = (got - ref).abs(), (n + 3) * 2.0 ** -24 * mag + n * 2.0 ** -150
+    assert bool((off <= bound).all()), f"{label}: {float((off / bound.clamp_min(1e-300)).max())} of the bound"
+
+
+@pytest.mark.parametrize("small", [1.0, 2.0 ** -13, 2.0 ** -27, 2.0 ** -60, 2.0 ** -120])
+@pytest.mark.parametrize("name", BWW)
+def test_bww_channels_and_pixels_of_very_different_scale(name, small):
+    """Every other channel of x and of dy, or of the first halves of the blocks, then every other row of pixels: gradients that only small
+    values take part in are as exact as the others."""
+    d, x, dy = bww_inputs(*BWW[name], 91)
+    xs, dys = x.clone(), dy.clone()
+    xs[..., 1::2] *= small
+    dys[..., ::2] *= small
+    bww_within_fp32_sum(d, xs, dy, f"{name} x {small}")
+    bww_within_fp32_sum(d, x, dys, f"{name} dy {small}")
+    if small > 2.0 ** -100:
+        bww_within_fp32_sum(d, xs, dys / small, f"{name} both {small}")
+    xs, dys = x.clone(), dy.clone()
+    xs[:, :, 1::2] *= small
+    dys[:, :, 1::2] = 0
+    bww_within_fp32_sum(d, xs, dys, f"{name} rows {small}")
+
+
+@pytest.mark.parametrize("name", ["1024->1024 @56x55, 49 tiles", "1040->528 @14, 56"])
+def test_bww_values_outside_the_pieces_and_zeros(name):
+    d, x, dy = bww_inputs(*BWW[name], 93)
+    bww_within_fp32_sum(d, torch.zeros_like(x), dy, "zeros")
+    for a, b in ((2.0 ** 100, 2.0 ** -90), (2.0 ** -110, 2.0 ** 90)):
+        bww_within_fp32_sum(d, x * a, dy * b, f"{a} {b}")
+    for big in (2.0 ** 4, 2.0 ** 9, 2.0 ** 60):                 # no sample is likely to see them; h is infinite from 2^5 on
+        xb = x.clone()
+        xb.view(-1)[[7, x.numel() // 2, x.numel() - 3]] = 5 * big
+        bww_within_fp32_sum(d, xb, dy, f"{big}")
+    one = torch.zeros_like(x)
+    one.view(-1)[x.numel() // 3] = 2.0 ** -126
+    bww_within_fp32_sum(d, one, dy, "one value")
+    xi = x.clone()
+    xi.view(-1)[x.numel() // 2] = float("inf")
+    got, ref = bww_result(d, xi, dy), bww_exact(d, xi, dy)[0]
+    assert torch.equal(torch.isfinite(got), torch.isfinite(ref))
+    fine = torch.isfinite(ref)
+    assert bool(((got - ref)[fine].abs() <= 1e-6 * ref[fine].abs().max()).all())
+
+
+def test_bww_workgroups_that_sample_few_products_stay_on_bf16_pieces():
+    """95 % zeros in x and in dy: the error that bf16 pieces leave, which two f16 pieces could not reach."""
+    d, x, dy = bww_inputs(1, 1024, 1024, 56, 55, 1, 95)
+    gen = torch.Generator(device="cuda").manual_seed(96)
+    x *= torch.rand(x.shape, device="cuda", generator=gen) < 0.1
+    dy *= torch.rand(dy.shape, device="cuda", generator=gen) < 0.1
+    ref = bww_exact(d, x, dy)[0]
+    err = float((bww_result(d, x, dy) - ref).norm() / ref.norm())
+    # 8 terms a gradient: 2.4e-8 for each rounding of a product or a sum, of which a join is one every fourth tile; f16 pieces alone leave out 7.5e-8
+    assert err <= 7e-8, err
