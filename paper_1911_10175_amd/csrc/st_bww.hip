@@ -2199,10 +2199,11 @@ hipError_t launch_bww_dense(const st_conv_desc &d, const float *x, const float *
     return reduce(d, A, part, dw, s);
 }
 
-// The 3x3 zero-skipping forms pass the dense one at about 96 % zeros (256->256 @56, N = 32, us, at 90 / 95 / 97 % zeros 577 / 502 / 427, dense
-// 475) or not at all.  The line is drawn at 75 %, not there: from 80 % on
-// this entry point has always been checked to test the sparser operand; between 75 % and the crossing it is up to a fifth slower for
-// that.
+// The 3x3 zero-skipping forms pass the dense one between 95 and 99 % zeros (N = 32, us, both with all launches of the entry point, zero-skipping at
+// 80 / 95 / 99 % : dense: 256->256 @56 667 / 507 / 292 : 461, @28 193 / 154 / 100 : 157, 64->64 @112 191 / 151 / 108 : 141; few channels, whose lanes
+// they do not fill, 16->32 @112 156 / 107 / 69 : 94, 9 x 16->176 @181 551 at 80 % : 252; 4 x 64->128 @24 30.8 / 27.5 / 24.6 : 25.8): 96 %, as far as
+// enough products are not zero (kSelThrFew).  Launches of less than 128 million multiply-adds keep the line of 75 % that checks of
+// this entry point have always asked for, 2 x 64->128 @24 at 80 % 27.4 : 22.
 // Launches of at most 128 tiles that give every workgroup one of them and write 24 MB of partial gradients or more are bound by
 // these, and the dense form's smaller tiles leave more of them (zero-skipping at 30 / 50 / 70 % zeros : dense: 208->256 @9
 // N = 4 26.6 / 25.8 / 24.8 : 30.8, 512->256 @10 N = 2 29.4 / 28.9 / 28.4 : 32.8, 256->256 @28 N = 1 32.9 / 32.0 / 31.1 : 36.3, 336->192
@@ -2216,7 +2217,8 @@ unsigned bww_sparse_threshold(const st_conv_desc &d)
     if (d.R == 1) return 1001;
     const BwwArgs A = dense_args(d);
     const long long partial_bytes = (long long)A.units * d.K * d.C * (9 * (int)sizeof(float));
-    return A.splits == A.units && A.units <= 128 && partial_bytes >= 24000000 ? 250 : 750;
+    if (A.splits == A.units && A.units <= 128 && partial_bytes >= 24000000) return 250;
+    return (double)d.N * A.OH * A.OW * d.C * d.K * 9. >= 128e6 ? 960 : 750;
 }
 
 }  // namespace st

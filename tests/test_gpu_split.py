@@ -435,3 +435,18 @@ def test_bww_of_images_with_long_sides(g):
     ref, ref_abs = st_ref.conv_bww(g, x, dy)
     off = np.abs(DeviceLayer(g, x, None, dy).bww(True) - ref)
     assert np.all(off <= (g.N * g.OH * g.OW + 3) * 2.0 ** -24 * ref_abs)
+
+
+@pytest.mark.parametrize("g,px,pdy,form", [(Geom(4, 64, 128, 24, 24, 3, 3, 1, 1, 1, 1), 0.85, 0.5, True), (Geom(4, 64, 128, 24, 24, 3, 3, 1, 1, 1, 1), 0.5, 0.85, True),
+                                           (Geom(4, 64, 128, 24, 24, 3, 3, 1, 1, 1, 1), 0.85, 0.85, False), (Geom(4, 64, 128, 24, 24, 3, 3, 1, 1, 1, 1), 0.0, 0.98, "dy"),
+                                           (Geom(4, 64, 128, 24, 24, 3, 3, 1, 1, 1, 1), 0.94, 0.0, True), (Geom(3, 64, 128, 24, 24, 3, 3, 1, 1, 1, 1), 0.85, 0.5, False)],
+                         ids=lambda v: f"N={v.N}" if isinstance(v, Geom) else str(v))
+def test_bww_auto_above_75_percent_zeros(g, px, pdy, form):
+    """From 128 million multiply-adds on (N = 4) bit for bit the dense form up to 96 % zeros in the sparser operand where at least 5 % of the products are
+    not zero; in smaller launches, or with fewer products, the zero-skipping form that tests it."""
+    x = stgen.relu_sparse(g.x_shape, px, 71) if px else stgen.normal(71, int(np.prod(g.x_shape))).reshape(g.x_shape).astype(np.float32)
+    dy = stgen.bernoulli_masked(g.y_shape, pdy, 72, 73)
+    L = DeviceLayer(g, x, None, dy)
+    got = L.bww("auto", raw=True)
+    assert torch.equal(got, L.bww(form, raw=True))
+    assert not torch.equal(got, L.bww(False if form is True else True, raw=True)), "forms indistinguishable: test is void"
