@@ -771,7 +771,7 @@ struct BwwWideStage {
     static __device__ __forceinline__ void ask(const float *t, int n, int cb, int CB, int h0, int w0, int H, int W, float4 (&to)[NP])
     {
         // (thread index the compiler cannot see through: see above)
-        int tid = threadIdx.x;
+        int tid = threadIdx.x % 256;
         asm volatile("" : "+v"(tid));
         const int q = tid & 15, pix0 = tid >> 4;
         const float *base = t + ((size_t)n * CB + cb) * H * W * kBlk;
@@ -809,7 +809,7 @@ struct BwwWideStage {
     // three bf16 pieces of a tile
     static __device__ __forceinline__ void stash(const float4 (&sd)[2], const float4 (&sx)[4], float sign, char *buf)
     {
-        int tid = threadIdx.x;
+        int tid = threadIdx.x % 256;
         asm volatile("" : "+v"(tid));
         const int q = tid & 15, pix0 = tid >> 4, at = pix0 * 64 + (q & 7) * 8;
         char *d = buf + (q >> 3) * DB + at, *h = buf + 6 * DB + (q >> 3) * XB + at;
@@ -826,7 +826,7 @@ struct BwwWideStage {
     template <int BYTES, int NP>
     static __device__ __forceinline__ unsigned stash_half(const float4 (&v)[NP], float sign, int e, char *buf)
     {
-        int tid = threadIdx.x;
+        int tid = threadIdx.x % 256;
         asm volatile("" : "+v"(tid));
         const int q = tid & 15, pix0 = tid >> 4;
         char *d = buf + (q >> 3) * BYTES + pix0 * 64 + (q & 7) * 8;
@@ -845,6 +845,44 @@ struct BwwWideStage {
     }
 };
 
+// A workgroup of the unit-stride kernels is one team of four wavefronts or, where more of these than compute units would run, two, which take tiles of
+// their own and add their sums up in LDS: what used to be two workgroups on a compute unit writes one set of partial gradients instead of two, and the
+// final sum reads half as many (75 MB each for 512 teams): 2 x 256->256 @28 36.8 -> 30.6 us, 32 x 256->256 @56 356 -> 338.
+// Tiles of the teams: first, then one past the last of each, steps = the most tiles of one of them.
+template <int TEAMS>
+struct BwwTeam {
+    int team, first, u0, u1, last, steps;
+    __device__ __forceinline__ BwwTeam(const BwwArgs &A)
+    {
+        team = TEAMS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / 256);
+        auto bound = [&](int i) __attribute__((always_inline)) {
+            return (int)((long long)A.units * min((int)blockIdx.x * TEAMS + i, A.splits) / A.splits);
+        };
+        first = bound(0);
+        last = bound(TEAMS);
+        u0 = bound(team);
+        u1 = bound(team + 1);
+        steps = TEAMS == 1 ? u1 - u0 : max(bound(1) - first, last - bound(1));
+    }
+    // the sums of both in those of the first; every thread makes the call.  False: nothing left to do
+    template <int N>
+    __device__ __forceinline__ bool join(floatx4 (&acc)[N][2][2], bool active, int wave, int lane, char *lds) const
+    {
+        if constexpr (TEAMS == 1) return active;
+        __syncthreads();                                        // every wavefront is done with its tiles
+        floatx4 *ex = reinterpret_cast<floatx4 *>(lds) + wave * (N * 4 * kWave) + lane;
+        if (team == 1 && active) {
+#pragma unroll
+            for (int t = 0; t < N * 4; ++t) ex[t * kWave] = acc[t / 4][t / 2 % 2][t % 2];
+        }
+        __syncthreads();
+        if (team == 1 || !active) return false;
+#pragma unroll
+        for (int t = 0; t < N * 4; ++t) acc[t / 4][t / 2 % 2][t % 2] += ex[t * kWave];
+        return true;
+    }
+};
+
 // The same for unit stride (the kernel above serves stride 2) with v_mfma_f32_16x16x32_bf16, 32 pixels (a whole tile) at a
 // time: it reaches 2050 TFLOP/s where 32x32x16 reaches 1760 (st_fwd_dense_wide.hpp), and its sum joins the running one once per
 // tile instead of once per 16 pixels.  A wavefront's 32 x 32 channels are 2 x 2 blocks of 16 x 16.  The registers are full (144 sums,
@@ -853,18 +891,20 @@ struct BwwWideStage {
 // 607 -> 542, @14 170 -> 154, 64->64 @224 614 -> 540, 128->128 @28 63.5 -> 61.6, one image 64->64 @14 14.4 -> 12.5; error against
 // 64 bits 2.55e-7 -> 1.86e-7, 2.72e-7 -> 2.03e-7, 1.46e-7 -> 1.15e-7, 2.62e-7 -> 1.95e-7, 9.3e-8 -> 8.2e-8, 4.5e-8 -> 3.8e-8.
 // Bound: power (see there) and, beside the products, splitting and stashing the next tile.
-// lds: two buffers of three pieces, which take turns
-template <int R, int S, int TH, int TW, bool SHORT, bool BIG>
-__device__ __forceinline__ void bww_dense_wide_body(const BwwArgs &A, const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part, char *lds)
+// lds_all: for each team two buffers of three pieces, which take turns
+template <int R, int S, int TH, int TW, bool SHORT, bool BIG, int TEAMS>
+__device__ __forceinline__ void bww_dense_wide_body(const BwwArgs &A, const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part, char *lds_all)
 {
     using Stage = BwwWideStage<TH, TW, BIG>;
     constexpr int HW = Stage::HW, TP = TH * TW, XB = Stage::XB, DB = Stage::DB;
 
     // the wavefront index is the same in every lane: kept in a scalar register, and with it every tile coordinate
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x % 256 / kWave), lane = threadIdx.x % kWave;
     const int l16 = lane % 16, grp = lane / 16;
     const int kh = wave % 2, ch = wave / 2;
-    const int split = blockIdx.x;
+    const BwwTeam<TEAMS> team(A);
+    const int u0 = team.u0, u1 = team.u1;
+    char *const lds = lds_all + team.team * (2 * Stage::bytes(3));
     const int kt = blockIdx.y / A.cgroups, cg = blockIdx.y % A.cgroups;
     const int CB = A.C / kBlk;
     const bool active = kt * 64 + kh * 32 < A.K && cg * 64 + ch * 32 < A.C;
@@ -876,9 +916,6 @@ __device__ __forceinline__ void bww_dense_wide_body(const BwwArgs &A, const floa
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb) acc[t][kb][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-    const int u0 = (int)((long long)A.units * split / A.splits);
-    const int u1 = (int)((long long)A.units * (split + 1) / A.splits);
 
     // the next tile is written into the other buffer: one barrier a tile (256->256 @56 502 -> 490; a piece after each of the last taps
     // has no registers, 76 spilled, 514)
@@ -905,12 +942,14 @@ __device__ __forceinline__ void bww_dense_wide_body(const BwwArgs &A, const floa
         }
     }
 
-    fetch();                                                 // (a split has at least one tile)
-    Stage::stash(sd, sx, sign(u0), lds);
+    if (TEAMS == 1 || u0 < u1) {                             // (one team has at least one tile)
+        fetch();
+        Stage::stash(sd, sx, sign(u0), lds);
+    }
     __syncthreads();
     for (int unit = u0; unit < u1; ++unit) {
         char *const buf = lds + (unit - u0) % 2 * Stage::bytes(3);
-        if (unit + 1 < u1) fetch();                  // in flight during this tile's MFMAs
+        if (unit + 1 < u1) fetch();                          // in flight during this tile's MFMAs
         if (active) {
             const float sg = sign(unit);
             auto at = [&](int offset) __attribute__((always_inline)) { return (LdsTr)(buf + offset); };
@@ -973,16 +1012,18 @@ __device__ __forceinline__ void bww_dense_wide_body(const BwwArgs &A, const floa
                         for (int r = 0; r < 4; ++r) acc[tap][kb][cb][r] = __builtin_fmaf(t[kb][cb][r], sg, acc[tap][kb][cb][r]);
             });
         }
-        if (unit + 1 == u1) break;
-        Stage::stash(sd, sx, sign(unit + 1), lds + (unit + 1 - u0) % 2 * Stage::bytes(3));
-        __syncthreads();
+        if (unit + 1 - u0 == team.steps) break;
+        if (TEAMS == 1 || unit + 1 < u1) Stage::stash(sd, sx, sign(unit + 1), lds + (unit + 1 - u0) % 2 * Stage::bytes(3));
+        __syncthreads();                                     // (as often by a team of one tile less: not after the other's last)
     }
-    if (!active) return;
+    if (TEAMS > 1)
+        for (int i = u1 - u0; i + 1 < team.steps; ++i) __syncthreads();         // a team without tiles
+    if (!team.join(acc, active, wave, lane, lds_all)) return;
 
     // D layout of a 16x16 block: column (c) = lane % 16, row (k) = 4*(lane/16) + r: four consecutive output channels, one 16-byte store,
     // the lanes' side by side
     const int k32 = kt * 64 + kh * 32, c32 = cg * 64 + ch * 32;
-    float *pbase = part + (size_t)split * A.K * A.C * (S * R);
+    float *pbase = part + (size_t)blockIdx.x * A.K * A.C * (S * R);
     auto element = [&](int k, int c, int tap) __attribute__((always_inline)) {
         return pbase + (((size_t)(k / kBlk) * CB + c / kBlk) * (S * R) + tap) * (kBlk * kBlk) + (c % kBlk) * kBlk + k % kBlk;
     };
@@ -1005,7 +1046,7 @@ __device__ __forceinline__ void bww_dense_wide_body(const BwwArgs &A, const floa
     if (__builtin_expect(__ballot(!finite) != 0, 0)) {
         split_lanes_fence();
         floatx16 redo[S * R];
-        bww_redo<R, S, TH, TW, 1>(A, x, dy, k32, c32, u0, u1, redo);
+        bww_redo<R, S, TH, TW, 1>(A, x, dy, k32, c32, team.first, team.last, redo);
         const int c = c32 + lane % 32;
         if (c >= A.C) return;
 #pragma unroll
@@ -1018,13 +1059,13 @@ __device__ __forceinline__ void bww_dense_wide_body(const BwwArgs &A, const floa
     }
 }
 
-template <int R, int S, int TH, int TW, bool SHORT, bool BIG>
-__global__ __launch_bounds__(256, 2) void bww_dense_wide_kernel(BwwArgs A, const float *__restrict__ x,
-                                                                const float *__restrict__ dy, float *__restrict__ part)
+template <int R, int S, int TH, int TW, bool SHORT, bool BIG, int TEAMS>
+__global__ __launch_bounds__(256 * TEAMS, 2) void bww_dense_wide_kernel(BwwArgs A, const float *__restrict__ x,
+                                                                        const float *__restrict__ dy, float *__restrict__ part)
 {
     if (deselected(A.sel, A.want)) return;              // uniform over the grid, before any barrier
-    __shared__ __attribute__((aligned(16))) char lds[2 * BwwWideStage<TH, TW>::bytes(3)];
-    bww_dense_wide_body<R, S, TH, TW, SHORT, BIG>(A, x, dy, part, lds);
+    __shared__ __attribute__((aligned(16))) char lds[TEAMS * 2 * BwwWideStage<TH, TW>::bytes(3)];
+    bww_dense_wide_body<R, S, TH, TW, SHORT, BIG, TEAMS>(A, x, dy, part, lds);
 }
 
 // The same with two f16 pieces (st_split.hpp) where a workgroup has many tiles (kBwwHalfTiles): three products instead of six.  N = 32, half zeros, us:
@@ -1035,34 +1076,34 @@ __global__ __launch_bounds__(256, 2) void bww_dense_wide_kernel(BwwArgs A, const
 // it is split: the halo of its first tile into the third of three buffers that take turns, both dy tiles into the second pair of buffers, the halo
 // of the second tile into the first buffer when this pair is done (two barriers a pair).  (24 registers, two steps: 20 spilled, 345 -> 372 us.)
 // A tap of a tile is three groups of four instructions; the large and the small products have a sum each.
-template <int TH, int TW>
-__global__ __launch_bounds__(256, 2) void bww_dense_half_kernel(BwwArgs A, const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part)
+template <int TH, int TW, int TEAMS>
+__global__ __launch_bounds__(256 * TEAMS, 2) void bww_dense_half_kernel(BwwArgs A, const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part)
 {
     constexpr int R = 3, S = 3, TAPS = R * S;
     using Stage = BwwWideStage<TH, TW>;
     if (deselected(A.sel, A.want)) return;              // uniform over the grid, before any barrier
     constexpr int HW = Stage::HW, TP = TH * TW, XB = Stage::XB, DB = Stage::DB, XBUF = 4 * XB, DBUF = 4 * DB, LDS = 3 * XBUF + 4 * DBUF;
-    static_assert(LDS >= 2 * Stage::bytes(3) && 2 * LDS <= 160 * 1024, "either form in one array, two workgroups a compute unit");
-    __shared__ __attribute__((aligned(16))) char lds[LDS];
-    unsigned *misc = reinterpret_cast<unsigned *>(lds);         // before the first tile and after the last
+    static_assert(LDS >= 2 * Stage::bytes(3) && 2 * LDS <= 160 * 1024, "either form in one array, two teams a compute unit");
+    __shared__ __attribute__((aligned(16))) char lds_all[TEAMS * LDS];
+    unsigned *misc = reinterpret_cast<unsigned *>(lds_all);     // before the first tile
 
     // the wavefront index is the same in every lane: kept in a scalar register, and with it every tile coordinate
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x % 256 / kWave), lane = threadIdx.x % kWave;
     const int l16 = lane % 16, grp = lane / 16;
     const int kh = wave % 2, ch = wave / 2;
-    const int split = blockIdx.x;
+    const BwwTeam<TEAMS> team(A);
+    const int u0 = team.u0, u1 = team.u1;
+    char *const lds = lds_all + team.team * LDS;
     const int kt = blockIdx.y / A.cgroups, cg = blockIdx.y % A.cgroups;
     const int CB = A.C / kBlk, KB = A.K / kBlk;
     const bool active = kt * 64 + kh * 32 < A.K && cg * 64 + ch * 32 < A.C;
 
-    const int u0 = (int)((long long)A.units * split / A.splits);
-    const int u1 = (int)((long long)A.units * (split + 1) / A.splits);
-
-    // a sample for the scales: the first pixels of 16 tiles
+    // a sample for the scales, which the teams share: the first pixels of 16 tiles for each of them
     int xe, de;
     {
-        const int slot = threadIdx.x / 16, q = threadIdx.x % 16;
-        const int u = u0 + (int)((long long)(u1 - u0) * slot / 16);
+        constexpr int SLOTS = 16 * TEAMS, WAVES = 4 * TEAMS;
+        const int slot = threadIdx.x / 16, q = threadIdx.x % 16, w = team.team * 4 + wave;
+        const int u = team.first + (int)((long long)(team.last - team.first) * slot / SLOTS);
         const int tw = u % A.tiles_w, th = u / A.tiles_w % A.tiles_h, n = u / A.tiles_w / A.tiles_h;
         const int cb = min(cg * 4 + q / 4, CB - 1), kb = min(kt * 4 + q / 4, KB - 1);
         const float4 vx = *reinterpret_cast<const float4 *>(x + act_off(n, cb, min(th * TH, A.H - 1), min(tw * TW, A.W - 1), CB, A.H, A.W) + q % 4 * 4);
@@ -1072,15 +1113,22 @@ __global__ __launch_bounds__(256, 2) void bww_dense_half_kernel(BwwArgs A, const
             return (unsigned)(__popcll(__ballot(v.x != 0.f)) + __popcll(__ballot(v.y != 0.f)) + __popcll(__ballot(v.z != 0.f)) + __popcll(__ballot(v.w != 0.f)));
         };
         const unsigned fx = filled(vx), fd = filled(vd);
-        if (lane == 0) { misc[wave] = mx; misc[4 + wave] = md; misc[8 + wave] = fx; misc[12 + wave] = fd; }
+        if (lane == 0) { misc[w] = mx; misc[8 + w] = md; misc[16 + w] = fx; misc[24 + w] = fd; }
         __syncthreads();
-        const unsigned products = (misc[8] + misc[9] + misc[10] + misc[11]) * (misc[12] + misc[13] + misc[14] + misc[15]);
-        const unsigned bits_x = max(max(misc[0], misc[1]), max(misc[2], misc[3])), bits_d = max(max(misc[4], misc[5]), max(misc[6], misc[7]));
+        unsigned bits_x = 0, bits_d = 0, sum_x = 0, sum_d = 0;
+#pragma unroll
+        for (int i = 0; i < WAVES; ++i) {
+            bits_x = max(bits_x, misc[i]);
+            bits_d = max(bits_d, misc[8 + i]);
+            sum_x += misc[16 + i];
+            sum_d += misc[24 + i];
+        }
+        const unsigned products = sum_x * sum_d;
         xe = __builtin_amdgcn_readfirstlane(half_exponent(bits_x));
         de = __builtin_amdgcn_readfirstlane(half_exponent(bits_d));
         __syncthreads();                                        // (misc is overwritten from here on)
-        if ((unsigned)__builtin_amdgcn_readfirstlane((int)products) < (1u << 20) / 20) {        // of 1024 x 1024
-            bww_dense_wide_body<R, S, TH, TW, false, false>(A, x, dy, part, lds);
+        if ((unsigned)__builtin_amdgcn_readfirstlane((int)products) < (unsigned)(TEAMS * TEAMS) * ((1u << 20) / 20)) {         // of 1024 x 1024 a team
+            bww_dense_wide_body<R, S, TH, TW, false, false, TEAMS>(A, x, dy, part, lds_all);
             return;
         }
     }
@@ -1095,6 +1143,7 @@ __global__ __launch_bounds__(256, 2) void bww_dense_half_kernel(BwwArgs A, const
     auto sign = [](int pair) __attribute__((always_inline)) { return pair % 2 ? -1.f : 1.f; };
     typename Stage::Tile ta, tb;                                // the two tiles to ask for next
     ta.start(A, u0);
+    if (TEAMS > 1 && u0 == u1) { ta.n = 0; ta.th = 40000 / TH; }                // (a team without tiles)
     tb = ta;
     // a second tile that does not exist: rows that no image of these sizes has, all zeros
     auto second = [&](int unit) __attribute__((always_inline)) {
@@ -1110,7 +1159,7 @@ __global__ __launch_bounds__(256, 2) void bww_dense_half_kernel(BwwArgs A, const
     float4 sx[4], sda[2], sdb[2];
     unsigned lows = 0;
     char *const xlds = lds, *const dlds = lds + 3 * XBUF;
-    Stage::fetch_x(A, x, cg, ta, sx);                           // (a split has at least one tile)
+    Stage::fetch_x(A, x, cg, ta, sx);
     lows += Stage::template stash_half<XB>(sx, 1.f, xe, xlds);
     second(u0 + 1);
     Stage::fetch_dy(A, dy, kt, ta, sda);
@@ -1135,7 +1184,7 @@ __global__ __launch_bounds__(256, 2) void bww_dense_half_kernel(BwwArgs A, const
     }
     int slot = 0;                                               // buffer of the pair's first tile; the second one's is the next
     for (int unit = u0, pair = 0;; unit += 2, ++pair) {
-        const bool more = unit + 2 < u1;
+        const bool more = 2 * pair + 2 < team.steps;
         char *const tile[2] = {xlds + slot * XBUF, xlds + (slot + 1) % 3 * XBUF}, *const spare = xlds + (slot + 2) % 3 * XBUF;
         char *const dtile = dlds + pair % 2 * (2 * DBUF), *const dspare = dlds + (1 - pair % 2) * (2 * DBUF);
         // (no branches around what follows, also not for a last pair's successor or for wavefronts without channels of their own, which multiply
@@ -1215,22 +1264,27 @@ __global__ __launch_bounds__(256, 2) void bww_dense_half_kernel(BwwArgs A, const
         slot = (slot + 2) % 3;
     }
 
-    // values below the pieces' range that the workgroup has met
-    misc = reinterpret_cast<unsigned *>(xlds + (slot + 2) % 3 * XBUF);          // (no one reads the third buffer now)
+    // values below the pieces' range that the workgroup has met, behind what the teams exchange (one team: in the third halo buffer, which no one reads now)
+    static_assert(TEAMS == 1 || TEAMS * LDS >= 4 * TAPS * 4 * kWave * 16 + 32, "room for both");
+    misc = reinterpret_cast<unsigned *>(TEAMS == 1 ? xlds + (slot + 2) % 3 * XBUF : lds_all + 4 * TAPS * 4 * kWave * 16);
     {
         unsigned c = 0;
         if (__ballot(lows != 0) != 0)
             for (int l = 0; l < kWave; ++l) c += (unsigned)__builtin_amdgcn_readlane((int)lows, l);
-        if (lane == 0) misc[wave] = c;
-        __syncthreads();
+        if (TEAMS > 1) __syncthreads();                         // (the second team's last pair may lie there)
+        if (lane == 0) misc[team.team * 4 + wave] = c;
+        if (TEAMS == 1) __syncthreads();
     }
-    if (!active) return;
-    const float safe = kHalfSafe * fminf(4.f * (float)(misc[0] + misc[1] + misc[2] + misc[3]) / (float)((u1 - u0) * TP), 1.f);
+    if (!team.join(acc, active, wave, lane, lds_all)) return;
+    unsigned lost = 0;
+#pragma unroll
+    for (int i = 0; i < 4 * TEAMS; ++i) lost += misc[i];
+    const float safe = kHalfSafe * fminf(4.f * (float)lost / (float)((team.last - team.first) * TP), 1.f);
 
     // D layout of a 16x16 block: column (c) = lane % 16, row (k) = 4*(lane/16) + r: four consecutive output channels, one 16-byte store,
     // the lanes' side by side
     const int k32 = kt * 64 + kh * 32, c32 = cg * 64 + ch * 32, exponent = -(xe + de);
-    float *pbase = part + (size_t)split * A.K * A.C * TAPS;
+    float *pbase = part + (size_t)blockIdx.x * A.K * A.C * TAPS;
     auto element = [&](int k, int c, int tap) __attribute__((always_inline)) {
         return pbase + (((size_t)(k / kBlk) * CB + c / kBlk) * TAPS + tap) * (kBlk * kBlk) + (c % kBlk) * kBlk + k % kBlk;
     };
@@ -1254,7 +1308,7 @@ __global__ __launch_bounds__(256, 2) void bww_dense_half_kernel(BwwArgs A, const
     if (__builtin_expect(__ballot(!finite) != 0, 0)) {
         split_lanes_fence();
         floatx16 redo[TAPS];
-        bww_redo<R, S, TH, TW, 1>(A, x, dy, k32, c32, u0, u1, redo);
+        bww_redo<R, S, TH, TW, 1>(A, x, dy, k32, c32, team.first, team.last, redo);
         const int c = c32 + lane % 32;
         if (c >= A.C) return;
 #pragma unroll
@@ -1872,15 +1926,30 @@ bool bww_big_image(const BwwArgs &A)
 
 bool bww_half_tiles(const BwwArgs &A) { return A.units >= kBwwHalfTiles * A.splits && !bww_big_image(A); }
 
-template <int TH, int TW>
+// Teams of a workgroup of the unit-stride kernels (BwwTeam).  The two share their barriers, which costs more than the partial gradients from some eight
+// tiles on (one : two, us, tiles a team: 16 x 128->128 @28, 4, 42.1 : 38.7, N = 32, 7, 58 : 54, 32 x 512->512 @14, 28, 148 : 150) unless they multiply f16 pieces
+// (256->256 @56 356 : 338).  Where a group of 64 channels has at most 32, half of a team's wavefronts only stage, and two such teams on a
+// compute unit leave it to others with two full ones (27 x 288->80 @39x8, 6, 41.3 : 43.0): up to two tiles only, and not where both channel counts end like
+// that (5 x 144->304 @8x12 27.0 : 22.1, 3 x 80->48 @37x53 23.8 : 22.3, 20 x 48->32 @33x12 22.5 : 20.1, 5 x 112->224 @21 28.5 : 29.0, but 3 x 80->32 @54
+// 20.2 : 23.1).
+int bww_teams(const BwwArgs &A)
+{
+    if (A.splits == 1 || A.splits * ceil_div(A.K, 64) * A.cgroups <= 256) return 1;
+    const int tiles = ceil_div(A.units, A.splits);
+    auto full = [](int channels) { return (channels + 63) % 64 >= 32; };
+    if (tiles <= 2) return full(A.C) || full(A.K) ? 2 : 1;
+    return full(A.C) && full(A.K) && (tiles <= 8 || bww_half_tiles(A)) ? 2 : 1;
+}
+
+template <int TH, int TW, int TEAMS>
 void launch_bww_dense_wide(const BwwArgs &A, const float *x, const float *dy, float *part, hipStream_t s)
 {
-    const dim3 grid(A.splits, ceil_div(A.K, 64) * A.cgroups);
-    if (bww_big_image(A)) hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, false, true>), grid, dim3(256), 0, s, A, x, dy, part);
+    const dim3 grid(ceil_div(A.splits, TEAMS), ceil_div(A.K, 64) * A.cgroups), block(256 * TEAMS);
+    if (bww_big_image(A)) hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, false, true, TEAMS>), grid, block, 0, s, A, x, dy, part);
     else if (A.units <= kBwwShortUnits && A.units <= 2 * A.splits)
-        hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, true, false>), grid, dim3(256), 0, s, A, x, dy, part);
-    else if (bww_half_tiles(A)) hipLaunchKernelGGL((bww_dense_half_kernel<TH, TW>), grid, dim3(256), 0, s, A, x, dy, part);
-    else hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, false, false>), grid, dim3(256), 0, s, A, x, dy, part);
+        hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, true, false, TEAMS>), grid, block, 0, s, A, x, dy, part);
+    else if (bww_half_tiles(A)) hipLaunchKernelGGL((bww_dense_half_kernel<TH, TW, TEAMS>), grid, block, 0, s, A, x, dy, part);
+    else hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, false, false, TEAMS>), grid, block, 0, s, A, x, dy, part);
 }
 
 template <int TH, int TW, int PSTEP>
@@ -1892,12 +1961,18 @@ void launch_bww_dense_tiles(const BwwArgs &A, const float *x, const float *dy, f
     else hipLaunchKernelGGL((bww_dense_kernel<3, 3, TH, TW, PSTEP, false>), grid, dim3(256), 0, s, A, x, dy, part);
 }
 
+// partial gradients a launch of it writes (the workspace query counts one for each team)
+int bww_dense_partials(const st_conv_desc &d, const BwwArgs &A) { return bww_s2(d) ? A.splits : ceil_div(A.splits, bww_teams(A)); }
+
 // the 3x3 dense kernel with A = dense_args(d)
 hipError_t launch_bww_dense_3x3(const st_conv_desc &d, const BwwArgs &A, const float *x, const float *dy, float *part, hipStream_t s)
 {
     if (bww_s2(d)) launch_bww_dense_tiles<kDenseS2TH, kDenseS2TW, 2>(A, x, dy, part, s);
-    else if (dense_wide(d)) launch_bww_dense_wide<kDenseWideTH, kDenseWideTW>(A, x, dy, part, s);
-    else launch_bww_dense_wide<kDenseTH, kDenseTW>(A, x, dy, part, s);
+    else if (dense_wide(d)) {
+        if (bww_teams(A) == 2) launch_bww_dense_wide<kDenseWideTH, kDenseWideTW, 2>(A, x, dy, part, s);
+        else launch_bww_dense_wide<kDenseWideTH, kDenseWideTW, 1>(A, x, dy, part, s);
+    } else if (bww_teams(A) == 2) launch_bww_dense_wide<kDenseTH, kDenseTW, 2>(A, x, dy, part, s);
+    else launch_bww_dense_wide<kDenseTH, kDenseTW, 1>(A, x, dy, part, s);
     return hipGetLastError();
 }
 
@@ -2162,7 +2237,7 @@ hipError_t launch_bww_auto_merged(const st_conv_desc &d, const float *x, const f
     if ((err = launch_bww_dense_3x3(d, A2, x, dy, ws, s)) != hipSuccess) return err;
     const size_t n4 = (size_t)d.K * d.C * d.S * d.R / 4;
     const size_t nblk = (n4 + 63) / 64;
-    Splits3 sp = {{A0.splits, A1.splits, A2.splits}};
+    Splits3 sp = {{A0.splits, A1.splits, bww_dense_partials(d, A2)}};
     hipLaunchKernelGGL(bww_reduce_kernel, dim3((unsigned)(nblk < kReduceGrid ? nblk : kReduceGrid)), dim3(1024), 0, s,
                        reinterpret_cast<const float4 *>(ws), reinterpret_cast<float4 *>(dw), n4, sp, sel, direct ? 2 : kAnyForm);
     return hipGetLastError();
@@ -2193,9 +2268,11 @@ hipError_t launch_bww_dense(const st_conv_desc &d, const float *x, const float *
     }
     BwwArgs A = dense_args(d);
     A.sel = sel; A.want = 2;
-    float *part = A.splits == 1 ? dw : ws;
+    const int partials = bww_dense_partials(d, A);
+    float *part = partials == 1 ? dw : ws;
     hipError_t e = launch_bww_dense_3x3(d, A, x, dy, part, s);
     if (e != hipSuccess) return e;
+    A.splits = partials;
     return reduce(d, A, part, dw, s);
 }
 

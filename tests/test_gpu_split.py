@@ -450,3 +450,26 @@ def test_bww_auto_above_75_percent_zeros(g, px, pdy, form):
     got = L.bww("auto", raw=True)
     assert torch.equal(got, L.bww(form, raw=True))
     assert not torch.equal(got, L.bww(False if form is True else True, raw=True)), "forms indistinguishable: test is void"
+
+
+@pytest.mark.parametrize("zeros", [0.0, 0.7])
+@pytest.mark.parametrize("g", [Geom(2, 256, 256, 28, 28, 3, 3, 1, 1, 1, 1), Geom(1, 512, 512, 14, 14, 3, 3, 1, 1, 1, 1), Geom(5, 144, 304, 8, 12, 3, 3, 1, 1, 1, 1),
+                               Geom(3, 80, 48, 37, 53, 3, 3, 1, 1, 1, 1), Geom(16, 128, 128, 28, 28, 3, 3, 1, 1, 1, 1), Geom(4, 432, 48, 19, 19, 3, 3, 1, 1, 2, 2)],
+                         ids=lambda g: f"{g.N}x{g.C}to{g.K} {g.H}" if isinstance(g, Geom) else "")
+def test_bww_of_two_teams_in_a_workgroup(g, zeros):
+    """Teams of 1, 2, 4 and 5 tiles, even and odd numbers of teams (7: the last one has no partner), channel counts that leave wavefronts without any;
+    the direct call and the self-selecting one, whose final sum is another launch; an infinity in the second team's tiles."""
+    x = stgen.relu_sparse(g.x_shape, zeros, 81) if zeros else stgen.normal(81, int(np.prod(g.x_shape))).reshape(g.x_shape).astype(np.float32)
+    dy = stgen.bernoulli_masked(g.y_shape, 0.5, 82, 83)
+    L = DeviceLayer(g, x, None, dy)
+    ref, ref_abs = st_ref.conv_bww(g, x, dy)
+    bound = (g.N * g.OH * g.OW + 3) * 2.0 ** -24 * ref_abs
+    first = L.bww(True)
+    assert np.all(np.abs(first - ref) <= bound)
+    assert np.all(np.abs(L.bww("auto") - ref) <= bound)
+    assert np.array_equal(first, L.bww(True)), "two runs differ"
+    x[-1, 3, -2, 1] = np.inf
+    ref = st_ref.conv_bww(g, x, dy)[0]
+    got = DeviceLayer(g, x, None, dy).bww(True)
+    fine = np.isfinite(ref)
+    assert np.array_equal(np.isfinite(got), fine) and np.all(np.abs(got[fine] - ref[fine]) <= bound[fine])
