@@ -169,6 +169,7 @@ bool fwd_dense_supported(const Geom &g);
 // the dense kernel reads filters from a reformatted copy (fwd_dense_filter_bytes) written by
 // launch_reformat_filters; transpose selects the BWI form (channel roles swapped, taps reversed)
 size_t fwd_dense_filter_bytes(const Geom &g);
+size_t fwd_dense_copy_units(const Geom &g);
 // whole workspace of the dense form: the filter copy, then the partial outputs of launches whose
 // reduction is split over workgroups (few pixel tiles)
 size_t fwd_dense_workspace_bytes(const Geom &g);

@@ -183,7 +183,7 @@ __device__ __forceinline__ void stage_filters_block(size_t block, int Ko, int Ci
 __device__ __forceinline__ void half_filters_block(size_t block, int Ko, int Ci, int S, int R, int transpose, const float *__restrict__ w,
                                                    float *__restrict__ wd, unsigned *red)
 {
-    const int TAPS = S * R, CiB = Ci / kBlk, KoB = Ko / kBlk, NS = CiB / 2;
+    const int TAPS = S * R, CiB = Ci / kBlk, KoB = Ko / kBlk, NS = (CiB + 1) / 2;
     const int l16 = threadIdx.x % 16, grp = threadIdx.x / 16 % 4, kh = threadIdx.x / kWave % 2;
     const size_t step = block * 2 + threadIdx.x / 128;  // (kb32 * NS + stage) * TAPS + tap: 4 blocks of 32 k, an even number
     size_t t = step;
@@ -195,7 +195,8 @@ __device__ __forceinline__ void half_filters_block(size_t block, int Ko, int Ci,
     };
     float4 lo = make_float4(0.f, 0.f, 0.f, 0.f), hi = lo, sample[2] = {lo, lo};
     if (kb < KoB) {
-        if (!transpose) {
+        if (cb >= CiB) {                                // zeros beside an odd last block
+        } else if (!transpose) {
             const float *p = filters_of(kb, cb, tap) + c0 * kBlk + l16;
             lo = make_float4(p[0], p[kBlk], p[2 * kBlk], p[3 * kBlk]);
             hi = make_float4(p[4 * kBlk], p[5 * kBlk], p[6 * kBlk], p[7 * kBlk]);
@@ -221,7 +222,7 @@ __device__ __forceinline__ void half_filters_block(size_t block, int Ko, int Ci,
     const unsigned lows = __popcll(__ballot(half_low(lo, key) != 0)) + __popcll(__ballot(half_low(hi, key) != 0));
     if (threadIdx.x % kWave == 0) red[4 + wave] = lows;
     __syncthreads();
-    int *notes = reinterpret_cast<int *>(wd) + half_notes(Ko, Ci * TAPS);
+    int *notes = reinterpret_cast<int *>(wd) + half_notes(Ko, NS * (2 * kBlk * TAPS));
     if (threadIdx.x % 128 == 0) {
         notes[kb32] = e;                                // (the same value from every step)
         notes[half_blocks(Ko) + step] = (int)(red[4 + wave] + red[5 + wave]);

@@ -69,7 +69,7 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
     const int l16 = lane % 16, grp = lane / 16;
     const int kqi = wave % KQ, tqi = wave / KQ;
     const int kg = wg % kgroups, tile = wg / kgroups;
-    const int CiB = g.Ci / kBlk, KoB = g.Ko / kBlk, NS = CiB / 2;
+    const int CiB = g.Ci / kBlk, KoB = g.Ko / kBlk, NS = (CiB + 1) / 2;      // (HALF: the last stage may have one block only)
 
     // strip of the tile, its columns c0 .. c0+w-1 and its pixels q0 .. of npx
     const int strip = tile % fq.strips, ti = tile / fq.strips;
@@ -133,12 +133,14 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
     const size_t plane = (size_t)HW * kBlk;
     const float *in0 = in + (size_t)n0 * CiB * plane + threadIdx.x % 4 * 4;
     float4 hreg[NLD];
+    auto absent = [&](int st) __attribute__((always_inline)) { return HALF && 2 * st + sblock >= CiB; };
     // (unconditional loads, padding from a block of zeros: a load under a condition is waited for where the condition ends)
     auto fetch = [&](int st) __attribute__((always_inline)) {
         const float *base = in0 + 2 * st * plane;
+        const bool none = absent(st);
 #pragma unroll
         for (int jj = 0; jj < NLD; ++jj) {
-            const float *src = poff[jj] < 0 ? kSplitZeros : base + (size_t)(unsigned)poff[jj] * kBlk;
+            const float *src = poff[jj] < 0 || none ? kSplitZeros : base + (size_t)(unsigned)poff[jj] * kBlk;
             hreg[jj] = *reinterpret_cast<const float4 *>(src);
         }
     };
@@ -184,7 +186,7 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
     if constexpr (HALF) {
         // the first stage and, spread over the others, a piece of each lane
         const int st = st0 + (int)((threadIdx.x / 4u) % (unsigned)(st1 - st0));
-        const float *src = poff[0] < 0 ? kSplitZeros : in0 + 2 * st * plane + (size_t)(unsigned)poff[0] * kBlk;
+        const float *src = poff[0] < 0 || absent(st) ? kSplitZeros : in0 + 2 * st * plane + (size_t)(unsigned)poff[0] * kBlk;
         unsigned m = half_magnitude(*reinterpret_cast<const float4 *>(src));
 #pragma unroll
         for (int jj = 0; jj < NLD; ++jj) m = max(m, half_magnitude(hreg[jj]));
@@ -307,7 +309,7 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
     int exponent = 0;
     float safe = 0.f;                                   // HALF: smaller outputs do not count
     if constexpr (HALF) {
-        const int *notes = reinterpret_cast<const int *>(wd) + half_notes(g.Ko, g.Ci * TAPS);
+        const int *notes = reinterpret_cast<const int *>(wd) + half_notes(g.Ko, NS * (kStageC * TAPS));
         exponent = -(xe + notes[kb32]);
         float least = kHalfSafe;
 #pragma unroll
@@ -354,7 +356,7 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
             if (__ballot(!finite[pb]) == 0) continue;
             int n, oh, ow;
             const bool valid = where(qs + pb * 32 + lane % 32, n, oh, ow);
-            split_redo_corr(g, in, out, valid, n, oh, ow, kb32, 2 * st0, 2 * st1);
+            split_redo_corr(g, in, out, valid, n, oh, ow, kb32, 2 * st0, min(2 * st1, CiB));
         }
     }
 }

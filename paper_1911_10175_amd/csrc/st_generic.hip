@@ -291,7 +291,7 @@ hipError_t launch_auto_prepare(const Geom &g, bool transpose, const float *act, 
     a.wide = fwd_dense_wide(g) ? 1 : 0;
     a.half = fwd_dense_half(g) ? 1 : 0;
     const long long n_wave = fwd_direct(g) ? 0 : (long long)a.KB * a.CB;
-    a.total_dense = fwd_dense_filter_bytes(g) / 48;
+    a.total_dense = fwd_dense_copy_units(g);
     const long long n_dense = (long long)((a.total_dense + 255) / 256);
     if (n_wave + n_dense + kSampleParts > 0x7fffffffLL) return hipErrorInvalidValue;
     a.n_wave = (unsigned)n_wave;

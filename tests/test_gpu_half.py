@@ -23,6 +23,11 @@ GEOMS = {
     "256->144 @14": Geom(44, 256, 144, 14, 14, 3, 3, 1, 1, 1, 1),
     "128->64 @57x61": Geom(11, 128, 64, 57, 61, 3, 3, 1, 1, 1, 1),
     "192->48 3x5": Geom(2600, 192, 48, 3, 5, 3, 3, 1, 1, 1, 1),
+    # an odd last block of 16 channels: 112 whole, 400 in shares, stride 2
+    "112->144 @28": Geom(22, 112, 144, 28, 28, 3, 3, 1, 1, 1, 1),
+    "400->96 17x31, shares": Geom(11, 400, 96, 17, 31, 3, 3, 1, 1, 1, 1),
+    "176->48 @40 pad 2": Geom(22, 176, 48, 40, 40, 3, 3, 1, 1, 2, 2),
+    "stride 2 144->112 45x27": Geom(64, 144, 112, 45, 27, 3, 3, 2, 2, 1, 1),
     "stride 2 160->160 45x27": Geom(32, 160, 160, 45, 27, 3, 3, 2, 2, 1, 1),
 }
 
