@@ -31,13 +31,15 @@ constexpr int kStageC = 32, kWavePx = 64;       // channels of a stage, pixels o
 // pixels, kWideHaloS2 at stride 2, and with 64 output channels, where a tile has 128 pixels, kWideHalo2 (six pieces a lane) where at most a
 // tenth more tiles come of it, else kWideHalo2Max (seven, and a dozen spilled registers: 64->64 @224, N = 32 535 : 547 us, 256->64 @56
 // 145 : 155; but 128->64 @31x57, N = 16, where a halo of 192 samples would hold 98 pixels, 40 : 33)
+// With at most 32 output channels, f16 pieces only, a tile has 256 pixels and all four wavefronts read the same filters; one buffer of 352
+// samples (32 x 256->32 @56 90.2 -> 57.6 us, 10 x 512->32 @58 89.6 -> 49.0, 22 x 112->16 @165 202 -> 152; 320 samples cut some tiles short: 7 x 256->32 @123 60.5 : 85.5).
 // (f16 pieces take less of LDS: 224, whole rounds of the 256 lanes; at stride 2 two buffers of 304 would fit, but ten pieces of
 // staging beside nine taps spill 40 registers, 128->128 @56 35.7 : 42.4)
-constexpr int kWideHalo = 160, kWideHaloS2 = 320, kWideHalo2 = 192, kWideHalo2Max = 212, kWideHalo2MaxHalf = 224;
+constexpr int kWideHalo = 160, kWideHaloS2 = 320, kWideHalo2 = 192, kWideHalo2Max = 212, kWideHalo2MaxHalf = 224, kWideHalo1 = 352;
 template <int KQ, int HPC, bool HALF = false>
 struct WideLds {
     static constexpr int TQ = 4 / KQ, PX = TQ * kWavePx;
-    static constexpr int BUFS = HPC == kWideHaloS2 ? 1 : 2;         // two buffers where both fit twice on a compute unit
+    static constexpr int BUFS = HPC == kWideHaloS2 || HPC == kWideHalo1 ? 1 : 2;         // two buffers where both fit twice on a compute unit
     // pieces: [3 or 2 pieces][4 groups of 8 channels][sample][8 channels] of 16 bits, i.e. 16 bytes per sample and group,
     // so that neighbouring lanes (pixels) of an operand read are 16 bytes apart
     static constexpr int NP = HALF ? 2 : 3, BUF = HPC * 16 * NP;

@@ -62,9 +62,9 @@ unsigned fwd_auto_threshold(const Geom &g)
     const unsigned t = fwd_sparse_threshold(g);
     if (t == 0 || t > 1000 || !fwd_dense_supported(g)) return t;
     if (g.sw == 2 || g.uw == 2) return 1001;
-    // (an odd number of channel blocks on f16 pieces; 8 x 112->128 @56, us, zero-skipping at 70 / 90 / 97 % : dense: 80 / 59 / 46 : 32.  Even ones would
+    // (an odd number of channel blocks, or few produced channels, on f16 pieces; 8 x 112->128 @56, us, zero-skipping at 70 / 90 / 97 % : dense: 80 / 59 / 46 : 32.  Even ones would
     // have the same line; theirs are the ones that checks of this entry point ask for)
-    if (fwd_dense_half(g) && g.Ci % 32 != 0) return 950;
+    if (fwd_dense_half(g) && (g.Ci % 32 != 0 || g.Ko <= 32)) return 950;
     if (!fwd_auto_tiles(g)) return 850;
     return g.Ci >= 128 ? 950 : 650;
 }

@@ -185,9 +185,9 @@ def test_1x1_shares_of_launches_near_a_workgroup_per_compute_unit():
 @pytest.mark.parametrize("N,C,K,H,W,half", [
     # seven blocks and more, whole launches or shares of more than three stages; short reductions, short shares and few workgroups stay
     (20, 112, 256, 76, 76, True), (17, 304, 128, 35, 35, True), (11, 400, 96, 17, 31, True), (21, 112, 128, 29, 29, True), (32, 80, 128, 56, 56, False),
-    (11, 272, 96, 17, 31, False), (9, 112, 128, 68, 23, False), (1, 112, 128, 28, 28, False), (20, 112, 32, 76, 76, False)])
+    (11, 272, 96, 17, 31, False), (9, 112, 128, 68, 23, False), (1, 112, 128, 28, 28, False), (20, 112, 32, 76, 76, True), (5, 112, 32, 76, 76, False)])
 def test_odd_numbers_of_channel_blocks_on_f16_pieces(N, C, K, H, W, half):
     d = st.ConvDesc(N, C, K, H, W, 3, 3, 1, 1, 1, 1)
     assert (dense_kernel(d), f16_pieces(d)) == (("32", True) if half else ("16", False))
-    if half and K >= 64:
+    if half:
         assert st.st_conv_sparse_threshold(d, st.ST_PASS_FWD_AUTO) == 950

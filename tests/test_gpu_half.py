@@ -23,6 +23,10 @@ GEOMS = {
     "256->144 @14": Geom(44, 256, 144, 14, 14, 3, 3, 1, 1, 1, 1),
     "128->64 @57x61": Geom(11, 128, 64, 57, 61, 3, 3, 1, 1, 1, 1),
     "192->48 3x5": Geom(2600, 192, 48, 3, 5, 3, 3, 1, 1, 1, 1),
+    # at most 32 produced channels, tiles of 256 pixels: rows that fit and not, tiny images, an odd last block
+    "128->32 @57x61": Geom(24, 128, 32, 57, 61, 3, 3, 1, 1, 1, 1),
+    "144->16 3x5": Geom(4600, 144, 16, 3, 5, 3, 3, 1, 1, 1, 1),
+    "16->112 @28, BWI": Geom(100, 16, 112, 28, 28, 3, 3, 1, 1, 1, 1),
     # an odd last block of 16 channels: 112 whole, 400 in shares, stride 2
     "112->144 @28": Geom(22, 112, 144, 28, 28, 3, 3, 1, 1, 1, 1),
     "400->96 17x31, shares": Geom(11, 400, 96, 17, 31, 3, 3, 1, 1, 1, 1),
