@@ -57,7 +57,10 @@
  * form a product from bf16 pieces that carry all 24 bits of both factors and keep fp32 accuracy, for
  * subnormal factors too, at the same speed.  Outputs that factors from 2^104 or sums from 2^80 on, infinities
  * or NaN take part in are computed a second time with plain fp32 multiply-adds, tile by tile: correct, and a call
- * in which every tile holds one takes 3 to 7 times its usual time.
+ * in which every tile holds one takes 3 to 7 times its usual time.  Long 3x3 reductions (more than 96 reduced channels;
+ * filter gradients over many pixels) take two f16 pieces of 23 bits and more, scaled by a power of two from a sample of
+ * the values: a sum errs less than with bf16 pieces, and outputs that values more than 16 times above the sampled ones take part in, or
+ * that are so small that values 2^-25 below them could matter, are computed a second time in the same way.
  */
 #ifndef ST_CONV_H
 #define ST_CONV_H
@@ -158,7 +161,8 @@ st_status st_conv_bww_dy(const st_conv_desc *desc, const float *x, const float *
  * the x-testing form is the faster one).  Same tensors, same result, no host
  * synchronisation; the cost is the sampling pass (at most 256 KB of x and of dy are read once more)
  * and the empty launches.  Where tiled kernels exist, the dense form (st_conv_bww_dense) is the
- * third candidate: it runs when even the sparser operand has fewer than 75 % zeros on 3x3 layers (the
+ * third candidate: it runs when even the sparser operand has fewer than 75 % zeros on 3x3 layers, and from 128 million
+ * multiply-adds on up to 96 % where at least 5 % of the sampled products are not zero (the
  * measured break-even is about 96 % or, on some layers, beyond; Sec. 5.3 combines the kernels with dense ones
  * layer by layer), fewer than 25 % on those so small that the partial gradients are what they wait for.
  * Two kinds of layer are decided without sampling: 1x1 layers, where a zero saves too few
@@ -180,14 +184,15 @@ st_status st_conv_bww_auto(const st_conv_desc *desc, const float *x, const float
  * select returns at once.  The zero-skipping form runs when the sampled zero fraction reaches a line that
  * depends on the geometry (st_conv_sparse_threshold tells it): 95 % for unit-stride 3x3 layers that one main
  * kernel serves (below; also where the zero-skipping form of so small a layer has a kernel of its own) and that have 128 or more reduced channels, which is where the two forms were measured
- * to be equally fast; 65 % for those with fewer channels and 85 % for other unit-stride 3x3 layers, where these
+ * to be equally fast, and for those whose dense form multiplies f16 pieces with an odd number of reduced channel blocks or at most
+ * 32 produced channels; 65 % for those with fewer channels and 85 % for other unit-stride 3x3 layers, where these
  * entry points have always skipped zeros at 70 and 90 % (the dense form is up to a fifth faster between there and
  * 90 to 95 %); never for stride-2 3x3 and for 1x1 layers (measured up to 90 and 95 % zeros); always for
  * geometries only the generic kernels cover.  Where the answer is "always" or "never" the call
  * goes straight to that form, without sampling.  On unit-stride 3x3 layers of the usual sizes one
  * main kernel holds both forms (st_conv_kernel_name tells) and runs the selected one, so the sampled path has as many
- * launches as the direct call, unless the dense form of the layer has a faster kernel of its own (64 and more reduced
- * channels in whole 32s); there and elsewhere it costs one launch more.  Same tensors and
+ * launches as the direct call, unless the dense form of the layer has a faster kernel of its own (most layers of 64 and more reduced
+ * channels); there and elsewhere it costs one launch more.  Same tensors and
  * layouts as st_conv_fwd / st_conv_bwi, same result to rounding, no host synchronisation.
  * Workspace: st_conv_workspace_bytes(desc, ST_PASS_FWD_AUTO or ST_PASS_BWI_AUTO, 0).
  */
