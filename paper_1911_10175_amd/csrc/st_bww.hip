@@ -1264,14 +1264,15 @@ __global__ __launch_bounds__(256 * TEAMS, 2) void bww_dense_half_kernel(BwwArgs 
         slot = (slot + 2) % 3;
     }
 
-    // values below the pieces' range that the workgroup has met, behind what the teams exchange (one team: in the third halo buffer, which no one reads now)
+    // values below the pieces' range that the workgroup has met, behind what the teams exchange (one team: in the third halo buffer, which no one
+    // reads now).  Others may still be writing either place, also the halo of a tile that does not exist: not before a barrier
     static_assert(TEAMS == 1 || TEAMS * LDS >= 4 * TAPS * 4 * kWave * 16 + 32, "room for both");
     misc = reinterpret_cast<unsigned *>(TEAMS == 1 ? xlds + (slot + 2) % 3 * XBUF : lds_all + 4 * TAPS * 4 * kWave * 16);
     {
         unsigned c = 0;
         if (__ballot(lows != 0) != 0)
             for (int l = 0; l < kWave; ++l) c += (unsigned)__builtin_amdgcn_readlane((int)lows, l);
-        if (TEAMS > 1) __syncthreads();                         // (the second team's last pair may lie there)
+        __syncthreads();
         if (lane == 0) misc[team.team * 4 + wave] = c;
         if (TEAMS == 1) __syncthreads();
     }
