@@ -191,3 +191,16 @@ def test_odd_numbers_of_channel_blocks_on_f16_pieces(N, C, K, H, W, half):
     assert (dense_kernel(d), f16_pieces(d)) == (("32", True) if half else ("16", False))
     if half:
         assert st.st_conv_sparse_threshold(d, st.ST_PASS_FWD_AUTO) == 950
+
+
+@pytest.mark.parametrize("N,C,K,H,W,stride,pad,bwi,size", [
+    # an odd number of reduced channel blocks, whole and in shares, at stride 2; at most 32 produced channels
+    (6, 464, 688, 7, 21, 1, 1, False, 24097536), (6, 464, 688, 7, 21, 1, 1, True, 25569792), (2, 592, 720, 20, 20, 1, 1, True, 30566400),
+    (7, 560, 592, 128, 4, 1, 0, False, 19353600), (6, 400, 96, 76, 76, 2, 1, False, 6091776), (92, 288, 400, 9, 3, 1, 1, True, 8294400),
+    (10, 512, 32, 84, 84, 1, 1, False, 3538944), (18, 592, 32, 3, 233, 1, 1, False, 10533888), (7, 224, 16, 49, 199, 1, 2, False, 1548288),
+    (13, 32, 704, 239, 23, 1, 1, True, 4866048), (3, 16, 336, 223, 54, 1, 0, True, 4634496), (77, 736, 32, 5, 63, 1, 0, False, 12301824)])
+def test_workspaces_that_sufficed_suffice(N, C, K, H, W, stride, pad, bwi, size):
+    """Sizes that the query has told for these layers with the kernel of 16 channels at a time: a program may have kept them, and the kernel of
+    32 channels, with shares of its own, must not ask for more."""
+    d = st.ConvDesc(N, C, K, H, W, 3, 3, stride, stride, pad, pad)
+    assert st.st_conv_workspace_bytes(d, st.ST_PASS_BWI if bwi else st.ST_PASS_FWD, True) <= size
