@@ -845,9 +845,9 @@ struct BwwWideStage {
     }
 };
 
-// A workgroup of the unit-stride kernels is one team of four wavefronts or, where more of these than compute units would run, two, which take tiles of
+// A workgroup of the unit-stride kernel on bf16 pieces is one team of four wavefronts or (bww_teams) two, which take tiles of
 // their own and add their sums up in LDS: what used to be two workgroups on a compute unit writes one set of partial gradients instead of two, and the
-// final sum reads half as many (75 MB each for 512 teams): 2 x 256->256 @28 36.8 -> 30.6 us, 32 x 256->256 @56 356 -> 338.
+// final sum reads half as many: 32 x 128->128 @28 59.5 -> 56.0 us.
 // Tiles of the teams: first, then one past the last of each, steps = the most tiles of one of them.
 template <int TEAMS>
 struct BwwTeam {
@@ -1076,34 +1076,34 @@ __global__ __launch_bounds__(256 * TEAMS, 2) void bww_dense_wide_kernel(BwwArgs 
 // it is split: the halo of its first tile into the third of three buffers that take turns, both dy tiles into the second pair of buffers, the halo
 // of the second tile into the first buffer when this pair is done (two barriers a pair).  (24 registers, two steps: 20 spilled, 345 -> 372 us.)
 // A tap of a tile is three groups of four instructions; the large and the small products have a sum each.
-template <int TH, int TW, int TEAMS>
-__global__ __launch_bounds__(256 * TEAMS, 2) void bww_dense_half_kernel(BwwArgs A, const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part)
+template <int TH, int TW>
+__global__ __launch_bounds__(256, 2) void bww_dense_half_kernel(BwwArgs A, const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part)
 {
     constexpr int R = 3, S = 3, TAPS = R * S;
     using Stage = BwwWideStage<TH, TW>;
     if (deselected(A.sel, A.want)) return;              // uniform over the grid, before any barrier
     constexpr int HW = Stage::HW, TP = TH * TW, XB = Stage::XB, DB = Stage::DB, XBUF = 4 * XB, DBUF = 4 * DB, LDS = 3 * XBUF + 4 * DBUF;
-    static_assert(LDS >= 2 * Stage::bytes(3) && 2 * LDS <= 160 * 1024, "either form in one array, two teams a compute unit");
-    __shared__ __attribute__((aligned(16))) char lds_all[TEAMS * LDS];
-    unsigned *misc = reinterpret_cast<unsigned *>(lds_all);     // before the first tile
+    static_assert(LDS >= 2 * Stage::bytes(3) && 2 * LDS <= 160 * 1024, "either form in one array, two workgroups a compute unit");
+    __shared__ __attribute__((aligned(16))) char lds[LDS];
+    unsigned *misc = reinterpret_cast<unsigned *>(lds);         // before the first tile and after the last
 
     // the wavefront index is the same in every lane: kept in a scalar register, and with it every tile coordinate
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x % 256 / kWave), lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
     const int l16 = lane % 16, grp = lane / 16;
     const int kh = wave % 2, ch = wave / 2;
-    const BwwTeam<TEAMS> team(A);
-    const int u0 = team.u0, u1 = team.u1;
-    char *const lds = lds_all + team.team * LDS;
+    const int split = blockIdx.x;
     const int kt = blockIdx.y / A.cgroups, cg = blockIdx.y % A.cgroups;
     const int CB = A.C / kBlk, KB = A.K / kBlk;
     const bool active = kt * 64 + kh * 32 < A.K && cg * 64 + ch * 32 < A.C;
 
-    // a sample for the scales, which the teams share: the first pixels of 16 tiles for each of them
+    const int u0 = (int)((long long)A.units * split / A.splits);
+    const int u1 = (int)((long long)A.units * (split + 1) / A.splits);
+
+    // a sample for the scales: the first pixels of 16 tiles
     int xe, de;
     {
-        constexpr int SLOTS = 16 * TEAMS, WAVES = 4 * TEAMS;
-        const int slot = threadIdx.x / 16, q = threadIdx.x % 16, w = team.team * 4 + wave;
-        const int u = team.first + (int)((long long)(team.last - team.first) * slot / SLOTS);
+        const int slot = threadIdx.x / 16, q = threadIdx.x % 16;
+        const int u = u0 + (int)((long long)(u1 - u0) * slot / 16);
         const int tw = u % A.tiles_w, th = u / A.tiles_w % A.tiles_h, n = u / A.tiles_w / A.tiles_h;
         const int cb = min(cg * 4 + q / 4, CB - 1), kb = min(kt * 4 + q / 4, KB - 1);
         const float4 vx = *reinterpret_cast<const float4 *>(x + act_off(n, cb, min(th * TH, A.H - 1), min(tw * TW, A.W - 1), CB, A.H, A.W) + q % 4 * 4);
@@ -1113,22 +1113,15 @@ __global__ __launch_bounds__(256 * TEAMS, 2) void bww_dense_half_kernel(BwwArgs 
             return (unsigned)(__popcll(__ballot(v.x != 0.f)) + __popcll(__ballot(v.y != 0.f)) + __popcll(__ballot(v.z != 0.f)) + __popcll(__ballot(v.w != 0.f)));
         };
         const unsigned fx = filled(vx), fd = filled(vd);
-        if (lane == 0) { misc[w] = mx; misc[8 + w] = md; misc[16 + w] = fx; misc[24 + w] = fd; }
+        if (lane == 0) { misc[wave] = mx; misc[4 + wave] = md; misc[8 + wave] = fx; misc[12 + wave] = fd; }
         __syncthreads();
-        unsigned bits_x = 0, bits_d = 0, sum_x = 0, sum_d = 0;
-#pragma unroll
-        for (int i = 0; i < WAVES; ++i) {
-            bits_x = max(bits_x, misc[i]);
-            bits_d = max(bits_d, misc[8 + i]);
-            sum_x += misc[16 + i];
-            sum_d += misc[24 + i];
-        }
-        const unsigned products = sum_x * sum_d;
+        const unsigned products = (misc[8] + misc[9] + misc[10] + misc[11]) * (misc[12] + misc[13] + misc[14] + misc[15]);
+        const unsigned bits_x = max(max(misc[0], misc[1]), max(misc[2], misc[3])), bits_d = max(max(misc[4], misc[5]), max(misc[6], misc[7]));
         xe = __builtin_amdgcn_readfirstlane(half_exponent(bits_x));
         de = __builtin_amdgcn_readfirstlane(half_exponent(bits_d));
         __syncthreads();                                        // (misc is overwritten from here on)
-        if ((unsigned)__builtin_amdgcn_readfirstlane((int)products) < (unsigned)(TEAMS * TEAMS) * ((1u << 20) / 20)) {         // of 1024 x 1024 a team
-            bww_dense_wide_body<R, S, TH, TW, false, false, TEAMS>(A, x, dy, part, lds_all);
+        if ((unsigned)__builtin_amdgcn_readfirstlane((int)products) < (1u << 20) / 20) {        // of 1024 x 1024
+            bww_dense_wide_body<R, S, TH, TW, false, false, 1>(A, x, dy, part, lds);
             return;
         }
     }
@@ -1143,7 +1136,6 @@ __global__ __launch_bounds__(256 * TEAMS, 2) void bww_dense_half_kernel(BwwArgs 
     auto sign = [](int pair) __attribute__((always_inline)) { return pair % 2 ? -1.f : 1.f; };
     typename Stage::Tile ta, tb;                                // the two tiles to ask for next
     ta.start(A, u0);
-    if (TEAMS > 1 && u0 == u1) { ta.n = 0; ta.th = 40000 / TH; }                // (a team without tiles)
     tb = ta;
     // a second tile that does not exist: rows that no image of these sizes has, all zeros
     auto second = [&](int unit) __attribute__((always_inline)) {
@@ -1159,7 +1151,7 @@ __global__ __launch_bounds__(256 * TEAMS, 2) void bww_dense_half_kernel(BwwArgs 
     float4 sx[4], sda[2], sdb[2];
     unsigned lows = 0;
     char *const xlds = lds, *const dlds = lds + 3 * XBUF;
-    Stage::fetch_x(A, x, cg, ta, sx);
+    Stage::fetch_x(A, x, cg, ta, sx);                           // (a split has at least one tile)
     lows += Stage::template stash_half<XB>(sx, 1.f, xe, xlds);
     second(u0 + 1);
     Stage::fetch_dy(A, dy, kt, ta, sda);
@@ -1184,7 +1176,7 @@ __global__ __launch_bounds__(256 * TEAMS, 2) void bww_dense_half_kernel(BwwArgs 
     }
     int slot = 0;                                               // buffer of the pair's first tile; the second one's is the next
     for (int unit = u0, pair = 0;; unit += 2, ++pair) {
-        const bool more = 2 * pair + 2 < team.steps;
+        const bool more = unit + 2 < u1;
         char *const tile[2] = {xlds + slot * XBUF, xlds + (slot + 1) % 3 * XBUF}, *const spare = xlds + (slot + 2) % 3 * XBUF;
         char *const dtile = dlds + pair % 2 * (2 * DBUF), *const dspare = dlds + (1 - pair % 2) * (2 * DBUF);
         // (no branches around what follows, also not for a last pair's successor or for wavefronts without channels of their own, which multiply
@@ -1264,28 +1256,24 @@ __global__ __launch_bounds__(256 * TEAMS, 2) void bww_dense_half_kernel(BwwArgs 
         slot = (slot + 2) % 3;
     }
 
-    // values below the pieces' range that the workgroup has met, behind what the teams exchange (one team: in the third halo buffer, which no one
-    // reads now).  Others may still be writing either place, also the halo of a tile that does not exist: not before a barrier
-    static_assert(TEAMS == 1 || TEAMS * LDS >= 4 * TAPS * 4 * kWave * 16 + 32, "room for both");
-    misc = reinterpret_cast<unsigned *>(TEAMS == 1 ? xlds + (slot + 2) % 3 * XBUF : lds_all + 4 * TAPS * 4 * kWave * 16);
+    // values below the pieces' range that the workgroup has met, in the third halo buffer, which no one reads now.  Others may still be writing
+    // it, also the halo of a tile that does not exist: not before a barrier
+    misc = reinterpret_cast<unsigned *>(xlds + (slot + 2) % 3 * XBUF);
     {
         unsigned c = 0;
         if (__ballot(lows != 0) != 0)
             for (int l = 0; l < kWave; ++l) c += (unsigned)__builtin_amdgcn_readlane((int)lows, l);
         __syncthreads();
-        if (lane == 0) misc[team.team * 4 + wave] = c;
-        if (TEAMS == 1) __syncthreads();
+        if (lane == 0) misc[wave] = c;
+        __syncthreads();
     }
-    if (!team.join(acc, active, wave, lane, lds_all)) return;
-    unsigned lost = 0;
-#pragma unroll
-    for (int i = 0; i < 4 * TEAMS; ++i) lost += misc[i];
-    const float safe = kHalfSafe * fminf(4.f * (float)lost / (float)((team.last - team.first) * TP), 1.f);
+    if (!active) return;
+    const float safe = kHalfSafe * fminf(4.f * (float)(misc[0] + misc[1] + misc[2] + misc[3]) / (float)((u1 - u0) * TP), 1.f);
 
     // D layout of a 16x16 block: column (c) = lane % 16, row (k) = 4*(lane/16) + r: four consecutive output channels, one 16-byte store,
     // the lanes' side by side
     const int k32 = kt * 64 + kh * 32, c32 = cg * 64 + ch * 32, exponent = -(xe + de);
-    float *pbase = part + (size_t)blockIdx.x * A.K * A.C * TAPS;
+    float *pbase = part + (size_t)split * A.K * A.C * TAPS;
     auto element = [&](int k, int c, int tap) __attribute__((always_inline)) {
         return pbase + (((size_t)(k / kBlk) * CB + c / kBlk) * TAPS + tap) * (kBlk * kBlk) + (c % kBlk) * kBlk + k % kBlk;
     };
@@ -1309,7 +1297,7 @@ __global__ __launch_bounds__(256 * TEAMS, 2) void bww_dense_half_kernel(BwwArgs 
     if (__builtin_expect(__ballot(!finite) != 0, 0)) {
         split_lanes_fence();
         floatx16 redo[TAPS];
-        bww_redo<R, S, TH, TW, 1>(A, x, dy, k32, c32, team.first, team.last, redo);
+        bww_redo<R, S, TH, TW, 1>(A, x, dy, k32, c32, u0, u1, redo);
         const int c = c32 + lane % 32;
         if (c >= A.C) return;
 #pragma unroll
@@ -1761,14 +1749,15 @@ __global__ __launch_bounds__(512, 4) void pw_bww_sparse_kernel(BwwArgs A, const 
 // sp.f[form] = number of partial sums the form (0 tests x, 1 tests dy, 2 dense) leaves behind; with
 // want = kAnyForm the launch adds up those of whichever form the sampled counts selected, else it
 // belongs to the form `want` and does nothing when another one was selected.
-struct Splits3 { int f[3]; };
+// joined: the dense ones are sums of two teams each (bww_teams) and are added up in 64 bits.
+struct Splits3 { int f[3]; bool joined; };
 constexpr int kAnyForm = -2;
 // part[first] + part[first + step] + ... below `splits` (n4 float4 apart), eight loads in flight at a time: each eight in
 // pairs, their sums in 64 bits.  Added up one after the other in 32 bits, hundreds of partial sums round more often than
 // the products in them (3x3 64->64, 4 x 30 x 28 pixels, 105 partial sums, 4 % non-zero products: error 9.9e-8 of the norm one
 // after the other, 5.7e-8 here; v_mfma_f32_32x32x2_f32 and its 34 partial sums 9.6e-8).
 struct Sum4 { double x, y, z, w; };
-__device__ __forceinline__ Sum4 add_partials(const float4 *part, size_t n4, int first, int splits, int step)
+__device__ __forceinline__ Sum4 add_partials(const float4 *part, size_t n4, int first, int splits, int step, bool joined)
 {
     constexpr int BATCH = 8;
     Sum4 s = {0., 0., 0., 0.};
@@ -1777,6 +1766,11 @@ __device__ __forceinline__ Sum4 add_partials(const float4 *part, size_t n4, int 
         float4 v[BATCH];
 #pragma unroll
         for (int b = 0; b < BATCH; ++b) v[b] = part[(size_t)(p + b * step) * n4];
+        if (joined) {
+#pragma unroll
+            for (int b = 0; b < BATCH; ++b) { s.x += v[b].x; s.y += v[b].y; s.z += v[b].z; s.w += v[b].w; }
+            continue;
+        }
         const float4 t = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
         s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
     }
@@ -1787,7 +1781,7 @@ __device__ __forceinline__ Sum4 add_partials(const float4 *part, size_t n4, int 
     return s;
 }
 
-__global__ __launch_bounds__(1024) void bww_reduce_kernel(const float4 *part, float4 *dw, size_t n4, Splits3 sp,
+__global__ __launch_bounds__(1024, 8) void bww_reduce_kernel(const float4 *part, float4 *dw, size_t n4, Splits3 sp,
                                                           const unsigned *sel, int want)
 {
     int form = want < 0 ? 0 : want;
@@ -1796,12 +1790,13 @@ __global__ __launch_bounds__(1024) void bww_reduce_kernel(const float4 *part, fl
         if (want != kAnyForm && form != want) return;
     }
     const int splits = form == 0 ? sp.f[0] : form == 1 ? sp.f[1] : sp.f[2];
+    const bool joined = sp.joined && form == 2;
     // Few splits: a thread per output.  With few outputs as well, that many threads would wait for one load after the other;
     // there the 16 wavefronts of a workgroup share the partial sums (48->48 @12 stride 2, N = 4, 9 partial sums of 5184 float4:
     // 18.1 -> 16.4 us for the whole call; two partial sums of 576 are faster added up by one thread each, 17.5 : 18.4).
     if (splits <= 2 || (splits <= 16 && n4 >= 16384)) {
         for (size_t i = (size_t)blockIdx.x * 1024 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 1024) {
-            const Sum4 s = add_partials(part + i, n4, 0, splits, 1);
+            const Sum4 s = add_partials(part + i, n4, 0, splits, 1, joined);
             dw[i] = make_float4((float)s.x, (float)s.y, (float)s.z, (float)s.w);
         }
         return;
@@ -1813,7 +1808,7 @@ __global__ __launch_bounds__(1024) void bww_reduce_kernel(const float4 *part, fl
         const size_t i = blk * 64 + o;
         Sum4 s = {0., 0., 0., 0.};
         if (i < n4)
-            s = add_partials(part + i, n4, sl, splits, 16);
+            s = add_partials(part + i, n4, sl, splits, 16, joined);
         red[sl][o] = s;
         __syncthreads();
         if (sl == 0 && i < n4) {
@@ -1927,30 +1922,40 @@ bool bww_big_image(const BwwArgs &A)
 
 bool bww_half_tiles(const BwwArgs &A) { return A.units >= kBwwHalfTiles * A.splits && !bww_big_image(A); }
 
-// Teams of a workgroup of the unit-stride kernels (BwwTeam).  The two share their barriers, which costs more than the partial gradients from some eight
-// tiles on (one : two, us, tiles a team: 16 x 128->128 @28, 4, 42.1 : 38.7, N = 32, 7, 58 : 54, 32 x 512->512 @14, 28, 148 : 150) unless they multiply f16 pieces
-// (256->256 @56 356 : 338).  Where a group of 64 channels has at most 32, half of a team's wavefronts only stage, and two such teams on a
+// Teams of a workgroup of the unit-stride kernel on bf16 pieces (BwwTeam).  The two share their barriers, which costs more than the partial gradients from
+// some eight tiles on (one : two, us, tiles a team: 32 x 128->128 @28, 7, 58 : 54, 32 x 512->512 @14, 28, 148 : 150).  Where a group of 64 channels
+// has at most 32, half of a team's wavefronts only stage, and two such teams on a
 // compute unit leave it to others with two full ones (27 x 288->80 @39x8, 6, 41.3 : 43.0): up to two tiles only, and not where both channel counts end like
-// that (5 x 144->304 @8x12 27.0 : 22.1, 3 x 80->48 @37x53 23.8 : 22.3, 20 x 48->32 @33x12 22.5 : 20.1, 5 x 112->224 @21 28.5 : 29.0, but 3 x 80->32 @54
-// 20.2 : 23.1).
+// that (3 x 80->48 @37x53 23.8 : 22.3, 20 x 48->32 @33x12 22.5 : 20.1, but 3 x 80->32 @54 20.2 : 23.1).
+// The sum of two teams is rounded.  With hundreds of partial gradients the final sum of one for each team adds them up eight at a time in 32 bits, three
+// roundings, and that of two all in 64 bits: together one (3 x 80->48 @37x53, 240 teams, 5.5e-8 -> 4.9e-8 of the norm).  With fewer than
+// 120 few or none of them come in eights, and two teams would err more (2 x 256->256 @28, 32 teams, 5.0e-8 : 6.7e-8, though 36.8 : 31.0 us).
+constexpr int kBwwTeamSplits = 120;
 int bww_teams(const BwwArgs &A)
 {
-    if (A.splits == 1 || A.splits * ceil_div(A.K, 64) * A.cgroups <= 256) return 1;
+    if (A.splits < kBwwTeamSplits || A.splits * ceil_div(A.K, 64) * A.cgroups <= 256) return 1;
     const int tiles = ceil_div(A.units, A.splits);
     auto full = [](int channels) { return (channels + 63) % 64 >= 32; };
     if (tiles <= 2) return full(A.C) || full(A.K) ? 2 : 1;
-    return full(A.C) && full(A.K) && (tiles <= 8 || bww_half_tiles(A)) ? 2 : 1;
+    return full(A.C) && full(A.K) && tiles <= 8 ? 2 : 1;
 }
 
 template <int TH, int TW, int TEAMS>
-void launch_bww_dense_wide(const BwwArgs &A, const float *x, const float *dy, float *part, hipStream_t s)
+void launch_bww_teams(const BwwArgs &A, const float *x, const float *dy, float *part, hipStream_t s)
 {
     const dim3 grid(ceil_div(A.splits, TEAMS), ceil_div(A.K, 64) * A.cgroups), block(256 * TEAMS);
     if (bww_big_image(A)) hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, false, true, TEAMS>), grid, block, 0, s, A, x, dy, part);
-    else if (A.units <= kBwwShortUnits && A.units <= 2 * A.splits)
-        hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, true, false, TEAMS>), grid, block, 0, s, A, x, dy, part);
-    else if (bww_half_tiles(A)) hipLaunchKernelGGL((bww_dense_half_kernel<TH, TW, TEAMS>), grid, block, 0, s, A, x, dy, part);
     else hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, false, false, TEAMS>), grid, block, 0, s, A, x, dy, part);
+}
+
+template <int TH, int TW>
+void launch_bww_dense_wide(const BwwArgs &A, const float *x, const float *dy, float *part, hipStream_t s)
+{
+    if (bww_half_tiles(A)) hipLaunchKernelGGL((bww_dense_half_kernel<TH, TW>), dim3(A.splits, ceil_div(A.K, 64) * A.cgroups), dim3(256), 0, s, A, x, dy, part);
+    else if (A.units <= kBwwShortUnits && A.units <= 2 * A.splits && !bww_big_image(A))
+        hipLaunchKernelGGL((bww_dense_wide_kernel<3, 3, TH, TW, true, false, 1>), dim3(A.splits, ceil_div(A.K, 64) * A.cgroups), dim3(256), 0, s, A, x, dy, part);
+    else if (bww_teams(A) == 2) launch_bww_teams<TH, TW, 2>(A, x, dy, part, s);
+    else launch_bww_teams<TH, TW, 1>(A, x, dy, part, s);
 }
 
 template <int TH, int TW, int PSTEP>
@@ -1963,17 +1968,14 @@ void launch_bww_dense_tiles(const BwwArgs &A, const float *x, const float *dy, f
 }
 
 // partial gradients a launch of it writes (the workspace query counts one for each team)
-int bww_dense_partials(const st_conv_desc &d, const BwwArgs &A) { return bww_s2(d) ? A.splits : ceil_div(A.splits, bww_teams(A)); }
+int bww_dense_partials(const st_conv_desc &d, const BwwArgs &A) { return bww_s2(d) || bww_half_tiles(A) ? A.splits : ceil_div(A.splits, bww_teams(A)); }
 
 // the 3x3 dense kernel with A = dense_args(d)
 hipError_t launch_bww_dense_3x3(const st_conv_desc &d, const BwwArgs &A, const float *x, const float *dy, float *part, hipStream_t s)
 {
     if (bww_s2(d)) launch_bww_dense_tiles<kDenseS2TH, kDenseS2TW, 2>(A, x, dy, part, s);
-    else if (dense_wide(d)) {
-        if (bww_teams(A) == 2) launch_bww_dense_wide<kDenseWideTH, kDenseWideTW, 2>(A, x, dy, part, s);
-        else launch_bww_dense_wide<kDenseWideTH, kDenseWideTW, 1>(A, x, dy, part, s);
-    } else if (bww_teams(A) == 2) launch_bww_dense_wide<kDenseTH, kDenseTW, 2>(A, x, dy, part, s);
-    else launch_bww_dense_wide<kDenseTH, kDenseTW, 1>(A, x, dy, part, s);
+    else if (dense_wide(d)) launch_bww_dense_wide<kDenseWideTH, kDenseWideTW>(A, x, dy, part, s);
+    else launch_bww_dense_wide<kDenseTH, kDenseTW>(A, x, dy, part, s);
     return hipGetLastError();
 }
 
@@ -2025,15 +2027,14 @@ size_t partial_bytes(const st_conv_desc &d, const BwwArgs &A)
     return (size_t)A.splits * d.K * d.C * d.S * d.R * sizeof(float);
 }
 
-hipError_t reduce(const st_conv_desc &d, const BwwArgs &A, const float *part, float *dw, hipStream_t s)
+hipError_t reduce(const st_conv_desc &d, const BwwArgs &A, const float *part, float *dw, hipStream_t s, bool joined = false)
 {
     if (A.splits == 1) return hipSuccess;               // the kernel wrote dw itself
     const size_t n4 = (size_t)d.K * d.C * d.S * d.R / 4;
     const size_t nblk = (n4 + 63) / 64;
-    const int form = A.sel ? A.want : 0;
-    Splits3 sp = {{A.splits, A.splits, A.splits}};
+    const Splits3 sp = {{A.splits, A.splits, A.splits}, joined};
     hipLaunchKernelGGL(bww_reduce_kernel, dim3((unsigned)(nblk < kReduceGrid ? nblk : kReduceGrid)), dim3(1024), 0, s,
-                       reinterpret_cast<const float4 *>(part), reinterpret_cast<float4 *>(dw), n4, sp, A.sel, form);
+                       reinterpret_cast<const float4 *>(part), reinterpret_cast<float4 *>(dw), n4, sp, A.sel, A.want);
     return hipGetLastError();
 }
 
@@ -2238,7 +2239,8 @@ hipError_t launch_bww_auto_merged(const st_conv_desc &d, const float *x, const f
     if ((err = launch_bww_dense_3x3(d, A2, x, dy, ws, s)) != hipSuccess) return err;
     const size_t n4 = (size_t)d.K * d.C * d.S * d.R / 4;
     const size_t nblk = (n4 + 63) / 64;
-    Splits3 sp = {{A0.splits, A1.splits, bww_dense_partials(d, A2)}};
+    const int partials = bww_dense_partials(d, A2);
+    const Splits3 sp = {{A0.splits, A1.splits, partials}, partials < A2.splits};
     hipLaunchKernelGGL(bww_reduce_kernel, dim3((unsigned)(nblk < kReduceGrid ? nblk : kReduceGrid)), dim3(1024), 0, s,
                        reinterpret_cast<const float4 *>(ws), reinterpret_cast<float4 *>(dw), n4, sp, sel, direct ? 2 : kAnyForm);
     return hipGetLastError();
@@ -2273,8 +2275,9 @@ hipError_t launch_bww_dense(const st_conv_desc &d, const float *x, const float *
     float *part = partials == 1 ? dw : ws;
     hipError_t e = launch_bww_dense_3x3(d, A, x, dy, part, s);
     if (e != hipSuccess) return e;
+    const bool joined = partials < A.splits;
     A.splits = partials;
-    return reduce(d, A, part, dw, s);
+    return reduce(d, A, part, dw, s, joined);
 }
 
 // The 3x3 zero-skipping forms pass the dense one between 95 and 99 % zeros (N = 32, us, both with all launches of the entry point, zero-skipping at

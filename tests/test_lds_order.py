@@ -75,7 +75,7 @@ def test_counts_of_small_values_are_not_overwritten_by_tiles(tmp_path):
     """Filter gradients on f16 pieces: a wavefront's count lies where others may still write the halo of a tile.  Without a barrier before it
     the count is lost, and gradients that should have been computed again are not."""
     found = kernels("bww_dense_half_kernel", tmp_path)
-    assert len(found) == 4, sorted(found)                       # two tile shapes, one and two teams
+    assert len(found) == 2, sorted(found)                       # two tile shapes
     for name, body in found.items():
         ops = [op for _, op, _ in body]
         assert any(op.startswith("ds_write") and op.endswith("_b64") for op in ops) and any(op.startswith("ds_write") and op.endswith("_b32") for op in ops), name
