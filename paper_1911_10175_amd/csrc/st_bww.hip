@@ -1068,6 +1068,68 @@ __global__ __launch_bounds__(256 * TEAMS, 2) void bww_dense_wide_kernel(BwwArgs 
     bww_dense_wide_body<R, S, TH, TW, SHORT, BIG, TEAMS>(A, x, dy, part, lds);
 }
 
+// Up to eight elements of a partial gradient once more, by the 64 lanes of a wavefront in 64 bits.  list: output channel - k32, input channel - c32 and tap,
+// five, five and four bits, `count` of them
+constexpr unsigned kBwwHalfFew = 8;
+template <int TH, int TW>
+__device__ __forceinline__ void bww_some(const BwwArgs &A, const float *x, const float *dy, int k32, int c32, const unsigned (&list)[kBwwHalfFew], unsigned count,
+                                         int u0, int u1, double (&sum)[kBwwHalfFew])
+{
+    const int lane = threadIdx.x % kWave, p = lane % 32;
+#pragma unroll
+    for (unsigned i = 0; i < kBwwHalfFew; ++i) sum[i] = 0.;
+#pragma unroll 2
+    for (int unit = u0 + lane / 32; unit < u1; unit += 2) {
+        const int tw = unit % A.tiles_w, th = unit / A.tiles_w % A.tiles_h, n = unit / A.tiles_w / A.tiles_h;
+        const int oh = th * TH + p / TW, ow = tw * TW + p % TW;
+#pragma unroll
+        for (unsigned i = 0; i < kBwwHalfFew; ++i) {
+            if (i >= count) break;
+            const int k = k32 + (int)(list[i] & 31), c = c32 + (int)(list[i] >> 5 & 31), tap = (int)(list[i] >> 10);
+            const int ih = oh - A.ph + tap / 3, iw = ow - A.pw + tap % 3;
+            const bool in = p < TH * TW && oh < A.OH && ow < A.OW && ih >= 0 && ih < A.H && iw >= 0 && iw < A.W;
+            const float d = dy[act_off(n, k / kBlk, in ? oh : 0, in ? ow : 0, A.K / kBlk, A.OH, A.OW) + k % kBlk];
+            const float v = x[act_off(n, c / kBlk, in ? ih : 0, in ? iw : 0, A.C / kBlk, A.H, A.W) + c % kBlk];
+            sum[i] += in ? (double)d * v : 0.;
+        }
+    }
+#pragma unroll
+    for (unsigned i = 0; i < kBwwHalfFew; ++i)
+        for (int m = kWave / 2; m > 0; m /= 2) sum[i] += __shfl_xor(sum[i], m);
+}
+
+// The largest magnitude, in bits, of each of the 64 channels of x and of dy that a workgroup meets in tiles u0 .. u1-1: into most[0 ..], most[64 ..]
+template <int TH, int TW>
+__device__ __forceinline__ void bww_channels(const BwwArgs &A, const float *x, const float *dy, int kt, int cg, int u0, int u1, unsigned *most)
+{
+    using Stage = BwwWideStage<TH, TW>;
+    if (threadIdx.x < 128) most[threadIdx.x] = 0;
+    __syncthreads();
+    unsigned mx[4] = {0u, 0u, 0u, 0u}, md[4] = {0u, 0u, 0u, 0u};
+    typename Stage::Tile t;
+    t.start(A, u0);
+    auto meet = [](unsigned (&m)[4], float4 v) __attribute__((always_inline)) {
+        m[0] = max(m[0], __float_as_uint(v.x) & 0x7fffffffu); m[1] = max(m[1], __float_as_uint(v.y) & 0x7fffffffu);
+        m[2] = max(m[2], __float_as_uint(v.z) & 0x7fffffffu); m[3] = max(m[3], __float_as_uint(v.w) & 0x7fffffffu);
+    };
+#pragma unroll 4
+    for (int unit = u0; unit < u1; ++unit) {
+        float4 sd[2], sx[4];
+        Stage::fetch_dy(A, dy, kt, t, sd);
+        Stage::fetch_x(A, x, cg, t, sx);
+        t.step(A);
+        meet(md, sd[0]); meet(md, sd[1]);
+        meet(mx, sx[0]); meet(mx, sx[1]); meet(mx, sx[2]); meet(mx, sx[3]);
+    }
+    const int q = threadIdx.x % 16 * 4;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        atomicMax(most + q + i, mx[i]);
+        atomicMax(most + 64 + q + i, md[i]);
+    }
+    __syncthreads();
+}
+
 // The same with two f16 pieces (st_split.hpp) where a workgroup has many tiles (kBwwHalfTiles): three products instead of six.  N = 32, half zeros, us:
 // 256->256 @56 478 -> 353 (335 TFLOP/s), 512->512 @28 529 -> 375, 128->256 @56 246 -> 191, 64->64 @224 518 -> 425.  Bound: issue, half of it vector
 // instructions (800 beside the 216 matrix instructions of a pair of tiles: splitting them, their addresses, joining the sums).  Workgroups take two tiles
@@ -1076,15 +1138,24 @@ __global__ __launch_bounds__(256 * TEAMS, 2) void bww_dense_wide_kernel(BwwArgs 
 // it is split: the halo of its first tile into the third of three buffers that take turns, both dy tiles into the second pair of buffers, the halo
 // of the second tile into the first buffer when this pair is done (two barriers a pair).  (24 registers, two steps: 20 spilled, 345 -> 372 us.)
 // A tap of a tile is three groups of four instructions; the large and the small products have a sum each.
+// False where the workgroup has to do all its tiles on bf16 pieces, instead or again.  All workgroups run at once, so the launch takes as long as the
+// slowest: fp32 multiply-adds for a block with a single gradient that the pieces cannot give took 1300 us (below).  Instead: where fewer than four
+// fifths of the sampled values of an operand are within 2^6 of the largest, so that values outside the pieces' range are to be expected, bf16
+// pieces from the start; else a few gradients are computed one by one, those of channels without values are zeros (padding, ReLU: any lost value of the other
+// operand makes them suspect), and only for more all tiles are done again.  us, bf16 pieces : fp32 multiply-adds : now, 16 x 256->256 @56 normal values
+// 330 : 237 : 237, Laplace 304 : - : 250, 3 and 2 degrees of freedom 320 : - : 307, 294 : 1306 : 292, log-normal 2 294 : 1304 : 291, one in 10^4 100 times as
+// large 289 : 1394 : 481, one in 10^4 2^-40 as large 291 : 203 : 241, all between 2^-40 and 1 305 : 1410 : 328; 13 of 16 channels zero,
+// 32 x 128->64 @224 921 : 7446 : 899, 16->64 439 : 1598 : 430.
+// Every thread makes the call.
 template <int TH, int TW>
-__global__ __launch_bounds__(256, 2) void bww_dense_half_kernel(BwwArgs A, const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part)
+constexpr int kBwwHalfLds = 12 * BwwWideStage<TH, TW>::XB + 16 * BwwWideStage<TH, TW>::DB;
+template <int TH, int TW>
+__device__ __forceinline__ bool bww_dense_half_body(const BwwArgs &A, const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part, char *lds)
 {
     constexpr int R = 3, S = 3, TAPS = R * S;
     using Stage = BwwWideStage<TH, TW>;
-    if (deselected(A.sel, A.want)) return;              // uniform over the grid, before any barrier
-    constexpr int HW = Stage::HW, TP = TH * TW, XB = Stage::XB, DB = Stage::DB, XBUF = 4 * XB, DBUF = 4 * DB, LDS = 3 * XBUF + 4 * DBUF;
-    static_assert(LDS >= 2 * Stage::bytes(3) && 2 * LDS <= 160 * 1024, "either form in one array, two workgroups a compute unit");
-    __shared__ __attribute__((aligned(16))) char lds[LDS];
+    constexpr int HW = Stage::HW, TP = TH * TW, XB = Stage::XB, DB = Stage::DB, XBUF = 4 * XB, DBUF = 4 * DB;
+    static_assert(kBwwHalfLds<TH, TW> == 3 * XBUF + 4 * DBUF, "three halos, four dy tiles");
     unsigned *misc = reinterpret_cast<unsigned *>(lds);         // before the first tile and after the last
 
     // the wavefront index is the same in every lane: kept in a scalar register, and with it every tile coordinate
@@ -1112,18 +1183,27 @@ __global__ __launch_bounds__(256, 2) void bww_dense_half_kernel(BwwArgs A, const
         auto filled = [](float4 v) __attribute__((always_inline)) {             // values of the wavefront that are not zero
             return (unsigned)(__popcll(__ballot(v.x != 0.f)) + __popcll(__ballot(v.y != 0.f)) + __popcll(__ballot(v.z != 0.f)) + __popcll(__ballot(v.w != 0.f)));
         };
+        auto over4 = [&](int at) __attribute__((always_inline)) { return misc[at] + misc[at + 1] + misc[at + 2] + misc[at + 3]; };
         const unsigned fx = filled(vx), fd = filled(vd);
         if (lane == 0) { misc[wave] = mx; misc[4 + wave] = md; misc[8 + wave] = fx; misc[12 + wave] = fd; }
         __syncthreads();
-        const unsigned products = (misc[8] + misc[9] + misc[10] + misc[11]) * (misc[12] + misc[13] + misc[14] + misc[15]);
+        const unsigned some_x = over4(8), some_d = over4(12);
         const unsigned bits_x = max(max(misc[0], misc[1]), max(misc[2], misc[3])), bits_d = max(max(misc[4], misc[5]), max(misc[6], misc[7]));
-        xe = __builtin_amdgcn_readfirstlane(half_exponent(bits_x));
-        de = __builtin_amdgcn_readfirstlane(half_exponent(bits_d));
+        xe = __builtin_amdgcn_readfirstlane(half_exponent(bits_x, kHalfTopInput));
+        de = __builtin_amdgcn_readfirstlane(half_exponent(bits_d, kHalfTopInput));
+        // those within 2^6 of the largest
+        auto near = [](float4 v, unsigned bits) __attribute__((always_inline)) {
+            const unsigned least = max(bits, (6u << 23) + 1) - (6u << 23);
+            return (unsigned)(__popcll(__ballot(half_magnitude(v.x) >= least)) + __popcll(__ballot(half_magnitude(v.y) >= least)) +
+                              __popcll(__ballot(half_magnitude(v.z) >= least)) + __popcll(__ballot(half_magnitude(v.w) >= least)));
+        };
+        const unsigned nx = near(vx, bits_x), nd = near(vd, bits_d);
+        if (lane == 0) { misc[16 + wave] = nx; misc[20 + wave] = nd; }
+        __syncthreads();
+        const bool few = some_x * some_d < (1u << 20) / 20;     // of 1024 x 1024
+        const bool wide = over4(16) * 5 < some_x * 4 || over4(20) * 5 < some_d * 4;
         __syncthreads();                                        // (misc is overwritten from here on)
-        if ((unsigned)__builtin_amdgcn_readfirstlane((int)products) < (1u << 20) / 20) {        // of 1024 x 1024
-            bww_dense_wide_body<R, S, TH, TW, false, false, 1>(A, x, dy, part, lds);
-            return;
-        }
+        if (__builtin_amdgcn_readfirstlane((int)(few || wide))) return false;
     }
     floatx4 acc[TAPS][2][2];                            // [tap][16 k][16 c]
 #pragma unroll
@@ -1149,17 +1229,17 @@ __global__ __launch_bounds__(256, 2) void bww_dense_half_kernel(BwwArgs A, const
         if (unit >= u1) { ta.n = 0; ta.th = 40000 / TH; }
     };
     float4 sx[4], sda[2], sdb[2];
-    unsigned lows = 0;
+    unsigned lows_x = 0, lows_d = 0;                            // of the four channels of x and of dy that this thread stages
     char *const xlds = lds, *const dlds = lds + 3 * XBUF;
     Stage::fetch_x(A, x, cg, ta, sx);                           // (a split has at least one tile)
-    lows += Stage::template stash_half<XB>(sx, 1.f, xe, xlds);
+    lows_x += Stage::template stash_half<XB>(sx, 1.f, xe, xlds);
     second(u0 + 1);
     Stage::fetch_dy(A, dy, kt, ta, sda);
     Stage::fetch_dy(A, dy, kt, tb, sdb);
     Stage::fetch_x(A, x, cg, tb, sx);
-    lows += Stage::template stash_half<DB>(sda, 1.f, de, dlds);
-    lows += Stage::template stash_half<DB>(sdb, 1.f, de, dlds + DBUF);
-    lows += Stage::template stash_half<XB>(sx, 1.f, xe, xlds + XBUF);
+    lows_d += Stage::template stash_half<DB>(sda, 1.f, de, dlds);
+    lows_d += Stage::template stash_half<DB>(sdb, 1.f, de, dlds + DBUF);
+    lows_x += Stage::template stash_half<XB>(sx, 1.f, xe, xlds + XBUF);
     __syncthreads();
 
     // operands: lane l takes channel l % 16 of a block and pixels 8*(l/16) .. +7 of the tile, four per transposing read, for which
@@ -1239,36 +1319,40 @@ __global__ __launch_bounds__(256, 2) void bww_dense_half_kernel(BwwArgs A, const
         input(0, 0, 0, f[0]);
         input(0, 0, 1, f[1]);
         taps(std::integral_constant<int, 0>{}, std::integral_constant<int, 3>{});
-        lows += Stage::template stash_half<XB>(sx, 1.f, xe, spare);
+        lows_x += Stage::template stash_half<XB>(sx, 1.f, xe, spare);
         Stage::fetch_dy(A, dy, kt, ta, sda);
         Stage::fetch_dy(A, dy, kt, tb, sdb);
         __builtin_amdgcn_sched_barrier(0);
         taps(std::integral_constant<int, 3>{}, std::integral_constant<int, 6>{});
-        lows += Stage::template stash_half<DB>(sda, nsg, de, dspare);
-        lows += Stage::template stash_half<DB>(sdb, nsg, de, dspare + DBUF);
+        lows_d += Stage::template stash_half<DB>(sda, nsg, de, dspare);
+        lows_d += Stage::template stash_half<DB>(sdb, nsg, de, dspare + DBUF);
         Stage::fetch_x(A, x, cg, tb, sx);
         __builtin_amdgcn_sched_barrier(0);
         taps(std::integral_constant<int, 6>{}, std::integral_constant<int, TAPS>{});
         if (!more) break;
         __syncthreads();                                        // every wavefront is done with the pair
-        lows += Stage::template stash_half<XB>(sx, 1.f, xe, tile[0]);
+        lows_x += Stage::template stash_half<XB>(sx, 1.f, xe, tile[0]);
         __syncthreads();
         slot = (slot + 2) % 3;
     }
 
-    // values below the pieces' range that the workgroup has met, in the third halo buffer, which no one reads now.  Others may still be writing
-    // it, also the halo of a tile that does not exist: not before a barrier
+    // Fours with a value below the pieces' range, of each four channels of x, then of dy, in the third halo buffer, which no one reads now.
+    // Others may still be writing it, also the halo of a tile that does not exist: not before a barrier
     misc = reinterpret_cast<unsigned *>(xlds + (slot + 2) % 3 * XBUF);
     {
-        unsigned c = 0;
-        if (__ballot(lows != 0) != 0)
-            for (int l = 0; l < kWave; ++l) c += (unsigned)__builtin_amdgcn_readlane((int)lows, l);
+        if (__ballot((lows_x | lows_d) != 0) != 0) {
+            lows_x += __shfl_xor(lows_x, 16); lows_x += __shfl_xor(lows_x, 32);
+            lows_d += __shfl_xor(lows_d, 16); lows_d += __shfl_xor(lows_d, 32);
+        }
         __syncthreads();
-        if (lane == 0) misc[wave] = c;
+        if (lane < 16) { misc[wave * 32 + l16] = lows_x; misc[wave * 32 + 16 + l16] = lows_d; }
         __syncthreads();
     }
-    if (!active) return;
-    const float safe = kHalfSafe * fminf(4.f * (float)(misc[0] + misc[1] + misc[2] + misc[3]) / (float)((u1 - u0) * TP), 1.f);
+    auto safe = [&](int kb, int cb) __attribute__((always_inline)) {
+        const int at_x = ch * 8 + cb * 4 + l16 / 4, at_d = 16 + kh * 8 + kb * 4 + grp;
+        const unsigned lost = misc[at_x] + misc[32 + at_x] + misc[64 + at_x] + misc[96 + at_x] + misc[at_d] + misc[32 + at_d] + misc[64 + at_d] + misc[96 + at_d];
+        return kHalfSafe * fminf(4.f * (float)lost / (float)((u1 - u0) * TP), 1.f);
+    };
 
     // D layout of a 16x16 block: column (c) = lane % 16, row (k) = 4*(lane/16) + r: four consecutive output channels, one 16-byte store,
     // the lanes' side by side
@@ -1277,14 +1361,15 @@ __global__ __launch_bounds__(256, 2) void bww_dense_half_kernel(BwwArgs A, const
     auto element = [&](int k, int c, int tap) __attribute__((always_inline)) {
         return pbase + (((size_t)(k / kBlk) * CB + c / kBlk) * TAPS + tap) * (kBlk * kBlk) + (c % kBlk) * kBlk + k % kBlk;
     };
-    auto finish = [&](float v) __attribute__((always_inline)) { return fabsf(v) < safe ? __builtin_nanf("") : ldexpf(v, exponent); };
     bool finite = true;
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb) {
             const int k = k32 + kb * 16 + 4 * grp, c = c32 + cb * 16 + l16;
-            if (k >= A.K || c >= A.C) continue;
+            const float least = safe(kb, cb);
+            auto finish = [&](float v) __attribute__((always_inline)) { return fabsf(v) < least ? __builtin_nanf("") : ldexpf(v, exponent); };
+            if (!active || k >= A.K || c >= A.C) continue;
 #pragma unroll
             for (int tap = 0; tap < TAPS; ++tap) {
                 const floatx4 a = acc[tap][kb][cb];
@@ -1293,21 +1378,89 @@ __global__ __launch_bounds__(256, 2) void bww_dense_half_kernel(BwwArgs A, const
                 *reinterpret_cast<float4 *>(element(k, c, tap)) = v;
             }
         }
-    // sums that values outside the range of the pieces took part in
-    if (__builtin_expect(__ballot(!finite) != 0, 0)) {
-        split_lanes_fence();
-        floatx16 redo[TAPS];
-        bww_redo<R, S, TH, TW, 1>(A, x, dy, k32, c32, u0, u1, redo);
-        const int c = c32 + lane % 32;
-        if (c >= A.C) return;
+
+    // Gradients that are infinite (values above the pieces' range took part in them) or so small that lost values may matter: a few are
+    // computed one by one; if there are more, those of channels without any values are zeros; and for more than a few others the workgroup
+    // starts again on bf16 pieces
+    unsigned *const votes = misc + 128, *const most = misc + 256;
+    auto vote = [&](unsigned n) __attribute__((always_inline)) {
+        if (lane == 0) votes[wave] = n;
+        __syncthreads();
+        const unsigned m = max(max(votes[0], votes[1]), max(votes[2], votes[3]));
+        __syncthreads();                                        // (the words, and all others here, are written again)
+        return (unsigned)__builtin_amdgcn_readfirstlane((int)m);
+    };
+    // what(whether it is one of these, ...) of the lane's outputs, one of each lane at a time; those of three taps are asked for together
+    auto each = [&](auto what) __attribute__((always_inline)) {
+#pragma unroll 1
+        for (int t = 0; t < TAPS / 3 * 4; ++t) {
+            const int kl = t / 2 % 2 * 16 + 4 * grp, cl = t % 2 * 16 + l16;
+            const bool exists = k32 + kl < A.K && c32 + cl < A.C;
+            float *at[3];
+            float4 v[3];
 #pragma unroll
-        for (int tap = 0; tap < TAPS; ++tap)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int k = k32 + 8 * (r / 4) + 4 * (lane / 32) + r % 4;
-                if (k < A.K && !split_finite(*element(k, c, tap))) *element(k, c, tap) = redo[tap][r];
+            for (int i = 0; i < 3; ++i) {
+                at[i] = element(exists ? k32 + kl : k32, exists ? c32 + cl : c32, t / 4 * 3 + i);
+                v[i] = *reinterpret_cast<const float4 *>(at[i]);
             }
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                what(exists && !split_finite(v[i].x), kl, cl, t / 4 * 3 + i, at[i]);
+                what(exists && !split_finite(v[i].y), kl + 1, cl, t / 4 * 3 + i, at[i] + 1);
+                what(exists && !split_finite(v[i].z), kl + 2, cl, t / 4 * 3 + i, at[i] + 2);
+                what(exists && !split_finite(v[i].w), kl + 3, cl, t / 4 * 3 + i, at[i] + 3);
+            }
+        }
+    };
+    auto count = [&]() __attribute__((always_inline)) {
+        unsigned n = 0;
+        each([&](bool again, int, int, int, float *) __attribute__((always_inline)) { n += (unsigned)__popcll(__ballot(again)); });
+        return n;
+    };
+    unsigned open = 0;
+    if (__builtin_expect(__ballot(!finite) != 0, 0)) open = count();
+    unsigned worst = vote(open);
+    if (__builtin_expect(worst == 0, 1)) return true;
+    if (worst > kBwwHalfFew) {
+        bww_channels<TH, TW>(A, x, dy, kt, cg, u0, u1, most);
+        unsigned above = max(most[lane], most[64 + lane]);
+        const bool all_finite = __ballot(above >= 0x7f800000u) == 0;            // (0 * inf is not 0)
+        if (open != 0 && all_finite)
+            each([&](bool again, int kl, int cl, int, float *at) __attribute__((always_inline)) {
+                if (again && (most[ch * 32 + cl] == 0 || most[64 + kh * 32 + kl] == 0)) *at = 0.f;
+            });
+        if (open != 0) open = count();
+        worst = vote(open);
     }
+    if (worst > kBwwHalfFew) return false;
+    if (open != 0) {
+        unsigned list[kBwwHalfFew] = {}, n = 0;
+        each([&](bool again, int kl, int cl, int tap, float *) __attribute__((always_inline)) {
+            for (unsigned long long m = __ballot(again); m != 0; m &= m - 1, ++n) {
+                const int l = __builtin_ctzll(m);
+                const unsigned entry = (unsigned)(__builtin_amdgcn_readlane(kl, l) | __builtin_amdgcn_readlane(cl, l) << 5 | tap << 10);
+#pragma unroll
+                for (unsigned i = 0; i < kBwwHalfFew; ++i) list[i] = n == i ? entry : list[i];
+            }
+        });
+        double sum[kBwwHalfFew];
+        bww_some<TH, TW>(A, x, dy, k32, c32, list, open, u0, u1, sum);
+        split_lanes_fence();                                    // (other lanes wrote what the first one replaces)
+#pragma unroll
+        for (unsigned i = 0; i < kBwwHalfFew; ++i)
+            if (i < open && lane == 0) *element(k32 + (int)(list[i] & 31), c32 + (int)(list[i] >> 5 & 31), (int)(list[i] >> 10)) = (float)sum[i];
+    }
+    return true;
+}
+
+template <int TH, int TW>
+__global__ __launch_bounds__(256, 2) void bww_dense_half_kernel(BwwArgs A, const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part)
+{
+    if (deselected(A.sel, A.want)) return;              // uniform over the grid, before any barrier
+    constexpr int LDS = kBwwHalfLds<TH, TW>;
+    static_assert(LDS >= 2 * BwwWideStage<TH, TW>::bytes(3) && 2 * LDS <= 160 * 1024, "either form in one array, two workgroups a compute unit");
+    __shared__ __attribute__((aligned(16))) char lds[LDS];
+    if (!bww_dense_half_body<TH, TW>(A, x, dy, part, lds)) bww_dense_wide_body<3, 3, TH, TW, false, false, 1>(A, x, dy, part, lds);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -217,7 +217,7 @@ __device__ __forceinline__ void half_filters_block(size_t block, int Ko, int Ci,
     const int wave = threadIdx.x / kWave;
     if (threadIdx.x % kWave == 0) red[wave] = m;
     __syncthreads();
-    const int e = half_exponent(max(red[wave & 2], red[wave | 1]));
+    const int e = half_exponent(max(red[wave & 2], red[wave | 1]), kHalfTopFilters);
     const unsigned key = half_low_key(e);
     const unsigned lows = __popcll(__ballot(half_low(lo, key) != 0)) + __popcll(__ballot(half_low(hi, key) != 0));
     if (threadIdx.x % kWave == 0) red[4 + wave] = lows;

@@ -195,7 +195,7 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
         m = wave_max(m);
         if (lane == 0) misc[wave] = m;
         __syncthreads();
-        xe = __builtin_amdgcn_readfirstlane(half_exponent(max(max(misc[0], misc[1]), max(misc[2], misc[3]))));
+        xe = __builtin_amdgcn_readfirstlane(half_exponent(max(max(misc[0], misc[1]), max(misc[2], misc[3])), kHalfTopInput));
         xscale = half_scale(xe);
         xscale_low = half_scale(xe + 11);
         low_key = half_low_key(xe);

@@ -119,12 +119,13 @@ __device__ __forceinline__ void split_lanes_fence()
 // theoretical peak performance", 2022: the remainder scaled by 2^11).
 //
 // f16 has 5 exponent bits, so values are scaled by a power of two.  A workgroup takes the one that puts the largest of some
-// thousand of the values it will read into [2^11, 2^12), a block of 32 rows of filters likewise: larger ones may be
-// 16 times as large before h is infinite (such outputs come out non-finite and are computed again, as above), and from 2^-14 on, 2^25 below the
-// largest, all bits are kept.  Of a smaller value what lies below 2^-36 is lost, 2^-36 2^16 of a product at most.  An fp32 sum of n terms may
-// be off by n 2^-24 of their magnitudes, so c such values are within it in outputs of 2^5 c / n and more.  Smaller outputs (twice as large, with what else is left
+// thousand of the values it will read into [2^9, 2^10), a block of 32 rows of filters, which have no outliers as a rule, into [2^11, 2^12): larger ones may be
+// 64 or 16 times as large before h is infinite (such outputs come out non-finite and are computed again, as above).  From 2^-13 on, 2^22 or 2^24 below the
+// largest, both pieces have all their bits.  Of a smaller value what lies below 2^-36 is lost, 2^-36 2^16 of a product at most: from 2^-14 on that is
+// 2^-22 of the value, and no more is made of it.  An fp32 sum of n terms may
+// be off by n 2^-24 of their magnitudes, so c values below 2^-14 are within it in outputs of 2^5 c / n and more.  Smaller outputs (twice as large, with what else is left
 // out) are computed again, as above, where c is not zero: half_low counts the values a workgroup meets, the copy of the filters tells theirs.
-// In normal layers one value in 2^24 is as small as that and an output in 2^30 is smaller than 2^6 / n.  (Without the count, any output below
+// In normal layers one value in 2^22 (2^24) is as small as that and an output in 2^28 is smaller than 2^6 / n.  (Without the count, any output below
 // 2^6 where there is one such value: 512->512 @28 345 -> 445 us with one such filter.)
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
@@ -138,11 +139,12 @@ __host__ __device__ __forceinline__ size_t half_notes(int Ko, int terms) { retur
 constexpr float kHalfLow = 2048.f;                          // scale of l beside h
 constexpr float kHalfSafe = 64.f;                           // times c / n: outputs from here on need no second look
 
-// exponent of the scale for the largest magnitude `bits` (of a finite fp32 value; 0: nothing but zeros seen)
-__device__ __forceinline__ int half_exponent(unsigned bits)
+// exponent of the scale that brings the largest magnitude `bits` (of a finite fp32 value; 0: nothing but zeros seen) below 2^top
+constexpr int kHalfTopInput = 10, kHalfTopFilters = 12;
+__device__ __forceinline__ int half_exponent(unsigned bits, int top)
 {
     const int e = (int)(bits >> 23);
-    return bits == 0 ? 0 : min(138 - max(e, 1), 116);       // (2^(e + 11), the scale of l, is finite)
+    return bits == 0 ? 0 : min(126 + top - max(e, 1), 116);       // (2^(e + 11), the scale of l, is finite)
 }
 __device__ __forceinline__ float half_scale(int e) { return __uint_as_float((unsigned)(e + 127) << 23); }
 __device__ __forceinline__ unsigned half_magnitude(float v)

@@ -241,3 +241,71 @@ def test_bww_workgroups_that_sample_few_products_stay_on_bf16_pieces():
     err = float((bww_result(d, x, dy) - ref).norm() / ref.norm())
     # 8 terms a gradient: 2.4e-8 for each rounding of a product or a sum, of which a join is one every fourth tile; f16 pieces alone leave out 7.5e-8
     assert err <= 7e-8, err
+
+
+@pytest.mark.parametrize("name", ["1024->1024 @56x55, 49 tiles", "528->1040 37x41 pad 2"])
+def test_bww_of_channels_without_values(name):
+    """Channels that padding or ReLU has left without values, and values below the pieces' range in the other operand: the zeros are exact, other
+    gradients as exact as ever, and an infinity meets the zeros as it would in a plain sum (NaN)."""
+    d, x, dy = bww_inputs(*BWW[name], 97)
+    dead = torch.arange(16, device="cuda") >= 3
+    for a, b in ((x, dy), (dy, x)):
+        a, b = a.clone(), b.clone()
+        a[..., dead] = 0
+        b.view(-1)[::4099] = 2.0 ** -60
+        xs, dys = (a, b) if a.shape == x.shape and b.shape == dy.shape else (b, a)
+        bww_within_fp32_sum(d, xs, dys, name)
+    a = dy.clone()
+    a[..., dead] = 0
+    x[-1, 0, 1, 1, 2] = float("inf")
+    got, ref = bww_result(d, x, a), bww_exact(d, x, a)[0]
+    assert torch.equal(torch.isnan(got), torch.isnan(ref)) and torch.equal(torch.isfinite(got), torch.isfinite(ref))
+
+
+@pytest.mark.parametrize("name", BWW)
+@pytest.mark.parametrize("share,few", [(1e-3, 4), (0.3, 64)])
+def test_bww_gradients_below_what_lost_values_may_matter_to(name, share, few):
+    """A part of the values of some channels is below the pieces' range, so that now and then a gradient is too, few of a wavefront's (computed one by
+    one) or, with these channels' other values made small as well, all of them (the workgroup starts again)."""
+    d, x, dy = bww_inputs(*BWW[name], 99)
+    gen = torch.Generator(device="cuda").manual_seed(100)
+    small = torch.rand(x.shape, device="cuda", generator=gen) < share
+    small[..., few:] = False
+    x = torch.where(small, x * 2.0 ** -40, x)
+    bww_within_fp32_sum(d, x, dy, name)
+    x[:, 1, ..., :4] *= 2.0 ** -18
+    bww_within_fp32_sum(d, x, dy, name)
+
+
+@pytest.mark.parametrize("case", ["channels without values", "heavy tails", "one outlier in 10^6"])
+def test_time_of_bww_on_values_that_are_not_normal(case):
+    """Each of these had taken four to eight times as long, as one workgroup that computes its gradients again with fp32 multiply-adds is all it
+    takes.  Twice the time is what starting again on bf16 pieces costs; half of that again for noise."""
+    gen = torch.Generator(device="cuda").manual_seed(101)
+    d = st.ConvDesc(16, 64, 64, 224, 224, 3, 3, 1, 1, 1, 1)
+    assert bww_f16_pieces(d)
+    dw, ws = torch.empty((4, 4, 3, 3, 16, 16), device="cuda"), workspace(d, st.ST_PASS_BWW, True)
+
+    def time(x, dy):
+        took = []
+        for _ in range(12):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            st.st_conv_bww_dense(d, x, dy, dw, ws)
+            end.record()
+            torch.cuda.synchronize()
+            took.append(start.elapsed_time(end))
+        return sorted(took)[3]
+
+    x = torch.randn((16, 4, 224, 224, 16), device="cuda", generator=gen)
+    dy = torch.randn((16, 4, 224, 224, 16), device="cuda", generator=gen)
+    usual = time(x, dy)
+    if case == "channels without values":
+        x[..., 10:] = 0
+        dy.view(-1)[::1000003] = 2.0 ** -60
+    elif case == "heavy tails":
+        for t in (x, dy):
+            t /= torch.sqrt(-torch.log(torch.rand(t.shape, device="cuda", generator=gen).clamp_min(1e-30)))
+    else:
+        x *= torch.where(torch.rand(x.shape, device="cuda", generator=gen) < 1e-6, 100.0, 1.0)
+    assert time(x, dy) <= 3 * usual
