@@ -738,9 +738,14 @@ __global__ __launch_bounds__(256, 2) void bww_dense_kernel(BwwArgs A, const floa
 // Staging of the unit-stride kernel: as above, with the vector instructions that cost the matrix cores their issue slots taken out (203 -> 92 to ask for a
 // tile, 191 -> 167 to split and write it: 256->256 @56, N = 32, 494 -> 478 us, 512->512 @28 547 -> 529, 64->64 @224 536 -> 518).  Addresses are 32 bits behind a buffer descriptor per image, whose range check returns the zeros of channels past
 // the end; pixels outside the image ask beyond it.  A row and a column are compared as one packed pair.  Layout of a buffer: [pieces][2 halves of the 64
-// channels][32 pixels][32 channels] of dy, the same of x with kHaloRows pixels.
+// channels][32 pixels][32 channels] of dy, the same of x with XPX pixels.
+constexpr int kBwwNoTileRow = 40000;            // row of tiles that do not exist: images of these sizes have fewer (bww_big_image)
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+// Bytes of sample (h, w) within a channel block.  Unsigned: above and left of the image it wraps, as the sums it takes part in do, and for the rows of tiles
+// that do not exist, whose offset no one uses, it may
+constexpr unsigned bww_sample_offset(int h, int w, int W) { return ((unsigned)h * (unsigned)W + (unsigned)w) * (unsigned)(kBlk * 4); }
+static_assert(bww_sample_offset(kBwwNoTileRow, 31999, 32000) != 0 && bww_sample_offset(-1, -1, 5) + 6u * (kBlk * 4) == 0, "(an overflow of int is no constant)");
 // BIG: images of any size (bww_big_image), with 64-bit addresses.
 template <int TH, int TW, bool BIG = false>
 struct BwwWideStage {
@@ -786,7 +791,7 @@ struct BwwWideStage {
         } else {
             const __amdgpu_buffer_rsrc_t from =
                 __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base), 0, min(4, CB - cb) * (H * W) * (kBlk * 4), 0x00020000);
-            const unsigned at = (unsigned)((h0 * W + w0) * (kBlk * 4) + (q >> 2) * (H * W * (kBlk * 4)) + (q & 3) * 16);
+            const unsigned at = bww_sample_offset(h0, w0, W) + (unsigned)((q >> 2) * (H * W * (kBlk * 4)) + (q & 3) * 16);
             const u16x2 first = {(unsigned short)h0, (unsigned short)w0}, last = {(unsigned short)(H - 1), (unsigned short)(W - 1)};
 #pragma unroll
             for (int i = 0; i < NP; ++i) {
@@ -1221,12 +1226,12 @@ __device__ __forceinline__ bool bww_dense_half_body(const BwwArgs &A, const floa
     auto second = [&](int unit) __attribute__((always_inline)) {
         tb = ta;
         tb.step(A);
-        if (unit >= u1) { tb.n = 0; tb.th = 40000 / TH; }
+        if (unit >= u1) { tb.n = 0; tb.th = kBwwNoTileRow / TH; }
     };
     auto first = [&](int unit) __attribute__((always_inline)) {
         ta = tb;
         ta.step(A);
-        if (unit >= u1) { ta.n = 0; ta.th = 40000 / TH; }
+        if (unit >= u1) { ta.n = 0; ta.th = kBwwNoTileRow / TH; }
     };
     float4 sx[4], sda[2], sdb[2];
     unsigned lows_x = 0, lows_d = 0;                            // of the four channels of x and of dy that this thread stages
