@@ -1915,7 +1915,7 @@ constexpr int kAnyForm = -2;
 // the products in them (3x3 64->64, 4 x 30 x 28 pixels, 105 partial sums, 4 % non-zero products: error 9.9e-8 of the norm one
 // after the other, 5.7e-8 here; v_mfma_f32_32x32x2_f32 and its 34 partial sums 9.6e-8).
 struct Sum4 { double x, y, z, w; };
-__device__ __forceinline__ Sum4 add_partials(const float4 *part, size_t n4, int first, int splits, int step, bool joined)
+__device__ __forceinline__ Sum4 add_partials(const float4 *part, size_t n4, int first, int splits, int step)
 {
     constexpr int BATCH = 8;
     Sum4 s = {0., 0., 0., 0.};
@@ -1924,11 +1924,6 @@ __device__ __forceinline__ Sum4 add_partials(const float4 *part, size_t n4, int 
         float4 v[BATCH];
 #pragma unroll
         for (int b = 0; b < BATCH; ++b) v[b] = part[(size_t)(p + b * step) * n4];
-        if (joined) {
-#pragma unroll
-            for (int b = 0; b < BATCH; ++b) { s.x += v[b].x; s.y += v[b].y; s.z += v[b].z; s.w += v[b].w; }
-            continue;
-        }
         const float4 t = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
         s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
     }
@@ -1939,7 +1934,26 @@ __device__ __forceinline__ Sum4 add_partials(const float4 *part, size_t n4, int 
     return s;
 }
 
-__global__ __launch_bounds__(1024, 8) void bww_reduce_kernel(const float4 *part, float4 *dw, size_t n4, Splits3 sp,
+// The same all in 64 bits, for sums of two teams each (bww_teams)
+__device__ __forceinline__ Sum4 add_joined(const float4 *part, size_t n4, int first, int splits, int step)
+{
+    constexpr int BATCH = 8;
+    Sum4 s = {0., 0., 0., 0.};
+    for (int p = first; p < splits; p += BATCH * step) {
+        float4 v[BATCH];
+#pragma unroll
+        for (int b = 0; b < BATCH; ++b) v[b] = part[(size_t)min(p + b * step, splits - 1) * n4];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int b = 0; b < BATCH; ++b) {
+            if (p + b * step >= splits) break;
+            s.x += v[b].x; s.y += v[b].y; s.z += v[b].z; s.w += v[b].w;
+        }
+    }
+    return s;
+}
+
+__global__ __launch_bounds__(1024) void bww_reduce_kernel(const float4 *part, float4 *dw, size_t n4, Splits3 sp,
                                                           const unsigned *sel, int want)
 {
     int form = want < 0 ? 0 : want;
@@ -1954,7 +1968,7 @@ __global__ __launch_bounds__(1024, 8) void bww_reduce_kernel(const float4 *part,
     // 18.1 -> 16.4 us for the whole call; two partial sums of 576 are faster added up by one thread each, 17.5 : 18.4).
     if (splits <= 2 || (splits <= 16 && n4 >= 16384)) {
         for (size_t i = (size_t)blockIdx.x * 1024 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 1024) {
-            const Sum4 s = add_partials(part + i, n4, 0, splits, 1, joined);
+            const Sum4 s = joined ? add_joined(part + i, n4, 0, splits, 1) : add_partials(part + i, n4, 0, splits, 1);
             dw[i] = make_float4((float)s.x, (float)s.y, (float)s.z, (float)s.w);
         }
         return;
@@ -1966,7 +1980,7 @@ __global__ __launch_bounds__(1024, 8) void bww_reduce_kernel(const float4 *part,
         const size_t i = blk * 64 + o;
         Sum4 s = {0., 0., 0., 0.};
         if (i < n4)
-            s = add_partials(part + i, n4, sl, splits, 16, joined);
+            s = joined ? add_joined(part + i, n4, sl, splits, 16) : add_partials(part + i, n4, sl, splits, 16);
         red[sl][o] = s;
         __syncthreads();
         if (sl == 0 && i < n4) {
