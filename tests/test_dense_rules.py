@@ -204,3 +204,11 @@ def test_workspaces_that_sufficed_suffice(N, C, K, H, W, stride, pad, bwi, size)
     32 channels, with shares of its own, must not ask for more."""
     d = st.ConvDesc(N, C, K, H, W, 3, 3, stride, stride, pad, pad)
     assert st.st_conv_workspace_bytes(d, st.ST_PASS_BWI if bwi else st.ST_PASS_FWD, True) <= size
+
+
+@pytest.mark.parametrize("N,C,K,H,W,kernel", [(4, 112, 32, 174, 174, "16"), (4, 144, 32, 174, 174, "16"), (4, 256, 32, 174, 174, "32"), (5, 112, 32, 174, 174, "32"),
+                                              (41, 112, 32, 56, 56, "32"), (42, 112, 32, 56, 56, "32")])
+def test_tiles_of_256_pixels_that_take_one_round_more(N, C, K, H, W, kernel):
+    """479 workgroups of the kernel of 16 channels are one round of the chip, 525 of the other, whose tiles strips of 174 columns cut short, two."""
+    assert dense_kernel(st.ConvDesc(N, C, K, H, W, 3, 3, 1, 1, 1, 1)) == kernel
+    assert dense_kernel(st.ConvDesc(N, K, C, H, W, 3, 3, 1, 1, 1, 1), bwi=True) == kernel
