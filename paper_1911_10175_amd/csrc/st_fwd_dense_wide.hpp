@@ -1,4 +1,4 @@
-// The dense matrix-core kernel of the 3x3 correlations with an even number of input channel blocks as a template: 32 channels
+// The dense matrix-core kernel of most 3x3 correlations of 64 and more input channels (fwd_dense_wide) as a template: 32 channels
 // at a time through v_mfma_f32_16x16x32_f16 (three products of two f16 pieces, HALF) or _bf16 (six of three bf16 pieces); st_split.hpp has both.
 //
 // Why another instruction than st_fwd_dense_impl.hpp uses: with two operands of random values in registers and nothing else to

@@ -309,3 +309,47 @@ def test_time_of_bww_on_values_that_are_not_normal(case):
     else:
         x *= torch.where(torch.rand(x.shape, device="cuda", generator=gen) < 1e-6, 100.0, 1.0)
     assert time(x, dy) <= 3 * usual
+
+
+ROUNDING = 2.4e-8                                   # of one rounding to 24 bits, in the root mean square, and what two pieces leave out of a product
+PIECES = 7.5e-8
+
+
+def stages_of(d, bwi):
+    """Reduced channels of the longest share of a launch, from its workspace: the filter copy (a multiple of 256 bytes), then the partial outputs."""
+    Ci, Ko, px = (d.K, d.C, d.H * d.W) if bwi else (d.C, d.K, d.OH * d.OW)
+    need = st.st_conv_workspace_bytes(d, st.ST_PASS_BWI if bwi else st.ST_PASS_FWD, True)
+    extra = max(0, need - (Ko + 127) // 128 * 128 * Ci * 9 * 6)
+    shares = 1 + extra // (4 * d.N * Ko * px)
+    return -(-(-(-Ci // 32)) // shares) * 32
+
+
+@pytest.mark.parametrize("name", GEOMS)
+def test_error_of_every_kernel_on_ordinary_values(name):
+    """Every column-block width, halo size, stride and kind of last stage.  Terms of independent signs: the three taps of 32 channels of a sum round 12 times on the
+    way up (6.5 roundings of the whole), T = C / 32 * 3 sums join one after the other ((T + 1) / 2), and the pieces leave out theirs.  A quarter more
+    for what products cut off of each other.  Without one of the cross products it would be 3e-4."""
+    g = GEOMS[name]
+    x, w, dy = inputs(g, 87)
+    L = DeviceLayer(g, x, w, dy)
+    passes = half_passes(g)
+    assert passes, "another kernel: test is void"
+    for p in passes:
+        ref = corr(g, x, w, dy, p)[0]
+        T = stages_of(desc_of(g), p == "bwi") // 32 * 3
+        bound = 1.25 * np.hypot(np.sqrt(6.5 + (T + 1) / 2) * ROUNDING, PIECES)
+        err = np.linalg.norm(getattr(L, p)(True) - ref) / np.linalg.norm(ref)
+        assert err <= bound, f"{p}: {err:.3g}, bound {bound:.3g}"
+
+
+@pytest.mark.parametrize("name", BWW)
+def test_error_of_bww_on_ordinary_values(name):
+    """Both tile shapes.  A pair of tiles rounds 8 times on the way up (4.5), T / 2 pairs join."""
+    d, x, dy = bww_inputs(*BWW[name], 103)
+    splits = max(1, st.st_conv_workspace_bytes(d, st.ST_PASS_BWW, True) // (d.K * d.C * 36))
+    tiles = d.N * min(-(-d.OH // h) * -(-d.OW // w) for h, w in ((4, 8), (2, 14)))
+    pairs = -(-(-(-tiles // splits)) // 2)
+    got, ref = bww_result(d, x, dy), bww_exact(d, x, dy)[0]
+    bound = 1.25 * np.hypot(np.sqrt(4.5 + (pairs + 1) / 2) * ROUNDING, PIECES)
+    err = float((got - ref).norm() / ref.norm())
+    assert err <= bound, f"{err:.3g}, bound {bound:.3g}"
