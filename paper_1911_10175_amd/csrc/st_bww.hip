@@ -1907,8 +1907,9 @@ __global__ __launch_bounds__(512, 4) void pw_bww_sparse_kernel(BwwArgs A, const 
 // sp.f[form] = number of partial sums the form (0 tests x, 1 tests dy, 2 dense) leaves behind; with
 // want = kAnyForm the launch adds up those of whichever form the sampled counts selected, else it
 // belongs to the form `want` and does nothing when another one was selected.
-// joined: the dense ones are sums of two teams each (bww_teams) and are added up in 64 bits.
-struct Splits3 { int f[3]; bool joined; };
+// JOINED: those of the dense form are sums of two teams each (bww_teams) and are added up in 64 bits (an instance of its own: the loop beside the other
+// costs every launch 0.2 to 0.4 us).
+struct Splits3 { int f[3]; };
 constexpr int kAnyForm = -2;
 // part[first] + part[first + step] + ... below `splits` (n4 float4 apart), eight loads in flight at a time: each eight in
 // pairs, their sums in 64 bits.  Added up one after the other in 32 bits, hundreds of partial sums round more often than
@@ -1953,6 +1954,7 @@ __device__ __forceinline__ Sum4 add_joined(const float4 *part, size_t n4, int fi
     return s;
 }
 
+template <bool JOINED>
 __global__ __launch_bounds__(1024) void bww_reduce_kernel(const float4 *part, float4 *dw, size_t n4, Splits3 sp,
                                                           const unsigned *sel, int want)
 {
@@ -1962,13 +1964,17 @@ __global__ __launch_bounds__(1024) void bww_reduce_kernel(const float4 *part, fl
         if (want != kAnyForm && form != want) return;
     }
     const int splits = form == 0 ? sp.f[0] : form == 1 ? sp.f[1] : sp.f[2];
-    const bool joined = sp.joined && form == 2;
+    auto add = [&](const float4 *p, int first, int step) __attribute__((always_inline)) {
+        if constexpr (JOINED)
+            if (form == 2) return add_joined(p, n4, first, splits, step);
+        return add_partials(p, n4, first, splits, step);
+    };
     // Few splits: a thread per output.  With few outputs as well, that many threads would wait for one load after the other;
     // there the 16 wavefronts of a workgroup share the partial sums (48->48 @12 stride 2, N = 4, 9 partial sums of 5184 float4:
     // 18.1 -> 16.4 us for the whole call; two partial sums of 576 are faster added up by one thread each, 17.5 : 18.4).
     if (splits <= 2 || (splits <= 16 && n4 >= 16384)) {
         for (size_t i = (size_t)blockIdx.x * 1024 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 1024) {
-            const Sum4 s = joined ? add_joined(part + i, n4, 0, splits, 1) : add_partials(part + i, n4, 0, splits, 1);
+            const Sum4 s = add(part + i, 0, 1);
             dw[i] = make_float4((float)s.x, (float)s.y, (float)s.z, (float)s.w);
         }
         return;
@@ -1980,7 +1986,7 @@ __global__ __launch_bounds__(1024) void bww_reduce_kernel(const float4 *part, fl
         const size_t i = blk * 64 + o;
         Sum4 s = {0., 0., 0., 0.};
         if (i < n4)
-            s = joined ? add_joined(part + i, n4, sl, splits, 16) : add_partials(part + i, n4, sl, splits, 16);
+            s = add(part + i, sl, 16);
         red[sl][o] = s;
         __syncthreads();
         if (sl == 0 && i < n4) {
@@ -2199,15 +2205,21 @@ size_t partial_bytes(const st_conv_desc &d, const BwwArgs &A)
     return (size_t)A.splits * d.K * d.C * d.S * d.R * sizeof(float);
 }
 
+hipError_t launch_reduce(const st_conv_desc &d, const Splits3 &sp, bool joined, const float *part, float *dw, const unsigned *sel, int want, hipStream_t s)
+{
+    const size_t n4 = (size_t)d.K * d.C * d.S * d.R / 4, nblk = (n4 + 63) / 64;
+    const dim3 grid((unsigned)(nblk < kReduceGrid ? nblk : kReduceGrid));
+    const float4 *p4 = reinterpret_cast<const float4 *>(part);
+    float4 *dw4 = reinterpret_cast<float4 *>(dw);
+    if (joined) hipLaunchKernelGGL(bww_reduce_kernel<true>, grid, dim3(1024), 0, s, p4, dw4, n4, sp, sel, want);
+    else hipLaunchKernelGGL(bww_reduce_kernel<false>, grid, dim3(1024), 0, s, p4, dw4, n4, sp, sel, want);
+    return hipGetLastError();
+}
+
 hipError_t reduce(const st_conv_desc &d, const BwwArgs &A, const float *part, float *dw, hipStream_t s, bool joined = false)
 {
     if (A.splits == 1) return hipSuccess;               // the kernel wrote dw itself
-    const size_t n4 = (size_t)d.K * d.C * d.S * d.R / 4;
-    const size_t nblk = (n4 + 63) / 64;
-    const Splits3 sp = {{A.splits, A.splits, A.splits}, joined};
-    hipLaunchKernelGGL(bww_reduce_kernel, dim3((unsigned)(nblk < kReduceGrid ? nblk : kReduceGrid)), dim3(1024), 0, s,
-                       reinterpret_cast<const float4 *>(part), reinterpret_cast<float4 *>(dw), n4, sp, A.sel, A.want);
-    return hipGetLastError();
+    return launch_reduce(d, Splits3{{A.splits, A.splits, A.splits}}, joined, part, dw, A.sel, A.want, s);
 }
 
 }  // namespace
@@ -2409,13 +2421,8 @@ hipError_t launch_bww_auto_merged(const st_conv_desc &d, const float *x, const f
         if (err != hipSuccess) return err;
     }
     if ((err = launch_bww_dense_3x3(d, A2, x, dy, ws, s)) != hipSuccess) return err;
-    const size_t n4 = (size_t)d.K * d.C * d.S * d.R / 4;
-    const size_t nblk = (n4 + 63) / 64;
     const int partials = bww_dense_partials(d, A2);
-    const Splits3 sp = {{A0.splits, A1.splits, partials}, partials < A2.splits};
-    hipLaunchKernelGGL(bww_reduce_kernel, dim3((unsigned)(nblk < kReduceGrid ? nblk : kReduceGrid)), dim3(1024), 0, s,
-                       reinterpret_cast<const float4 *>(ws), reinterpret_cast<float4 *>(dw), n4, sp, sel, direct ? 2 : kAnyForm);
-    return hipGetLastError();
+    return launch_reduce(d, Splits3{{A0.splits, A1.splits, partials}}, partials < A2.splits, ws, dw, sel, direct ? 2 : kAnyForm, s);
 }
 
 hipError_t launch_bww_dense(const st_conv_desc &d, const float *x, const float *dy, float *dw,
