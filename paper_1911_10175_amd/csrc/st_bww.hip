@@ -1205,7 +1205,7 @@ __device__ __forceinline__ bool bww_dense_half_body(const BwwArgs &A, const floa
         const unsigned nx = near(vx, bits_x), nd = near(vd, bits_d);
         if (lane == 0) { misc[16 + wave] = nx; misc[20 + wave] = nd; }
         __syncthreads();
-        const bool few = some_x * some_d < (1u << 20) / 20;     // of 1024 x 1024
+        const bool few = some_x * some_d < (1u << 20) / 14;     // of 1024 x 1024 (kBwwHalfTiles)
         const bool wide = over4(16) * 5 < some_x * 4 || over4(20) * 5 < some_d * 4;
         __syncthreads();                                        // (misc is overwritten from here on)
         if (__builtin_amdgcn_readfirstlane((int)(few || wide))) return false;
@@ -2040,8 +2040,10 @@ constexpr int kBwwTargetWorkgroups = 512;
 constexpr int kBwwShortUnits = 16;
 // Unit-stride dense launches with this many tiles for a workgroup multiply f16 pieces.  In units of (1e-8 of the norm) squared T tiles err 54 + 2.9 T with
 // bf16 pieces, whose sums join once a tile, and 130 + 1.3 T with f16 ones (256->256 @56, N = 32, half zeros, T = 98, 1.85e-7 : 1.61e-7, at 50 / 90 %
-// 1.69e-7 : 1.62e-7, 128->256 @56, T = 49, 1.37e-7 : 1.36e-7, 512->512 @14, T = 28, 1.17e-7 : 1.28e-7).  Where fewer than 5 % of the products are not
-// zero sums have few terms to round, and a workgroup that samples that stays on bf16 pieces (90 / 90 %: 1.06e-7 : 1.17e-7)
+// 1.69e-7 : 1.62e-7, 128->256 @56, T = 49, 1.37e-7 : 1.36e-7, 512->512 @14, T = 28, 1.17e-7 : 1.28e-7).  Where few products are not zero
+// sums have few terms to round, and a workgroup that samples that stays on bf16 pieces.  The line is at one in 14 (bf16 : f16, 1e-8 of the norm, zeros in x / in
+// dy: 32 x 128->256 @56 at 50 / 85 %, 7.5 % of the products, 12.71 : 12.66, 0 / 93 %, 7 %, 13.01 : 13.04, 50 / 88 %, 6 %, 12.36 : 12.55, 77 / 77 %, 5.3 %,
+// 12.40 : 12.48; 16 x 256->256 @56 at the same 13.16 : 13.09, 13.06 : 13.06, 12.85 : 13.03, 12.59 : 12.67)
 constexpr long long kBwwHalfTiles = 48;
 
 BwwArgs make_args(const st_conv_desc &d, int TH, int TW, bool tiles_over_input)

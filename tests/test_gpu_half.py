@@ -243,6 +243,19 @@ def test_bww_workgroups_that_sample_few_products_stay_on_bf16_pieces():
     assert err <= 7e-8, err
 
 
+def test_bww_of_one_product_in_18_stays_on_bf16_pieces():
+    """Half zeros in x, 89 % in dy, and values whose pieces leave 2^-22 of every product out, whatever the signs: 2.4e-7 of the norm."""
+    d, x, dy = bww_inputs(1, 1024, 1024, 56, 55, 1, 99)
+    gen = torch.Generator(device="cuda").manual_seed(100)
+    v = 1 + 2.0 ** -11 - 2.0 ** -22
+    x = (x > 0) * v
+    dy = torch.sign(dy) * (torch.rand(dy.shape, device="cuda", generator=gen) < 0.22) * v
+    ref = bww_exact(d, x, dy)[0]
+    err = float((bww_result(d, x, dy) - ref).norm() / ref.norm())
+    # 170 terms a gradient, a rounding of 2.4e-8 to 3.5e-8 each eight of them and each join
+    assert err <= 1.7e-7, err
+
+
 @pytest.mark.parametrize("name", ["1024->1024 @56x55, 49 tiles", "528->1040 37x41 pad 2"])
 def test_bww_of_channels_without_values(name):
     """Channels that padding or ReLU has left without values, and values below the pieces' range in the other operand: the zeros are exact, other
