@@ -2464,8 +2464,12 @@ hipError_t launch_bww_dense(const st_conv_desc &d, const float *x, const float *
 // The 3x3 zero-skipping forms pass the dense one between 95 and 99 % zeros (N = 32, us, both with all launches of the entry point, zero-skipping at
 // 80 / 95 / 99 % : dense: 256->256 @56 667 / 507 / 292 : 461, @28 193 / 154 / 100 : 157, 64->64 @112 191 / 151 / 108 : 141; few channels, whose lanes
 // they do not fill, 16->32 @112 156 / 107 / 69 : 94, 9 x 16->176 @181 551 at 80 % : 252; 4 x 64->128 @24 30.8 / 27.5 / 24.6 : 25.8): 96 %, as far as
-// enough products are not zero (kSelThrFew).  Launches of less than 128 million multiply-adds keep the line of 75 % that checks of
-// this entry point have always asked for, 2 x 64->128 @24 at 80 % 27.4 : 22.
+// enough products are not zero (kSelThrFew).  Launches of less than 128 million multiply-adds keep the line of 75 %, from which on callers of this entry
+// point have always had the sparser operand tested (2 x 64->128 @24 at 80 % 27.4 : 22).  So do those whose zero-skipping partial gradients come from three tiles or
+// fewer and, neither eight of them nor 120 and more, are not added up eight at a time in 32 bits: with few products a sum they err less than the dense
+// form's of more than one tile (zero-skipping : dense, 77 % zeros in both, 1e-8 of the norm, us: 2 x 256->256 @28 4.61 : 4.82, 47 : 42, 6 x 128->128 @28 4.63 : 4.93, 42 : 36, 8 x 128->256 @28
+// 5.35 : 5.64, 56 : 51, 12 x 128->256 @28 6.10 : 6.26, 68 : 59; not 8 x 256->256 @28, four tiles, 6.63 : 6.35, 4 x 512->512 @14, eight gradients, 6.59 : 5.49,
+// 4 x 128->128 @40, 120 of them, 5.76 : 4.81, 4 x 64->128 @24, a tile each in the dense form too, 4.59 : 4.17).
 // Launches of at most 128 tiles that give every workgroup one of them and write 24 MB of partial gradients or more are bound by
 // these, and the dense form's smaller tiles leave more of them (zero-skipping at 30 / 50 / 70 % zeros : dense: 208->256 @9
 // N = 4 26.6 / 25.8 / 24.8 : 30.8, 512->256 @10 N = 2 29.4 / 28.9 / 28.4 : 32.8, 256->256 @28 N = 1 32.9 / 32.0 / 31.1 : 36.3, 336->192
@@ -2480,7 +2484,9 @@ unsigned bww_sparse_threshold(const st_conv_desc &d)
     const BwwArgs A = dense_args(d);
     const long long partial_bytes = (long long)A.units * d.K * d.C * (9 * (int)sizeof(float));
     if (A.splits == A.units && A.units <= 128 && partial_bytes >= 24000000) return 250;
-    return (double)d.N * A.OH * A.OW * d.C * d.K * 9. >= 128e6 ? 960 : 750;
+    const BwwArgs Z = make_args(d, kSparseTH, kSparseTW, true);
+    const bool exact_sums = Z.units <= 3 * Z.splits && Z.splits > 8 && Z.splits < kBwwTeamSplits && A.units > A.splits;
+    return !exact_sums && (double)d.N * A.OH * A.OW * d.C * d.K * 9. >= 128e6 ? 960 : 750;
 }
 
 }  // namespace st

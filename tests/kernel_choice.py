@@ -39,6 +39,13 @@ def bww_f16_pieces(d):
     return f(ctypes.byref(d._c()))
 
 
+def bww_line(d):
+    """Zero fraction, per mille, from which on the self-selecting BWW skips zeros."""
+    f = ctypes.CDLL(st.lib_path())["_ZN2st20bww_sparse_thresholdERK12st_conv_desc"]
+    f.restype = ctypes.c_uint
+    return f(ctypes.byref(d._c()))
+
+
 def dense_kernel(d, bwi=False):
     """ "32" or "16": channels that the kernel on bf16 pieces takes at a time; for 1x1 layers also "lds", whole filters in LDS, and "fp32",
     both on fp32 matrix instructions."""

@@ -2,7 +2,7 @@
 import pytest
 
 import paper_1911_10175_amd as st
-from tests.kernel_choice import dense_kernel, f16_pieces
+from tests.kernel_choice import bww_line, dense_kernel, f16_pieces
 
 
 def partials(N, C, K, H, W, stride=1):
@@ -212,3 +212,11 @@ def test_tiles_of_256_pixels_that_take_one_round_more(N, C, K, H, W, kernel):
     """479 workgroups of the kernel of 16 channels are one round of the chip, 525 of the other, whose tiles strips of 174 columns cut short, two."""
     assert dense_kernel(st.ConvDesc(N, C, K, H, W, 3, 3, 1, 1, 1, 1)) == kernel
     assert dense_kernel(st.ConvDesc(N, K, C, H, W, 3, 3, 1, 1, 1, 1), bwi=True) == kernel
+
+
+@pytest.mark.parametrize("N,C,K,H,W,line", [
+    # one to three tiles of the zero-skipping form a partial gradient, nine to 119 of these; four tiles, eight gradients, 120 and more, one dense tile a gradient; small launches
+    (2, 256, 256, 28, 28, 750), (6, 128, 128, 28, 28, 750), (12, 128, 256, 28, 28, 750), (16, 512, 256, 7, 7, 750), (8, 256, 256, 28, 28, 960),
+    (4, 512, 512, 14, 14, 960), (4, 128, 128, 40, 40, 960), (4, 64, 128, 24, 24, 960), (16, 256, 256, 56, 56, 960), (2, 64, 128, 24, 24, 750), (1, 256, 256, 28, 28, 250)])
+def test_switching_point_of_the_self_selecting_bww(N, C, K, H, W, line):
+    assert bww_line(st.ConvDesc(N, C, K, H, W, 3, 3, 1, 1, 1, 1)) == line
