@@ -43,18 +43,27 @@ struct WideLds {
     // pieces: [3 or 2 pieces][4 groups of 8 channels][sample][8 channels] of 16 bits, i.e. 16 bytes per sample and group,
     // so that neighbouring lanes (pixels) of an operand read are 16 bytes apart
     static constexpr int NP = HALF ? 2 : 3, BUF = HPC * 16 * NP;
-    // then, HALF: the largest magnitudes the four wavefronts have sampled, and the fours they have staged with one below the pieces' range
-    static constexpr int MISC = BUFS * BUF, FLOATS = MISC + (HALF ? 8 : 0);
+    // then, HALF, for each of the four wavefronts: the largest magnitude it has met, the fours it has staged with one below the pieces' range,
+    // whether outputs of it are to be computed again
+    static constexpr int MISC = BUFS * BUF, FLOATS = MISC + (HALF ? 12 : 0);
+    // whether there may be a second pass.  Not with one buffer: its code, though it seldom runs, has 6 to 16 more registers spilled there (32 x 256->32 @56 56.4 : 58.5 us,
+    // 22 x 112->16 @165 149.6 : 156.3, stride 2 128->128 @56 34.9 : 35.2)
+    static constexpr bool TWICE = HALF && BUFS == 2;
 };
 
 
 // wg = index of the workgroup among those of the launch, cshare = its share of the channel split; lds: WideLds::FLOATS floats, 16-byte
 // aligned.  Every thread of the workgroup makes the call (the body contains barriers).
-// HALF: products from two f16 pieces, else, for short reductions (kSplitApart), from three bf16 pieces
-template <int KQ, int HPC, bool HALF, int MODE>
-__device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *__restrict__ in, const float *__restrict__ wd,
+// HALF: products from two f16 pieces, else, for short reductions (kSplitApart), from three bf16 pieces.  With f16 pieces the outputs that these cannot give
+// (values above their range took part, or small ones that may matter) are left to a second pass (TWICE): the first one (FIRST) returns whether any wavefront
+// has such, which ones in `redo`, the scale in `xe`.  The second one looks for the largest value and multiplies all over with a scale that holds it;
+// where that can't help, and after it, they are computed with fp32 multiply-adds, 32 x 32 at a time, which takes five times as long as a whole workgroup.  us, bf16 pieces : fp32
+// only : both, one in 10^4 or 10^6 values 1000 times as large: BWI 32 x 128->128 @28 42 : 312 : 75, 42 : 176 : 46, 16 x 256->256 @56 253 : 993 : 283, 254 : 225 : 163,
+// FWD 296 : 502 : 262, 258 : 195 : 195; all between 2^-40 and 1 as before, BWI 42 : 105, 254 : 300.
+template <int KQ, int HPC, bool HALF, int MODE, bool FIRST>
+__device__ __forceinline__ bool fwd_dense_wide_body(const Geom &g, const float *__restrict__ in, const float *__restrict__ wd,
                                                float *__restrict__ out, float *__restrict__ parts, const FlatGrid &fq, int kgroups,
-                                               int csplit, size_t part_stride, int wg, int cshare, float *lds_base)
+                                               int csplit, size_t part_stride, int wg, int cshare, int &xe, unsigned &redo, float *lds_base)
 {
     using Cfg = FlatCfg<MODE>;
     using Lds = WideLds<KQ, HPC, HALF>;
@@ -66,8 +75,10 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
     constexpr bool DB = Lds::BUFS == 2;
     static_assert(!DB || NLD <= NT, "a piece a tap");
 
+    unsigned tid = threadIdx.x;
+    if constexpr (!FIRST) asm volatile("" : "+v"(tid));         // (nothing of the first pass is kept for this one)
     // the wavefront index is the same in every lane: kept in a scalar register, and with it every tile coordinate
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(tid / kWave)), lane = (int)(tid % kWave);
     const int l16 = lane % 16, grp = lane / 16;
     const int kqi = wave % KQ, tqi = wave / KQ;
     const int kg = wg % kgroups, tile = wg / kgroups;
@@ -77,7 +88,7 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
     const int strip = tile % fq.strips, ti = tile / fq.strips;
     const int c0 = (int)((long long)fq.cols * strip / fq.strips), w = (int)((long long)fq.cols * (strip + 1) / fq.strips) - c0;
     const int npx = g.N * fq.rows * w, q0 = ti * fq.tpx;
-    if (q0 >= npx) return;                                       // (narrower strips have fewer tiles; uniform)
+    if (q0 >= npx) return false;                                 // (narrower strips have fewer tiles; uniform)
     const int qend = min(q0 + fq.tpx, npx), qs = q0 + tqi * kWavePx;
     // virtual rows: image n, grid row oh starts at n * VR + oh * PSTEP with VR = (rows-1)*PSTEP + NV
     const int VR = (fq.rows - 1) * PSTEP + NV, pitch = (w - 1) * PSTEP + NU;
@@ -121,7 +132,7 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
     // halo staging: the 16-byte pieces of a stage, eight for a sample, are split among the 256 lanes, so that a lane's are 32 samples apart.
     // poff: the piece's pixel relative to the stage's first plane of image n0, -1 for padding
     int poff[NLD];
-    const int sample0 = (int)threadIdx.x / 8, sblock = (int)threadIdx.x / 4 % 2;
+    const int sample0 = (int)(tid / 8), sblock = (int)(tid / 4 % 2);
     const int HW = g.Hi * g.Wi;
 #pragma unroll
     for (int jj = 0; jj < NLD; ++jj) {
@@ -133,7 +144,7 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
         poff[jj] = ok ? ((n - n0) * CiB + sblock) * HW + ih * g.Wi + iw : -1;
     }
     const size_t plane = (size_t)HW * kBlk;
-    const float *in0 = in + (size_t)n0 * CiB * plane + threadIdx.x % 4 * 4;
+    const float *in0 = in + (size_t)n0 * CiB * plane + tid % 4 * 4;
     float4 hreg[NLD];
     auto absent = [&](int st) __attribute__((always_inline)) { return HALF && 2 * st + sblock >= CiB; };
     // (unconditional loads, padding from a block of zeros: a load under a condition is waited for where the condition ends)
@@ -148,7 +159,7 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
     };
     float xscale = 0.f, xscale_low = 0.f;                        // HALF: of the input's pieces h and l
     unsigned low_key = 0, lows = 0;
-    const int stash_at = ((sblock * 2 + ((int)threadIdx.x >> 1 & 1)) * HPC + sample0) * 2 + (threadIdx.x & 1);
+    const int stash_at = ((sblock * 2 + (int)(tid >> 1 & 1)) * HPC + sample0) * 2 + (int)(tid & 1);
     auto stash1 = [&](char *buf, int jj) __attribute__((always_inline)) {
         if ((jj + 1) * 32 > HPC && jj * 32 + sample0 >= HPC) return;
         // (the paths that stash are many, and what they share must not be computed ahead of them all, where the loads would be waited for)
@@ -180,22 +191,64 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
             for (int l = 0; l < kWave; ++l) c += (unsigned)__builtin_amdgcn_readlane((int)lows, l);
         if (lane == 0) misc[4 + wave] = c;
     };
+    auto where = [&](int q, int &n, int &oh, int &ow) __attribute__((always_inline)) {
+        const int row = q / w;
+        n = row / fq.rows;
+        oh = row % fq.rows;
+        ow = c0 + q % w;
+        return q < qend;
+    };
+    // outputs that values outside the range of the scaled pieces took part in
+    auto recompute = [&]() __attribute__((always_inline)) {
+        split_lanes_fence();
+#pragma unroll 1
+        for (int pb = 0; pb < 2; ++pb) {
+            if ((redo >> pb & 1) == 0) continue;
+            int n, oh, ow;
+            const bool valid = where(qs + pb * 32 + lane % 32, n, oh, ow);
+            split_redo_corr(g, in, out, valid, n, oh, ow, kb32, 2 * st0, min(2 * st1, CiB));
+        }
+    };
+    if constexpr (!FIRST) {
+        // the largest value of all: whether those above the sampled ones are the reason for the second pass, and not so far above that the others
+        // would be small beside them
+        unsigned m = 0;
+#pragma unroll 1
+        for (int st = st0; st < st1; ++st) {
+            fetch(st);
+#pragma unroll
+            for (int jj = 0; jj < NLD; ++jj) m = max(m, half_magnitude_or_infinite(hreg[jj]));
+        }
+        m = wave_max(m);
+        if (lane == 0) misc[wave] = m;
+        __syncthreads();
+        const unsigned most = (unsigned)__builtin_amdgcn_readfirstlane((int)max(max(misc[0], misc[1]), max(misc[2], misc[3])));
+        const int e = half_exponent(most, kHalfTop);
+        if (most >= 0x7f800000u || e >= xe || xe - e > kHalfLower) {
+            if (redo != 0) recompute();
+            return false;
+        }
+        xe = e;
+#pragma unroll
+        for (int jj = 0; jj < NLD; ++jj) asm volatile("" : "+v"(poff[jj]));           // (else addresses are kept from here on)
+    }
     fetch(st0);
     Op f[NP][2];
 #pragma unroll
     for (int q = 0; q < NP; ++q) filters(st0 * TAPS + Cfg::ftap(0), q, f[q]);
-    int xe = 0;                                                  // exponent of the input's scale
     if constexpr (HALF) {
-        // the first stage and, spread over the others, a piece of each lane
-        const int st = st0 + (int)((threadIdx.x / 4u) % (unsigned)(st1 - st0));
-        const float *src = poff[0] < 0 || absent(st) ? kSplitZeros : in0 + 2 * st * plane + (size_t)(unsigned)poff[0] * kBlk;
-        unsigned m = half_magnitude(*reinterpret_cast<const float4 *>(src));
+        if constexpr (FIRST) {
+            // the first stage and, spread over the others, a piece of each lane
+            const int st = st0 + (int)((tid / 4u) % (unsigned)(st1 - st0));
+            const float *src = poff[0] < 0 || absent(st) ? kSplitZeros : in0 + 2 * st * plane + (size_t)(unsigned)poff[0] * kBlk;
+            unsigned m = half_magnitude(*reinterpret_cast<const float4 *>(src));
 #pragma unroll
-        for (int jj = 0; jj < NLD; ++jj) m = max(m, half_magnitude(hreg[jj]));
-        m = wave_max(m);
-        if (lane == 0) misc[wave] = m;
-        __syncthreads();
-        xe = __builtin_amdgcn_readfirstlane(half_exponent(max(max(misc[0], misc[1]), max(misc[2], misc[3])), kHalfTopInput));
+            for (int jj = 0; jj < NLD; ++jj) m = max(m, half_magnitude(hreg[jj]));
+            m = wave_max(m);
+            if (lane == 0) misc[wave] = m;
+            __syncthreads();
+            xe = __builtin_amdgcn_readfirstlane(half_exponent(max(max(misc[0], misc[1]), max(misc[2], misc[3])), kHalfTopInput));
+        }
         xscale = half_scale(xe);
         xscale_low = half_scale(xe + 11);
         low_key = half_low_key(xe);
@@ -299,78 +352,94 @@ __device__ __forceinline__ void fwd_dense_wide_body(const Geom &g, const float *
 
     // D layout of a 16x16 block: column (pixel) = lane % 16, row (channel) = 4*(lane/16) + r: four consecutive channels, one
     // 16-byte store
-    if (!active) return;
-    auto where = [&](int q, int &n, int &oh, int &ow) __attribute__((always_inline)) {
-        const int row = q / w;
-        n = row / fq.rows;
-        oh = row % fq.rows;
-        ow = c0 + q % w;
-        return q < qend;
-    };
-    const float scale = (st1 % 2 ? -1.f : 1.f) * (HALF ? 1.f : kSplitUnscale);
-    int exponent = 0;
-    float safe = 0.f;                                   // HALF: smaller outputs do not count
-    if constexpr (HALF) {
-        const int *notes = reinterpret_cast<const int *>(wd) + half_notes(g.Ko, NS * (kStageC * TAPS));
-        exponent = -(xe + notes[kb32]);
-        float least = kHalfSafe;
+    if (active) {
+        bool finite[2] = {true, true};
+        const float scale = (st1 % 2 ? -1.f : 1.f) * (HALF ? 1.f : kSplitUnscale);
+        int exponent = 0;
+        float safe = 0.f;                                   // HALF: smaller outputs do not count
+        if constexpr (HALF) {
+            const int *notes = reinterpret_cast<const int *>(wd) + half_notes(g.Ko, NS * (kStageC * TAPS));
+            exponent = -(xe + notes[kb32]);
+            float least = kHalfSafe;
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+            for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-            for (int pb = 0; pb < 4; ++pb)
+                for (int pb = 0; pb < 4; ++pb)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    acc[kb][pb][r] = __builtin_fmaf(low[kb][pb][r], 1.f / kHalfLow, acc[kb][pb][r]);
-                    least = fminf(least, fabsf(acc[kb][pb][r]));
-                }
-        if (__ballot(least < kHalfSafe) != 0) {
-            unsigned c = lane < 4 ? misc[4 + lane] : 0;
-            for (int i = st0 * TAPS + lane; i < st1 * TAPS; i += kWave) c += (unsigned)notes[half_blocks(g.Ko) + kb32 * (NS * TAPS) + i];
-            unsigned sum = 0;
-            if (__ballot(c != 0) != 0)
-                for (int l = 0; l < kWave; ++l) sum += (unsigned)__builtin_amdgcn_readlane((int)c, l);
-            safe = kHalfSafe * fminf(4.f * (float)sum / (float)((st1 - st0) * (kStageC * TAPS)), 1.f);
-        }
-    }
-    bool finite[2] = {true, true};
-#pragma unroll
-    for (int pb = 0; pb < 4; ++pb) {
-        int n, oh, ow;
-        if (!where(qs + pb * 16 + l16, n, oh, ow)) continue;
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            if (kb32 * 2 + kb >= KoB) continue;
-            const floatx4 a = acc[kb][pb];
-            float4 r = make_float4(a[0] * scale, a[1] * scale, a[2] * scale, a[3] * scale);
-            if constexpr (HALF) {
-                auto finish = [&](float v) __attribute__((always_inline)) { return fabsf(v) < safe ? __builtin_nanf("") : ldexpf(v, exponent); };
-                r = make_float4(finish(r.x), finish(r.y), finish(r.z), finish(r.w));
+                    for (int r = 0; r < 4; ++r) {
+                        acc[kb][pb][r] = __builtin_fmaf(low[kb][pb][r], 1.f / kHalfLow, acc[kb][pb][r]);
+                        least = fminf(least, fabsf(acc[kb][pb][r]));
+                    }
+            if (__ballot(least < kHalfSafe) != 0) {
+                unsigned c = lane < 4 ? misc[4 + lane] : 0;
+                for (int i = st0 * TAPS + lane; i < st1 * TAPS; i += kWave) c += (unsigned)notes[half_blocks(g.Ko) + kb32 * (NS * TAPS) + i];
+                unsigned sum = 0;
+                if (__ballot(c != 0) != 0)
+                    for (int l = 0; l < kWave; ++l) sum += (unsigned)__builtin_amdgcn_readlane((int)c, l);
+                safe = kHalfSafe * fminf(4.f * (float)sum / (float)((st1 - st0) * (kStageC * TAPS)), 1.f);
             }
-            finite[pb / 2] = finite[pb / 2] && split_finite(r);
-            *reinterpret_cast<float4 *>(out + act_off(n, kb32 * 2 + kb, oh, ow, KoB, g.Ho, g.Wo) + 4 * grp) = r;
         }
-    }
-    // outputs that values outside the range of the scaled pieces took part in
-    if (__builtin_expect(__ballot(!finite[0] || !finite[1]) != 0, 0)) {
-        split_lanes_fence();
-#pragma unroll 1
-        for (int pb = 0; pb < 2; ++pb) {
-            if (__ballot(!finite[pb]) == 0) continue;
+#pragma unroll
+        for (int pb = 0; pb < 4; ++pb) {
             int n, oh, ow;
-            const bool valid = where(qs + pb * 32 + lane % 32, n, oh, ow);
-            split_redo_corr(g, in, out, valid, n, oh, ow, kb32, 2 * st0, min(2 * st1, CiB));
+            if (!where(qs + pb * 16 + l16, n, oh, ow)) continue;
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+                if (kb32 * 2 + kb >= KoB) continue;
+                const floatx4 a = acc[kb][pb];
+                float4 r = make_float4(a[0] * scale, a[1] * scale, a[2] * scale, a[3] * scale);
+                if constexpr (HALF) {
+                    auto finish = [&](float v) __attribute__((always_inline)) { return fabsf(v) < safe ? __builtin_nanf("") : ldexpf(v, exponent); };
+                    r = make_float4(finish(r.x), finish(r.y), finish(r.z), finish(r.w));
+                }
+                finite[pb / 2] = finite[pb / 2] && split_finite(r);
+                *reinterpret_cast<float4 *>(out + act_off(n, kb32 * 2 + kb, oh, ow, KoB, g.Ho, g.Wo) + 4 * grp) = r;
+            }
         }
+        redo = (__ballot(!finite[0]) != 0 ? 1u : 0u) | (__ballot(!finite[1]) != 0 ? 2u : 0u);
     }
+    if constexpr (Lds::TWICE && FIRST) {
+        if (lane == 0) misc[8 + wave] = redo;
+        __syncthreads();
+        return __builtin_amdgcn_readfirstlane((int)(misc[8] | misc[9] | misc[10] | misc[11])) != 0;
+    }
+    if (__builtin_expect(redo != 0, 0)) recompute();
+    return false;
 }
 
+// The arguments of the kernel as they lie in memory
+struct WideArgs {
+    Geom g;
+    const float *in, *wd;
+    float *out, *parts;
+    FlatGrid fq;
+    int kgroups, csplit;
+    size_t part_stride;
+};
+
 template <int KQ, int HPC, bool HALF, int MODE>
-__global__ __launch_bounds__(256, 2) void fwd_dense_wide_kernel(
-    Geom g, const float *__restrict__ in, const float *__restrict__ wd, float *__restrict__ out, float *__restrict__ parts,
-    FlatGrid fq, int kgroups, int csplit, size_t part_stride)
+__global__ __launch_bounds__(256, 2) void fwd_dense_wide_kernel(WideArgs a)
 {
-    if (form_deselected(g.sel, g.want, g.thr)) return;
+    if (form_deselected(a.g.sel, a.g.want, a.g.thr)) return;
     __shared__ __attribute__((aligned(16))) float lds[WideLds<KQ, HPC, HALF>::FLOATS];
-    fwd_dense_wide_body<KQ, HPC, HALF, MODE>(g, in, wd, out, parts, fq, kgroups, csplit, part_stride, (int)blockIdx.x, (int)blockIdx.y, lds);
+    int xe = 0;
+    unsigned redo = 0;
+    const bool again = fwd_dense_wide_body<KQ, HPC, HALF, MODE, true>(a.g, a.in, a.wd, a.out, a.parts, a.fq, a.kgroups, a.csplit, a.part_stride,
+                                                                      (int)blockIdx.x, (int)blockIdx.y, xe, redo, lds);
+    if constexpr (WideLds<KQ, HPC, HALF>::TWICE) {
+        if (__builtin_expect(!again, 1)) return;
+        // (loads the arguments itself: kept for this they take 50 scalar registers more than there are, and vector registers with them)
+        typedef const float __attribute__((address_space(1))) *In;
+        typedef float __attribute__((address_space(1))) *Out;
+        const WideArgs __attribute__((address_space(4))) *p = (const WideArgs __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr();
+        int wg = (int)blockIdx.x, share = (int)blockIdx.y;
+        asm volatile("" : "+s"(p), "+s"(wg), "+s"(share));
+        Geom g = *(const Geom *)&p->g;
+        g.w = (const float *)(In)g.w;
+        const FlatGrid fq = *(const FlatGrid *)&p->fq;
+        fwd_dense_wide_body<KQ, HPC, HALF, MODE, false>(g, (const float *)(In)p->in, (const float *)(In)p->wd, (float *)(Out)p->out, (float *)(Out)p->parts, fq,
+                                                        p->kgroups, p->csplit, p->part_stride, wg, share, xe, redo, lds);
+    }
 }
 
 }  // namespace

@@ -140,7 +140,8 @@ constexpr float kHalfLow = 2048.f;                          // scale of l beside
 constexpr float kHalfSafe = 64.f;                           // times c / n: outputs from here on need no second look
 
 // exponent of the scale that brings the largest magnitude `bits` (of a finite fp32 value; 0: nothing but zeros seen) below 2^top
-constexpr int kHalfTopInput = 10, kHalfTopFilters = 12;
+constexpr int kHalfTopInput = 10, kHalfTopFilters = 12, kHalfTop = 15;       // (of samples; of all values)
+constexpr int kHalfLower = 10;                              // by how much more an input's scale may be lowered for its outliers (fwd_dense_wide_body)
 __device__ __forceinline__ int half_exponent(unsigned bits, int top)
 {
     const int e = (int)(bits >> 23);
@@ -155,6 +156,10 @@ __device__ __forceinline__ unsigned half_magnitude(float v)
 __device__ __forceinline__ unsigned half_magnitude(float4 v)
 {
     return max(max(half_magnitude(v.x), half_magnitude(v.y)), max(half_magnitude(v.z), half_magnitude(v.w)));
+}
+__device__ __forceinline__ unsigned half_magnitude_or_infinite(float4 v)
+{
+    return max(max(__float_as_uint(v.x) & 0x7fffffffu, __float_as_uint(v.y) & 0x7fffffffu), max(__float_as_uint(v.z) & 0x7fffffffu, __float_as_uint(v.w) & 0x7fffffffu));
 }
 // the largest m of the wavefront's lanes
 __device__ __forceinline__ unsigned wave_max(unsigned m)
