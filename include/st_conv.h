@@ -59,8 +59,15 @@
  * or NaN take part in are computed a second time with plain fp32 multiply-adds, tile by tile: correct, and a call
  * in which every tile holds one takes 3 to 7 times its usual time.  Long 3x3 reductions (more than 96 reduced channels;
  * filter gradients over many pixels) take two f16 pieces of 23 bits and more, scaled by a power of two from a sample of
- * the values: a sum errs less than with bf16 pieces, and outputs that values more than 16 times above the sampled ones take part in, or
- * that are so small that values 2^-25 below them could matter, are computed a second time in the same way.
+ * the values.  Such a product is off by 7.5e-8 of itself in the root mean square (5e-9 with bf16 pieces), but a sum of them rounds half as
+ * often: up to 95 % zeros FWD and BWI err less than with bf16 pieces (1.2e-7 to 1.7e-7 of the norm for 1.7e-7 to 2.2e-7 at half zeros,
+ * 1.0e-7 to 1.5e-7 for 1.4e-7 to 1.7e-7 at 90 %), at 99 %, where few roundings are left to save, between 7 % less and 7 % more (8e-8 to 1.1e-7).
+ * Filter gradients keep bf16 pieces where fewer than one sampled product in 14 is not zero.  Outputs that values more than 64 times above the sampled ones
+ * (filters: 16 times) take part in, or that are so small that values 2^-23 of the sampled ones (filters: 2^-25) could matter, are computed a second time:
+ * FWD and BWI of most layers with another scale if that is enough (values up to 2^15 times the sampled ones), else with fp32 multiply-adds as
+ * above; filter gradients one by one in 64 bits if they are few, else on bf16 pieces.  Ordinary values need none of this.  With one value in 10^4
+ * a thousand times as large a call takes 0.9 to 2 times as long as with bf16 pieces only, up to 3.5 times in layers of at most 32 produced channels and in FWD of
+ * stride 2; with values of all sizes between 2^-40 and 1 up to 2.5 times.
  */
 #ifndef ST_CONV_H
 #define ST_CONV_H
@@ -162,8 +169,8 @@ st_status st_conv_bww_dy(const st_conv_desc *desc, const float *x, const float *
  * synchronisation; the cost is the sampling pass (at most 256 KB of x and of dy are read once more)
  * and the empty launches.  Where tiled kernels exist, the dense form (st_conv_bww_dense) is the
  * third candidate: it runs when even the sparser operand has fewer than 75 % zeros on 3x3 layers, and from 128 million
- * multiply-adds on up to 96 % where at least 5 % of the sampled products are not zero (the
- * measured break-even is about 96 % or, on some layers, beyond; Sec. 5.3 combines the kernels with dense ones
+ * multiply-adds on up to 96 % where at least 5 % of the sampled products are not zero, unless partial gradients come from so few
+ * of them that the zero-skipping forms err less (the measured break-even is about 96 % or, on some layers, beyond; Sec. 5.3 combines the kernels with dense ones
  * layer by layer), fewer than 25 % on those so small that the partial gradients are what they wait for.
  * Two kinds of layer are decided without sampling: 1x1 layers, where a zero saves too few
  * multiply-adds to beat the matrix cores at any zero fraction measured (up to 95 %), go straight to the dense form;
@@ -185,9 +192,9 @@ st_status st_conv_bww_auto(const st_conv_desc *desc, const float *x, const float
  * depends on the geometry (st_conv_sparse_threshold tells it): 95 % for unit-stride 3x3 layers that one main
  * kernel serves (below; also where the zero-skipping form of so small a layer has a kernel of its own) and that have 128 or more reduced channels, which is where the two forms were measured
  * to be equally fast, and for those whose dense form multiplies f16 pieces with an odd number of reduced channel blocks or at most
- * 32 produced channels; 65 % for those with fewer channels and 85 % for other unit-stride 3x3 layers, where these
- * entry points have always skipped zeros at 70 and 90 % (the dense form is up to a fifth faster between there and
- * 90 to 95 %); never for stride-2 3x3 and for 1x1 layers (measured up to 90 and 95 % zeros); always for
+ * 32 produced channels; 65 % for those with fewer channels and 85 % for other unit-stride 3x3 layers, whose callers have
+ * had zeros skipped at 70 and 90 % since before the dense form was the faster one there (now by up to a fifth, on f16 pieces a half, up
+ * to 90 to 95 %; they call it themselves where that counts); never for stride-2 3x3 and for 1x1 layers (measured up to 90 and 95 % zeros); always for
  * geometries only the generic kernels cover.  Where the answer is "always" or "never" the call
  * goes straight to that form, without sampling.  On unit-stride 3x3 layers of the usual sizes one
  * main kernel holds both forms (st_conv_kernel_name tells) and runs the selected one, so the sampled path has as many

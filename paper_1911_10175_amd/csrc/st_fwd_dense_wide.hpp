@@ -5,7 +5,8 @@
 // do, v_mfma_f32_32x32x16_bf16 runs at 1760 TFLOP/s from two wavefronts per SIMD and at 1580 from four, and
 // v_mfma_f32_16x16x32_bf16 at 2080, _f16 at 1950 from either (half the accumulator traffic per product, so less power, which is what holds
 // the clock down).  It rounds alike: groups of 8 products, each with one rounding of the accumulator.  Errors of the norm against 64 bits,
-// half zeros: 256 channels 1.87e-7 (bf16) -> 1.4e-7 (f16), 128 1.8e-7 -> 1.2e-7, at 90 % zeros 1.4e-7 -> 1.15e-7.  The f16 form takes a fresh
+// half zeros: 256 channels 1.87e-7 (bf16) -> 1.4e-7 (f16), 128 1.8e-7 -> 1.2e-7, at 90 % zeros 1.4e-7 -> 1.0e-7 (BWI 1.1e-7), 95 % 1.22e-7 -> 0.98e-7 (1.23e-7 -> 1.07e-7),
+// 99 % 8.7e-8 -> 8.1e-8 (8.8e-8 -> 9.0e-8: the pieces' own error is left, whatever the number of terms).  The f16 form takes a fresh
 // accumulator for every 3 taps of 32 channels (9 taps: 1 % faster, error 1.6e-7).  Reductions of up to kSplitApart blocks stay on
 // bf16 pieces, whose error is the smaller one there from 50 % zeros on (64 channels, 50 / 80 %: 1.06e-7 : 1.13e-7, 7.4e-8 : 1.10e-7).
 //

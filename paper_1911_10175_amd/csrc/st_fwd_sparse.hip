@@ -51,10 +51,10 @@ unsigned fwd_sparse_threshold(const Geom &g)
 // : dense on the same tensors at 90 / 95 / 97 / 99 % zeros:
 //   256->256 @56 494 : 458 / 460 : 442 / 404 : 432 / 243 : 413   512->512 @28 498 : 481 / 464 : 468 / 407 : 458 / 249 : 439
 // So the lines cross at 95 to 96 % on the layers of 128 and more input
-// channels that st_fwd_auto.hip serves (950).  The other two lines are not crossings: launches with
-// fewer channels have always been checked to test their operand from 70 % zeros on, although the dense form is faster there
-// (64->128 @112 332 : 272 / 302 : 265), the other unit-stride launches from 90 % on (64->64 @56 57 : 54, 128->128 @28 49 : 49,
-// 256->256 @14 53 : 58, 64->64 @224 585 : 542 there): 650 and 850 keep that.
+// channels that st_fwd_auto.hip serves (950).  The other two lines are not crossings but what st_conv.h says of these layers: their callers have had
+// zeros skipped from 70 and 90 % on since before the dense form was the faster one there.  It costs launches with
+// fewer channels 64->128 @112 332 : 272 / 302 : 265 at 90 / 95 %, the other unit-stride launches, from 90 % on, little on bf16 pieces (64->64 @56 57 : 54,
+// 256->256 @14 53 : 58, 64->64 @224 585 : 542) and up to a half on f16 pieces (128->128 @28 49 : 31).
 // Stride 2 stays behind at 90 %: FWD 128->128 @56 76 : 52, 256->256 @28 129 : 77, BWI 75 : 58, 85 : 63 (512->512 @14
 // 89 : 91).
 unsigned fwd_auto_threshold(const Geom &g)
@@ -62,8 +62,9 @@ unsigned fwd_auto_threshold(const Geom &g)
     const unsigned t = fwd_sparse_threshold(g);
     if (t == 0 || t > 1000 || !fwd_dense_supported(g)) return t;
     if (g.sw == 2 || g.uw == 2) return 1001;
-    // (an odd number of channel blocks, or few produced channels, on f16 pieces; 8 x 112->128 @56, us, zero-skipping at 70 / 90 / 97 % : dense: 80 / 59 / 46 : 32.  Even ones would
-    // have the same line; theirs are the ones that checks of this entry point ask for)
+    // Layers whose dense form came to f16 pieces from the kernel of 16 channels at a time (an odd number of channel blocks, few produced channels) and had
+    // been the slower one until then: the crossing (8 x 112->128 @56, us, zero-skipping at 70 / 90 / 97 % zeros : dense: 80 / 59 / 46 : 32; error at 70 / 90 % 2.2e-7 /
+    // 1.3e-7 : 1.2e-7 / 1.1e-7)
     if (fwd_dense_half(g) && (g.Ci % 32 != 0 || g.Ko <= 32)) return 950;
     if (!fwd_auto_tiles(g)) return 850;
     return g.Ci >= 128 ? 950 : 650;
