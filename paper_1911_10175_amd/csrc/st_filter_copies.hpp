@@ -220,12 +220,15 @@ __device__ __forceinline__ void half_filters_block(size_t block, int Ko, int Ci,
     const int e = half_exponent(max(red[wave & 2], red[wave | 1]), kHalfTopFilters);
     const unsigned key = half_low_key(e);
     const unsigned lows = __popcll(__ballot(half_low(lo, key) != 0)) + __popcll(__ballot(half_low(hi, key) != 0));
-    if (threadIdx.x % kWave == 0) red[4 + wave] = lows;
+    const unsigned long long filled = __ballot(lo.x != 0.f || lo.y != 0.f || lo.z != 0.f || lo.w != 0.f || hi.x != 0.f || hi.y != 0.f || hi.z != 0.f || hi.w != 0.f);
+    const unsigned of_k = (unsigned)(filled | filled >> 16 | filled >> 32 | filled >> 48) & 0xffffu;
+    if (threadIdx.x % kWave == 0) red[4 + wave] = lows | of_k << 16;
     __syncthreads();
     int *notes = reinterpret_cast<int *>(wd) + half_notes(Ko, NS * (2 * kBlk * TAPS));
     if (threadIdx.x % 128 == 0) {
         notes[kb32] = e;                                // (the same value from every step)
-        notes[half_blocks(Ko) + step] = (int)(red[4 + wave] + red[5 + wave]);
+        notes[half_blocks(Ko) + step] = (int)((red[4 + wave] & 0xffffu) + (red[5 + wave] & 0xffffu));
+        notes[half_blocks(Ko) * (1 + NS * TAPS) + step] = (int)(red[4 + wave] >> 16 | (red[5 + wave] & 0xffff0000u));
     }
     const float scale = st % 2 ? -half_scale(e) : half_scale(e);
     f16x4 a[2], b[2];

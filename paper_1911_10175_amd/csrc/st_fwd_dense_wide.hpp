@@ -357,7 +357,6 @@ __device__ __forceinline__ bool fwd_dense_wide_body(const Geom &g, const float *
         bool finite[2] = {true, true};
         const float scale = (st1 % 2 ? -1.f : 1.f) * (HALF ? 1.f : kSplitUnscale);
         int exponent = 0;
-        float safe = 0.f;                                   // HALF: smaller outputs do not count
         if constexpr (HALF) {
             const int *notes = reinterpret_cast<const int *>(wd) + half_notes(g.Ko, NS * (kStageC * TAPS));
             exponent = -(xe + notes[kb32]);
@@ -371,13 +370,29 @@ __device__ __forceinline__ bool fwd_dense_wide_body(const Geom &g, const float *
                         acc[kb][pb][r] = __builtin_fmaf(low[kb][pb][r], 1.f / kHalfLow, acc[kb][pb][r]);
                         least = fminf(least, fabsf(acc[kb][pb][r]));
                     }
+            // smaller ones than this may lack what values below the pieces' range would have given, but for channels without filters, whose outputs are zeros
             if (__ballot(least < kHalfSafe) != 0) {
-                unsigned c = lane < 4 ? misc[4 + lane] : 0;
-                for (int i = st0 * TAPS + lane; i < st1 * TAPS; i += kWave) c += (unsigned)notes[half_blocks(g.Ko) + kb32 * (NS * TAPS) + i];
-                unsigned sum = 0;
-                if (__ballot(c != 0) != 0)
-                    for (int l = 0; l < kWave; ++l) sum += (unsigned)__builtin_amdgcn_readlane((int)c, l);
-                safe = kHalfSafe * fminf(4.f * (float)sum / (float)((st1 - st0) * (kStageC * TAPS)), 1.f);
+                unsigned c = lane < 4 ? misc[4 + lane] : 0, filled = 0;
+                const int *counts = notes + half_blocks(g.Ko) + kb32 * (NS * TAPS), *channels = counts + half_blocks(g.Ko) * (NS * TAPS);
+                for (int i = st0 * TAPS + lane; i < st1 * TAPS; i += kWave) {
+                    c += (unsigned)counts[i];
+                    filled |= (unsigned)channels[i];
+                }
+                if (__ballot(c != 0) != 0) {
+                    unsigned sum = 0, any = 0;
+                    for (int l = 0; l < kWave; ++l) {
+                        sum += (unsigned)__builtin_amdgcn_readlane((int)c, l);
+                        any |= (unsigned)__builtin_amdgcn_readlane((int)filled, l);
+                    }
+                    const float safe = kHalfSafe * fminf(4.f * (float)sum / (float)((st1 - st0) * (kStageC * TAPS)), 1.f);
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                        for (int pb = 0; pb < 4; ++pb)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r)
+                                if (fabsf(acc[kb][pb][r]) < safe && (any >> (kb * 16 + 4 * grp + r) & 1) != 0) acc[kb][pb][r] = __builtin_nanf("");
+                }
             }
         }
 #pragma unroll
@@ -389,10 +404,7 @@ __device__ __forceinline__ bool fwd_dense_wide_body(const Geom &g, const float *
                 if (kb32 * 2 + kb >= KoB) continue;
                 const floatx4 a = acc[kb][pb];
                 float4 r = make_float4(a[0] * scale, a[1] * scale, a[2] * scale, a[3] * scale);
-                if constexpr (HALF) {
-                    auto finish = [&](float v) __attribute__((always_inline)) { return fabsf(v) < safe ? __builtin_nanf("") : ldexpf(v, exponent); };
-                    r = make_float4(finish(r.x), finish(r.y), finish(r.z), finish(r.w));
-                }
+                if constexpr (HALF) r = make_float4(ldexpf(r.x, exponent), ldexpf(r.y, exponent), ldexpf(r.z, exponent), ldexpf(r.w, exponent));
                 finite[pb / 2] = finite[pb / 2] && split_finite(r);
                 *reinterpret_cast<float4 *>(out + act_off(n, kb32 * 2 + kb, oh, ow, KoB, g.Ho, g.Wo) + 4 * grp) = r;
             }

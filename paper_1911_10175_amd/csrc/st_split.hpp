@@ -132,7 +132,7 @@ typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 // The copy of the filters: [Ko/32][Ci/32][tap][2 pieces][2 halves of the 32 k][4 groups of 8 c][16 k][8 c] f16 (Ko padded to whole
 // groups of 128), then an int per 32 produced channels, the exponent of their scale, then one per 32 produced channels and step
-// (stage and tap), how many fours of its values hold one below the pieces' range
+// (stage and tap), how many fours of its values hold one below the pieces' range, then another, which of the 32 channels have any filter there that is not zero
 __host__ __device__ __forceinline__ int half_blocks(int Ko) { return (Ko + 127) / 128 * 4; }
 __host__ __device__ __forceinline__ size_t half_notes(int Ko, int terms) { return (size_t)half_blocks(Ko) * 32 * terms; }      // in 4 bytes
 

@@ -155,6 +155,59 @@ def test_time_of_a_few_values_above_the_sampled_ones(p):
     assert took <= 3 * usual, (took, usual)
 
 
+@pytest.mark.parametrize("name", ["128->128 @56", "128->64 @57x61", "144->16 3x5", "16->112 @28, BWI", "400->96 17x31, shares", "stride 2 160->160 45x27"])
+def test_channels_without_filters(name):
+    """Produced channels that padding has left without filters, and values below the pieces' range that make small outputs suspect: zeros, but where an
+    infinity meets a filter of zero; a channel with one filter, however small, is as exact as the others."""
+    g = GEOMS[name]
+    x, w, dy = inputs(g, 115)
+    dead = np.arange(g.K) % 16 >= 4
+    if half_passes(g)[0] == "fwd":
+        w[dead] = 0
+        w[5, 0, 0, 0] = np.float32(2.0 ** -70)
+    else:
+        w[:, np.arange(g.C) % 16 >= 4] = 0
+        w[0, 5, 0, 0] = np.float32(2.0 ** -70)
+    for t in (x, dy):
+        t.reshape(-1)[::997] = np.float32(2.0 ** -60)
+    within_fp32_sum(g, x, w, dy, name)
+    x[0, 0, 1, 1] = dy[0, 0, 1, 1] = np.inf
+    L = DeviceLayer(g, x, w, dy)
+    for p in half_passes(g):
+        with np.errstate(invalid="ignore"):
+            ref = corr(g, x, w, dy, p)[0]
+        got = getattr(L, p)(True)
+        assert np.array_equal(np.isnan(got[0]), np.isnan(ref[0])), f"{name} {p}"
+
+
+@pytest.mark.parametrize("N,C,K,H", [(32, 256, 32, 56), (16, 128, 64, 112), (32, 128, 128, 28)])
+def test_time_of_channels_without_filters(N, C, K, H):
+    """A value below the pieces' range in the same tile had all of these computed again with fp32 multiply-adds: two to five times the time."""
+    gen = torch.Generator(device="cuda").manual_seed(105)
+    d = st.ConvDesc(N, C, K, H, H, 3, 3, 1, 1, 1, 1)
+    assert f16_pieces(d)
+    w = torch.randn((K // 16, C // 16, 3, 3, 16, 16), device="cuda", generator=gen)
+    x, y = torch.randn((N, C // 16, H, H, 16), device="cuda", generator=gen), torch.empty((N, K // 16, H, H, 16), device="cuda")
+    ws = workspace(d, st.ST_PASS_FWD, True)
+
+    def time():
+        took = []
+        for _ in range(20):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            st.st_conv_fwd_dense(d, x, w, y, ws)
+            end.record()
+            torch.cuda.synchronize()
+            took.append(start.elapsed_time(end))
+        return sorted(took)[5]
+
+    usual = time()
+    w[-1, ..., 4:] = 0
+    x.view(-1)[::10007] = 2.0 ** -60
+    took = time()
+    assert took <= 1.5 * usual, (took, usual)
+
+
 def test_infinities_and_nan():
     for name in ("128->64 @57x61", "256->144 @14"):
         g = GEOMS[name]
