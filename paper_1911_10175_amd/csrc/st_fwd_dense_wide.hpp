@@ -57,14 +57,15 @@ struct WideLds {
 // aligned.  Every thread of the workgroup makes the call (the body contains barriers).
 // HALF: products from two f16 pieces, else, for short reductions (kSplitApart), from three bf16 pieces.  With f16 pieces the outputs that these cannot give
 // (values above their range took part, or small ones that may matter) are left to a second pass (TWICE): the first one (FIRST) returns whether any wavefront
-// has such, which ones in `redo`, the scale in `xe`.  The second one looks for the largest value and multiplies all over with a scale that holds it;
+// has such, which ones in `redo`, pixels of 16 whose outputs were zeros in `zero` (of the lane), the scale in `xe`.  The second one sets outputs of pixels that meet no value to
+// zero, looks for the largest value and multiplies all over with a scale that holds it;
 // where that can't help, and after it, they are computed with fp32 multiply-adds, 32 x 32 at a time, which takes five times as long as a whole workgroup.  us, bf16 pieces : fp32
 // only : both, one in 10^4 or 10^6 values 1000 times as large: BWI 32 x 128->128 @28 42 : 312 : 75, 42 : 176 : 46, 16 x 256->256 @56 253 : 993 : 283, 254 : 225 : 163,
 // FWD 296 : 502 : 262, 258 : 195 : 195; all between 2^-40 and 1 as before, BWI 42 : 105, 254 : 300.
 template <int KQ, int HPC, bool HALF, int MODE, bool FIRST>
 __device__ __forceinline__ bool fwd_dense_wide_body(const Geom &g, const float *__restrict__ in, const float *__restrict__ wd,
                                                float *__restrict__ out, float *__restrict__ parts, const FlatGrid &fq, int kgroups,
-                                               int csplit, size_t part_stride, int wg, int cshare, int &xe, unsigned &redo, float *lds_base)
+                                               int csplit, size_t part_stride, int wg, int cshare, int &xe, unsigned &redo, unsigned &zero, float *lds_base)
 {
     using Cfg = FlatCfg<MODE>;
     using Lds = WideLds<KQ, HPC, HALF>;
@@ -210,23 +211,59 @@ __device__ __forceinline__ bool fwd_dense_wide_body(const Geom &g, const float *
             split_redo_corr(g, in, out, valid, n, oh, ow, kb32, 2 * st0, min(2 * st1, CiB));
         }
     };
+    // outputs of pixels that meet no value are zeros (those of all the lane's channels were)
+    unsigned empty = 0;                                          // !FIRST: such pixels, pb a bit
+    auto settle = [&]() __attribute__((always_inline)) {
+        const unsigned zeros = zero & empty;
+        if (active && __ballot(zeros != 0) != 0) {
+            bool finite[2] = {true, true};
+            for (int pb = 0; pb < 4; ++pb) {
+                int n, oh, ow;
+                if (!where(qs + pb * 16 + l16, n, oh, ow)) continue;
+                for (int kb = 0; kb < 2; ++kb) {
+                    if (kb32 * 2 + kb >= KoB) continue;
+                    float4 *o = reinterpret_cast<float4 *>(out + act_off(n, kb32 * 2 + kb, oh, ow, KoB, g.Ho, g.Wo) + 4 * grp);
+                    if ((zeros >> pb & 1) != 0) *o = make_float4(0.f, 0.f, 0.f, 0.f);
+                    else finite[pb / 2] = finite[pb / 2] && split_finite(*o);
+                }
+            }
+            redo = (__ballot(!finite[0]) != 0 ? 1u : 0u) | (__ballot(!finite[1]) != 0 ? 2u : 0u);
+        }
+        if (redo != 0) recompute();
+    };
     if constexpr (!FIRST) {
         // the largest value of all: whether those above the sampled ones are the reason for the second pass, and not so far above that the others
-        // would be small beside them
-        unsigned m = 0;
+        // would be small beside them; and which samples hold any value
+        unsigned *const filled = reinterpret_cast<unsigned *>(lds_base);
+        if (tid < HPC) filled[tid] = 0;
+        static_assert(HPC <= 256, "a sample a thread");
+        unsigned m = 0, most_of[NLD] = {};
 #pragma unroll 1
         for (int st = st0; st < st1; ++st) {
             fetch(st);
 #pragma unroll
-            for (int jj = 0; jj < NLD; ++jj) m = max(m, half_magnitude_or_infinite(hreg[jj]));
+            for (int jj = 0; jj < NLD; ++jj) most_of[jj] = max(most_of[jj], half_magnitude_or_infinite(hreg[jj]));
+        }
+        __syncthreads();
+#pragma unroll
+        for (int jj = 0; jj < NLD; ++jj) {
+            m = max(m, most_of[jj]);
+            if (most_of[jj] != 0 && jj * 32 + sample0 < HPC) filled[jj * 32 + sample0] = 1;        // (the same value from every thread)
         }
         m = wave_max(m);
         if (lane == 0) misc[wave] = m;
         __syncthreads();
+#pragma unroll
+        for (int pb = 0; pb < 4; ++pb) {
+            unsigned any = 0;
+            static_for<0, NT>([&](auto T) __attribute__((always_inline)) { any |= filled[apix[pb] - grp * HPC + Cfg::dv(decltype(T)::value) * pitch + Cfg::du(decltype(T)::value)]; });
+            if (any == 0) empty |= 1u << pb;
+        }
+        __syncthreads();                                         // (the samples of the second pass go there)
         const unsigned most = (unsigned)__builtin_amdgcn_readfirstlane((int)max(max(misc[0], misc[1]), max(misc[2], misc[3])));
         const int e = half_exponent(most, kHalfTop);
         if (most >= 0x7f800000u || e >= xe || xe - e > kHalfLower) {
-            if (redo != 0) recompute();
+            settle();
             return false;
         }
         xe = e;
@@ -384,6 +421,16 @@ __device__ __forceinline__ bool fwd_dense_wide_body(const Geom &g, const float *
                         sum += (unsigned)__builtin_amdgcn_readlane((int)c, l);
                         any |= (unsigned)__builtin_amdgcn_readlane((int)filled, l);
                     }
+                    if constexpr (Lds::TWICE) {
+                        zero = 0;
+#pragma unroll
+                        for (int pb = 0; pb < 4; ++pb) {
+                            bool all = true;
+#pragma unroll
+                            for (int i = 0; i < 8; ++i) all = all && acc[i / 4][pb][i % 4] == 0.f;
+                            if (all) zero |= 1u << pb;
+                        }
+                    }
                     const float safe = kHalfSafe * fminf(4.f * (float)sum / (float)((st1 - st0) * (kStageC * TAPS)), 1.f);
 #pragma unroll
                     for (int kb = 0; kb < 2; ++kb)
@@ -416,7 +463,8 @@ __device__ __forceinline__ bool fwd_dense_wide_body(const Geom &g, const float *
         __syncthreads();
         return __builtin_amdgcn_readfirstlane((int)(misc[8] | misc[9] | misc[10] | misc[11])) != 0;
     }
-    if (__builtin_expect(redo != 0, 0)) recompute();
+    if constexpr (!FIRST) settle();
+    else if (__builtin_expect(redo != 0, 0)) recompute();
     return false;
 }
 
@@ -436,9 +484,9 @@ __global__ __launch_bounds__(256, 2) void fwd_dense_wide_kernel(WideArgs a)
     if (form_deselected(a.g.sel, a.g.want, a.g.thr)) return;
     __shared__ __attribute__((aligned(16))) float lds[WideLds<KQ, HPC, HALF>::FLOATS];
     int xe = 0;
-    unsigned redo = 0;
+    unsigned redo = 0, zero = 0;
     const bool again = fwd_dense_wide_body<KQ, HPC, HALF, MODE, true>(a.g, a.in, a.wd, a.out, a.parts, a.fq, a.kgroups, a.csplit, a.part_stride,
-                                                                      (int)blockIdx.x, (int)blockIdx.y, xe, redo, lds);
+                                                                      (int)blockIdx.x, (int)blockIdx.y, xe, redo, zero, lds);
     if constexpr (WideLds<KQ, HPC, HALF>::TWICE) {
         if (__builtin_expect(!again, 1)) return;
         // (loads the arguments itself: kept for this they take 50 scalar registers more than there are, and vector registers with them)
@@ -451,7 +499,7 @@ __global__ __launch_bounds__(256, 2) void fwd_dense_wide_kernel(WideArgs a)
         g.w = (const float *)(In)g.w;
         const FlatGrid fq = *(const FlatGrid *)&p->fq;
         fwd_dense_wide_body<KQ, HPC, HALF, MODE, false>(g, (const float *)(In)p->in, (const float *)(In)p->wd, (float *)(Out)p->out, (float *)(Out)p->parts, fq,
-                                                        p->kgroups, p->csplit, p->part_stride, wg, share, xe, redo, lds);
+                                                        p->kgroups, p->csplit, p->part_stride, wg, share, xe, redo, zero, lds);
     }
 }
 

@@ -155,6 +155,18 @@ def test_time_of_a_few_values_above_the_sampled_ones(p):
     assert took <= 3 * usual, (took, usual)
 
 
+def time_of_fwd(d, x, w, y):
+    ws, took = workspace(d, st.ST_PASS_FWD, True), []
+    for _ in range(20):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        st.st_conv_fwd_dense(d, x, w, y, ws)
+        end.record()
+        torch.cuda.synchronize()
+        took.append(start.elapsed_time(end))
+    return sorted(took)[5]
+
+
 @pytest.mark.parametrize("name", ["128->128 @56", "128->64 @57x61", "144->16 3x5", "16->112 @28, BWI", "400->96 17x31, shares", "stride 2 160->160 45x27"])
 def test_channels_without_filters(name):
     """Produced channels that padding has left without filters, and values below the pieces' range that make small outputs suspect: zeros, but where an
@@ -180,6 +192,43 @@ def test_channels_without_filters(name):
         assert np.array_equal(np.isnan(got[0]), np.isnan(ref[0])), f"{name} {p}"
 
 
+@pytest.mark.parametrize("name", ["128->128 @56", "128->64 @57x61", "192->48 3x5", "256->144 @14", "400->96 17x31, shares", "176->48 @40 pad 2"])
+def test_pixels_that_meet_no_value(name):
+    """Rows of an image without values, and values below the pieces' range, or above it, in others: zeros, but where an infinite filter meets them; a pixel that
+    meets one value, however small, is as exact as the others."""
+    g = GEOMS[name]
+    for above in (1.0, 3.0 * 2 ** 10):
+        x, w, dy = inputs(g, 117)
+        for t in (x, dy):
+            t.reshape(-1)[::997] = np.float32(2.0 ** -60)
+            t.reshape(-1)[11::40009] *= np.float32(above)
+            t[1::2, :, : t.shape[2] - 2] = 0
+            t[0, :, t.shape[2] // 2:] = 0
+            t[0, 1, -1, -1] = np.float32(2.0 ** -70)
+        within_fp32_sum(g, x, w, dy, f"{name} {above}")
+    w[3, 5, 1, 1] = np.inf
+    L = DeviceLayer(g, x, w, dy)
+    for p in half_passes(g):
+        with np.errstate(invalid="ignore"):
+            ref = corr(g, x, w, dy, p)[0]
+        assert np.array_equal(np.isnan(getattr(L, p)(True)), np.isnan(ref)), f"{name} {p}"
+
+
+@pytest.mark.parametrize("N,C,K,H", [(16, 128, 64, 112), (32, 128, 128, 28)])
+def test_time_of_pixels_that_meet_no_value(N, C, K, H):
+    """As below, three to six times the time.  Looking for these takes each workgroup a second look at its input."""
+    gen = torch.Generator(device="cuda").manual_seed(107)
+    d = st.ConvDesc(N, C, K, H, H, 3, 3, 1, 1, 1, 1)
+    assert f16_pieces(d)
+    w = torch.randn((K // 16, C // 16, 3, 3, 16, 16), device="cuda", generator=gen)
+    x, y = torch.randn((N, C // 16, H, H, 16), device="cuda", generator=gen), torch.empty((N, K // 16, H, H, 16), device="cuda")
+    usual = time_of_fwd(d, x, w, y)
+    x[:, :, : H // 2] = 0
+    x.view(-1)[::10007] *= 2.0 ** -60
+    took = time_of_fwd(d, x, w, y)
+    assert took <= 2 * usual, (took, usual)
+
+
 @pytest.mark.parametrize("N,C,K,H", [(32, 256, 32, 56), (16, 128, 64, 112), (32, 128, 128, 28)])
 def test_time_of_channels_without_filters(N, C, K, H):
     """A value below the pieces' range in the same tile had all of these computed again with fp32 multiply-adds: two to five times the time."""
@@ -188,23 +237,10 @@ def test_time_of_channels_without_filters(N, C, K, H):
     assert f16_pieces(d)
     w = torch.randn((K // 16, C // 16, 3, 3, 16, 16), device="cuda", generator=gen)
     x, y = torch.randn((N, C // 16, H, H, 16), device="cuda", generator=gen), torch.empty((N, K // 16, H, H, 16), device="cuda")
-    ws = workspace(d, st.ST_PASS_FWD, True)
-
-    def time():
-        took = []
-        for _ in range(20):
-            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            start.record()
-            st.st_conv_fwd_dense(d, x, w, y, ws)
-            end.record()
-            torch.cuda.synchronize()
-            took.append(start.elapsed_time(end))
-        return sorted(took)[5]
-
-    usual = time()
+    usual = time_of_fwd(d, x, w, y)
     w[-1, ..., 4:] = 0
     x.view(-1)[::10007] = 2.0 ** -60
-    took = time()
+    took = time_of_fwd(d, x, w, y)
     assert took <= 1.5 * usual, (took, usual)
 
 
