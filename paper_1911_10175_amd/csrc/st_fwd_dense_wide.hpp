@@ -208,6 +208,8 @@ __device__ __forceinline__ bool fwd_dense_wide_body(const Geom &g, const float *
             if ((redo >> pb & 1) == 0) continue;
             int n, oh, ow;
             const bool valid = where(qs + pb * 32 + lane % 32, n, oh, ow);
+            if constexpr (!FIRST)
+                if (split_redo_few(g, in, out, valid, n, oh, ow, kb32, 2 * st0, min(2 * st1, CiB))) continue;
             split_redo_corr(g, in, out, valid, n, oh, ow, kb32, 2 * st0, min(2 * st1, CiB));
         }
     };

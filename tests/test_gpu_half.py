@@ -192,6 +192,20 @@ def test_channels_without_filters(name):
         assert np.array_equal(np.isnan(got[0]), np.isnan(ref[0])), f"{name} {p}"
 
 
+@pytest.mark.parametrize("every", [1, 101, 9973])
+@pytest.mark.parametrize("name", ["128->128 @56", "192->48 3x5", "256->144 @14", "112->144 @28", "400->96 17x31, shares", "176->48 @40 pad 2"])
+def test_a_few_outputs_that_small_values_may_matter_to(name, every):
+    """Values of all sizes down to 2^-40, all or some of them: the outputs near zero are computed one by one, where there are more than eight of 32 x 32 with
+    fp32 multiply-adds."""
+    g = GEOMS[name]
+    x, w, dy = inputs(g, 119)
+    rng = np.random.default_rng(121)
+    for t in (x, dy):
+        some = t.reshape(-1)[::every]
+        some *= np.exp2(-40 * rng.random(some.size)).astype(np.float32)
+    within_fp32_sum(g, x, w, dy, f"{name} {every}")
+
+
 @pytest.mark.parametrize("name", ["128->128 @56", "128->64 @57x61", "192->48 3x5", "256->144 @14", "400->96 17x31, shares", "176->48 @40 pad 2"])
 def test_pixels_that_meet_no_value(name):
     """Rows of an image without values, and values below the pieces' range, or above it, in others: zeros, but where an infinite filter meets them; a pixel that
