@@ -64,10 +64,10 @@
  * 1.0e-7 to 1.5e-7 for 1.4e-7 to 1.7e-7 at 90 %), at 99 %, where few roundings are left to save, between 7 % less and 7 % more (8e-8 to 1.1e-7).
  * Filter gradients keep bf16 pieces where fewer than one sampled product in 14 is not zero.  Outputs that values more than 64 times above the sampled ones
  * (filters: 16 times) take part in, or that are so small that values 2^-23 of the sampled ones (filters: 2^-25) could matter, are computed a second time:
- * FWD and BWI of most layers with another scale if that is enough (values up to 2^15 times the sampled ones), else with fp32 multiply-adds as
- * above; filter gradients one by one in 64 bits if they are few, else on bf16 pieces.  Ordinary values need none of this.  With one value in 10^4
- * a thousand times as large a call takes 0.9 to 2 times as long as with bf16 pieces only, up to 3.5 times in layers of at most 32 produced channels and in FWD of
- * stride 2; with values of all sizes between 2^-40 and 1 up to 2.5 times.
+ * FWD and BWI of most layers with another scale if that is enough (values up to 2^15 times the sampled ones), one by one in 64 bits if they are few, else
+ * with fp32 multiply-adds as above; filter gradients one by one if they are few, else on bf16 pieces.  Ordinary values, and pixels and channels that hold
+ * none, need none of this.  With one value in 10^4 a thousand times as large a call takes 1 to 2 times as long as with bf16 pieces only, up to 3.5 times in layers of
+ * at most 32 produced channels and in FWD of stride 2; with values of all sizes between 2^-40 and 1 up to 1.7 times.
  */
 #ifndef ST_CONV_H
 #define ST_CONV_H

@@ -59,9 +59,10 @@ struct WideLds {
 // (values above their range took part, or small ones that may matter) are left to a second pass (TWICE): the first one (FIRST) returns whether any wavefront
 // has such, which ones in `redo`, pixels of 16 whose outputs were zeros in `zero` (of the lane), the scale in `xe`.  The second one sets outputs of pixels that meet no value to
 // zero, looks for the largest value and multiplies all over with a scale that holds it;
-// where that can't help, and after it, they are computed with fp32 multiply-adds, 32 x 32 at a time, which takes five times as long as a whole workgroup.  us, bf16 pieces : fp32
-// only : both, one in 10^4 or 10^6 values 1000 times as large: BWI 32 x 128->128 @28 42 : 312 : 75, 42 : 176 : 46, 16 x 256->256 @56 253 : 993 : 283, 254 : 225 : 163,
-// FWD 296 : 502 : 262, 258 : 195 : 195; all between 2^-40 and 1 as before, BWI 42 : 105, 254 : 300.
+// where that can't help, and after it, they are computed one by one (split_redo_few) or with fp32 multiply-adds, 32 x 32 at a time, which takes five times as long as a
+// whole workgroup.  us, bf16 pieces : fp32 multiply-adds only : now, one in 10^4 or 10^6 values 1000 times as large: BWI 32 x 128->128 @28 42 : 312 : 51, 42 : 176 : 47,
+// 16 x 256->256 @56 253 : 993 : 257, 254 : 225 : 166, FWD 270 : 502 : 266, 258 : 195 : 173; half of the rows zero and one value in 10^4 2^-60 as large, BWI 42 : 322 : 44,
+// 225 : 437 : 157.
 template <int KQ, int HPC, bool HALF, int MODE, bool FIRST>
 __device__ __forceinline__ bool fwd_dense_wide_body(const Geom &g, const float *__restrict__ in, const float *__restrict__ wd,
                                                float *__restrict__ out, float *__restrict__ parts, const FlatGrid &fq, int kgroups,
